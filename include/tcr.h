@@ -35,7 +35,7 @@
  *   call that would have to allocate, grow or initialise workspace while its stream is capturing returns
  *   TCR_ERR_UNSUPPORTED and records nothing (run the same call once outside the capture, or supply a workspace
  *   and run one chained scan on it first).  Calls that use no workspace (scans with seg_len <= 4096, reduces
- *   with seg_len <= 262144 -- powers of two from 16 on; default variant and tuning) never do.
+ *   with seg_len <= 131072 -- powers of two from 16 on; default variant and tuning) never do.
  *   From the first recorded chained scan on, the workspace keeps its launch counters on the device and every
  *   chained scan on it, recorded or not, is preceded by one small bookkeeping kernel.  The "fused"
  *   reduce_finish variant cannot be recorded.
@@ -73,8 +73,8 @@ typedef enum {
  * irregular calls below; they use the workspace), except scans of a multiple of 8 elements from 65536 on (the
  * chained scan) and of a multiple of 64 elements up to 8192 that fills a workgroup's tiles to four fifths (one
  * workgroup per segment; the tuning table can give it every multiple of 8 between 520 and 65528); longer
- * reductions run one wavefront per
- * segment (per 65536-element piece of one, from 131072 elements) over zero-masked tiles of the array, the
+ * reductions run one, 4 or 16 wavefronts per segment, by how many segments there are (pieces of longer segments,
+ * from 131073 elements, and a second kernel over the pieces) over zero-masked tiles of the array, the
  * paper's padding of such segments (Section 4) applied in registers.
  */
 tcr_status tcr_segmented_reduce(const void *in, float *out, uint64_t n, uint64_t seg_len, void *stream);
@@ -172,8 +172,8 @@ tcr_status tcr_irregular_scan_ex(const void *in, const uint64_t *offsets, void *
  * squares one product per segment of a row, of the row's elements of that segment with the row; other lengths
  * from 17 to 2999: whole segments per workgroup with the data operand masked row by row, the squares from the
  * masked operand times itself; 8 to 15 elements from arrays that are not 4-byte aligned: the fixed tiles of the
- * irregular kernels with both moments in one pass (they use the workspace); longer ones: one wavefront per segment
- * (per 65536-element piece of a long one).
+ * irregular kernels with both moments in one pass (they use the workspace); longer ones: one, 4 or 16 wavefronts per
+ * segment (pieces of a long one).
  */
 tcr_status tcr_segmented_moments(const void *in, float *sum, float *sumsq, uint64_t n, uint64_t seg_len, void *stream);
 /* The same for irregular segments (offsets, n, nseg as for tcr_irregular_reduce; empty segments give 0 and 0):

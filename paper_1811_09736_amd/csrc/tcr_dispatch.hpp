@@ -142,12 +142,18 @@ inline tcr_status launch_reduce_span(const _Float16* in, float* dst, uint64_t n,
         }
         return check_launch("reduce_span_kernel");
     }
-    if (combine_waves == 4) {
-        reduce_span_kernel<FORM, 8, 4, true><<<dim3((unsigned)ceil_div(nspans, 4)), dim3(4 * kWave), 0, s>>>(
-            in, dst, n, span, nspans, none);
+    if (combine_waves == 16) {
+        if (span >= 8 * kTile) reduce_span_kernel<FORM, 8, 16, true><<<dim3((unsigned)ceil_div(nspans, 16)), dim3(16 * kWave), 0, s>>>(in, dst, n, span, nspans, none);
+        else reduce_span_kernel<FORM, 4, 16, true><<<dim3((unsigned)ceil_div(nspans, 16)), dim3(16 * kWave), 0, s>>>(in, dst, n, span, nspans, none);
+    } else if (combine_waves == 8) {
+        if (span >= 8 * kTile) reduce_span_kernel<FORM, 8, 8, true><<<dim3((unsigned)ceil_div(nspans, 8)), dim3(8 * kWave), 0, s>>>(in, dst, n, span, nspans, none);
+        else reduce_span_kernel<FORM, 4, 8, true><<<dim3((unsigned)ceil_div(nspans, 8)), dim3(8 * kWave), 0, s>>>(in, dst, n, span, nspans, none);
+    } else if (combine_waves == 4) {
+        if (span >= 8 * kTile) reduce_span_kernel<FORM, 8, 4, true><<<dim3((unsigned)ceil_div(nspans, 4)), dim3(4 * kWave), 0, s>>>(in, dst, n, span, nspans, none);
+        else reduce_span_kernel<FORM, 4, 4, true><<<dim3((unsigned)ceil_div(nspans, 4)), dim3(4 * kWave), 0, s>>>(in, dst, n, span, nspans, none);
     } else if (combine_waves == 2) {
-        reduce_span_kernel<FORM, 8, 2, true><<<dim3((unsigned)ceil_div(nspans, 2)), dim3(2 * kWave), 0, s>>>(
-            in, dst, n, span, nspans, none);
+        if (span >= 8 * kTile) reduce_span_kernel<FORM, 8, 2, true><<<dim3((unsigned)ceil_div(nspans, 2)), dim3(2 * kWave), 0, s>>>(in, dst, n, span, nspans, none);
+        else reduce_span_kernel<FORM, 4, 2, true><<<dim3((unsigned)ceil_div(nspans, 2)), dim3(2 * kWave), 0, s>>>(in, dst, n, span, nspans, none);
     } else {
         const dim3 grid((unsigned)nspans), block(kWave);
         if (span >= 8 * kTile) reduce_span_kernel<FORM, 8, 1, false><<<grid, block, 0, s>>>(in, dst, n, span, nspans, none);
@@ -165,6 +171,18 @@ struct ReducePlan {
 };
 
 
+// How many wavefronts an array is shared among, if its size allows: a wavefront keeps 8 KiB of loads in flight, and 16
+// wavefronts per compute unit is where more of them no longer help.
+constexpr uint64_t kWavesWanted = 4096;
+constexpr uint64_t kSpanMin = 2048;                      // no share below four tiles ...
+constexpr uint64_t kOneGroupSegment = 1ull << 17;        // longest segment that one workgroup of 16 wavefronts takes
+// Share of a wavefront when the array may be cut anywhere.
+inline uint64_t free_span(uint64_t n) {
+    uint64_t span = 4096;
+    while (span < kWaveSpanMax && n / span > kWavesWanted) span <<= 1;
+    return span;
+}
+
 // Reduce candidates for seg_len >= 1024 (power of two) or one segment: (span, combine) pairs.
 struct ReduceShape { uint64_t span; int combine; };
 inline int reduce_candidates(uint64_t n, uint64_t seg_len, bool whole, ReduceShape* c) {
@@ -176,8 +194,7 @@ inline int reduce_candidates(uint64_t n, uint64_t seg_len, bool whole, ReduceSha
         return k;
     }
     if (whole) {
-        uint64_t span = 4096;
-        while (span < kWaveSpanMax && n / span > 4096) span <<= 1;
+        const uint64_t span = free_span(n);
         if (ceil_div(n, span) == 1) {
             c[k++] = {ceil_div(n, kTile) * kTile, 1};
             return k;
@@ -196,18 +213,32 @@ inline int reduce_candidates(uint64_t n, uint64_t seg_len, bool whole, ReduceSha
 }
 
 // seg_len >= 1024 (a power of two), or one segment of any length (whole).
-inline ReducePlan plan_reduce(uint64_t n, uint64_t seg_len, bool whole) {
+// coarse: no more partials than one per 65536 elements of a segment (a workspace that cannot be grown).
+inline ReducePlan plan_reduce(uint64_t n, uint64_t seg_len, bool whole, bool coarse = false) {
     ReduceShape cand[4];
     const int count = reduce_candidates(n, seg_len, whole, cand);
     int pick = tuned_id(kTuneReduce, tuning_class(seg_len, whole));
     if (pick < 0 || pick >= count) {
-        // frozen defaults: segments of 8192 .. 32768 elements are split over 2 or 4 wavefronts; from 2^18 elements
-        // on (and for one segment) every wavefront leaves a partial of its own for the second kernel -- combining
-        // the wavefronts of a workgroup first holds each back to the slowest (n = 2^28: 81.5-81.9 us against
-        // 83.9-86.1 us with 4 combined; 8 or 16 combined, which make a segment of 2^19 or 2^20 elements one
-        // workgroup's and the second kernel unnecessary, 84.1 and 90.8 us)
+        // frozen defaults for an array that fills the chip whatever the split: segments of 8192 .. 32768 elements over
+        // 2 or 4 wavefronts; from 2^18 elements on (and for one segment) every wavefront leaves a partial of its own
+        // for the second kernel -- combining the wavefronts of a workgroup first holds each back to the slowest
+        // (n = 2^28: 81.5-81.9 us against 83.9-86.1 us with 4 combined; 8 or 16 combined, which make a segment of 2^19
+        // or 2^20 elements one workgroup's and the second kernel unnecessary, 84.1 and 90.8 us)
         if (whole || seg_len >= (1ull << 18)) pick = count > 1 ? 1 : 0;
         else pick = (seg_len < 8192 || seg_len > 32768) ? 0 : (seg_len == 8192 ? 1 : 2);
+        if (!whole) {
+            ReduceShape c = cand[pick];
+            if (seg_len <= kOneGroupSegment) {
+                // too few wavefronts to fill the chip: halve their shares, up to one workgroup of 16 per segment
+                const uint64_t w0 = seg_len / c.span;
+                uint64_t w = w0;
+                while (w < 16 && (n / seg_len) * w < kWavesWanted / 2 && seg_len / w > kSpanMin) w <<= 1;
+                if (w != w0) c = {seg_len / w, (int)w};
+            } else if (!coarse) {
+                c.span = free_span(n);                           // (a divisor of seg_len: both are powers of two)
+            }
+            cand[pick = 0] = c;
+        }
     }
     ReducePlan p;
     p.span = cand[pick].span;
@@ -218,8 +249,16 @@ inline ReducePlan plan_reduce(uint64_t n, uint64_t seg_len, bool whole) {
     return p;
 }
 
+// The second kernel of the device-level reduction: one workgroup per segment over its `per` partials.
+// out2: a second set of nseg * per partials behind the first goes there (the sums of squares), in the same launch.
+inline void launch_reduce_final(const float* partials, float* out, float* out2, uint64_t nseg, uint64_t per, hipStream_t s) {
+    const dim3 grid((unsigned)nseg, out2 != nullptr ? 2u : 1u);
+    if (per > kFinalThreads) reduce_final_kernel<kFinalThreadsMax><<<grid, dim3(kFinalThreadsMax), 0, s>>>(partials, out, out2, per, nseg * per);
+    else reduce_final_kernel<kFinalThreads><<<grid, dim3(kFinalThreads), 0, s>>>(partials, out, out2, per, nseg * per);
+}
+
 inline tcr_status reduce_long(const _Float16* in, float* out, uint64_t n, uint64_t seg_len, bool whole, hipStream_t s) {
-    const ReducePlan p = plan_reduce(n, seg_len, whole);
+    ReducePlan p = plan_reduce(n, seg_len, whole);
     const int form = tuned_formulation(kTuneReduce, tuning_class(seg_len, whole));
     const uint64_t nseg = whole ? 1 : n / seg_len;
     float* dst = out;
@@ -228,6 +267,7 @@ inline tcr_status reduce_long(const _Float16* in, float* out, uint64_t n, uint64
     if (p.per > 1) {
         tcr_status st = get_workspace(s, &ws, &capturing);
         if (st != TCR_OK) return st;
+        if (nseg * p.per > partials_limit(ws, capturing)) p = plan_reduce(n, seg_len, whole, true);
         st = ensure_partials(ws, s, nseg * p.per, capturing);
         if (st != TCR_OK) return st;
         dst = ws->partials;
@@ -252,7 +292,7 @@ inline tcr_status reduce_long(const _Float16* in, float* out, uint64_t n, uint64
                                                    : launch_reduce_span<kDpp>(in, dst, n, p.span, p.nspans, p.combine, s);
     if (st != TCR_OK) return st;
     if (p.per > 1) {
-        reduce_final_kernel<<<dim3((unsigned)nseg), dim3(kFinalThreads), 0, s>>>(dst, out, p.per);
+        launch_reduce_final(dst, out, nullptr, nseg, p.per, s);
         st = check_launch("reduce_final_kernel");
     }
     return st;
@@ -826,6 +866,61 @@ inline int pick_reduce_any(uint64_t seg_len, bool packed_ok = true) {
     return kReduceAnyMasked;                            // (or one thread per segment, below 8 elements)
 }
 
+// Sums (kSum) or both moments (kBoth, the second in out2) over masked tiles of the array.
+// Wavefronts per segment: one where that fills the chip or the segment is one step of a wavefront, else 4 or 16 (W
+// wavefronts of a workgroup take 4096 elements each per step).  Longer segments than one workgroup should walk are cut
+// into pieces of four wavefronts' free shares -- of one wavefront's where the array fills the chip anyway: the
+// wavefronts of a workgroup then need not wait for each other.  At n = 2^24 one wavefront per segment or per
+// 65536-element piece took 22.6 us at 50001 elements, 41.5 at 100001 and 30 at 300001 and 1000001.
+template <int KIND, int W>
+inline void launch_masked_pieces(const _Float16* in, float* dst, float* dst2, uint64_t nseg, uint64_t seg_len, uint64_t span,
+                                 uint64_t per, hipStream_t s) {
+    const dim3 grid((unsigned)ceil_div(nseg * per, W == 1 ? kMaskedWaves : 1)), block(masked_group_waves<W>() * kWave);
+    const bool four = W == 1 && seg_len > 4096;          // a wavefront that takes several steps: shorter ones (8192 elements: 21.7 against 22.8 us)
+    if constexpr (KIND == kBoth) {
+        if (per > 1) masked_moments_kernel<8, W, true><<<grid, block, 0, s>>>(in, dst, dst2, nseg, seg_len, span, per);
+        else if (four) masked_moments_kernel<4, W, false><<<grid, block, 0, s>>>(in, dst, dst2, nseg, seg_len, span, per);
+        else masked_moments_kernel<8, W, false><<<grid, block, 0, s>>>(in, dst, dst2, nseg, seg_len, span, per);
+    } else {
+        if (per > 1) masked_span_reduce_kernel<W><<<grid, block, 0, s>>>(in, dst, nseg, seg_len, span, per);
+        else if (four) masked_wave_reduce_kernel<4, W><<<grid, block, 0, s>>>(in, dst, nseg, seg_len);
+        else masked_wave_reduce_kernel<8, W><<<grid, block, 0, s>>>(in, dst, nseg, seg_len);
+    }
+}
+template <int KIND>
+inline tcr_status launch_masked(const _Float16* in, float* out, float* out2, uint64_t n, uint64_t seg_len, hipStream_t s) {
+    const uint64_t nseg = n / seg_len;
+    if (seg_len <= 2 * kWaveSpanMax) {
+        if (seg_len <= 4096 || nseg >= (seg_len <= 8192 ? kWavesWanted / 2 : kWavesWanted)) launch_masked_pieces<KIND, 1>(in, out, out2, nseg, seg_len, seg_len, 1, s);
+        else if (seg_len <= 16384 || 4 * nseg >= kWavesWanted / 2) launch_masked_pieces<KIND, 4>(in, out, out2, nseg, seg_len, seg_len, 1, s);
+        else launch_masked_pieces<KIND, 16>(in, out, out2, nseg, seg_len, seg_len, 1, s);
+        return check_launch("masked_wave_reduce_kernel");
+    }
+    // pieces, then the paper's second kernel over the pieces (for each moment)
+    constexpr uint64_t ch = KIND == kBoth ? 2 : 1;
+    uint64_t span = free_span(n);
+    const bool grouped = span < kWaveSpanMax;
+    if (grouped) span *= 4;
+    Workspace* ws = nullptr;
+    bool capturing = false;
+    tcr_status st = get_workspace(s, &ws, &capturing);
+    if (st != TCR_OK) return st;
+    // (a workspace that cannot be grown and is too small for that: pieces of 65536 elements, as few as there need be)
+    if (span < kWaveSpanMax && ch * nseg * ceil_div(seg_len, span) > partials_limit(ws, capturing)) span = kWaveSpanMax;
+    uint64_t per = ceil_div(seg_len, span);
+    if (span < seg_len) span = ceil_div(ceil_div(seg_len, per), 8 * (uint64_t)kTile) * (8 * (uint64_t)kTile);   // pieces of one size, in whole steps
+    per = ceil_div(seg_len, span);
+    const uint64_t pieces = nseg * per;
+    st = ensure_partials(ws, s, ch * pieces, capturing);
+    if (st != TCR_OK) return st;
+    if (grouped) launch_masked_pieces<KIND, 4>(in, ws->partials, ws->partials + pieces, nseg, seg_len, span, per, s);
+    else launch_masked_pieces<KIND, 1>(in, ws->partials, ws->partials + pieces, nseg, seg_len, span, per, s);
+    st = check_launch("masked_span_reduce_kernel");
+    if (st != TCR_OK) return st;
+    launch_reduce_final(ws->partials, out, out2, nseg, per, s);
+    return check_launch("reduce_final_kernel");
+}
+
 template <bool SCAN>
 inline tcr_status launch_generic(const _Float16* in, void* out, uint64_t n, uint64_t seg_len, uint32_t flags, hipStream_t s,
                                  int tiles_shape = 0) {
@@ -879,26 +974,8 @@ inline tcr_status launch_generic(const _Float16* in, void* out, uint64_t n, uint
             in, out, nseg, seg_len, excl, f16);
         return check_launch("generic_thread_kernel");
     }
-    // reductions from 1000 elements on: masked 512-element tiles of the array, one wavefront per segment
-    const dim3 grid((unsigned)ceil_div(nseg, kMaskedWaves)), block(kMaskedWaves * kWave);
-    if (seg_len <= 2 * kWaveSpanMax) {
-        masked_wave_reduce_kernel<<<grid, block, 0, s>>>(in, static_cast<float*>(out), nseg, seg_len);
-        return check_launch("masked_wave_reduce_kernel");
-    }
-    // long segments: pieces of 65536 elements per wavefront, then the paper's second kernel over the pieces
-    const uint64_t per = ceil_div(seg_len, kWaveSpanMax);
-    Workspace* ws = nullptr;
-    bool capturing = false;
-    tcr_status st = get_workspace(s, &ws, &capturing);
-    if (st != TCR_OK) return st;
-    st = ensure_partials(ws, s, nseg * per, capturing);
-    if (st != TCR_OK) return st;
-    masked_span_reduce_kernel<<<dim3((unsigned)ceil_div(nseg * per, kMaskedWaves)), block, 0, s>>>(
-        in, ws->partials, nseg, seg_len, kWaveSpanMax, per);
-    st = check_launch("masked_span_reduce_kernel");
-    if (st != TCR_OK) return st;
-    reduce_final_kernel<<<dim3((unsigned)nseg), dim3(kFinalThreads), 0, s>>>(ws->partials, static_cast<float*>(out), per);
-    return check_launch("reduce_final_kernel");
+    // reductions from 1000 elements on: masked 512-element tiles of the array
+    return launch_masked<kSum>(in, static_cast<float*>(out), nullptr, n, seg_len, s);
 }
 
 // The tuned scan paths for one (formulation, mode) pair.
@@ -941,27 +1018,7 @@ inline tcr_status launch_moments(const _Float16* in, float* sum, float* sumsq, u
             in, sum, sumsq, nseg, seg_len);
         return check_launch("generic_moments_kernel");
     }
-    const dim3 block(kMaskedWaves * kWave);
-    if (seg_len <= 2 * kWaveSpanMax) {
-        masked_moments_kernel<<<dim3((unsigned)ceil_div(nseg, kMaskedWaves)), block, 0, s>>>(in, sum, sumsq, nseg, seg_len,
-                                                                                             seg_len, 1);
-        return check_launch("masked_moments_kernel");
-    }
-    // long segments: 65536-element pieces, then the second kernel of the device-level reduction for each moment
-    const uint64_t per = ceil_div(seg_len, kWaveSpanMax), pieces = nseg * per;
-    Workspace* ws = nullptr;
-    bool capturing = false;
-    tcr_status st = get_workspace(s, &ws, &capturing);
-    if (st != TCR_OK) return st;
-    st = ensure_partials(ws, s, 2 * pieces, capturing);
-    if (st != TCR_OK) return st;
-    masked_moments_kernel<<<dim3((unsigned)ceil_div(pieces, kMaskedWaves)), block, 0, s>>>(
-        in, ws->partials, ws->partials + pieces, nseg, seg_len, kWaveSpanMax, per);
-    st = check_launch("masked_moments_kernel");
-    if (st != TCR_OK) return st;
-    reduce_final_kernel<<<dim3((unsigned)nseg), dim3(kFinalThreads), 0, s>>>(ws->partials, sum, per);
-    reduce_final_kernel<<<dim3((unsigned)nseg), dim3(kFinalThreads), 0, s>>>(ws->partials + pieces, sumsq, per);
-    return check_launch("reduce_final_kernel");
+    return launch_masked<kBoth>(in, sum, sumsq, n, seg_len, s);
 }
 
 // Segment lengths that are no power of two, a multiple of 8, and fit one workgroup: scan_segment_kernel with the

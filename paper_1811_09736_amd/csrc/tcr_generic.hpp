@@ -3,18 +3,18 @@
 // moments.  The paper handles such sizes by zero padding
 // or by masking (Section 4, "Support for arbitrary segment sizes ...").  Padding in place is not possible
 // behind this interface, so:
-//   masked_*        one wavefront per segment (or per 65536-element piece of one) walks the 512-element
+//   masked_*        one to 16 wavefronts per segment (or per piece of a long one) walk the 512-element
 //                   tiles of the ARRAY (aligned to the array, not to the segment) that the segment
-//                   touches; elements of a tile outside the segment are read as zero -- the paper's
+//                   touches; elements of a tile outside the segment count as zero -- the paper's
 //                   zero padding, applied to the operand registers -- and the matrix-core products,
 //                   the running sums through the accumulator and the 128-bit loads of the tuned
-//                   kernels apply unchanged; only the 8-element groups cut by a segment end are read
-//                   element by element.
+//                   kernels apply unchanged.
 //   generic_*       one thread per segment: 16-bit loads, binary32 adds.
 // They are correct for every seg_len >= 1; none of them is tuned.
 #pragma once
 #include "tcr_device.hpp"
 #include "tcr_scan.hpp"
+#include "tcr_irregular.hpp"
 
 namespace tcr {
 
@@ -101,115 +101,124 @@ __global__ __launch_bounds__(kGenericThreads) void tiny_scan_kernel(const _Float
 }
 
 // ---------------------------------------------------------------------------------------- masked tiles
-// 8 inputs at element g (a multiple of 8), those outside [begin, end) read as zero.
-template <bool STREAM = false>
-__device__ __forceinline__ half8 load8_masked(const _Float16* __restrict__ in, uint64_t g, uint64_t begin, uint64_t end) {
-    if (g >= begin && g + 8 <= end) return load8<STREAM>(in, g);
-    half8 v;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = (g + e >= begin && g + e < end) ? in[g + e] : (_Float16)0.0f;
-    return v;
-}
-
-// One wavefront adds up the segment [begin, end); the result is uniform.  `in` is 16-byte aligned.
-__device__ __forceinline__ float masked_wave_reduce(const _Float16* __restrict__ in, uint64_t begin, uint64_t end,
-                                                    const LaneId& id) {
-    constexpr int kSteps = 4;
-    float4v acc = splat(0.0f);                           // running row sums (the accumulator matrix V of Reduction_256N)
-    for (uint64_t t0 = begin & ~(uint64_t)(kTile - 1); t0 < end; t0 += (uint64_t)(kTile * kSteps)) {
-        half8 x[kSteps];
-#pragma unroll
-        for (int i = 0; i < kSteps; ++i) {
-            const uint64_t tile = t0 + (uint64_t)(kTile * i);
-            x[i] = (tile < end) ? load8_masked<true>(in, tile + (uint64_t)(kRow * id.j + 8 * id.g), begin, end)
-                                : __builtin_bit_cast(half8, splat(0.0f));
-        }
-#pragma unroll
-        for (int i = 0; i < kSteps; ++i) acc = mfma(const_ones(), x[i], acc);
-    }
-    return read_lane(row_sum_to_last<16>(acc[0]), 15);
-}
-
-constexpr int kMaskedWaves = 4;                          // wavefronts (segments) per workgroup
-
-__global__ __launch_bounds__(kMaskedWaves * kWave) void masked_wave_reduce_kernel(const _Float16* __restrict__ in,
-                                                                                  float* __restrict__ out, uint64_t nseg,
-                                                                                  uint64_t seg_len) {
-    const LaneId id;
-    const uint64_t s = (uint64_t)blockIdx.x * kMaskedWaves + (uint64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (s >= nseg) return;
-    const float total = masked_wave_reduce(in, s * seg_len, (s + 1) * seg_len, id);
-    if (id.lane == 0) out[s] = total;
-}
-
-// Long segments of any length: wavefront w adds up piece w % per of segment w / per (pieces of `span` elements
-// counted from the segment's start, the last one shorter) into dst[w]; reduce_final_kernel adds the pieces.
-__global__ __launch_bounds__(kMaskedWaves * kWave) void masked_span_reduce_kernel(const _Float16* __restrict__ in,
-                                                                                  float* __restrict__ dst, uint64_t nseg,
-                                                                                  uint64_t seg_len, uint64_t span,
-                                                                                  uint64_t per) {
-    const LaneId id;
-    const uint64_t w = (uint64_t)blockIdx.x * kMaskedWaves + (uint64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (w >= nseg * per) return;
-    const uint64_t s = w / per, piece = w - s * per;
-    const uint64_t begin = s * seg_len + piece * span;
-    const uint64_t seg_end = (s + 1) * seg_len;
-    const uint64_t end = begin + span < seg_end ? begin + span : seg_end;
-    const float total = masked_wave_reduce(in, begin, end, id);
-    if (id.lane == 0) dst[w] = total;
-}
-
-// ---------------------------------------------------------------------------------------- first two moments
-// Sum and sum of squares of a segment -- the statistics of a normalisation layer, which the paper's conclusion
-// names as the next use of reductions on matrix cores.  The sum is Reduction_256N (V <- ones . X^T + V).  The
-// sum of squares takes the data as BOTH operands: entry (i, j) of X . X^T is the inner product of data rows i
-// and j, so the DIAGONAL of W <- X . X^T + W accumulates the sums of squares of the 16 rows (the other entries
-// are not used).  A product of two binary16 values is exact in the binary32 accumulator.
-// One wavefront, segment [begin, end) over zero-masked tiles of the array; both results are uniform.
-__device__ __forceinline__ void masked_wave_moments(const _Float16* __restrict__ in, uint64_t begin, uint64_t end,
-                                                    const LaneId& id, float& sum, float& sumsq) {
-    constexpr int kSteps = 4;
+// What one wavefront -- number `part` of the W that share the work -- adds up of the elements [begin, end): the sum,
+// and for kBoth the sum of squares (uniform).  `in` is 16-byte aligned, end <= n, end - begin < 2^30.
+// The sum is Reduction_256N (V <- ones . X^T + V).  The sum of squares takes the data as BOTH operands: entry (i, j) of
+// X . X^T is the inner product of data rows i and j, so the DIAGONAL of W <- X . X^T + W accumulates the sums of
+// squares of the 16 rows (the other entries are not used); a product of two binary16 values is exact in the binary32
+// accumulator.
+// The tiles of the ARRAY from the one that holds `begin` on, U of them per step and wavefront, all U loads on their way
+// at once: a buffer resource that ends with the group of 8 that holds the last element keeps them free of branches (a
+// branch around a load makes the compiler wait where the paths rejoin: 10 % at segments of 4096 elements), and what the
+// first and the last tile hold of neighbours is masked in the registers afterwards.
+template <int KIND, int U, int W>
+__device__ __forceinline__ void masked_part_sums(const _Float16* __restrict__ in, uint64_t n, uint64_t begin, uint64_t end,
+                                                 int part, const LaneId& id, float& sum, float& sumsq) {
+    const uint64_t first = begin & ~(uint64_t)(kTile - 1);
+    const uint32_t lead = (uint32_t)(begin - first), len = (uint32_t)(end - first);      // the range, counted from `first`
+    // whole groups of 8 inside the array; the one that the end of the array cuts is read element by element
+    const bool cut = ((end + 7) & ~7ull) > n;
+    const __amdgpu_buffer_rsrc_t src = make_rsrc(in + first, (cut ? len & ~7u : (len + 7u) & ~7u) * 2u);
+    const uint32_t lane_off = (uint32_t)(kRow * id.j + 8 * id.g);
     float4v acc = splat(0.0f), sq = splat(0.0f);
-    for (uint64_t t0 = begin & ~(uint64_t)(kTile - 1); t0 < end; t0 += (uint64_t)(kTile * kSteps)) {
-        half8 x[kSteps];
+    for (uint32_t t = (uint32_t)part * (uint32_t)(kTile * U); t < len; t += (uint32_t)(kTile * U * W)) {
+        half8 x[U];
 #pragma unroll
-        for (int i = 0; i < kSteps; ++i) {
-            const uint64_t tile = t0 + (uint64_t)(kTile * i);
-            x[i] = (tile < end) ? load8_masked<true>(in, tile + (uint64_t)(kRow * id.j + 8 * id.g), begin, end)
-                                : __builtin_bit_cast(half8, splat(0.0f));
+        for (int u = 0; u < U; ++u) x[u] = buffer_load8<true>(src, (t + (uint32_t)(kTile * u) + lane_off) * 2u);
+        if (t < lead) x[0] = drop_leading(x[0], (int)lead - (int)lane_off);              // (t == 0: the first tile)
+        if ((len & 7u) != 0u && len - t <= (uint32_t)(kTile * U)) {                      // the step that holds the last tile
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t at = t + (uint32_t)(kTile * u) + lane_off;
+                if (cut && at < len && at + 8u > len) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        x[u][e] = at + (uint32_t)e >= lead && at + (uint32_t)e < len ? in[first + at + (uint32_t)e] : (_Float16)0.0f;
+                }
+                x[u] = keep_leading(x[u], (int)len - (int)at);
+            }
         }
 #pragma unroll
-        for (int i = 0; i < kSteps; ++i) {
-            acc = mfma(const_ones(), x[i], acc);
-            sq = __builtin_amdgcn_mfma_f32_16x16x32_f16(x[i], x[i], sq, 0, 0, 0);
+        for (int u = 0; u < U; ++u) {
+            acc = mfma(const_ones(), x[u], acc);
+            if constexpr (KIND == kBoth) sq = mfma(x[u], x[u], sq);
         }
     }
     sum = read_lane(row_sum_to_last<16>(acc[0]), 15);
-    // lane (j, g) holds rows 4g .. 4g+3 of column j: the diagonal entry of column j sits in lane (j, j / 4), register j % 4
-    const int r = id.j & 3;
-    const float d = r == 0 ? sq[0] : (r == 1 ? sq[1] : (r == 2 ? sq[2] : sq[3]));
-    sumsq = wave_sum(id.g == (id.j >> 2) ? d : 0.0f);
+    if constexpr (KIND == kBoth) {
+        // lane (j, g) holds rows 4g .. 4g+3 of column j: the diagonal entry of column j sits in lane (j, j / 4), register j % 4
+        const int r = id.j & 3;
+        const float d = r == 0 ? sq[0] : (r == 1 ? sq[1] : (r == 2 ? sq[2] : sq[3]));
+        sumsq = wave_sum(id.g == (id.j >> 2) ? d : 0.0f);
+    }
 }
 
-// One wavefront per piece: piece w % per of segment w / per (pieces of `span` elements from the segment's
-// start; per == 1: whole segments).  sum[w], sumsq[w] receive the piece's moments.
-__global__ __launch_bounds__(kMaskedWaves * kWave) void masked_moments_kernel(const _Float16* __restrict__ in,
-                                                                              float* __restrict__ sum,
-                                                                              float* __restrict__ sumsq, uint64_t nseg,
-                                                                              uint64_t seg_len, uint64_t span, uint64_t per) {
+// Piece w % per of segment w / per (pieces of `span` elements counted from the segment's start, the last one shorter;
+// per == 1: whole segments) -> dst[w], dst2[w].  W == 1: a wavefront per piece, kMaskedWaves of them in a workgroup.
+// W > 1: a workgroup of W wavefronts per piece, their sums added through LDS in wavefront order.
+// Bound by memory.  One wavefront per segment leaves the chip idle when there are few segments (16 KiB in flight per
+// wavefront, and 256 compute units): the launch picks W and the span so that about 4096 wavefronts share the array.
+constexpr int kMaskedWaves = 4;
+template <int W>
+constexpr int masked_group_waves() { return W == 1 ? kMaskedWaves : W; }
+template <int KIND, int U, int W, bool PIECES>
+__device__ __forceinline__ void masked_piece(const _Float16* __restrict__ in, float* __restrict__ dst, float* __restrict__ dst2,
+                                             uint64_t nseg, uint64_t seg_len, uint64_t span, uint64_t per) {
     const LaneId id;
-    const uint64_t w = (uint64_t)blockIdx.x * kMaskedWaves + (uint64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (w >= nseg * per) return;
-    const uint64_t s = w / per, piece = w - s * per;
-    const uint64_t begin = s * seg_len + piece * span;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint64_t w = W == 1 ? (uint64_t)blockIdx.x * kMaskedWaves + (uint64_t)wave : (uint64_t)blockIdx.x;
+    if (w >= (PIECES ? nseg * per : nseg)) return;       // (W > 1: the whole workgroup alike)
+    const uint64_t s = PIECES ? w / per : w;
     const uint64_t seg_end = (s + 1) * seg_len;
-    const uint64_t end = begin + span < seg_end ? begin + span : seg_end;
-    float a, q;
-    masked_wave_moments(in, begin, end, id, a, q);
-    if (id.lane == 0) {
-        sum[w] = a;
-        sumsq[w] = q;
+    uint64_t begin = s * seg_len, end = seg_end;
+    if constexpr (PIECES) {
+        begin += (w - s * per) * span;
+        if (begin + span < seg_end) end = begin + span;
     }
+    float a = 0.0f, q = 0.0f;
+    masked_part_sums<KIND, U, W>(in, nseg * seg_len, begin, end, W == 1 ? 0 : wave, id, a, q);
+    if constexpr (W > 1) {
+        __shared__ float s_part[2][W];
+        if (id.lane == 0) {
+            s_part[0][wave] = a;
+            s_part[1][wave] = q;
+        }
+        __syncthreads();
+        if (threadIdx.x != 0) return;
+        a = q = 0.0f;
+#pragma unroll
+        for (int v = 0; v < W; ++v) {
+            a += s_part[0][v];
+            q += s_part[1][v];
+        }
+    }
+    if (id.lane == 0) {
+        dst[w] = a;
+        if constexpr (KIND == kBoth) dst2[w] = q;
+    }
+}
+
+// Whole segments; pieces of long ones (reduce_final_kernel adds them); both moments of either -- the statistics of a
+// normalisation layer, which the paper's conclusion names as the next use of reductions on matrix cores.
+template <int U, int W>
+__global__ __launch_bounds__(masked_group_waves<W>() * kWave) void masked_wave_reduce_kernel(const _Float16* __restrict__ in,
+                                                                                             float* __restrict__ out,
+                                                                                             uint64_t nseg, uint64_t seg_len) {
+    masked_piece<kSum, U, W, false>(in, out, nullptr, nseg, seg_len, seg_len, 1);
+}
+template <int W>
+__global__ __launch_bounds__(masked_group_waves<W>() * kWave) void masked_span_reduce_kernel(const _Float16* __restrict__ in,
+                                                                                             float* __restrict__ dst, uint64_t nseg,
+                                                                                             uint64_t seg_len, uint64_t span,
+                                                                                             uint64_t per) {
+    masked_piece<kSum, 8, W, true>(in, dst, nullptr, nseg, seg_len, span, per);
+}
+template <int U, int W, bool PIECES>
+__global__ __launch_bounds__(masked_group_waves<W>() * kWave) void masked_moments_kernel(const _Float16* __restrict__ in,
+                                                                                         float* __restrict__ sum,
+                                                                                         float* __restrict__ sumsq, uint64_t nseg,
+                                                                                         uint64_t seg_len, uint64_t span, uint64_t per) {
+    masked_piece<kBoth, U, W, PIECES>(in, sum, sumsq, nseg, seg_len, span, per);
 }
 
 // Short segments: one thread per segment, binary32 adds and fused multiply-adds.

@@ -208,14 +208,19 @@ __global__ __launch_bounds__(WAVES * kWave) void reduce_span_kernel(const _Float
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: keeps per-wave branches and addresses scalar
     const uint64_t w = (uint64_t)blockIdx.x * WAVES + wave;
     float total = 0.0f;
-    if (w < nspans) {
-        const uint64_t begin = w * span;
-        const uint64_t end = (begin + span < n) ? begin + span : n;
+    if (COMBINE || w < nspans) {            // (a workgroup's piece of the array is never empty)
+        // COMBINE: the wavefronts of a workgroup take turns over its WAVES spans, U tiles each, so that what they have
+        // in flight together is one contiguous piece of the array (segments of 2^17, 512 of them: 24.4 us with a span
+        // of its own per wavefront, 22.1 in turns)
+        constexpr int kTurns = COMBINE ? WAVES : 1;
+        const uint64_t piece = COMBINE ? span * (uint64_t)WAVES : span;
+        const uint64_t begin = COMBINE ? (uint64_t)blockIdx.x * piece : w * span;
+        const uint64_t end = (begin + piece < n) ? begin + piece : n;
         const int lane_off = (FORM == kMfma) ? (kRow * id.j + 8 * id.g) : (8 * id.lane);
         float4v acc = splat(0.0f);          // MFMA: running row sums (the accumulator matrix V)
         float s0 = 0.0f, s1 = 0.0f;         // DPP: per-lane running sums
-        uint64_t t = begin;
-        for (; t + (uint64_t)(kTile * U) <= end; t += (uint64_t)(kTile * U)) {
+        uint64_t t = begin + (COMBINE ? (uint64_t)(wave * kTile * U) : 0);
+        for (; t + (uint64_t)(kTile * U) <= end; t += (uint64_t)(kTile * U * kTurns)) {
             half8 x[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) x[u] = load8<true>(in, t + (uint64_t)(kTile * u + lane_off));
@@ -226,10 +231,26 @@ __global__ __launch_bounds__(WAVES * kWave) void reduce_span_kernel(const _Float
                 else s0 += sum8(x[u]);
             }
         }
-        for (; t < end; t += kTile) {
-            const half8 x = load8_guarded<true>(in, t + (uint64_t)lane_off, end);
-            if constexpr (FORM == kMfma) acc = mfma(const_ones(), x, acc);
-            else s0 += sum8(x);
+        if (t < end) {
+            // fewer than U tiles left, for the wavefront whose turn it is: one step whose loads are cut off by the range
+            // check of a buffer that ends with the last whole group of 8; what remains is read element by element
+            const uint32_t left = (uint32_t)(end - t);
+            const __amdgpu_buffer_rsrc_t src = make_rsrc(in + t, (left & ~7u) * 2u);
+            half8 x[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) x[u] = buffer_load8<true>(src, (uint32_t)(kTile * u + lane_off) * 2u);
+            if (left & 7u) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t at = (uint32_t)(kTile * u + lane_off);
+                    if (at == (left & ~7u)) x[u] = load8_guarded<true>(in, t + at, end);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if constexpr (FORM == kMfma) acc = mfma(const_ones(), x[u], acc);
+                else s0 += sum8(x[u]);
+            }
         }
         if constexpr (FORM == kMfma) total = read_lane(row_sum_to_last<16>(acc[0]), 15);   // fold the 16 row sums
         else total = read_lane(lanes_sum_to_last<64>(s0 + s1), 63);
@@ -279,26 +300,41 @@ __global__ __launch_bounds__(WAVES * kWave) void reduce_span_kernel(const _Float
 }
 
 // ------------------------------------------------------------------------------ partials -> result
-// Workgroup s adds the `per` binary32 partials of segment s in a fixed order.
-constexpr int kFinalThreads = 256;
-__global__ __launch_bounds__(kFinalThreads) void reduce_final_kernel(const float* __restrict__ partials,
-                                                                     float* __restrict__ out, uint64_t per) {
-    constexpr int kBlockThreads = kFinalThreads;
-    __shared__ float wave_tot[kFinalThreads / kWave];
+// Workgroup s adds the `per` binary32 partials of segment s in a fixed order.  Latency: a load's way is most of its
+// time, so every thread asks for its four at once and large counts take large workgroups (4096 partials: 4.6 us with 256
+// threads, one dependent round after another).
+constexpr int kFinalThreads = 256, kFinalThreadsMax = 1024;
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void reduce_final_kernel(const float* __restrict__ partials, float* __restrict__ out,
+                                                               float* __restrict__ out2, uint64_t per, uint64_t second) {
+    __shared__ float wave_tot[THREADS / kWave];
     const float* p = partials + (uint64_t)blockIdx.x * per;
-    float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f;
-    uint64_t i = threadIdx.x;
-    for (; i + 3 * kBlockThreads < per; i += 4 * kBlockThreads) {
-        a0 += p[i];
-        a1 += p[i + kBlockThreads];
-        a2 += p[i + 2 * kBlockThreads];
-        a3 += p[i + 3 * kBlockThreads];
+    if (blockIdx.y) {                     // the second set of partials, `second` behind the first
+        p += second;
+        out = out2;
     }
-    for (; i < per; i += kBlockThreads) a0 += p[i];
-    const float t = wave_sum((a0 + a1) + (a2 + a3));
+    float a[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (uint64_t i = threadIdx.x; i < per; i += 4 * THREADS) {
+        float v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            // (beyond the end: the thread's first partial again, not added)
+            const uint64_t at = i + (uint64_t)(k * THREADS);
+            v[k] = p[at < per ? at : i];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (i + (uint64_t)(k * THREADS) < per) a[k] += v[k];
+    }
+    const float t = wave_sum((a[0] + a[1]) + (a[2] + a[3]));
     if ((threadIdx.x & 63) == 0) wave_tot[threadIdx.x >> 6] = t;
     __syncthreads();
-    if (threadIdx.x == 0) out[blockIdx.x] = (wave_tot[0] + wave_tot[1]) + (wave_tot[2] + wave_tot[3]);
+    if (threadIdx.x == 0) {
+        float sum = 0.0f;
+#pragma unroll
+        for (int w = 0; w < THREADS / kWave; ++w) sum += wave_tot[w];
+        out[blockIdx.x] = sum;
+    }
 }
 
 }  // namespace tcr

@@ -143,6 +143,11 @@ inline tcr_status get_workspace(hipStream_t stream, Workspace** out, bool* captu
     return TCR_OK;
 }
 
+// How many partials a call may plan for: what is there, where that cannot be grown (the caller's buffer, a capture).
+inline uint64_t partials_limit(const Workspace* ws, bool capturing) {
+    return (ws->caller_owned || capturing) ? ws->partials_capacity : ~0ull;
+}
+
 inline tcr_status ensure_partials(Workspace* ws, hipStream_t stream, uint64_t floats, bool capturing) {
     if (floats <= ws->partials_capacity) return TCR_OK;
     if (ws->caller_owned) return TCR_ERR_WORKSPACE;
