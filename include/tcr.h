@@ -211,6 +211,9 @@ tcr_status tcr_scan(const void *in, float *out, uint64_t n, void *stream);
  *   "irregular_scan" "auto" (default: one kernel or two by the number of segments) | "single" (always the one
  *                  kernel of chained tiles) | "chain" (always two, where the launch allows it: default tile shape,
  *                  16-byte aligned arrays, matrix-core formulation)
+ *   "scan_wait"    "bounded" (default: the chained scan of an array that the chip holds at once waits a bounded time for
+ *                  the sum of an earlier tile, then adds that tile up again) | "none" (adds up at once what is not there
+ *                  yet; for tests)
  *   "reduce_finish" "second_kernel" (default: the paper's two-kernel device-level reduction, Section 4) |
  *                  "fused" (one kernel: the workgroup that finishes last adds up the partials)
  *   "reset"        any value: back to the defaults

@@ -254,6 +254,12 @@ extern "C" tcr_status tcr_set_variant(const char* key, const char* value) {
         else return TCR_ERR_INVALID_ARG;
         return TCR_OK;
     }
+    if (std::strcmp(key, "scan_wait") == 0) {
+        if (std::strcmp(value, "bounded") == 0) g_variant.scan_wait = true;
+        else if (std::strcmp(value, "none") == 0) g_variant.scan_wait = false;
+        else return TCR_ERR_INVALID_ARG;
+        return TCR_OK;
+    }
     if (std::strcmp(key, "reduce_finish") == 0) {
         if (std::strcmp(value, "fused") == 0) g_variant.reduce_fused = true;
         else if (std::strcmp(value, "second_kernel") == 0) g_variant.reduce_fused = false;
@@ -470,11 +476,12 @@ extern "C" const char* tcr_kernel_name(int op, uint64_t n, uint64_t seg_len) {
         if (!whole && seg_len <= kTile) return mf ? "scan_small_kernel<mfma>" : "scan_small_kernel<dpp>";
         // the carry strategy as scan_long resolves it
         int strategy = g_variant.scan_carry;
-        int shape = strategy == kStrategyLookback ? pick_scan_shape(seg_len, whole) : -1;
+        int shape = strategy == kStrategyLookback ? pick_scan_shape(n, seg_len, whole) : -1;
         if (shape == kScanIdReduceThenScan) strategy = kStrategyReduceThenScan;
         if (shape == kScanIdScanThenPropagate) strategy = kStrategyScanThenPropagate;
+        if (shape == kScanIdChainTail && mf && once_share(n, n, ~0ull) != 0) return "scan_chain_kernel<mfma,ragged>";
         if (shape == kScanIdChainTail) return mf ? "scan_chain_kernel<mfma>+scan_tail_kernel" : "scan_chain_kernel<dpp>+scan_tail_kernel";
-        if (shape >= kScanShapeCount) shape = default_scan_shape(seg_len, whole, mf ? kMfma : kDpp);
+        if (shape >= kScanShapeCount) shape = default_scan_shape(n, seg_len, whole, mf ? kMfma : kDpp);
         if (shape == kScanIdChainTail) shape = 9;
         const bool table = strategy != kStrategyLookback;
         if (table && seg_len <= kCarryTile)

@@ -361,7 +361,7 @@ inline void launch_scan_block(const _Float16* in, void* out, uint64_t n, uint64_
 // Ids 10 and 11 are scan_chain_kernel: persistent workgroups (one per compute unit) that take
 // 32768-element tiles by ticket in a loop and keep three in flight (loading, aggregate published,
 // carry looked up and stored); for segments of at least one tile and the one-segment scan,
-// matrix-core formulation only, n a multiple of 8.
+// n a multiple of 8.  Id 10 runs arrays that the chip holds all at once as one tile per workgroup (once_share).
 struct ScanShape { int u, w; bool ticket; int persistent; };      // persistent: workgroups per compute unit (0: one per tile)
 constexpr ScanShape kScanShapes[] = {{1, 2, false, 0}, {1, 4, false, 0}, {1, 8, false, 0}, {1, 16, false, 0},
                                      {2, 16, false, 0}, {4, 16, false, 0}, {8, 16, false, 0}, {2, 16, true, 0},
@@ -395,11 +395,17 @@ inline int compute_units() {
     return cached[dev];
 }
 
-inline int default_scan_shape(uint64_t len, bool whole, int form) {
+// n: elements of the whole call (the defaults for segments of 8192 and 16384 depend on it).
+inline int default_scan_shape(uint64_t n, uint64_t len, bool whole, int form) {
     if (len <= 1024) return 0;
     if (len <= 2048) return 1;
     if (len <= 4096) return 2;
     if (len < 8192 || (whole && len == 8192)) return 3;
+    // one workgroup per segment, in blockIdx order while the array is not much larger than the memory-side cache (8192
+    // elements: n = 2^20 / 2^24 / 2^26 / 2^27 3.8 / 20.8 / 70.5 / 136 us against 5.3 / 28.6 / 79.8 / 147 by ticket; 16384:
+    // 4.4 / 23.3 / 76.6 / 151 against 5.3 / 28.9 / 77.5 / 141), by ticket in arrays that stream from memory
+    if (!whole && len == 8192 && n < (1ull << 28)) return 3;
+    if (!whole && len == 16384 && n < (1ull << 27)) return 4;
     if (!whole && len <= 16384) return 7;          // one ticketed share per segment (two segments of 8192)
     // the pipelined chain: segments of 32768 and more, one segment with n % 8 == 0.  (16 wavefronts of 4 tiles
     // for the matrix cores; the DPP arithmetic needs more registers and takes 8 wavefronts of 8 tiles.)
@@ -407,13 +413,14 @@ inline int default_scan_shape(uint64_t len, bool whole, int form) {
     // n not a multiple of 8: the chain over the whole groups of 8 and a second, tiny kernel for the rest (measured
     // at n = 2^28 - 3: 297 us against 307-323 us for scan_block_kernel with decoupled look-back, which short arrays keep)
     if (scan_shape_valid(kScanIdChainTail, len, whole)) return kScanIdChainTail;
+    if (whole && len < (1u << 16)) return 7;       // a few shares (n = 2^15: 5.2 us against 7.4 with one large share)
     return (whole || len >= (1u << 20)) ? 9 : 8;
 }
 
-inline int pick_scan_shape(uint64_t len, bool whole) {
+inline int pick_scan_shape(uint64_t n, uint64_t len, bool whole) {
     const int cls = tuning_class(len, whole);
     const int tuned = tuned_id(kTuneScan, cls);
-    return scan_shape_valid(tuned, len, whole) ? tuned : default_scan_shape(len, whole, tuned_formulation(kTuneScan, cls));
+    return scan_shape_valid(tuned, len, whole) ? tuned : default_scan_shape(n, len, whole, tuned_formulation(kTuneScan, cls));
 }
 
 template <int FORM, int CARRY, int MODE>
@@ -446,11 +453,52 @@ inline int nocarry_shape_for(uint64_t fit) {
     return 6;
 }
 
+// The chain as one tile per workgroup: tiles of 16 wavefronts with the result's number of 512-element tiles each -- the
+// smallest of which there are no more than compute units and no more than `limit` (descriptors of a workspace that
+// cannot be grown).  Segments that overhang their last tile may need more tiles than that; they take 32768-element
+// tiles, up to the same size of array.  0: the array is too large for the chip to hold at once (2^24 elements: 22.5 us
+// against 28.5 with the pipeline; 2^24 + 32768: 30.8 against 28.7).
+inline uint64_t once_tiles(uint64_t n, uint64_t seg_len, int u) { return (n / seg_len) * ceil_div(seg_len, (uint64_t)(kTile * 16 * u)); }
+inline int once_share(uint64_t n, uint64_t seg_len, uint64_t limit) {
+    const uint64_t units = (uint64_t)compute_units();
+    if (n > units * (uint64_t)(kTile * 16 * 8)) return 0;
+    for (int u = 1; u <= 8; u *= 2) {
+        if (u > 1 && (uint64_t)(kTile * 16 * u) > seg_len) break;
+        const uint64_t tiles = once_tiles(n, seg_len, u);
+        if (tiles <= units && tiles <= limit) return u;
+    }
+    return 4;
+}
+template <int MODE>
+tcr_status launch_chain_once(const _Float16* in, void* out, uint64_t n, uint64_t seg_len, hipStream_t s) {
+    ScanWorkspace dev = {};
+    Workspace* ws = nullptr;
+    bool capturing = false;
+    tcr_status st = get_workspace(s, &ws, &capturing);
+    if (st != TCR_OK) return st;
+    const int u = once_share(n, seg_len, ws->caller_owned || capturing ? ws->desc_capacity : ~0ull);
+    const uint64_t tiles = once_tiles(n, seg_len, u);
+    st = begin_lookback(ws, s, tiles, &dev, capturing);
+    if (st != TCR_OK) return st;
+    const ChainGrid grid = {seg_len, (uint32_t)(tiles / (n / seg_len)), (uint32_t)tiles, g_variant.scan_wait ? kOncePatience : 0u};
+    const dim3 blocks((unsigned)tiles), block(16 * kWave);
+    if (u == 1) scan_chain_kernel<kMfma, 1, 16, MODE, false, true><<<blocks, block, 0, s>>>(in, out, grid, dev, nullptr);
+    else if (u == 2) scan_chain_kernel<kMfma, 2, 16, MODE, false, true><<<blocks, block, 0, s>>>(in, out, grid, dev, nullptr);
+    else if (u == 4) scan_chain_kernel<kMfma, 4, 16, MODE, false, true><<<blocks, block, 0, s>>>(in, out, grid, dev, nullptr);
+    else scan_chain_kernel<kMfma, 8, 16, MODE, false, true><<<blocks, block, 0, s>>>(in, out, grid, dev, nullptr);
+    st = check_launch("scan_chain_kernel");
+    if (st != TCR_OK) ws->dirty = true;
+    return st;
+}
+
 // The persistent chain (shape 10 or 11) over segments of `seg_len` elements: any multiple of 8 that is at
 // least one tile, or one segment of n elements (n a multiple of 8).
 template <int FORM, int MODE>
 tcr_status launch_chain(int shape, const _Float16* in, void* out, uint64_t n, uint64_t seg_len, hipStream_t s,
                         ScanWorkspace* used = nullptr, uint32_t* used_tiles = nullptr) {
+    if constexpr (FORM == kMfma) {
+        if (shape == 10 && once_share(n, seg_len, ~0ull) != 0) return launch_chain_once<MODE>(in, out, n, seg_len, s);
+    }
     const uint64_t tile = scan_shape_tile(shape);
     const uint64_t per_segment = ceil_div(seg_len, tile);
     const uint64_t tiles = (n / seg_len) * per_segment;
@@ -463,7 +511,7 @@ tcr_status launch_chain(int shape, const _Float16* in, void* out, uint64_t n, ui
     if (st != TCR_OK) return st;
     const uint64_t resident = (uint64_t)compute_units() * (uint64_t)kScanShapes[shape].persistent;
     const uint64_t groups = tiles < resident ? tiles : resident;
-    const ChainGrid grid = {seg_len, (uint32_t)per_segment, (uint32_t)tiles};
+    const ChainGrid grid = {seg_len, (uint32_t)per_segment, (uint32_t)tiles, 0};
     if (shape == 10) scan_chain_kernel<FORM, 4, 16, MODE><<<dim3((unsigned)groups), dim3(16 * kWave), 0, s>>>(in, out, grid, dev, nullptr);
     else scan_chain_kernel<FORM, 8, 8, MODE><<<dim3((unsigned)groups), dim3(8 * kWave), 0, s>>>(in, out, grid, dev, nullptr);
     st = check_launch("scan_chain_kernel");
@@ -480,6 +528,9 @@ tcr_status launch_chain(int shape, const _Float16* in, void* out, uint64_t n, ui
 // One segment of n elements, n no multiple of 8: the chain over the first n - n % 8, then the rest.
 template <int FORM, int MODE>
 tcr_status launch_chain_tail(const _Float16* in, void* out, uint64_t n, hipStream_t s) {
+    if constexpr (FORM == kMfma) {
+        if (once_share(n, n, ~0ull) != 0) return launch_chain_once<MODE>(in, out, n, n, s);      // (cuts its last group itself)
+    }
     const uint64_t n8 = n & ~7ull;
     ScanWorkspace dev = {};
     uint32_t tiles = 0;
@@ -497,11 +548,11 @@ inline tcr_status scan_long(const _Float16* in, void* out, uint64_t n, uint64_t 
     if (whole) seg_len = ~0ull;                       // length for the one-segment case (n need not be a power of two)
     // the carry strategy: forced by tcr_set_variant, else the class's tuned choice, else the single pass
     int strategy = g_variant.scan_carry;
-    int shape = strategy == kStrategyLookback ? pick_scan_shape(host_seg_len, whole) : -1;
+    int shape = strategy == kStrategyLookback ? pick_scan_shape(n, host_seg_len, whole) : -1;
     if (shape == kScanIdReduceThenScan) strategy = kStrategyReduceThenScan;
     if (shape == kScanIdScanThenPropagate) strategy = MODE == 0 ? kStrategyScanThenPropagate : kStrategyLookback;
     if (shape == kScanIdChainTail) return launch_chain_tail<FORM, MODE>(in, out, n, s);
-    if (shape >= kScanShapeCount) shape = default_scan_shape(host_seg_len, whole, FORM);    // (the strategies have fixed shapes)
+    if (shape >= kScanShapeCount) shape = default_scan_shape(n, host_seg_len, whole, FORM);    // (the strategies have fixed shapes)
     if (shape == kScanIdChainTail) shape = 9;             // (a forced multi-kernel strategy: its no-carry shares do not use it)
     const bool table = strategy != kStrategyLookback;     // the two multi-kernel strategies
     if (table && host_seg_len <= kCarryTile) {
@@ -672,7 +723,7 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
         const uint64_t resident = (uint64_t)compute_units();
         const uint64_t groups = tiles < resident ? tiles : resident;
         scan_chain_kernel<kMfma, 4, 16, MODE, true><<<dim3((unsigned)groups), dim3(16 * kWave), 0, s>>>(
-            in, out, ChainGrid{n, (uint32_t)tiles, (uint32_t)tiles}, dev, links);
+            in, out, ChainGrid{n, (uint32_t)tiles, (uint32_t)tiles, 0}, dev, links);
         st = check_launch("scan_chain_kernel");
         if (st != TCR_OK) {
             ws->dirty = true;

@@ -522,6 +522,7 @@ struct ChainGrid {
     uint64_t seg_len;
     uint32_t per_segment;
     uint32_t tiles;
+    uint32_t patience;       // ONCE: looks at an aggregate before its tile is added up here
 };
 
 // Stage C: request the data of ticket `tile`.
@@ -668,14 +669,169 @@ __device__ __forceinline__ uint32_t chain_finish(ChainTile<U>& t, void* __restri
     return fresh;
 }
 
-template <int FORM, int U, int WAVES, int MODE, bool IRREG = false>
+// ONCE: the chain for arrays that the chip holds all at once.  Every workgroup takes one tile, that of its blockIdx, and
+// nothing is drawn: its tile's aggregate is published as soon as its totals are known, the aggregates of the segment's
+// earlier tiles are read in one round trip, and the results go out.  Such arrays are bound by latency: the pipeline
+// above starts with three draws one after another and the loads between them, 9 us before the first store.  Nothing
+// guarantees that the workgroups of lower tiles are running, so nobody relies on it: a wavefront that has not seen an
+// aggregate after `patience` looks adds up that tile's elements itself, and every wait ends whatever else runs.
+// Full scan of n = 2^16 / 2^20 / 2^22 / 2^23 / 2^24 elements: 9.0 / 9.7 / 13.1 / 21.7 / 28.5 us with the pipeline,
+// 4.2 / 5.0 / 7.7 / 12.6 / 22.5 here with the smallest tiles of which there are no more than compute units (tiles four
+// times as large take 7.2 / 8.0 / 9.7 us at the first three sizes, a quarter as large 9.7 us at 2^22: every tile reads
+// the aggregates of all the earlier ones).
+
+// The total of tile `t` from its elements, by one whole wavefront.
+template <int U, int WAVES>
+__device__ __forceinline__ float once_tile_total(uint32_t t, const _Float16* __restrict__ in, const ChainGrid& grid, const LaneId& id) {
+    constexpr uint32_t kBlockTile = (uint32_t)(kTile * U * WAVES);
+    const uint32_t seg = t / grid.per_segment;
+    const uint64_t seg_begin = (uint64_t)seg * grid.seg_len, seg_end = seg_begin + grid.seg_len;
+    const uint64_t base = seg_begin + (uint64_t)(t - seg * grid.per_segment) * kBlockTile;
+    const uint32_t count = seg_end - base < kBlockTile ? (uint32_t)(seg_end - base) : kBlockTile;     // (a tile with successors is whole)
+    const __amdgpu_buffer_rsrc_t src = make_rsrc(in + base, (count & ~7u) * 2u);
+    float4v acc = splat(0.0f);
+    for (uint32_t e = 0; e < count; e += (uint32_t)kTile) acc = mfma(const_ones(), buffer_load8(src, (e + (uint32_t)(kRow * id.j + 8 * id.g)) * 2u), acc);
+    return read_lane(row_sum_to_last<16>(acc[0]), 15);
+}
+
+// Executed by one whole wavefront: the sum of the totals of tiles lo .. tile-1.
+constexpr uint32_t kOncePatience = 4096;
+template <int U, int WAVES>
+__device__ __forceinline__ float once_sum_totals(const ScanWorkspace& ws, uint32_t lo, uint32_t tile, const _Float16* __restrict__ in,
+                                                 const ChainGrid& grid, const LaneId& id) {
+    const uint32_t want = ws.epoch * 4u + kStatusAggregate;
+    float acc = 0.0f;
+    for (uint32_t hi = tile; hi > lo;) {                 // 256 at a time, the nearest first
+        const uint32_t span = (hi - lo > 256u) ? 256u : hi - lo;
+        float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        bool need[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) need[q] = (uint32_t)(id.lane + 64 * q) < span;
+        uint32_t polls = 0;
+        while (true) {
+            unsigned long long d[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if ((uint32_t)(64 * q) < span) d[q] = load_descriptor(&ws.desc[need[q] ? hi - 1u - (uint32_t)(id.lane + 64 * q) : tile]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if ((uint32_t)(64 * q) < span && need[q] && (uint32_t)(d[q] >> 32) == want) {
+                    v[q] = __builtin_bit_cast(float, (uint32_t)d[q]);
+                    need[q] = false;
+                }
+            }
+            if (__ballot(need[0] || need[1] || need[2] || need[3]) == 0ull) break;
+            if (++polls > grid.patience) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    for (unsigned long long m = __ballot(need[q]); m != 0ull; m &= m - 1ull) {
+                        const int from = __builtin_ctzll(m);
+                        const float t = once_tile_total<U, WAVES>(hi - 1u - (uint32_t)(from + 64 * q), in, grid, id);
+                        if (id.lane == from) v[q] = t;
+                    }
+                }
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+        acc += wave_sum((v[0] + v[1]) + (v[2] + v[3]));
+        hi -= span;
+    }
+    return acc;
+}
+
+template <int U, int WAVES, int MODE>
+__device__ __forceinline__ void chain_once(const _Float16* __restrict__ in, void* __restrict__ out, const ChainGrid& grid,
+                                           const ScanWorkspace& ws, ChainShared& sh) {
+    constexpr int EXCL = MODE & 1, F16 = MODE >> 1;
+    constexpr uint32_t kChunk = (uint32_t)kTile * U;
+    constexpr uint32_t kBlockTile = kChunk * WAVES;
+    const LaneId id;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t tile = blockIdx.x;
+    if (tile == 0 && threadIdx.x == 0 && ws.state != nullptr && !ws.device_managed) ws.state[0] = ws.epoch;
+    const uint32_t seg = tile / grid.per_segment, pos = tile - seg * grid.per_segment;
+    const uint64_t seg_begin = (uint64_t)seg * grid.seg_len, seg_end = seg_begin + grid.seg_len;
+    const uint64_t base = seg_begin + (uint64_t)pos * kBlockTile + (uint64_t)wave * kChunk;
+    const uint64_t left = base < seg_end ? seg_end - base : 0;
+    const uint32_t count = left < kChunk ? (uint32_t)left : kChunk;
+    const uint32_t whole = count & ~7u;                   // (one segment of any length: its last group of 8 may be cut)
+    const uint32_t lane_off = (uint32_t)(kRow * id.j + 8 * id.g);
+    const __amdgpu_buffer_rsrc_t src = make_rsrc(in + (count ? base : 0), whole * 2u);
+    half8 x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = buffer_load8(src, ((uint32_t)(kTile * u) + lane_off) * 2u);
+    if (count != whole) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if ((uint32_t)(kTile * u) + lane_off == whole) x[u] = load8_guarded(in, base + whole, seg_end);
+    }
+    float pre[U], run = 0.0f;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const float4v tot = mfma(const_ones(), x[u], splat(0.0f));
+        const float incl = row_scan_inclusive<16>(tot[0], id.j);
+        pre[u] = row_shr<1>(incl) + run;
+        run += read_lane(incl, 15);
+    }
+    if (id.lane == 0) sh.wave_total[wave] = run;
+    __syncthreads();
+    float ext = 0.0f, total = 0.0f;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        const float t = sh.wave_total[w];
+        if (w < wave) ext += t;
+        total += t;
+    }
+    if (pos + 1u < grid.per_segment && wave == 0 && id.lane == 0)      // (the segment's last tile is nobody's predecessor)
+        __hip_atomic_store(&ws.desc[tile], pack_desc(ws.epoch, kStatusAggregate, total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (pos != 0u) {
+        if (wave == 0) {
+            const float before = once_sum_totals<U, WAVES>(ws, tile - pos, tile, in, grid, id);
+            if (id.lane == 0) sh.prefix = before;
+        }
+        __syncthreads();
+        ext += sh.prefix;
+    }
+    const __amdgpu_buffer_rsrc_t dst = make_rsrc(static_cast<char*>(out) + (count ? base : 0) * (F16 ? 2u : 4u), whole * (F16 ? 2u : 4u));
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const float carry = pre[u] + ext;
+        const float4v lo = mfma(const_tri_lo<EXCL>(id), x[u], splat(carry));
+        const float4v hi = mfma(const_tri_hi<EXCL>(id), x[u], splat(carry));
+        buffer_store_tile_rows_t<F16>(dst, (uint32_t)(kTile * u), id.j, id.g, lo, hi);
+        if (count != whole) {
+            // the group that the end of the array cuts: its first four positions and its last four lie in two lanes
+            const uint32_t at = (uint32_t)(kTile * u + kRow * id.j + 4 * id.g);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t a = at + (uint32_t)e, b = a + 16u;
+                if (a >= whole && a < count) {
+                    if constexpr (F16) static_cast<_Float16*>(out)[base + a] = (_Float16)lo[e];
+                    else static_cast<float*>(out)[base + a] = lo[e];
+                }
+                if (b >= whole && b < count) {
+                    if constexpr (F16) static_cast<_Float16*>(out)[base + b] = (_Float16)hi[e];
+                    else static_cast<float*>(out)[base + b] = hi[e];
+                }
+            }
+        }
+    }
+}
+
+template <int FORM, int U, int WAVES, int MODE, bool IRREG = false, bool ONCE = false>
 __global__ __launch_bounds__(WAVES * kWave) void scan_chain_kernel(const _Float16* __restrict__ in,
                                                                    void* __restrict__ out, ChainGrid grid,
                                                                    ScanWorkspace ws_arg, const TileLink* __restrict__ links) {
     static_assert(WAVES <= 16, "");
+    static_assert(!ONCE || (FORM == kMfma && !IRREG), "");
     const uint32_t tiles = grid.tiles;
     const ScanWorkspace ws = resolve_workspace(ws_arg);
     __shared__ ChainShared sh;
+    if constexpr (ONCE) {
+        chain_once<U, WAVES, MODE>(in, out, grid, ws, sh);
+        return;
+    }
     __shared__ uint32_t s_draw;
 
     const LaneId id;
