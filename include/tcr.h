@@ -68,9 +68,10 @@ typedef enum {
  * (the masking that Section 4 proposes for arbitrary segment sizes; `in` 4-byte aligned, no workspace);
  * reductions of 17 to 8160 elements otherwise take whole segments per workgroup and mask the data operand of the
  * products row by row where a segment ends (the same masking moved from the constant matrix to the data; no
- * workspace); reductions of 5 to 15 elements from arrays that are not 4-byte aligned and all scans run on fixed
- * tiles of the array with the segment starts marked (the kernels of the
- * irregular calls below; they use the workspace), except scans of a multiple of 8 elements from 65536 on (the
+ * workspace); reductions of 5 to 15 elements from arrays that are not 4-byte aligned run on fixed
+ * tiles of the array with the segment starts marked (the kernels of the irregular calls below; they use the
+ * workspace); scans run on fixed tiles too, up to 8192 elements per segment with no workspace (a workgroup adds up the
+ * part of its open segment in front of its tile by itself), except scans of a multiple of 8 elements from 65536 on (the
  * chained scan) and of a multiple of 64 elements up to 8192 that fills a workgroup's tiles to four fifths (one
  * workgroup per segment; the tuning table can give it every multiple of 8 between 520 and 65528); longer
  * reductions run one, 4 or 16 wavefronts per segment, by how many segments there are (pieces of longer segments,
@@ -143,7 +144,8 @@ tcr_status tcr_scan_ex(const void *in, void *out, uint64_t n, uint32_t flags, vo
  * the mix of segment lengths.  Both use the workspace (tcr_workspace_bytes, op 4 and 5): one small kernel looks
  * up where the tile boundaries fall among the offsets; the scan chains its tiles like the long regular scans
  * (with fewer segments than a quarter of the tiles it runs as two kernels: the pipelined chain of the long
- * regular scans takes the tiles without a segment start, a second kernel the others);
+ * regular scans takes the tiles without a segment start, a second kernel the others); an array that the chip holds at
+ * once (up to 2^24 elements) is scanned by one kernel whose tiles search the offsets and look up what they need;
  * the reduction keeps its tiles independent and two small kernels add the one sum per tile that reaches in
  * from earlier tiles -- plain loads in a fixed order, so the reduction's results are the same from run to run.
  * in and out need only their natural alignment (2 and 4 bytes): the tiles start at the 16-byte boundary at or
@@ -159,6 +161,10 @@ tcr_status tcr_irregular_scan(const void *in, const uint64_t *offsets, float *ou
  * their size). */
 tcr_status tcr_irregular_scan_ex(const void *in, const uint64_t *offsets, void *out, uint64_t n, uint64_t nseg, uint32_t flags,
                                  void *stream);
+/* The same with every position of out written: 0 where no segment lies (nseg == 0: everywhere).  For callers whose `out`
+ * is fresh memory; clearing it first would be a pass of its own. */
+tcr_status tcr_irregular_scan_filled(const void *in, const uint64_t *offsets, void *out, uint64_t n, uint64_t nseg, uint32_t flags,
+                                     void *stream);
 
 /*
  * First two moments of every segment: the statistics of a normalisation layer, which the paper's conclusion
@@ -256,7 +262,8 @@ tcr_status tcr_tuning_import(const char *text);
 /*
  * Name of the kernel the dispatcher would launch for (op, n, seg_len) under the current
  * variant settings; op is 0 = segmented_reduce, 1 = segmented_scan, 2 = reduce, 3 = scan,
- * 4 = irregular_reduce, 5 = irregular_scan (seg_len is ignored).  The arrays are taken to be 16-byte aligned
+ * 4 = irregular_reduce, 5 = irregular_scan (seg_len is ignored; the kernels of a large array are named, smaller ones
+ * need fewer: their tiles search the offsets themselves).  The arrays are taken to be 16-byte aligned
  * (regular calls on arrays that are not run irregular_reduce_kernel<regular> / irregular_scan_kernel<regular>).
  * Returns a static string ("" when nothing would be launched); never NULL.
  */

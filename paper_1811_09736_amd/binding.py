@@ -23,7 +23,7 @@ SCAN_EXCLUSIVE, OUT_F16, ACC_F16 = 1, 2, 4
 
 EXPORTS = (
     "tcr_segmented_reduce", "tcr_segmented_scan", "tcr_segmented_scan_ex", "tcr_scan_ex", "tcr_reduce", "tcr_scan",
-    "tcr_irregular_reduce", "tcr_irregular_scan", "tcr_irregular_scan_ex", "tcr_irregular_moments", "tcr_autotune", "tcr_autotune_irregular", "tcr_tuning_export", "tcr_tuning_import",
+    "tcr_irregular_reduce", "tcr_irregular_scan", "tcr_irregular_scan_ex", "tcr_irregular_scan_filled", "tcr_irregular_moments", "tcr_autotune", "tcr_autotune_irregular", "tcr_tuning_export", "tcr_tuning_import",
     "tcr_workspace_bytes", "tcr_set_workspace", "tcr_segmented_moments",
     "tcr_set_variant", "tcr_segmented_scan_noalloc",
     "tcr_kernel_name", "tcr_check_device_flags", "tcr_release", "tcr_release_stream", "tcr_status_string", "tcr_last_hip_error",
@@ -56,6 +56,8 @@ def _load() -> ctypes.CDLL:
     lib.tcr_irregular_scan.argtypes = [vp, vp, fp, u64, u64, vp]
     lib.tcr_irregular_scan_ex.argtypes = [vp, vp, vp, u64, u64, ctypes.c_uint32, vp]
     lib.tcr_irregular_scan_ex.restype = ctypes.c_int
+    lib.tcr_irregular_scan_filled.argtypes = lib.tcr_irregular_scan_ex.argtypes
+    lib.tcr_irregular_scan_filled.restype = ctypes.c_int
     lib.tcr_irregular_moments.argtypes = [vp, vp, fp, fp, u64, u64, vp]
     lib.tcr_irregular_moments.restype = ctypes.c_int
     lib.tcr_irregular_reduce.restype = ctypes.c_int
@@ -226,18 +228,9 @@ def irregular_reduce(x: torch.Tensor, offsets: torch.Tensor, out: Optional[torch
 
 def irregular_scan(x: torch.Tensor, offsets: torch.Tensor, out: Optional[torch.Tensor] = None,
                    stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
-    """tcr_irregular_scan: inclusive running sums restarting at every offsets[s]; out is indexed like x."""
-    if not (x.is_cuda and x.dtype == torch.float16 and x.dim() == 1 and x.is_contiguous()):
-        raise TypeError("input must be a contiguous 1-D float16 CUDA tensor")
-    nseg = _check_offsets(x, offsets)
-    if out is None:
-        out = torch.zeros(x.numel(), dtype=torch.float32, device=x.device)
-    _check_output(out, x.numel(), x)
-    with torch.cuda.device(x.device):
-        st = _lib.tcr_irregular_scan(x.data_ptr(), offsets.data_ptr(), out.data_ptr(), x.numel(), nseg, _stream_handle(stream))
-    if st != OK:
-        raise TcrError(st, "tcr_irregular_scan")
-    return out
+    """tcr_irregular_scan: inclusive running sums restarting at every offsets[s]; out is indexed like x (without `out`:
+    a new tensor, 0 where no segment lies; a given one stays untouched there)."""
+    return irregular_scan_ex(x, offsets, 0, out, stream)
 
 
 def irregular_moments(x: torch.Tensor, offsets: torch.Tensor, stream: Optional[torch.cuda.Stream] = None):
@@ -262,15 +255,16 @@ def irregular_scan_ex(x: torch.Tensor, offsets: torch.Tensor, flags: int, out: O
         raise TypeError("input must be a contiguous 1-D float16 CUDA tensor")
     nseg = _check_offsets(x, offsets)
     dtype = torch.float16 if flags & OUT_F16 else torch.float32
-    if out is None:
-        out = torch.zeros(x.numel(), dtype=dtype, device=x.device)
-    if not (out.is_cuda and out.dtype == dtype and out.is_contiguous() and out.numel() == x.numel() and out.device == x.device):
+    fresh = out is None
+    if fresh:
+        out = torch.empty(x.numel(), dtype=dtype, device=x.device)
+    elif not (out.is_cuda and out.dtype == dtype and out.is_contiguous() and out.numel() == x.numel() and out.device == x.device):
         raise TypeError(f"out must be a contiguous {dtype} CUDA tensor of {x.numel()} elements on the input's device")
+    call = _lib.tcr_irregular_scan_filled if fresh else _lib.tcr_irregular_scan_ex
     with torch.cuda.device(x.device):
-        st = _lib.tcr_irregular_scan_ex(x.data_ptr(), offsets.data_ptr(), out.data_ptr(), x.numel(), nseg, flags,
-                                        _stream_handle(stream))
+        st = call(x.data_ptr(), offsets.data_ptr(), out.data_ptr(), x.numel(), nseg, flags, _stream_handle(stream))
     if st != OK:
-        raise TcrError(st, "tcr_irregular_scan_ex")
+        raise TcrError(st, "tcr_irregular_scan_ex" if flags else "tcr_irregular_scan")
     return out
 
 

@@ -162,20 +162,32 @@ extern "C" tcr_status tcr_irregular_moments(const void* in, const uint64_t* offs
     return launch_irregular_reduce(static_cast<const _Float16*>(in), offsets, sum, n, nseg, 0, s, kBoth, sumsq);
 }
 
-extern "C" tcr_status tcr_irregular_scan_ex(const void* in, const uint64_t* offsets, void* out, uint64_t n, uint64_t nseg,
-                                            uint32_t flags, void* stream) {
+static tcr_status irregular_scan_any(const void* in, const uint64_t* offsets, void* out, uint64_t n, uint64_t nseg, uint32_t flags,
+                                     void* stream, bool fill) {
     if ((flags & ~(uint32_t)(TCR_SCAN_EXCLUSIVE | TCR_OUT_F16)) != 0) return TCR_ERR_INVALID_ARG;
-    if (nseg == 0 || n == 0) return TCR_OK;
+    if ((nseg == 0 && !fill) || n == 0) return TCR_OK;
     const tcr_status st = validate_irregular(in, offsets, out, n, nseg, (flags & TCR_OUT_F16) ? 2 : 4);
     if (st != TCR_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const _Float16* x = static_cast<const _Float16*>(in);
+    if (nseg == 0)                           // no segment: nothing but the zeros
+        return (flags & TCR_OUT_F16) ? launch_fill_outside<1>(offsets, 0, out, n, 0, s) : launch_fill_outside<0>(offsets, 0, out, n, 0, s);
     switch (flags & 3u) {
-        case 0: return launch_irregular_scan<0>(x, offsets, out, n, nseg, 0, s);
-        case 1: return launch_irregular_scan<1>(x, offsets, out, n, nseg, 0, s);
-        case 2: return launch_irregular_scan<2>(x, offsets, out, n, nseg, 0, s);
-        default: return launch_irregular_scan<3>(x, offsets, out, n, nseg, 0, s);
+        case 0: return launch_irregular_scan<0>(x, offsets, out, n, nseg, 0, s, -1, fill);
+        case 1: return launch_irregular_scan<1>(x, offsets, out, n, nseg, 0, s, -1, fill);
+        case 2: return launch_irregular_scan<2>(x, offsets, out, n, nseg, 0, s, -1, fill);
+        default: return launch_irregular_scan<3>(x, offsets, out, n, nseg, 0, s, -1, fill);
     }
+}
+
+extern "C" tcr_status tcr_irregular_scan_ex(const void* in, const uint64_t* offsets, void* out, uint64_t n, uint64_t nseg,
+                                            uint32_t flags, void* stream) {
+    return irregular_scan_any(in, offsets, out, n, nseg, flags, stream, false);
+}
+
+extern "C" tcr_status tcr_irregular_scan_filled(const void* in, const uint64_t* offsets, void* out, uint64_t n, uint64_t nseg,
+                                                uint32_t flags, void* stream) {
+    return irregular_scan_any(in, offsets, out, n, nseg, flags, stream, true);
 }
 
 extern "C" tcr_status tcr_irregular_scan(const void* in, const uint64_t* offsets, float* out, uint64_t n, uint64_t nseg,

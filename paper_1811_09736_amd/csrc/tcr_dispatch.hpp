@@ -13,6 +13,25 @@ __global__ void fill_zero_kernel(float* out, uint64_t count) {
     if (i < count) out[i] = 0.0f;
 }
 
+// Zeros to the positions of [shift, n) outside [offsets[0] + shift, offsets[nseg] + shift).
+template <int F16>
+__global__ __launch_bounds__(256) void fill_outside_kernel(const uint64_t* __restrict__ offsets, uint64_t nseg, void* __restrict__ out,
+                                                           uint64_t n, uint32_t shift) {
+    uint64_t first = offsets[0] + shift, last = offsets[nseg] + shift;
+    if (first > n) first = n;
+    if (last < first) last = first;
+    const uint64_t stride = (uint64_t)gridDim.x * 256;
+    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x + shift; i < n; i += stride) {
+        if (i >= first && i < last) {                     // (jump over the covered part)
+            const uint64_t trips = (last - i + stride - 1) / stride;
+            i += trips * stride;
+            if (i >= n) return;
+        }
+        if constexpr (F16) static_cast<_Float16*>(out)[i] = (_Float16)0.0f;
+        else static_cast<float*>(out)[i] = 0.0f;
+    }
+}
+
 inline bool is_pow2(uint64_t v) { return v != 0 && (v & (v - 1)) == 0; }
 inline int log2u(uint64_t v) {
     int l = 0;
@@ -683,9 +702,74 @@ inline void launch_irregular_scan_shape(bool regular, const _Float16* in, const 
     else irregular_scan_kernel<U, W, false, MODE><<<grid, block, 0, s>>>(in, offsets, out, n, nseg, starts, 0, shift, vector_stores, dev);
 }
 
+// Zeros to the positions of [shift, n) that no segment covers.
+template <int F16>
+inline tcr_status launch_fill_outside(const uint64_t* offsets, uint64_t nseg, void* out, uint64_t n, uint32_t shift, hipStream_t s) {
+    fill_outside_kernel<F16><<<dim3((unsigned)compute_units()), dim3(256), 0, s>>>(offsets, nseg, out, n, shift);
+    return check_launch("fill_outside_kernel");
+}
+
+// One tile per workgroup (tcr_once.hpp).  in, out, n: already counted from the 16-byte boundary below the caller's array.
+template <int U, int W, int MODE>
+inline void launch_tile_scan(const TileScan& a, bool local, const ScanWorkspace& dev, hipStream_t s) {
+    const dim3 grid((unsigned)ceil_div(a.n, (uint64_t)(kTile * U * W))), block(W * kWave);
+    if (local) irregular_scan_kernel<U, W, true, MODE, true><<<grid, block, 0, s>>>(a, dev);
+    else if (a.offsets == nullptr) irregular_scan_kernel<U, W, true, MODE, false><<<grid, block, 0, s>>>(a, dev);
+    else irregular_scan_kernel<U, W, false, MODE, false><<<grid, block, 0, s>>>(a, dev);
+}
+template <int MODE>
+inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, void* out, uint64_t n, uint64_t nseg, uint64_t seg_len,
+                                   uint32_t shift, bool fill, hipStream_t s) {
+    TileScan a = {};
+    a.in = in;
+    a.offsets = offsets;
+    a.out = out;
+    a.n = n;
+    a.nseg = nseg;
+    a.seg_len = seg_len;
+    a.shift = shift;
+    a.vector_stores = aligned(out, 16) ? 1u : 0u;
+    a.fill = fill ? 1u : 0u;
+    a.patience = g_variant.scan_wait ? kOncePatience : 0u;
+    const bool local = offsets == nullptr && seg_len <= kLocalMax;
+    if (offsets == nullptr) {
+        a.per_elem = 1.0 / (double)seg_len;
+        for (uint32_t i = 0; i < 8; ++i)
+            if (i % seg_len == 0) a.pattern |= 1u << i;
+    }
+    ScanWorkspace dev = {};
+    if (local) {
+        a.magic = (uint32_t)(((1ull << 32) + seg_len - 1) / seg_len);
+        // 8 wavefronts, so that the open part is a small share of what a workgroup reads -- unless segments are short and
+        // the array streams from memory (seg_len 33 at n = 2^24 / 2^26 / 2^28: 23.2 / 74.8 / 285 us with 8, 23.6 / 73.3 /
+        // 276 with 16; 2001: 22.7 / 74.4 / 277 and 24.0 / 77.8 / 290), or longer than 8 wavefronts can add up at once
+        if (seg_len > 4096 || (seg_len <= 1024 && n > (1ull << 24))) launch_tile_scan<1, 16, MODE>(a, true, dev, s);
+        else launch_tile_scan<1, 8, MODE>(a, true, dev, s);
+        return check_launch("irregular_scan_kernel");
+    }
+    Workspace* ws = nullptr;
+    bool capturing = false;
+    tcr_status st = get_workspace(s, &ws, &capturing);
+    if (st != TCR_OK) return st;
+    const uint64_t limit = ws->caller_owned || capturing ? ws->desc_capacity : ~0ull;
+    // the smallest tiles of which there are no more than compute units (n = 2^22, seg_len 10001: 8.2 us with 16384-element
+    // tiles, 9.0 with 8192), at most 32768 elements (65536: 2 us slower at n = 2^24, one workgroup per compute unit)
+    const uint64_t units = (uint64_t)compute_units();
+    int u = 1;
+    while (u < 4 && (ceil_div(n, (uint64_t)(kTile * 16 * u)) > units || ceil_div(n, (uint64_t)(kTile * 16 * u)) > limit)) u *= 2;
+    st = begin_lookback(ws, s, ceil_div(n, (uint64_t)(kTile * 16 * u)), &dev, capturing);
+    if (st != TCR_OK) return st;
+    if (u == 1) launch_tile_scan<1, 16, MODE>(a, false, dev, s);
+    else if (u == 2) launch_tile_scan<2, 16, MODE>(a, false, dev, s);
+    else launch_tile_scan<4, 16, MODE>(a, false, dev, s);
+    st = check_launch("irregular_scan_kernel");
+    if (st != TCR_OK) ws->dirty = true;
+    return st;
+}
+
 template <int MODE>
 inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offsets, void* out, uint64_t n, uint64_t nseg,
-                                        uint64_t seg_len, hipStream_t s, int shape = -1) {
+                                        uint64_t seg_len, hipStream_t s, int shape = -1, bool fill = false) {
     if (shape < 0) shape = irregular_shape(true);
     const uint64_t elems = irregular_tile_elems(true, shape);
     const uint32_t shift = alignment_shift(in);
@@ -695,6 +779,18 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
     const uint32_t vector_stores = aligned(out, 16) ? 1u : 0u;
     const uint64_t tiles = irregular_tiles(true, n, shape);
     const bool regular = offsets == nullptr;
+    // One tile per workgroup with nothing chained: regular segments short enough for a workgroup to add up the open part by
+    // itself, at every size of array, and any segments in an array that the chip holds at once (at most a 65536-element
+    // share per compute unit).  n = 2^20 / 2^24 / 2^26, us, by ticket and look-back against this: seg_len 1001 8.2 / 27 / 85
+    // against 4.1 / 22.8 / 74; 100003 8.7 / 28 against 6.4 / 23.7; irregular, lognormal lengths 10.9 / 31.8 against 6.6 /
+    // 27.2, seven segments 20 / 40 against 6.9 / 28.
+    if (shape == 0 && g_variant.formulation == kMfma && (regular ? seg_len >= 2 : g_variant.irregular_scan == 0) &&
+        ((regular && seg_len <= kLocalMax) || n <= (uint64_t)compute_units() * (uint64_t)(kTile * 16 * 8)))
+        return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, s);
+    if (fill) {
+        const tcr_status filled = launch_fill_outside<(MODE >> 1)>(offsets, nseg, out, n, shift, s);
+        if (filled != TCR_OK) return filled;
+    }
     Workspace* ws = nullptr;
     bool capturing = false;
     tcr_status st = get_workspace(s, &ws, &capturing);

@@ -1,0 +1,305 @@
+// Scans of segments that start anywhere -- regular ones of a length no tuned kernel takes, and irregular ones -- with one
+// tile of the array per workgroup and nothing drawn or chained between workgroups.
+//
+// A tile needs one number from in front of it: the sum of its open segment, from that segment's start s0 to the tile's
+// own start.  s0 is known without asking another workgroup -- by a division for regular segments, from the offsets
+// entry in front of the tile for irregular ones -- and so is the way the sum is found:
+//   * s0 at most a tile or so in front: the workgroup adds those elements up itself, 512 to a wavefront, while its own
+//     data is on its way (they are a neighbour's data, mostly found in a cache);
+//   * further away: the published sums of the tiles from the one that holds s0 on, read in one round trip.  As in the
+//     chained scan of arrays that the chip holds at once, a sum that is not there after `patience` looks is added up
+//     from the elements, so no wait depends on which workgroups run.
+// Bound: memory for large arrays, the chain of dependent steps for the smaller ones.  The ticket, the look-back and, for
+// regular segments, the bitmap of the starts and its two barriers are what this form does without.
+// (The tile arithmetic is that of the fixed tiles of irregular_scan_kernel: running sums that restart at heads inside a
+// lane's eight elements, pairs of (head, sum) across lanes and wavefronts.)
+#pragma once
+#include "tcr_irregular.hpp"
+
+namespace tcr {
+
+struct TileScan {
+    const _Float16* in;           // `shift` elements in front of the caller's array, 16-byte aligned
+    const uint64_t* offsets;      // irregular: nseg + 1 entries
+    void* out;                    // `shift` elements in front of the caller's array
+    uint64_t n;                   // elements counted from `in`
+    uint64_t nseg;
+    uint64_t seg_len;             // regular
+    double per_elem;              // regular: 1 / seg_len
+    uint32_t magic;               // regular, seg_len <= kLocalMax: ceil(2^32 / seg_len)
+    uint32_t pattern;             // regular: bit i set iff i is a multiple of seg_len, i < 8
+    uint32_t shift;
+    uint32_t vector_stores;       // `out` is 16-byte aligned
+    uint32_t fill;                // irregular: positions outside the segments are set to 0
+    uint32_t patience;
+};
+constexpr uint64_t kLocalMax = 8192;          // longest regular segment whose open part the workgroup adds up itself
+
+// Number of entries of the sorted array a[0 .. count) below key; the 64 lanes of a wavefront probe together.
+__device__ __forceinline__ uint64_t wave_lower_bound(const uint64_t* __restrict__ a, uint64_t count, uint64_t key, int lane) {
+    uint64_t lo = 0, hi = count;              // a[i] < key for i < lo;  a[i] >= key for i >= hi
+    while (lo < hi) {
+        const uint64_t step = (hi - lo + 63) >> 6;
+        const uint64_t idx = lo + step * (uint64_t)(lane + 1) - 1;
+        const uint64_t c = (uint64_t)__builtin_popcountll(__ballot(idx < hi && a[idx] < key));
+        const uint64_t first_not_below = lo + step * (c + 1) - 1;
+        hi = first_not_below < hi ? first_not_below : hi;
+        lo = lo + step * c;
+    }
+    return lo;
+}
+
+// 512 elements from position `at` (a multiple of 512 inside the array) of which those in front of `from` do not count:
+// their sum, by one wavefront.
+__device__ __forceinline__ float masked_tile_sum(half8 x, uint64_t at, uint64_t from, int lane) {
+    const uint64_t mine = at + 8 * (uint64_t)lane;
+    const half8 kept = drop_leading(x, from > mine ? (int)(from - mine < 8 ? from - mine : 8) : 0);
+    return read_lane(row_sum_to_last<16>(mfma(const_ones(), kept, splat(0.0f))[0]), 15);
+}
+
+// The sum from position s0 to the start of `tile` out of what the tiles in between have published (whole wavefront).
+__device__ __forceinline__ float lookup_open_sum(const TileScan& a, const ScanWorkspace& ws, uint32_t tile, uint64_t s0, int tile_log2, int lane) {
+    const uint32_t first = (uint32_t)(s0 >> tile_log2);
+    const uint32_t want = ws.epoch * 4u + kStatusAggregate;
+    float acc = 0.0f;
+    for (uint32_t hi = tile; hi > first;) {
+        const uint32_t span = hi - first > 64u ? 64u : hi - first;
+        bool need = (uint32_t)lane < span;
+        float v = 0.0f;
+        uint32_t polls = 0;
+        while (true) {
+            if (need) {
+                const unsigned long long d = load_descriptor(&ws.desc[hi - 1u - (uint32_t)lane]);
+                if ((uint32_t)(d >> 32) == want) {
+                    v = __builtin_bit_cast(float, (uint32_t)d);
+                    need = false;
+                }
+            }
+            unsigned long long missing = __ballot(need);
+            if (missing == 0ull) break;
+            if (++polls > a.patience) {
+                for (; missing != 0ull; missing &= missing - 1ull) {
+                    const int slot = __builtin_ctzll(missing);
+                    const uint64_t begin = (uint64_t)(hi - 1u - (uint32_t)slot) << tile_log2;
+                    float sum = 0.0f;
+                    for (uint64_t at = begin; at < begin + (1ull << tile_log2); at += (uint64_t)kTile)
+                        if (at + (uint64_t)kTile > s0) sum += masked_tile_sum(load8(a.in, at + 8 * (uint64_t)lane), at, s0, lane);
+                    if (lane == slot) v = sum;
+                }
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+        acc += wave_sum(v);
+        hi -= span;
+    }
+    return acc;
+}
+
+// LOCAL (regular segments of 2 to WAVES * 512 elements): no sum is ever looked up, no workspace.
+template <int U, int WAVES, bool REGULAR, int MODE, bool LOCAL>
+__global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U == 4 ? 8 : 4, 8))) void irregular_scan_kernel(TileScan a, ScanWorkspace ws_arg) {
+    static_assert(!LOCAL || REGULAR, "");
+    constexpr int EXCL = MODE & 1, F16 = MODE >> 1;
+    constexpr uint32_t kChunk = (uint32_t)kTile * U;          // one wavefront's share
+    constexpr uint32_t kBlockTile = kChunk * WAVES;           // one workgroup's share
+    constexpr uint64_t kBackMax = (uint64_t)kTile * WAVES;    // the open part that the wavefronts add up themselves
+    constexpr int kTileLog2 = __builtin_ctz(kBlockTile);
+    __shared__ uint32_t s_heads[REGULAR ? 1 : kBlockTile / 32];
+    __shared__ uint64_t s_bound[2];
+    __shared__ float s_wave_value[WAVES], s_back[WAVES];
+    __shared__ uint32_t s_wave_flag[WAVES];
+    __shared__ float s_prefix;
+
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t tile = blockIdx.x;
+    const uint64_t tb = (uint64_t)tile * kBlockTile;
+    const uint64_t base = tb + (uint64_t)wave * kChunk;
+    // the wavefront's share: whole groups of 8 through the range check, the group that the array's end cuts by element
+    const uint64_t left = base < a.n ? a.n - base : 0;
+    const uint32_t count = left < kChunk ? (uint32_t)left : kChunk, whole = count & ~7u;
+    const __amdgpu_buffer_rsrc_t src = make_rsrc(a.in + (count ? base : 0), whole * 2u);
+    half8 x[U];
+    const auto load_share = [&] {
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = buffer_load8(src, (uint32_t)(kTile * u + 8 * lane) * 2u);
+    };
+    if constexpr (REGULAR) load_share();
+
+    // where the open segment starts (tb: nothing reaches into the tile), and which part of the array lies in a segment
+    uint64_t s0 = tb, first = a.shift, last = a.n;
+    uint32_t head = 0;                        // regular: position of the tile's first head
+    bool has_heads = true;
+    if constexpr (REGULAR) {
+        if (tb < a.shift) {
+            head = a.shift;                   // (the first tile of an array that is not 16-byte aligned)
+        } else {
+            const uint64_t p = tb - a.shift;
+            uint64_t q = (uint64_t)((double)p * a.per_elem);                  // p / seg_len, one off at most
+            if (q * a.seg_len > p) --q;
+            if ((q + 1) * a.seg_len <= p) ++q;
+            const uint64_t back = p - q * a.seg_len;
+            s0 = tb - back;
+            const uint64_t h = back ? a.seg_len - back : 0;
+            head = h < kBlockTile ? (uint32_t)h : kBlockTile;
+        }
+    } else {
+        for (uint32_t i = threadIdx.x; i < kBlockTile / 32; i += WAVES * kWave) s_heads[i] = 0u;
+        if (wave < 2) {
+            // entry s lies on position offsets[s] + shift
+            const uint64_t edge = tb + (wave ? (uint64_t)kBlockTile : 0);
+            const uint64_t below = wave_lower_bound(a.offsets, a.nseg + 1, edge > a.shift ? edge - a.shift : 0, lane);
+            if (lane == 0) s_bound[wave] = below;
+        }
+        first = a.offsets[0] + a.shift;
+        last = a.offsets[a.nseg] + a.shift;
+        if (last > a.n) last = a.n;
+        __syncthreads();
+        load_share();
+        const uint64_t lo = s_bound[0], hi = s_bound[1];
+        has_heads = lo < hi;
+        for (uint64_t s = lo + threadIdx.x; s < hi; s += (uint64_t)(WAVES * kWave)) {
+            const uint64_t pos = a.offsets[s] + a.shift - tb;
+            if (pos < (uint64_t)kBlockTile) atomicOr(&s_heads[pos >> 5], 1u << (pos & 31u));
+        }
+        // (nothing is open in front of the first entry and behind the last; an entry on tb itself restarts there)
+        if (lo > 0 && lo <= a.nseg) {
+            const uint64_t at = a.offsets[lo - 1] + a.shift;
+            if (at < tb) s0 = at;
+        }
+    }
+    const uint64_t back = tb - s0;
+    const bool far = !LOCAL && back > kBackMax;
+    // the wavefront's 512 elements of the open part, counted back from the tile's start
+    const uint64_t behind = (uint64_t)kTile * (uint64_t)wave;
+    const bool mine = !far && behind < back;
+    const uint64_t back_at = mine ? tb - behind - (uint64_t)kTile : 0;
+    const __amdgpu_buffer_rsrc_t back_src = make_rsrc(a.in + back_at, mine ? (uint32_t)kTile * 2u : 0u);
+    const half8 back_x = buffer_load8(back_src, 16u * (uint32_t)lane);
+    if constexpr (!REGULAR) __syncthreads();              // the heads are marked
+
+    if (count != whole) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if ((uint32_t)(kTile * u + 8 * lane) == whole) x[u] = load8_guarded(a.in, base + whole, a.n);
+    }
+    uint32_t bits[U];                             // the lane's heads
+    uint64_t flag_before[U];                      // bit l: a head in a lane in front of lane l inside the sub-tile
+    uint32_t seen_before[U];                      // a head in a sub-tile in front
+    float lane_value[U], before[U], run = 0.0f;
+    uint32_t chunk_flag = 0u;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if constexpr (REGULAR) {
+            // the lane's first head, counted from its first element (the heads are head, head + seg_len, ...)
+            const uint32_t at = (uint32_t)wave * kChunk + (uint32_t)(kTile * u + 8 * lane);
+            uint32_t c;
+            if constexpr (LOCAL) {
+                const uint32_t t = at - head;
+                c = at <= head ? head - at : __umulhi(t + (uint32_t)a.seg_len - 1u, a.magic) * (uint32_t)a.seg_len - t;
+            } else {
+                // (longer than kLocalMax: the next heads by repeated addition, a few at most per tile)
+                uint64_t h = head;
+                while (h < at) h += a.seg_len;
+                c = h - at < 8u ? (uint32_t)(h - at) : 8u;
+            }
+            bits[u] = c < 8u ? (a.pattern << c) & 0xffu : 0u;
+        } else {
+            bits[u] = has_heads ? (uint32_t)reinterpret_cast<const uint8_t*>(s_heads)[wave * (kChunk / 8) + (kTile / 8) * u + lane] : 0u;
+        }
+        uint64_t flags = __ballot(bits[u] != 0u);
+        float v[1] = {0.0f};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[0] = ((bits[u] >> e) & 1u ? 0.0f : v[0]) + (float)x[u][e];
+        flags = wave_seg_scan_inclusive_bits<1>(flags, v);
+        flag_before[u] = flags << 1;
+        const uint32_t sub_flag = (uint32_t)(flags >> 63);
+        seen_before[u] = chunk_flag;
+        lane_value[u] = wave_shr1(v[0]);
+        const float sub_value = read_lane(v[0], 63);
+        before[u] = run;
+        run = sub_flag ? sub_value : run + sub_value;
+        chunk_flag |= sub_flag;
+    }
+    const float back_sum = mine ? masked_tile_sum(back_x, back_at, s0, lane) : 0.0f;
+    if (lane == 0) {
+        s_wave_value[wave] = run;
+        s_wave_flag[wave] = chunk_flag;
+        s_back[wave] = back_sum;
+    }
+    __syncthreads();
+    if constexpr (!LOCAL) {
+        const ScanWorkspace ws = resolve_workspace(ws_arg);
+        if (wave == 0) {
+            // what later tiles may need of this one: the sum behind its last head
+            float total = 0.0f;
+            for (int v = WAVES - 1; v >= 0; --v) {
+                total += s_wave_value[v];
+                if (s_wave_flag[v]) break;
+            }
+            if (lane == 0) {
+                if (tile == 0 && ws.state != nullptr && !ws.device_managed) ws.state[0] = ws.epoch;
+                __hip_atomic_store(&ws.desc[tile], pack_desc(ws.epoch, kStatusAggregate, total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            if (far) {
+                const float pre = lookup_open_sum(a, ws, tile, s0, kTileLog2, lane);
+                if (lane == 0) s_prefix = pre;
+            }
+        }
+        if (far) __syncthreads();
+    }
+    // carry from the wavefronts in front, back to the nearest one that holds a head, else from in front of the tile
+    float ext = 0.0f;
+    bool open = true;
+    for (int v = wave - 1; v >= 0; --v) {
+        ext += s_wave_value[v];
+        if (s_wave_flag[v]) {
+            open = false;
+            break;
+        }
+    }
+    if (open && back != 0) {
+        if (far) {
+            ext += s_prefix;
+        } else {
+            float sum = 0.0f;
+#pragma unroll
+            for (int v = 0; v < WAVES; ++v) sum += s_back[v];
+            ext += sum;
+        }
+    }
+    const uint32_t valid_lo = first > base ? (uint32_t)(first - base < kChunk ? first - base : kChunk) : 0u;
+    const uint32_t valid_hi = last > base ? (uint32_t)(last - base < kChunk ? last - base : kChunk) : 0u;
+    const bool inside = valid_lo == 0u && valid_hi == kChunk && a.vector_stores != 0u;
+    void* const dst = F16 ? static_cast<void*>(static_cast<_Float16*>(a.out) + base) : static_cast<void*>(static_cast<float*>(a.out) + base);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const float into_sub = seen_before[u] ? before[u] : before[u] + ext;
+        float q = __builtin_amdgcn_inverse_ballot_w64(flag_before[u]) ? lane_value[u] : lane_value[u] + into_sub;
+        float p[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float kept = (bits[u] >> e) & 1u ? 0.0f : q;
+            q = kept + (float)x[u][e];
+            p[e] = EXCL ? kept : q;
+        }
+        const uint32_t k = (uint32_t)(kTile * u + 8 * lane);
+        if (inside) {
+            store8_t<F16>(dst, k, (float4v){p[0], p[1], p[2], p[3]}, (float4v){p[4], p[5], p[6], p[7]});
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const bool in_segment = k + e >= valid_lo && k + e < valid_hi;
+                const bool cleared = !REGULAR && a.fill && !in_segment && k + e < count && base + k + e >= a.shift;
+                if (in_segment || cleared) {
+                    const float r = in_segment ? p[e] : 0.0f;
+                    if constexpr (F16) static_cast<_Float16*>(dst)[k + e] = (_Float16)r;
+                    else static_cast<float*>(dst)[k + e] = r;
+                }
+            }
+        }
+    }
+}
+
+}  // namespace tcr

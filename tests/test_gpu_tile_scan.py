@@ -1,0 +1,173 @@
+"""Scans of one tile per workgroup with nothing chained: the open part of a segment in front of a tile is added up by the
+tile's own wavefronts or looked up from the tiles in between, and the positions outside the segments can be cleared in
+the same pass.  Whole numbers: exact."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1811_09736_amd import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tcr():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1811_09736_amd import binding
+    binding.set_variant("reset")
+    binding.tuning_import("")
+    yield binding
+    binding.set_variant("reset")
+    binding.set_workspace(None)
+    binding.check_device_flags()
+
+
+@pytest.fixture(params=["bounded", "none"])
+def wait(request, tcr):
+    tcr.set_variant("scan_wait", request.param)
+    yield request.param
+    tcr.set_variant("reset")
+
+
+def cut(n, recipe, seed):
+    return workloads.make_offsets(n, recipe, seed).view(np.int64)
+
+
+# several heads in a lane's eight elements (2 to 7), the last lengths whose open part 8 and 16 wavefronts add up, the first
+# that is looked up, and segments of several tiles; tile sizes change at 2^21, 2^22 and 2^23 elements
+@pytest.mark.parametrize("seg", [2, 3, 6, 7, 9, 31, 511, 513, 1023, 1025, 4095, 4097, 8191, 8193, 12345, 40001, 300007])
+@pytest.mark.parametrize("n", [70001, (1 << 21) + 4099, (1 << 23) + 70001])
+def test_regular_segments(tcr, oracle, wait, seg, n):
+    if n < 2 * seg or (wait == "none" and (seg <= 8192 or n > 1 << 23)):
+        pytest.skip("nothing is waited for" if seg <= 8192 else "too short, or every tile would add up a large array")
+    n = n // seg * seg
+    x = workloads.make_input(n, "int4", seg % 97)
+    xd = torch.from_numpy(x).cuda()
+    ref = oracle.segmented_scan(x, seg)
+    out = torch.full((n + 8,), -3.0, dtype=torch.float32, device="cuda")
+    tcr.segmented_scan(xd, seg, out=out[:n])
+    assert np.array_equal(out[:n].cpu().numpy().astype(np.float64), ref)
+    assert torch.all(out[n:] == -3.0)
+    if n < 1 << 22:
+        assert np.array_equal(tcr.segmented_scan_ex(xd, seg, tcr.SCAN_EXCLUSIVE).cpu().numpy().astype(np.float64), ref - x)
+        assert np.array_equal(tcr.segmented_scan_ex(xd, seg, tcr.OUT_F16).cpu().numpy(), ref.astype(np.float16))
+
+
+def test_regular_segments_in_an_array_that_streams(tcr, oracle):
+    # (the workgroup size for short segments changes behind 2^24 elements)
+    for seg in (7, 1001, 3001):
+        n = ((1 << 24) + 99999) // seg * seg
+        x = workloads.make_input(n, "int4", seg)
+        got = tcr.segmented_scan(torch.from_numpy(x).cuda(), seg).cpu().numpy().astype(np.float64)
+        assert np.array_equal(got, oracle.segmented_scan(x, seg))
+
+
+@pytest.mark.parametrize("recipe", ["uniform1", "uniform16", "uniform5000", "lognormal256", "few3"])
+@pytest.mark.parametrize("n,shift", [(1, 0), (8191, 0), (8193, 3), (70001, 0), ((1 << 21) + 5, 5), ((1 << 22) + 9, 0)])
+def test_irregular_segments(tcr, oracle, wait, recipe, n, shift):
+    base = workloads.make_input(n + 8, "int4", n % 89)
+    x = base[shift:shift + n].copy()
+    xd = torch.from_numpy(base).cuda()[shift:shift + n]
+    off = cut(n, recipe, 3)
+    od = torch.from_numpy(off).cuda()
+    ref = oracle.irregular_scan(x, off)
+    assert np.array_equal(tcr.irregular_scan(xd, od).cpu().numpy().astype(np.float64), ref)
+    assert np.array_equal(tcr.irregular_scan_ex(xd, od, tcr.SCAN_EXCLUSIVE).cpu().numpy().astype(np.float64),
+                          oracle.irregular_scan_exclusive(x, off))
+
+
+def test_offsets_on_the_edges_of_tiles(tcr, oracle, wait):
+    n = 6 * 8192 + 11
+    x = workloads.make_input(n, "int4", 9)
+    xd = torch.from_numpy(x).cuda()
+    t = 8192
+    for off in ([0, t, 2 * t, 5 * t, n], [0, t - 1, t + 1, 3 * t - 1, n], [t, t, t, 4 * t, 4 * t, 6 * t], [0, n], [0, 1, n - 1, n],
+                [5 * t + 3, 5 * t + 3, n], [0, 0, 0, 7, 3 * t + 8, 3 * t + 8, n, n, n]):
+        off = np.array(off, dtype=np.int64)
+        got = tcr.irregular_scan(xd, torch.from_numpy(off).cuda()).cpu().numpy().astype(np.float64)
+        assert np.array_equal(got, oracle.irregular_scan(x, off)), off
+
+
+@pytest.mark.parametrize("flags", [0, 1, 2])
+@pytest.mark.parametrize("n", [20000, (1 << 24) + 40000])
+def test_a_new_result_is_zero_outside_the_segments(tcr, oracle, n, flags):
+    # memory that the allocator hands out again, full of something else; above 2^24 elements a kernel of its own clears
+    x = workloads.make_input(n, "int4", 4)
+    xd = torch.from_numpy(x).cuda()
+    dtype = torch.float16 if flags & 2 else torch.float32
+    for off in ([9000, 9007, 15001], [0, 17], [n - 3, n], [777, 777], [n], [0, n]):
+        off = np.array(off, dtype=np.int64)
+        dirty = torch.full((n,), float("nan"), dtype=dtype, device="cuda")
+        del dirty
+        got = tcr.irregular_scan_ex(xd, torch.from_numpy(off).cuda(), flags)
+        assert got.dtype == dtype
+        ref = oracle.irregular_scan_exclusive(x, off) if flags & 1 else oracle.irregular_scan(x, off)
+        want = torch.from_numpy(ref.astype(np.float16 if flags & 2 else np.float32)).cuda()
+        assert torch.equal(got, want), off
+    for shift in (1, 6):
+        out = torch.full((n + 8,), float("nan"), dtype=dtype, device="cuda")
+        od = torch.tensor([9000, 9007, 15001], device="cuda")
+        st = tcr.raw().tcr_irregular_scan_filled(xd[shift:].data_ptr(), od.data_ptr(), out[shift:].data_ptr(), n - 8, 2, flags,
+                                                 int(torch.cuda.current_stream().cuda_stream))
+        assert st == tcr.OK
+        assert torch.isnan(out[:shift]).all() and torch.isnan(out[shift + n - 8:]).all()
+        assert not torch.isnan(out[shift:shift + n - 8]).any()
+        assert not out[shift:shift + 9000].any() and not out[shift + 15001:shift + n - 8].any()
+
+
+def test_a_small_caller_workspace(tcr, oracle):
+    # a descriptor per 32768 elements has always been enough
+    n = 1 << 20
+    x = workloads.make_input(n, "int4", 8)
+    xd = torch.from_numpy(x).cuda()
+    buf = torch.full((768,), 0x5A, dtype=torch.uint8, device="cuda")
+    try:
+        tcr.set_workspace(buf)
+        for seg in (12345, 1001):
+            m = n // seg * seg
+            assert np.array_equal(tcr.segmented_scan(xd[:m], seg).cpu().numpy().astype(np.float64), oracle.segmented_scan(x[:m], seg))
+    finally:
+        torch.cuda.synchronize()
+        tcr.set_workspace(None)
+
+
+def test_recorded(tcr, oracle):
+    n = 300 * 1001
+    x = workloads.make_input(n, "int4", 2)
+    xd = torch.from_numpy(x).cuda()
+    off = cut(n, "lognormal256", 1)
+    od = torch.from_numpy(off).cuda()
+    a, b, c = (torch.empty(n, dtype=torch.float32, device="cuda") for _ in range(3))
+    side = torch.cuda.Stream()
+
+    def calls():
+        tcr.segmented_scan(xd, 1001, out=a)
+        tcr.segmented_scan(xd, 30030, out=b)
+        tcr.irregular_scan(xd, od, out=c)
+
+    # lengths whose open part the workgroups add up themselves need no workspace: recorded on a stream that has none
+    fresh = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(fresh, stream=side):
+        tcr.segmented_scan(xd, 1001, out=a)
+    with torch.cuda.stream(side):
+        calls()
+    side.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        calls()
+    for _ in range(4):
+        for t in (a, b, c):
+            t.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(a.cpu().numpy().astype(np.float64), oracle.segmented_scan(x, 1001))
+        assert np.array_equal(b.cpu().numpy().astype(np.float64), oracle.segmented_scan(x, 30030))
+        assert np.array_equal(c.cpu().numpy().astype(np.float64), oracle.irregular_scan(x, off))
+        with torch.cuda.stream(side):
+            again = tcr.segmented_scan(xd, 30030)
+        side.synchronize()
+        assert torch.equal(again, b)
+    tcr.check_device_flags(side)
