@@ -146,7 +146,7 @@ tcr_status tcr_scan_ex(const void *in, void *out, uint64_t n, uint32_t flags, vo
  * (with fewer segments than a quarter of the tiles it runs as two kernels: the pipelined chain of the long
  * regular scans takes the tiles without a segment start, a second kernel the others); an array that the chip holds at
  * once (up to 2^24 elements) is scanned by one kernel whose tiles search the offsets and look up what they need;
- * the reduction keeps its tiles independent and two small kernels add the one sum per tile that reaches in
+ * the reduction keeps its tiles independent and a small kernel adds the one sum per tile that reaches in
  * from earlier tiles -- plain loads in a fixed order, so the reduction's results are the same from run to run.
  * in and out need only their natural alignment (2 and 4 bytes): the tiles start at the 16-byte boundary at or
  * below `in` (up to 7 elements in front of it are read and ignored), and a scan whose `out` does not sit at the

@@ -444,7 +444,7 @@ extern "C" tcr_status tcr_tuning_import(const char* text) {
 }
 
 extern "C" const char* tcr_kernel_name(int op, uint64_t n, uint64_t seg_len) {
-    if (op == 4) return n ? "irregular_bounds_kernel+irregular_reduce_kernel+irregular_groups_kernel+irregular_carry_kernel" : "fill_zero_kernel";
+    if (op == 4) return n ? "irregular_bounds_kernel+irregular_reduce_kernel+irregular_finish_kernel" : "fill_zero_kernel";
     if (op == 5) return n ? "irregular_bounds_kernel+irregular_scan_kernel" : "";
     if (op == 2 || op == 3) seg_len = n;
     if (n == 0 || seg_len == 0 || n % seg_len != 0) return "";
@@ -458,7 +458,7 @@ extern "C" const char* tcr_kernel_name(int op, uint64_t n, uint64_t seg_len) {
             if (pick == kReduceAnyPacked || pick == kReduceAnyPackedAlt) return "packed_rows_reduce_kernel";
             if (seg_len < kTiledReduceMin) return "generic_thread_kernel";
             if (pick == kReduceAnyRows) return "rows_reduce_kernel";
-            if (pick == kReduceAnyTiles || pick == kReduceAnyTilesAlt) return "irregular_reduce_kernel<regular>+irregular_groups_kernel+irregular_carry_kernel";
+            if (pick == kReduceAnyTiles || pick == kReduceAnyTilesAlt) return "irregular_reduce_kernel<regular>+irregular_finish_kernel";
             return seg_len <= 2 * kWaveSpanMax ? "masked_wave_reduce_kernel" : "masked_span_reduce_kernel+reduce_final_kernel";
         }
         if (is_pow2(seg_len) && seg_len <= 8) return "tiny_scan_kernel";            // (the plain scan; other modes: the tiles)
@@ -555,10 +555,9 @@ extern "C" uint64_t tcr_workspace_bytes(int op, uint64_t n, uint64_t seg_len) {
         desc = (irregular ? 2 : 1) * irregular_tiles_max(true, padded);
         if (irregular) words = irregular_words_max(true, padded); // where the tile boundaries fall among the offsets
     } else {
-        // tables, one carried-segment index and one pair per tile and per group of 64 tiles; the sums of squares
-        // add a second set of pairs
+        // tables, one carried-segment index and one pair per tile; the sums of squares add a second set of pairs
         const uint64_t tiles = irregular_tiles_max(false, padded);
-        words = irregular_words_max(false, padded) + (moments ? tiles + ceil_div(tiles, kWave) : 0);
+        words = irregular_words_max(false, padded) + (moments ? tiles : 0);
     }
     if (!irregular) {
         // Regular calls run the tiled kernels above for some lengths and alignments; otherwise, over every variant

@@ -668,11 +668,11 @@ inline uint64_t irregular_tile_elems(bool scan, int shape) {
 }
 inline uint64_t irregular_tiles(bool scan, uint64_t n, int shape) { return ceil_div(n, irregular_tile_elems(scan, shape)); }
 // 8-byte words of the partials area: the look-up table(s) of the tile boundaries, and for the reduction one
-// carried-segment index and one pair per tile and one pair per group of 64 tiles.
+// carried-segment index and one pair per tile.
 inline uint64_t irregular_words(bool scan, uint64_t n, int shape) {
     const uint64_t tiles = irregular_tiles(scan, n, shape);
     // (scan: the look-up table and one TileLink per tile)
-    return scan ? 2 * tiles + 1 : 2 * (tiles + 1) + 2 * tiles + ceil_div(tiles, kWave);
+    return scan ? 2 * tiles + 1 : 2 * (tiles + 1) + 2 * tiles;
 }
 // The largest of these over the tile shapes (the smallest tiles): what tcr_workspace_bytes reports.
 inline uint64_t irregular_tiles_max(bool scan, uint64_t n) {
@@ -869,37 +869,39 @@ inline tcr_status launch_irregular_reduce(const _Float16* in, const uint64_t* of
     in -= shift;
     n += shift;
     const uint64_t tiles = irregular_tiles(false, n, shape);
-    const uint64_t groups = ceil_div(tiles, kWave);
     const bool regular = offsets == nullptr;
     const unsigned ch = kind == kBoth ? 2u : 1u;
     Workspace* ws = nullptr;
     bool capturing = false;
     tcr_status st = get_workspace(s, &ws, &capturing);
     if (st != TCR_OK) return st;
-    st = ensure_partials(ws, s, 2 * (irregular_words(false, n, shape) + (ch - 1) * (tiles + groups)), capturing);
+    st = ensure_partials(ws, s, 2 * (irregular_words(false, n, shape) + (ch - 1) * tiles), capturing);
     if (st != TCR_OK) return st;
     uint64_t* starts = reinterpret_cast<uint64_t*>(ws->partials);
     uint64_t* ends = starts + (tiles + 1);
     uint64_t* carried = ends + (tiles + 1);
     TilePair* pairs = reinterpret_cast<TilePair*>(carried + tiles);              // ch * tiles
-    TilePair* group_pairs = pairs + ch * tiles;                                   // ch * groups
-    if (!regular) {
+    // (tiles that search the offsets themselves: n = 2^20 / 2^24, lognormal lengths, 11.4 / 15.9 us with the look-up kernel
+    // in front, 8.0 / 13.2 without; 2^25 22.0 / 22.2, 2^26 31.1 / 35.0 -- the searches are then what the tiles wait for)
+    const bool search = !regular && shape == 0 && tiles <= 2048;
+    if (!regular && !search) {
         irregular_bounds_kernel<<<dim3((unsigned)ceil_div(tiles + 1, kBoundsWaves * kBoundsPerWave)), dim3(kBoundsWaves * kWave), 0, s>>>(
             offsets, nseg + 1, elems, tiles + 1, shift, starts, ends);
         st = check_launch("irregular_bounds_kernel");
         if (st != TCR_OK) return st;
     }
-    if (shape == 1) launch_irregular_reduce_shape<4, 8>(regular, kind, in, offsets, out, out2, n, starts, ends, seg_len, nseg, shift, pairs, carried, tiles, s);
+    if (search) {
+        const dim3 grid((unsigned)tiles), block(4 * kWave);
+        if (kind == kBoth) irregular_reduce_kernel<4, 4, false, kBoth, true><<<grid, block, 0, s>>>(in, offsets, out, out2, n, nullptr, nullptr, 0, nseg, shift, pairs, carried);
+        else irregular_reduce_kernel<4, 4, false, kSum, true><<<grid, block, 0, s>>>(in, offsets, out, nullptr, n, nullptr, nullptr, 0, nseg, shift, pairs, carried);
+    } else if (shape == 1) launch_irregular_reduce_shape<4, 8>(regular, kind, in, offsets, out, out2, n, starts, ends, seg_len, nseg, shift, pairs, carried, tiles, s);
     else if (shape == 2) launch_irregular_reduce_shape<2, 8>(regular, kind, in, offsets, out, out2, n, starts, ends, seg_len, nseg, shift, pairs, carried, tiles, s);
     else launch_irregular_reduce_shape<4, 4>(regular, kind, in, offsets, out, out2, n, starts, ends, seg_len, nseg, shift, pairs, carried, tiles, s);
     st = check_launch("irregular_reduce_kernel");
     if (st != TCR_OK || tiles == 1) return st;          // a single tile has nothing in front of it
-    const dim3 carry_grid((unsigned)ceil_div(groups, kCarryWaves), ch);
-    irregular_groups_kernel<<<carry_grid, dim3(kCarryWaves * kWave), 0, s>>>(pairs, tiles, group_pairs);
-    st = check_launch("irregular_groups_kernel");
-    if (st != TCR_OK) return st;
-    irregular_carry_kernel<<<carry_grid, dim3(kCarryWaves * kWave), 0, s>>>(pairs, group_pairs, carried, tiles, out, out2);
-    return check_launch("irregular_carry_kernel");
+    irregular_finish_kernel<kFinishThreads, kFinishFar><<<dim3((unsigned)ceil_div(tiles, kFinishThreads), ch), dim3(kFinishThreads), 0, s>>>(
+        pairs, carried, tiles, out, out2);
+    return check_launch("irregular_finish_kernel");
 }
 
 // Regular segments from 17 elements on, no power of two: whole segments per workgroup, masked row products

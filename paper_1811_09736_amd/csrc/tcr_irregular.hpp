@@ -13,7 +13,7 @@
 // uses the descriptor chain of the regular scans -- a tile that contains a segment start publishes the
 // sum since its last start as a finished prefix at once, because no later tile can need more of it --
 // while the reduction, where at most one result per tile depends on earlier tiles, leaves the tiles
-// independent and adds that one carry afterwards (two small kernels over the per-tile sums).
+// independent and adds that one carry afterwards (a small kernel over the per-tile sums).
 //
 // What a tile needs from the offsets is found before it starts: irregular_bounds_kernel writes, per
 // tile boundary, how many offsets lie below it, so a tile reads its range of entries with one look-up
@@ -131,6 +131,20 @@ __device__ __forceinline__ uint64_t group_lower_bound(const uint64_t* __restrict
             hi = first_not_below < hi ? first_not_below : hi;
             lo = lo + step * c;
         }
+    }
+    return lo;
+}
+
+// Number of entries of the sorted array a[0 .. count) below key; the 64 lanes of a wavefront probe together.
+__device__ __forceinline__ uint64_t wave_lower_bound(const uint64_t* __restrict__ a, uint64_t count, uint64_t key, int lane) {
+    uint64_t lo = 0, hi = count;              // a[i] < key for i < lo;  a[i] >= key for i >= hi
+    while (lo < hi) {
+        const uint64_t step = (hi - lo + 63) >> 6;
+        const uint64_t idx = lo + step * (uint64_t)(lane + 1) - 1;
+        const uint64_t c = (uint64_t)__builtin_popcountll(__ballot(idx < hi && a[idx] < key));
+        const uint64_t first_not_below = lo + step * (c + 1) - 1;
+        hi = first_not_below < hi ? first_not_below : hi;
+        lo = lo + step * c;
     }
     return lo;
 }
@@ -466,12 +480,15 @@ __device__ __forceinline__ uint32_t wave_scan_inclusive_u32(uint32_t x) {
 // between the lane's first element and the segment's last, the sum from in front -- so consecutive lanes write
 // consecutive results.  The one result per tile that belongs to a segment begun in an earlier tile is written
 // without that earlier part; the tile records which segment it is (carried[tile], or none) and its own pair
-// (pairs[tile]) for the carry kernels.
+// (pairs[tile]) for the finishing kernel.
 // REGULAR: entry s is s * seg_len, s = 0 .. nseg, instead of offsets[s] (offsets and the tables are not read).
 // shift: as for irregular_scan_kernel (`in` points that many elements in front of the caller's array).
 // KIND: sums of the elements, of their squares, or both (out2 and the pairs of the second channel, which
 // follow the first channel's `tiles` pairs, are used for kBoth only).
-template <int U, int WAVES, bool REGULAR, int KIND = kSum>
+// SEARCH (irregular segments): the tile's range of entries is searched here, one edge per wavefront, instead of read from
+// the tables -- before the data is asked for: behind a tile's worth of loads every round of the search would wait for
+// them (arrays of up to 2^22 elements, where a launch in front costs more than the search).
+template <int U, int WAVES, bool REGULAR, int KIND = kSum, bool SEARCH = false>
 __global__ __launch_bounds__(WAVES * kWave) void irregular_reduce_kernel(const _Float16* __restrict__ in,
                                                                          const uint64_t* __restrict__ offsets,
                                                                          float* __restrict__ out, float* __restrict__ out2,
@@ -511,7 +528,20 @@ __global__ __launch_bounds__(WAVES * kWave) void irregular_reduce_kernel(const _
     // which offsets entries fall into the tile: asked for first, so that the entries themselves can be requested
     // while the tile's data is still on its way (the barriers below order LDS only and wait for neither)
     uint64_t head_lo = 0, head_hi = 0, end_lo = 0, end_hi = 0;
-    if constexpr (!REGULAR) {
+    if constexpr (SEARCH) {
+        static_assert(!SEARCH || (!REGULAR && WAVES >= 4), "");
+        if (wave < 4) {
+            // entries below tb, below te, and the same with the entries on the edge added (entry s lies on offsets[s] + shift)
+            const uint64_t edge = tb + ((wave & 1) ? (uint64_t)kBlockTile : 0) + (uint64_t)(wave >> 1);
+            const uint64_t below = wave_lower_bound(offsets, nseg + 1, edge > shift ? edge - shift : 0, lane);
+            if (lane == 0) s_bound[wave] = below;
+        }
+        __syncthreads();
+        head_lo = s_bound[0];
+        head_hi = s_bound[1];
+        end_lo = s_bound[2];
+        end_hi = s_bound[3];
+    } else if constexpr (!REGULAR) {
         head_lo = starts_below[tile];
         head_hi = starts_below[tile + 1];
         end_lo = ends_below[tile];
@@ -742,57 +772,97 @@ __global__ __launch_bounds__(WAVES * kWave) void irregular_reduce_kernel(const _
     }
 }
 
-// The pairs of 64 consecutive tiles combined into one (one wavefront per group).  blockIdx.y is the channel:
-// channel c has its `tiles` pairs behind those of channel c - 1, likewise its groups.
-constexpr int kCarryWaves = 4;
-__global__ __launch_bounds__(kCarryWaves * kWave) void irregular_groups_kernel(const TilePair* __restrict__ pairs,
-                                                                               uint64_t tiles,
-                                                                               TilePair* __restrict__ groups) {
+// Adds to the one carried result of every tile the sum that reaches the tile from the tiles in front of it.  A workgroup
+// takes THREADS consecutive tiles, one per thread; what reaches its first ones from further in front it adds up
+// itself, back to the nearest tile with a head -- the tile in front, mostly.
+// Latency: one launch whose loads do not wait for each other (two kernels, one combining groups of 64 tiles, took 8.7 us
+// at 8192 tiles and two launches).  Plain loads, fixed order: the results do not vary from run to run.  blockIdx.y is
+// the channel: channel c has its `tiles` pairs behind those of channel c - 1 (results: out, then out2).
+// 256 threads and 16 tiles each: segments of 16 elements / seven segments at n = 2^26 43.7 / 28.4 us for the whole
+// reduction, 45.4 / 29.6 with 1024 threads (slower to start), 43.7 / 29.3 with 32 tiles; 45.8 / 28.7 with the two kernels.
+constexpr int kFinishThreads = 256, kFinishFar = 16;
+template <int THREADS, int FAR>
+__global__ __launch_bounds__(THREADS) void irregular_finish_kernel(const TilePair* __restrict__ pairs,
+                                                                          const uint64_t* __restrict__ carried, uint64_t tiles,
+                                                                          float* __restrict__ out, float* __restrict__ out2) {
+    constexpr int kWaves = THREADS / kWave;
+    __shared__ float s_value[kWaves], s_far[kWaves];
+    __shared__ uint32_t s_flag[kWaves];
+    __shared__ uint32_t s_wanted, s_nearest;
     const int lane = threadIdx.x & (kWave - 1);
-    const uint64_t g = (uint64_t)blockIdx.x * kCarryWaves + (uint64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (g * kWave >= tiles) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     pairs += (uint64_t)blockIdx.y * tiles;
-    groups += (uint64_t)blockIdx.y * ((tiles + kWave - 1) / kWave);
-    const uint64_t t = g * kWave + (uint64_t)lane;
-    TilePair mine = {0.0f, 0u};
-    if (t < tiles) mine = pairs[t];
-    wave_seg_scan_inclusive(mine.flag, mine.value);
-    if (lane == kWave - 1) groups[g] = mine;
-}
-
-// Adds to the one carried result of every tile the sum that reaches the tile from the tiles in front of
-// it: the groups back to the nearest one with a head, then the tiles of its own group.  Plain loads, fixed
-// order: the results do not vary from run to run.  blockIdx.y is the channel (results: out, then out2).
-__global__ __launch_bounds__(kCarryWaves * kWave) void irregular_carry_kernel(const TilePair* __restrict__ pairs,
-                                                                              const TilePair* __restrict__ groups,
-                                                                              const uint64_t* __restrict__ carried,
-                                                                              uint64_t tiles, float* __restrict__ out,
-                                                                              float* __restrict__ out2) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const uint64_t g = (uint64_t)blockIdx.x * kCarryWaves + (uint64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (g * kWave >= tiles) return;
-    pairs += (uint64_t)blockIdx.y * tiles;
-    groups += (uint64_t)blockIdx.y * ((tiles + kWave - 1) / kWave);
     if (blockIdx.y) out = out2;
-    const uint64_t t = g * kWave + (uint64_t)lane;
-    const uint64_t seg = t < tiles ? carried[t] : kNoSegment;
-    if (__ballot(seg != kNoSegment) == 0ull) return;
-    float into_group = 0.0f;
-    for (uint64_t reach = g; reach > 0; reach = reach > (uint64_t)kWave ? reach - kWave : 0) {
-        const bool valid = (uint64_t)lane < reach;
-        TilePair q = {0.0f, 0u};
-        if (valid) q = groups[reach - 1 - (uint64_t)lane];          // lane 0 reads the nearest group
-        const unsigned long long closed = __ballot(valid && q.flag != 0u);
-        const int nearest = closed != 0ull ? __builtin_ctzll(closed) : kWave;
-        into_group += wave_sum((valid && lane <= nearest) ? q.value : 0.0f);
-        if (closed != 0ull) break;
-    }
+    const uint64_t first = (uint64_t)blockIdx.x * THREADS;
+    const uint64_t t = first + threadIdx.x;
+    if (threadIdx.x == 0) s_wanted = 0u;
     TilePair mine = {0.0f, 0u};
-    if (t < tiles) mine = pairs[t];
+    uint64_t seg = kNoSegment;
+    if (t < tiles) {
+        mine = pairs[t];
+        seg = carried[t];
+    }
+    const float had = seg != kNoSegment ? out[seg] : 0.0f;
     wave_seg_scan_inclusive(mine.flag, mine.value);
+    if (lane == kWave - 1) {
+        s_value[wave] = mine.value;
+        s_flag[wave] = mine.flag;
+    }
+    __syncthreads();
+    float ext = 0.0f;
+    bool open = true;                                     // no tile with a head in the wavefronts in front
+    for (int v = wave - 1; v >= 0; --v) {
+        ext += s_value[v];
+        if (s_flag[v]) {
+            open = false;
+            break;
+        }
+    }
     const uint32_t flag_before = wave_shr1_u32(mine.flag);
     const float value_before = wave_shr1(mine.value);
-    if (seg != kNoSegment) out[seg] += flag_before ? value_before : value_before + into_group;
+    const bool reaches = seg != kNoSegment && open && flag_before == 0u;     // a sum from in front of the workgroup's tiles
+    if (first != 0 && reaches) s_wanted = 1u;
+    __syncthreads();
+    float far = 0.0f;
+    if (s_wanted) {
+        // FAR tiles per thread and step, all asked for before the first is looked at; the nearest THREADS alone first
+        auto add_tiles = [&](uint64_t hi, auto tiles_per_thread) -> bool {
+            constexpr int kPer = decltype(tiles_per_thread)::value;
+            if (threadIdx.x == 0) s_nearest = ~0u;        // distance of the nearest tile with a head
+            __syncthreads();
+            TilePair q[kPer];
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                const uint64_t at = (uint64_t)(k * THREADS) + threadIdx.x;
+                q[k] = pairs[at < hi ? hi - 1 - at : 0];
+            }
+            uint32_t nearest = ~0u;
+#pragma unroll
+            for (int k = kPer - 1; k >= 0; --k) {
+                const uint32_t at = (uint32_t)(k * THREADS) + threadIdx.x;
+                if (at < hi && q[k].flag != 0u) nearest = at;
+            }
+            if (nearest != ~0u) atomicMin(&s_nearest, nearest);
+            __syncthreads();
+            const uint32_t stop = s_nearest;
+            float sum = 0.0f;
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                const uint32_t at = (uint32_t)(k * THREADS) + threadIdx.x;
+                if (at < hi && at <= stop) sum += q[k].value;
+            }
+            sum = wave_sum(sum);
+            if (lane == 0) s_far[wave] = sum;
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) far += s_far[w];
+            return stop != ~0u;                           // (the same in every thread)
+        };
+        if (!add_tiles(first, std::integral_constant<int, 1>{}))
+            for (uint64_t hi = first - THREADS; hi > 0; hi = hi > (uint64_t)(THREADS * FAR) ? hi - THREADS * FAR : 0)
+                if (add_tiles(hi, std::integral_constant<int, FAR>{})) break;
+    }
+    if (seg != kNoSegment) out[seg] = had + (flag_before ? value_before : value_before + ext + (open ? far : 0.0f));
 }
 
 }  // namespace tcr

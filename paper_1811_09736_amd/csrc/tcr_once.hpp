@@ -35,20 +35,6 @@ struct TileScan {
 };
 constexpr uint64_t kLocalMax = 8192;          // longest regular segment whose open part the workgroup adds up itself
 
-// Number of entries of the sorted array a[0 .. count) below key; the 64 lanes of a wavefront probe together.
-__device__ __forceinline__ uint64_t wave_lower_bound(const uint64_t* __restrict__ a, uint64_t count, uint64_t key, int lane) {
-    uint64_t lo = 0, hi = count;              // a[i] < key for i < lo;  a[i] >= key for i >= hi
-    while (lo < hi) {
-        const uint64_t step = (hi - lo + 63) >> 6;
-        const uint64_t idx = lo + step * (uint64_t)(lane + 1) - 1;
-        const uint64_t c = (uint64_t)__builtin_popcountll(__ballot(idx < hi && a[idx] < key));
-        const uint64_t first_not_below = lo + step * (c + 1) - 1;
-        hi = first_not_below < hi ? first_not_below : hi;
-        lo = lo + step * c;
-    }
-    return lo;
-}
-
 // 512 elements from position `at` (a multiple of 512 inside the array) of which those in front of `from` do not count:
 // their sum, by one wavefront.
 __device__ __forceinline__ float masked_tile_sum(half8 x, uint64_t at, uint64_t from, int lane) {
