@@ -220,7 +220,8 @@ tcr_status tcr_scan(const void *in, float *out, uint64_t n, void *stream);
  *   "scan_wait"    "bounded" (default: the chained scan of an array that the chip holds at once waits a bounded time for
  *                  the sum of an earlier tile, then adds that tile up again) | "none" (adds up at once what is not there
  *                  yet; for tests)
- *   "reduce_finish" "second_kernel" (default: the paper's two-kernel device-level reduction, Section 4) |
+ *   "reduce_finish" "second_kernel" (default: the paper's two-kernel device-level reduction, Section 4; arrays of up to 2^23
+ *                  elements finish in one launch all the same) |
  *                  "fused" (one kernel: the workgroup that finishes last adds up the partials)
  *   "reset"        any value: back to the defaults
  * Returns TCR_ERR_INVALID_ARG for an unknown key or value.  Process-wide; not thread safe.

@@ -459,7 +459,8 @@ extern "C" const char* tcr_kernel_name(int op, uint64_t n, uint64_t seg_len) {
             if (seg_len < kTiledReduceMin) return "generic_thread_kernel";
             if (pick == kReduceAnyRows) return "rows_reduce_kernel";
             if (pick == kReduceAnyTiles || pick == kReduceAnyTilesAlt) return "irregular_reduce_kernel<regular>+irregular_finish_kernel";
-            return seg_len <= 2 * kWaveSpanMax ? "masked_wave_reduce_kernel" : "masked_span_reduce_kernel+reduce_final_kernel";
+            if (seg_len <= 2 * kWaveSpanMax) return "masked_wave_reduce_kernel";
+            return masked_finishes(n, seg_len, 1) ? "masked_span_reduce_kernel<finish>" : "masked_span_reduce_kernel+reduce_final_kernel";
         }
         if (is_pow2(seg_len) && seg_len <= 8) return "tiny_scan_kernel";            // (the plain scan; other modes: the tiles)
         const int pick = pick_scan_any(seg_len);
@@ -473,7 +474,7 @@ extern "C" const char* tcr_kernel_name(int op, uint64_t n, uint64_t seg_len) {
         const ReducePlan p = plan_reduce(n, seg_len, whole);
         // <formulation, wave | block (wavefronts of a workgroup combined)>, and what adds up the partials, if any are left
         const uint64_t nseg = whole ? 1 : n / seg_len;
-        const bool fused = p.per > 1 && g_variant.reduce_fused && nseg * p.per <= kFusedPartialsMax;
+        const bool fused = p.finish || (p.per > 1 && g_variant.reduce_fused && nseg * p.per <= kFusedPartialsMax);
         if (p.combine == 1) {
             if (p.per == 1) return mf ? "reduce_span_kernel<mfma,wave>" : "reduce_span_kernel<dpp,wave>";
             if (fused) return mf ? "reduce_span_kernel<mfma,wave,finish>" : "reduce_span_kernel<dpp,wave,finish>";

@@ -149,7 +149,12 @@ inline tcr_status launch_reduce_span(const _Float16* in, float* dst, uint64_t n,
                               int combine_waves, hipStream_t s, const ReduceFinish* finish = nullptr) {
     const ReduceFinish none = {};
     if (finish != nullptr) {          // one partial per workgroup; the last workgroup adds them up
-        if (combine_waves == 4) {
+        if (combine_waves == 16) {
+            const dim3 grid((unsigned)ceil_div(nspans, 16)), block(16 * kWave);
+            if (span >= 8 * kTile) reduce_span_kernel<FORM, 8, 16, true, true><<<grid, block, 0, s>>>(in, dst, n, span, nspans, *finish);
+            else if (span >= 4 * kTile) reduce_span_kernel<FORM, 4, 16, true, true><<<grid, block, 0, s>>>(in, dst, n, span, nspans, *finish);
+            else reduce_span_kernel<FORM, 2, 16, true, true><<<grid, block, 0, s>>>(in, dst, n, span, nspans, *finish);
+        } else if (combine_waves == 4) {
             reduce_span_kernel<FORM, 8, 4, true, true><<<dim3((unsigned)ceil_div(nspans, 4)), dim3(4 * kWave), 0, s>>>(
                 in, dst, n, span, nspans, *finish);
         } else if (combine_waves == 2) {
@@ -187,7 +192,21 @@ struct ReducePlan {
     int combine;        // wavefronts per workgroup whose sums are added through LDS (1: none)
     uint64_t per;       // partials per segment left for reduce_final_kernel (1: results go straight to out)
     uint64_t nspans;    // wavefronts in total
+    bool finish;        // the partials are added up by the workgroup that finishes last
 };
+
+// Arrays whose partials the last workgroup adds up: at most 128 of them (one count on one address takes 12 ns), of a
+// workgroup's share each.  Full reduction of 2^18 / 2^20 / 2^22 / 2^23 elements, us back to back: two kernels 6.8 / 6.9 /
+// 6.7 / 6.7, one launch 4.5 / 4.5 / 5.9 / 7.0 -- and 3.3 us less for the host at every size, which is the longer of the two
+// up to there.  (One workgroup and no partials at all up to 2^17: 3.7 at 2^16, 4.9 at 2^17.)
+constexpr uint64_t kFinishElemsMax = 1ull << 23;
+constexpr uint64_t kFinishSums = 32;                     // results that the last workgroup adds up
+inline uint64_t finish_share(uint64_t n) {
+    uint64_t share = 16384;
+    while (ceil_div(n, share) > 128) share <<= 1;
+    return share;
+}
+
 
 
 // How many wavefronts an array is shared among, if its size allows: a wavefront keeps 8 KiB of loads in flight, and 16
@@ -232,10 +251,12 @@ inline int reduce_candidates(uint64_t n, uint64_t seg_len, bool whole, ReduceSha
 }
 
 // seg_len >= 1024 (a power of two), or one segment of any length (whole).
-// coarse: no more partials than one per 65536 elements of a segment (a workspace that cannot be grown).
-inline ReducePlan plan_reduce(uint64_t n, uint64_t seg_len, bool whole, bool coarse = false) {
+// coarse: no more partials than one per 65536 elements of a segment, or per 4096 of the array if it is one segment (a
+// workspace that cannot be grown).  two_kernels: the partials, if any, are left to reduce_final_kernel.
+inline ReducePlan plan_reduce(uint64_t n, uint64_t seg_len, bool whole, bool coarse = false, bool two_kernels = false) {
     ReduceShape cand[4];
     const int count = reduce_candidates(n, seg_len, whole, cand);
+    bool finish = false;
     int pick = tuned_id(kTuneReduce, tuning_class(seg_len, whole));
     if (pick < 0 || pick >= count) {
         // frozen defaults for an array that fills the chip whatever the split: segments of 8192 .. 32768 elements over
@@ -245,7 +266,13 @@ inline ReducePlan plan_reduce(uint64_t n, uint64_t seg_len, bool whole, bool coa
         // or 2^20 elements one workgroup's and the second kernel unnecessary, 84.1 and 90.8 us)
         if (whole || seg_len >= (1ull << 18)) pick = count > 1 ? 1 : 0;
         else pick = (seg_len < 8192 || seg_len > 32768) ? 0 : (seg_len == 8192 ? 1 : 2);
-        if (!whole) {
+        const bool long_one = whole ? count > 1 : seg_len > kOneGroupSegment;
+        if (whole && long_one && n <= kOneGroupSegment) {
+            cand[pick = 0] = {ceil_div(ceil_div(n, 16), kTile) * kTile, 16};       // one workgroup, no partials
+        } else if (long_one && n <= kFinishElemsMax && (whole || n / seg_len <= kFinishSums) && !coarse && !two_kernels && !g_variant.reduce_fused) {
+            cand[pick = 0] = {finish_share(n) / 16, 16};
+            finish = true;
+        } else if (!whole) {
             ReduceShape c = cand[pick];
             if (seg_len <= kOneGroupSegment) {
                 // too few wavefronts to fill the chip: halve their shares, up to one workgroup of 16 per segment
@@ -265,6 +292,7 @@ inline ReducePlan plan_reduce(uint64_t n, uint64_t seg_len, bool whole, bool coa
     const uint64_t len = whole ? n : seg_len;
     p.per = ceil_div(len, p.span * (uint64_t)p.combine);
     p.nspans = whole ? ceil_div(n, p.span) : n / p.span;
+    p.finish = finish && p.per > 1;
     return p;
 }
 
@@ -286,10 +314,17 @@ inline tcr_status reduce_long(const _Float16* in, float* out, uint64_t n, uint64
     if (p.per > 1) {
         tcr_status st = get_workspace(s, &ws, &capturing);
         if (st != TCR_OK) return st;
+        uint32_t* counter = p.finish ? finish_counter(ws, capturing) : nullptr;
+        if (p.finish && counter == nullptr) p = plan_reduce(n, seg_len, whole, false, true);
         if (nseg * p.per > partials_limit(ws, capturing)) p = plan_reduce(n, seg_len, whole, true);
         st = ensure_partials(ws, s, nseg * p.per, capturing);
         if (st != TCR_OK) return st;
         dst = ws->partials;
+        if (p.finish) {
+            const ReduceFinish fin = {out, nullptr, counter, 0u, (uint32_t)nseg, (uint32_t)p.per, 1u};
+            return form == kMfma ? launch_reduce_span<kMfma>(in, dst, n, p.span, p.nspans, p.combine, s, &fin)
+                                 : launch_reduce_span<kDpp>(in, dst, n, p.span, p.nspans, p.combine, s, &fin);
+        }
     }
     if (p.per > 1 && g_variant.reduce_fused && nseg * p.per <= kFusedPartialsMax) {
         // one kernel: the workgroup that finishes last adds up the partials
@@ -297,7 +332,7 @@ inline tcr_status reduce_long(const _Float16* in, float* out, uint64_t n, uint64
         ScanWorkspace dev = {};
         tcr_status st = begin_lookback(ws, s, 0, &dev, false);   // the running counter that also hands out scan tiles
         if (st != TCR_OK) return st;
-        const ReduceFinish fin = {out, dev.ticket, dev.ticket_base, (uint32_t)nseg, (uint32_t)p.per};
+        const ReduceFinish fin = {out, nullptr, dev.ticket, dev.ticket_base, (uint32_t)nseg, (uint32_t)p.per, 0u};
         st = form == kMfma ? launch_reduce_span<kMfma>(in, dst, n, p.span, p.nspans, p.combine, s, &fin)
                                             : launch_reduce_span<kDpp>(in, dst, n, p.span, p.nspans, p.combine, s, &fin);
         if (st != TCR_OK) {
@@ -1023,18 +1058,21 @@ inline int pick_reduce_any(uint64_t seg_len, bool packed_ok = true) {
 // 65536-element piece took 22.6 us at 50001 elements, 41.5 at 100001 and 30 at 300001 and 1000001.
 template <int KIND, int W>
 inline void launch_masked_pieces(const _Float16* in, float* dst, float* dst2, uint64_t nseg, uint64_t seg_len, uint64_t span,
-                                 uint64_t per, hipStream_t s) {
+                                 uint64_t per, hipStream_t s, const ReduceFinish& fin = {}) {
     const dim3 grid((unsigned)ceil_div(nseg * per, W == 1 ? kMaskedWaves : 1)), block(masked_group_waves<W>() * kWave);
     const bool four = W == 1 && seg_len > 4096;          // a wavefront that takes several steps: shorter ones (8192 elements: 21.7 against 22.8 us)
     if constexpr (KIND == kBoth) {
-        if (per > 1) masked_moments_kernel<8, W, true><<<grid, block, 0, s>>>(in, dst, dst2, nseg, seg_len, span, per);
-        else if (four) masked_moments_kernel<4, W, false><<<grid, block, 0, s>>>(in, dst, dst2, nseg, seg_len, span, per);
-        else masked_moments_kernel<8, W, false><<<grid, block, 0, s>>>(in, dst, dst2, nseg, seg_len, span, per);
+        if (per > 1) masked_moments_kernel<8, W, true><<<grid, block, 0, s>>>(in, dst, dst2, nseg, seg_len, span, per, fin);
+        else if (four) masked_moments_kernel<4, W, false><<<grid, block, 0, s>>>(in, dst, dst2, nseg, seg_len, span, per, fin);
+        else masked_moments_kernel<8, W, false><<<grid, block, 0, s>>>(in, dst, dst2, nseg, seg_len, span, per, fin);
     } else {
-        if (per > 1) masked_span_reduce_kernel<W><<<grid, block, 0, s>>>(in, dst, nseg, seg_len, span, per);
+        if (per > 1) masked_span_reduce_kernel<W><<<grid, block, 0, s>>>(in, dst, nseg, seg_len, span, per, fin);
         else if (four) masked_wave_reduce_kernel<4, W><<<grid, block, 0, s>>>(in, dst, nseg, seg_len);
         else masked_wave_reduce_kernel<8, W><<<grid, block, 0, s>>>(in, dst, nseg, seg_len);
     }
+}
+inline bool masked_finishes(uint64_t n, uint64_t seg_len, uint64_t ch) {
+    return seg_len > 2 * kWaveSpanMax && n <= kFinishElemsMax && ch * (n / seg_len) <= kFinishSums;
 }
 template <int KIND>
 inline tcr_status launch_masked(const _Float16* in, float* out, float* out2, uint64_t n, uint64_t seg_len, hipStream_t s) {
@@ -1047,13 +1085,14 @@ inline tcr_status launch_masked(const _Float16* in, float* out, float* out2, uin
     }
     // pieces, then the paper's second kernel over the pieces (for each moment)
     constexpr uint64_t ch = KIND == kBoth ? 2 : 1;
-    uint64_t span = free_span(n);
-    const bool grouped = span < kWaveSpanMax;
-    if (grouped) span *= 4;
     Workspace* ws = nullptr;
     bool capturing = false;
     tcr_status st = get_workspace(s, &ws, &capturing);
     if (st != TCR_OK) return st;
+    uint32_t* counter = masked_finishes(n, seg_len, ch) ? finish_counter(ws, capturing) : nullptr;
+    uint64_t span = counter != nullptr ? finish_share(n) : free_span(n);
+    const bool grouped = span < kWaveSpanMax;
+    if (grouped && counter == nullptr) span *= 4;
     // (a workspace that cannot be grown and is too small for that: pieces of 65536 elements, as few as there need be)
     if (span < kWaveSpanMax && ch * nseg * ceil_div(seg_len, span) > partials_limit(ws, capturing)) span = kWaveSpanMax;
     uint64_t per = ceil_div(seg_len, span);
@@ -1062,6 +1101,12 @@ inline tcr_status launch_masked(const _Float16* in, float* out, float* out2, uin
     const uint64_t pieces = nseg * per;
     st = ensure_partials(ws, s, ch * pieces, capturing);
     if (st != TCR_OK) return st;
+    if (counter != nullptr) {
+        const ReduceFinish fin = {out, KIND == kBoth ? out2 : nullptr, counter, 0u, (uint32_t)nseg, (uint32_t)per, 1u};
+        if (span <= 32768) launch_masked_pieces<KIND, 4>(in, ws->partials, ws->partials + pieces, nseg, seg_len, span, per, s, fin);
+        else launch_masked_pieces<KIND, 16>(in, ws->partials, ws->partials + pieces, nseg, seg_len, span, per, s, fin);
+        return check_launch("masked_span_reduce_kernel");
+    }
     if (grouped) launch_masked_pieces<KIND, 4>(in, ws->partials, ws->partials + pieces, nseg, seg_len, span, per, s);
     else launch_masked_pieces<KIND, 1>(in, ws->partials, ws->partials + pieces, nseg, seg_len, span, per, s);
     st = check_launch("masked_span_reduce_kernel");

@@ -15,6 +15,7 @@
 #include "tcr_device.hpp"
 #include "tcr_scan.hpp"
 #include "tcr_irregular.hpp"
+#include "tcr_reduce.hpp"
 
 namespace tcr {
 
@@ -155,7 +156,8 @@ __device__ __forceinline__ void masked_part_sums(const _Float16* __restrict__ in
 
 // Piece w % per of segment w / per (pieces of `span` elements counted from the segment's start, the last one shorter;
 // per == 1: whole segments) -> dst[w], dst2[w].  W == 1: a wavefront per piece, kMaskedWaves of them in a workgroup.
-// W > 1: a workgroup of W wavefronts per piece, their sums added through LDS in wavefront order.
+// W > 1: a workgroup of W wavefronts per piece, their sums added through LDS in wavefront order; with fin.counter the
+// workgroup that finishes last adds up the pieces too (dst2 follows dst's nseg * per).
 // Bound by memory.  One wavefront per segment leaves the chip idle when there are few segments (16 KiB in flight per
 // wavefront, and 256 compute units): the launch picks W and the span so that about 4096 wavefronts share the array.
 constexpr int kMaskedWaves = 4;
@@ -163,7 +165,7 @@ template <int W>
 constexpr int masked_group_waves() { return W == 1 ? kMaskedWaves : W; }
 template <int KIND, int U, int W, bool PIECES>
 __device__ __forceinline__ void masked_piece(const _Float16* __restrict__ in, float* __restrict__ dst, float* __restrict__ dst2,
-                                             uint64_t nseg, uint64_t seg_len, uint64_t span, uint64_t per) {
+                                             uint64_t nseg, uint64_t seg_len, uint64_t span, uint64_t per, const ReduceFinish& fin) {
     const LaneId id;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint64_t w = W == 1 ? (uint64_t)blockIdx.x * kMaskedWaves + (uint64_t)wave : (uint64_t)blockIdx.x;
@@ -184,12 +186,23 @@ __device__ __forceinline__ void masked_piece(const _Float16* __restrict__ in, fl
             s_part[1][wave] = q;
         }
         __syncthreads();
-        if (threadIdx.x != 0) return;
+        const bool finish = PIECES && fin.counter != nullptr;
+        if (threadIdx.x != 0 && !finish) return;
         a = q = 0.0f;
 #pragma unroll
         for (int v = 0; v < W; ++v) {
             a += s_part[0][v];
             q += s_part[1][v];
+        }
+        if constexpr (PIECES) {
+            if (finish) {
+                if (threadIdx.x == 0) {
+                    __hip_atomic_store(&dst[w], a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if constexpr (KIND == kBoth) __hip_atomic_store(&dst2[w], q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                finish_partials<W>(dst, fin, wave, id.lane);
+                return;
+            }
         }
     }
     if (id.lane == 0) {
@@ -204,21 +217,22 @@ template <int U, int W>
 __global__ __launch_bounds__(masked_group_waves<W>() * kWave) void masked_wave_reduce_kernel(const _Float16* __restrict__ in,
                                                                                              float* __restrict__ out,
                                                                                              uint64_t nseg, uint64_t seg_len) {
-    masked_piece<kSum, U, W, false>(in, out, nullptr, nseg, seg_len, seg_len, 1);
+    masked_piece<kSum, U, W, false>(in, out, nullptr, nseg, seg_len, seg_len, 1, ReduceFinish{});
 }
 template <int W>
 __global__ __launch_bounds__(masked_group_waves<W>() * kWave) void masked_span_reduce_kernel(const _Float16* __restrict__ in,
                                                                                              float* __restrict__ dst, uint64_t nseg,
                                                                                              uint64_t seg_len, uint64_t span,
-                                                                                             uint64_t per) {
-    masked_piece<kSum, 8, W, true>(in, dst, nullptr, nseg, seg_len, span, per);
+                                                                                             uint64_t per, ReduceFinish fin) {
+    masked_piece<kSum, 8, W, true>(in, dst, nullptr, nseg, seg_len, span, per, fin);
 }
 template <int U, int W, bool PIECES>
 __global__ __launch_bounds__(masked_group_waves<W>() * kWave) void masked_moments_kernel(const _Float16* __restrict__ in,
                                                                                          float* __restrict__ sum,
                                                                                          float* __restrict__ sumsq, uint64_t nseg,
-                                                                                         uint64_t seg_len, uint64_t span, uint64_t per) {
-    masked_piece<kBoth, U, W, PIECES>(in, sum, sumsq, nseg, seg_len, span, per);
+                                                                                         uint64_t seg_len, uint64_t span, uint64_t per,
+                                                                                         ReduceFinish fin) {
+    masked_piece<kBoth, U, W, PIECES>(in, sum, sumsq, nseg, seg_len, span, per, fin);
 }
 
 // Short segments: one thread per segment, binary32 adds and fused multiply-adds.

@@ -188,22 +188,53 @@ __global__ __launch_bounds__(WAVES * kWave) void moments_small_kernel(const _Flo
 // order and dst[blockIdx.x] receives the result (block-level Reduction_256N: one workgroup per
 // segment or per partial).
 // FINAL == true (device level, Section 4, as one kernel instead of the paper's two): dst holds `per`
-// partials per segment; every workgroup counts itself on a running counter after its partial is
-// visible, and the workgroup that counts last adds up the partials of every segment, in a fixed
-// order, into fin.out.  The counter is never reset: the host passes its value at launch.
+// partials per segment; every workgroup counts itself after its partial is visible, and the workgroup that
+// counts last adds up the partials of every segment, in a fixed order, into fin.out.
 struct ReduceFinish {
     float* out;            // [nseg]
-    uint32_t* counter;     // running count of finished workgroups
-    uint32_t base;         // value of *counter when this launch starts
+    float* out2;           // a second set of nseg * per partials behind the first goes there (the sums of squares), or null
+    uint32_t* counter;     // count of finished workgroups
+    uint32_t base;         // value of *counter when this launch starts (wrap == 0: a running count that is never reset)
     uint32_t nseg, per;    // dst holds nseg * per partials
+    uint32_t wrap;         // 1: the count returns to 0 with the last workgroup, so a recorded launch can be replayed
 };
+
+// Executed by every thread of a workgroup whose partial(s) thread 0 has just stored with device scope.
+// The partial is written through to device scope and its acknowledgement is waited for before the
+// count is issued; the last workgroup reads the partials with device-scope loads that bypass its
+// caches.  (A device-scope release / acquire pair instead would write back and invalidate the L2
+// once per workgroup: measured, it costs a third of the bandwidth.)
+template <int WAVES>
+__device__ __forceinline__ void finish_partials(const float* __restrict__ dst, const ReduceFinish& fin, int wave, int lane) {
+    __shared__ uint32_t s_last;
+    if (threadIdx.x == 0) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");       // compiler ordering
+        __builtin_amdgcn_s_waitcnt(0x0F70);                          // vmcnt(0): the store has been acknowledged
+        const uint32_t before = fin.wrap ? atomicInc(fin.counter, gridDim.x - 1u)
+                                         : __hip_atomic_fetch_add(fin.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - fin.base;
+        s_last = before == gridDim.x - 1u ? 1u : 0u;
+    }
+    __syncthreads();
+    if (s_last == 0u) return;
+    const uint32_t sums = fin.out2 != nullptr ? 2u * fin.nseg : fin.nseg;
+    for (uint32_t s = (uint32_t)wave; s < sums; s += WAVES) {
+        const float* p = dst + (uint64_t)s * fin.per;
+        float a = 0.0f;
+        for (uint32_t i = (uint32_t)lane; i < fin.per; i += kWave)
+            a += __hip_atomic_load(&p[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const float t = wave_sum(a);
+        if (lane == 0) {
+            if (s < fin.nseg) fin.out[s] = t;
+            else fin.out2[s - fin.nseg] = t;
+        }
+    }
+}
 
 template <int FORM, int U, int WAVES, bool COMBINE, bool FINAL = false>
 __global__ __launch_bounds__(WAVES * kWave) void reduce_span_kernel(const _Float16* __restrict__ in,
                                                                     float* __restrict__ dst, uint64_t n,
                                                                     uint64_t span, uint64_t nspans, ReduceFinish fin) {
     __shared__ float s_total[WAVES];
-    __shared__ uint32_t s_count;
     const LaneId id;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: keeps per-wave branches and addresses scalar
     const uint64_t w = (uint64_t)blockIdx.x * WAVES + wave;
@@ -276,26 +307,9 @@ __global__ __launch_bounds__(WAVES * kWave) void reduce_span_kernel(const _Float
             float sum = 0.0f;
 #pragma unroll
             for (int k = 0; k < WAVES; ++k) sum += s_total[k];
-            // The partial is written through to device scope and its acknowledgement is waited for before the
-            // count is issued; the last workgroup reads the partials with device-scope loads that bypass its
-            // caches.  (A device-scope release / acquire pair instead would write back and invalidate the L2
-            // once per workgroup: measured, it costs a third of the bandwidth.)
             __hip_atomic_store(&dst[blockIdx.x], sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");       // compiler ordering
-            __builtin_amdgcn_s_waitcnt(0x0F70);                          // vmcnt(0): the store has been acknowledged
-            s_count = __hip_atomic_fetch_add(fin.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - fin.base;
         }
-        __syncthreads();
-        if (s_count == gridDim.x - 1u) {
-            for (uint32_t seg = (uint32_t)wave; seg < fin.nseg; seg += WAVES) {
-                const float* p = dst + (uint64_t)seg * fin.per;
-                float a = 0.0f;
-                for (uint32_t i = (uint32_t)id.lane; i < fin.per; i += kWave)
-                    a += __hip_atomic_load(&p[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const float t = wave_sum(a);
-                if (id.lane == 0) fin.out[seg] = t;
-            }
-        }
+        finish_partials<WAVES>(dst, fin, wave, id.lane);
     }
 }
 

@@ -200,6 +200,7 @@ __global__ __launch_bounds__(kClearThreads) void workspace_clear_kernel(uint32_t
         if (!keep_flag) counters[1] = 0u;
         counters[2] = 0u;
         counters[3] = 0u;
+        counters[4] = 0u;
     }
 }
 

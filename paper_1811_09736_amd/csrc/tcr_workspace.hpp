@@ -73,7 +73,8 @@ struct Workspace {
     uint64_t desc_capacity = 0;     // tiles
     float* partials = nullptr;
     uint64_t partials_capacity = 0; // floats
-    uint32_t* counters = nullptr;   // [0] = ticket, [1] = gave_up flag, [2] = latest epoch, [3] = ticket base (device-managed)
+    uint32_t* counters = nullptr;   // [0] = ticket, [1] = gave_up flag, [2] = latest epoch, [3] = ticket base (device-managed),
+                                    // [4] = workgroups of a reduction that have finished (0 between launches)
     uint32_t tickets_issued = 0;    // host mirror of counters[0] once all enqueued launches finish
     uint32_t epoch = 0;
     // Once a launch that chains tiles has been recorded into a HIP graph, epoch and ticket base live on the
@@ -168,18 +169,38 @@ inline tcr_status ensure_partials(Workspace* ws, hipStream_t stream, uint64_t fl
     return TCR_OK;
 }
 
+// The count of finished workgroups of a one-launch reduction, or nullptr where it is not known to be 0 and cannot be
+// cleared now (a caller's buffer that no call has cleared yet, a workspace that would have to be created in a capture).
+constexpr uint64_t kCounterWords = 8;
+inline tcr_status create_counters(Workspace* ws) {
+    void* p = nullptr;
+    if (hipMalloc(&p, kCounterWords * sizeof(uint32_t)) != hipSuccess) {
+        (void)hipGetLastError();
+        return TCR_ERR_WORKSPACE;
+    }
+    const uint32_t zero[kCounterWords] = {};
+    if (hip_failed(hipMemcpy(p, zero, sizeof(zero), hipMemcpyHostToDevice), "hipMemcpy")) {      // (returns when they are there)
+        (void)hipFree(p);
+        return TCR_ERR_HIP;
+    }
+    ws->counters = static_cast<uint32_t*>(p);
+    ws->tickets_issued = 0;
+    ws->dirty = true;
+    return TCR_OK;
+}
+inline uint32_t* finish_counter(Workspace* ws, bool capturing) {
+    if (ws->caller_owned && ws->dirty) return nullptr;
+    if (ws->counters == nullptr && (capturing || create_counters(ws) != TCR_OK)) return nullptr;
+    return ws->counters + 4;
+}
+
 // Makes room for `tiles` descriptors and starts a new epoch (tiles == 0: only the running counter is wanted).
 inline tcr_status begin_lookback(Workspace* ws, hipStream_t stream, uint64_t tiles, ScanWorkspace* dev, bool capturing) {
     if (ws->caller_owned && tiles > ws->desc_capacity) return TCR_ERR_WORKSPACE;
     if (capturing && (ws->counters == nullptr || tiles > ws->desc_capacity || ws->dirty)) return TCR_ERR_UNSUPPORTED;
     if (ws->counters == nullptr) {
-        if (hipMalloc(&ws->counters, 4 * sizeof(uint32_t)) != hipSuccess) {
-            (void)hipGetLastError();
-            return TCR_ERR_WORKSPACE;
-        }
-        TCR_HIP(hipMemset(ws->counters, 0, 4 * sizeof(uint32_t)));
-        ws->tickets_issued = 0;
-        ws->dirty = true;
+        const tcr_status st = create_counters(ws);
+        if (st != TCR_OK) return st;
     }
     if (tiles > ws->desc_capacity) {
         TCR_HIP(hipStreamSynchronize(stream));
@@ -207,7 +228,7 @@ inline tcr_status begin_lookback(Workspace* ws, hipStream_t stream, uint64_t til
             if (ws->desc_capacity) TCR_HIP(hipMemset(ws->desc, 0, ws->desc_capacity * sizeof(unsigned long long)));
             uint32_t keep_flag = 0;
             if (ws->flag_valid) TCR_HIP(hipMemcpy(&keep_flag, ws->counters + 1, sizeof(uint32_t), hipMemcpyDeviceToHost));
-            uint32_t init[4] = {0u, keep_flag, 0u, 0u};
+            uint32_t init[kCounterWords] = {0u, keep_flag};
             TCR_HIP(hipMemcpy(ws->counters, init, sizeof(init), hipMemcpyHostToDevice));
         }
         ws->flag_valid = true;
