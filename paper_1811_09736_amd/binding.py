@@ -102,9 +102,28 @@ def _load() -> ctypes.CDLL:
 _lib = _load()
 
 
+# A call's own work on the host is a few microseconds, of which the launch is three; the public ways to ask for the current
+# device and stream (a guard object, a Stream object) cost more than that, so the plain integers are asked for instead.
+_current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
+_current_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda index: torch.cuda.current_stream(index).cuda_stream)
+
+
 def _stream_handle(stream: Optional[torch.cuda.Stream]) -> int:
     s = stream if stream is not None else torch.cuda.current_stream()
     return int(s.cuda_stream)
+
+
+def _run(call, where: str, x: torch.Tensor, stream: Optional[torch.cuda.Stream], *args) -> None:
+    """call(*args, stream handle) with x's device current; the handle of `stream`, or of that device's current stream."""
+    index = x.get_device()
+    handle = _current_stream(index) if stream is None else int(stream.cuda_stream)
+    if _current_device() == index:
+        st = call(*args, handle)
+    else:
+        with torch.cuda.device(index):
+            st = call(*args, handle)
+    if st != OK:
+        raise TcrError(st, where)
 
 
 def _check_input(x: torch.Tensor) -> None:
@@ -127,11 +146,9 @@ def segmented_reduce(x: torch.Tensor, seg_len: int, out: Optional[torch.Tensor] 
         raise TcrError(ERR_INVALID_ARG, "tcr_segmented_reduce")
     if out is None:
         out = torch.empty(n // seg_len, dtype=torch.float32, device=x.device)
-    _check_output(out, n // seg_len, x)
-    with torch.cuda.device(x.device):
-        st = _lib.tcr_segmented_reduce(x.data_ptr(), out.data_ptr(), n, seg_len, _stream_handle(stream))
-    if st != OK:
-        raise TcrError(st, "tcr_segmented_reduce")
+    else:
+        _check_output(out, n // seg_len, x)
+    _run(_lib.tcr_segmented_reduce, "tcr_segmented_reduce", x, stream, x.data_ptr(), out.data_ptr(), n, seg_len)
     return out
 
 
@@ -144,11 +161,9 @@ def segmented_scan(x: torch.Tensor, seg_len: int, out: Optional[torch.Tensor] = 
         raise TcrError(ERR_INVALID_ARG, "tcr_segmented_scan")
     if out is None:
         out = torch.empty(n, dtype=torch.float32, device=x.device)
-    _check_output(out, n, x)
-    with torch.cuda.device(x.device):
-        st = _lib.tcr_segmented_scan(x.data_ptr(), out.data_ptr(), n, seg_len, _stream_handle(stream))
-    if st != OK:
-        raise TcrError(st, "tcr_segmented_scan")
+    else:
+        _check_output(out, n, x)
+    _run(_lib.tcr_segmented_scan, "tcr_segmented_scan", x, stream, x.data_ptr(), out.data_ptr(), n, seg_len)
     return out
 
 
@@ -160,10 +175,7 @@ def segmented_scan_noalloc(x: torch.Tensor, seg_len: int, out: torch.Tensor,
     if seg_len <= 0 or n % seg_len:
         raise TcrError(ERR_INVALID_ARG, "tcr_segmented_scan_noalloc")
     _check_output(out, n, x)
-    with torch.cuda.device(x.device):
-        st = _lib.tcr_segmented_scan_noalloc(x.data_ptr(), out.data_ptr(), n, seg_len, _stream_handle(stream))
-    if st != OK:
-        raise TcrError(st, "tcr_segmented_scan_noalloc")
+    _run(_lib.tcr_segmented_scan_noalloc, "tcr_segmented_scan_noalloc", x, stream, x.data_ptr(), out.data_ptr(), n, seg_len)
     return out
 
 
@@ -177,12 +189,9 @@ def segmented_scan_ex(x: torch.Tensor, seg_len: int, flags: int, out: Optional[t
     dtype = torch.float16 if flags & OUT_F16 else torch.float32
     if out is None:
         out = torch.empty(n, dtype=dtype, device=x.device)
-    if not (out.is_cuda and out.dtype == dtype and out.is_contiguous() and out.numel() == n and out.device == x.device):
+    elif not (out.is_cuda and out.dtype == dtype and out.is_contiguous() and out.numel() == n and out.device == x.device):
         raise TypeError(f"out must be a contiguous {dtype} CUDA tensor of {n} elements on the input's device")
-    with torch.cuda.device(x.device):
-        st = _lib.tcr_segmented_scan_ex(x.data_ptr(), out.data_ptr(), n, seg_len, flags, _stream_handle(stream))
-    if st != OK:
-        raise TcrError(st, "tcr_segmented_scan_ex")
+    _run(_lib.tcr_segmented_scan_ex, "tcr_segmented_scan_ex", x, stream, x.data_ptr(), out.data_ptr(), n, seg_len, flags)
     return out
 
 
@@ -194,12 +203,9 @@ def scan_ex(x: torch.Tensor, flags: int, out: Optional[torch.Tensor] = None,
     dtype = torch.float16 if flags & OUT_F16 else torch.float32
     if out is None:
         out = torch.empty(n, dtype=dtype, device=x.device)
-    if not (out.is_cuda and out.dtype == dtype and out.is_contiguous() and out.numel() == n and out.device == x.device):
+    elif not (out.is_cuda and out.dtype == dtype and out.is_contiguous() and out.numel() == n and out.device == x.device):
         raise TypeError(f"out must be a contiguous {dtype} CUDA tensor of {n} elements on the input's device")
-    with torch.cuda.device(x.device):
-        st = _lib.tcr_scan_ex(x.data_ptr(), out.data_ptr(), n, flags, _stream_handle(stream))
-    if st != OK:
-        raise TcrError(st, "tcr_scan_ex")
+    _run(_lib.tcr_scan_ex, "tcr_scan_ex", x, stream, x.data_ptr(), out.data_ptr(), n, flags)
     return out
 
 
@@ -218,11 +224,10 @@ def irregular_reduce(x: torch.Tensor, offsets: torch.Tensor, out: Optional[torch
     nseg = _check_offsets(x, offsets)
     if out is None:
         out = torch.empty(nseg, dtype=torch.float32, device=x.device)
-    _check_output(out, nseg, x)
-    with torch.cuda.device(x.device):
-        st = _lib.tcr_irregular_reduce(x.data_ptr(), offsets.data_ptr(), out.data_ptr(), x.numel(), nseg, _stream_handle(stream))
-    if st != OK:
-        raise TcrError(st, "tcr_irregular_reduce")
+    else:
+        _check_output(out, nseg, x)
+    _run(_lib.tcr_irregular_reduce, "tcr_irregular_reduce", x, stream, x.data_ptr(), offsets.data_ptr(), out.data_ptr(),
+         x.numel(), nseg)
     return out
 
 
@@ -240,11 +245,8 @@ def irregular_moments(x: torch.Tensor, offsets: torch.Tensor, stream: Optional[t
     nseg = _check_offsets(x, offsets)
     a = torch.empty(nseg, dtype=torch.float32, device=x.device)
     q = torch.empty(nseg, dtype=torch.float32, device=x.device)
-    with torch.cuda.device(x.device):
-        st = _lib.tcr_irregular_moments(x.data_ptr(), offsets.data_ptr(), a.data_ptr(), q.data_ptr(), x.numel(), nseg,
-                                        _stream_handle(stream))
-    if st != OK:
-        raise TcrError(st, "tcr_irregular_moments")
+    _run(_lib.tcr_irregular_moments, "tcr_irregular_moments", x, stream, x.data_ptr(), offsets.data_ptr(), a.data_ptr(),
+         q.data_ptr(), x.numel(), nseg)
     return a, q
 
 
@@ -261,10 +263,8 @@ def irregular_scan_ex(x: torch.Tensor, offsets: torch.Tensor, flags: int, out: O
     elif not (out.is_cuda and out.dtype == dtype and out.is_contiguous() and out.numel() == x.numel() and out.device == x.device):
         raise TypeError(f"out must be a contiguous {dtype} CUDA tensor of {x.numel()} elements on the input's device")
     call = _lib.tcr_irregular_scan_filled if fresh else _lib.tcr_irregular_scan_ex
-    with torch.cuda.device(x.device):
-        st = call(x.data_ptr(), offsets.data_ptr(), out.data_ptr(), x.numel(), nseg, flags, _stream_handle(stream))
-    if st != OK:
-        raise TcrError(st, "tcr_irregular_scan_ex" if flags else "tcr_irregular_scan")
+    _run(call, "tcr_irregular_scan_ex" if flags else "tcr_irregular_scan", x, stream, x.data_ptr(), offsets.data_ptr(), out.data_ptr(),
+         x.numel(), nseg, flags)
     return out
 
 
@@ -274,11 +274,9 @@ def reduce(x: torch.Tensor, out: Optional[torch.Tensor] = None,
     _check_input(x)
     if out is None:
         out = torch.empty(1, dtype=torch.float32, device=x.device)
-    _check_output(out, 1, x)
-    with torch.cuda.device(x.device):
-        st = _lib.tcr_reduce(x.data_ptr(), out.data_ptr(), x.numel(), _stream_handle(stream))
-    if st != OK:
-        raise TcrError(st, "tcr_reduce")
+    else:
+        _check_output(out, 1, x)
+    _run(_lib.tcr_reduce, "tcr_reduce", x, stream, x.data_ptr(), out.data_ptr(), x.numel())
     return out
 
 
@@ -288,11 +286,9 @@ def scan(x: torch.Tensor, out: Optional[torch.Tensor] = None,
     _check_input(x)
     if out is None:
         out = torch.empty(x.numel(), dtype=torch.float32, device=x.device)
-    _check_output(out, x.numel(), x)
-    with torch.cuda.device(x.device):
-        st = _lib.tcr_scan(x.data_ptr(), out.data_ptr(), x.numel(), _stream_handle(stream))
-    if st != OK:
-        raise TcrError(st, "tcr_scan")
+    else:
+        _check_output(out, x.numel(), x)
+    _run(_lib.tcr_scan, "tcr_scan", x, stream, x.data_ptr(), out.data_ptr(), x.numel())
     return out
 
 
@@ -305,10 +301,7 @@ def autotune(op: int, x: torch.Tensor, out: torch.Tensor, seg_len: int,
     need = x.numel() if op in (OP_SEGMENTED_SCAN, OP_SCAN) else (1 if op == OP_REDUCE else x.numel() // max(seg_len, 1))
     if out.numel() < need:
         raise TypeError(f"out needs at least {need} elements")
-    with torch.cuda.device(x.device):
-        st = _lib.tcr_autotune(op, x.data_ptr(), out.data_ptr(), x.numel(), seg_len, _stream_handle(stream))
-    if st != OK:
-        raise TcrError(st, "tcr_autotune")
+    _run(_lib.tcr_autotune, "tcr_autotune", x, stream, op, x.data_ptr(), out.data_ptr(), x.numel(), seg_len)
 
 
 def autotune_irregular(op: int, x: torch.Tensor, offsets: torch.Tensor, out: torch.Tensor,
@@ -319,10 +312,8 @@ def autotune_irregular(op: int, x: torch.Tensor, offsets: torch.Tensor, out: tor
     need = x.numel() if op == OP_IRREGULAR_SCAN else nseg
     if not (out.is_cuda and out.dtype == torch.float32 and out.is_contiguous() and out.device == x.device and out.numel() >= need):
         raise TypeError(f"out must be a contiguous float32 CUDA tensor of at least {need} elements on the input's device")
-    with torch.cuda.device(x.device):
-        st = _lib.tcr_autotune_irregular(op, x.data_ptr(), offsets.data_ptr(), out.data_ptr(), x.numel(), nseg, _stream_handle(stream))
-    if st != OK:
-        raise TcrError(st, "tcr_autotune_irregular")
+    _run(_lib.tcr_autotune_irregular, "tcr_autotune_irregular", x, stream, op, x.data_ptr(), offsets.data_ptr(), out.data_ptr(),
+         x.numel(), nseg)
 
 
 def tuning_export() -> str:
@@ -345,10 +336,7 @@ def segmented_moments(x: torch.Tensor, seg_len: int, stream: Optional[torch.cuda
     count = n // seg_len if seg_len > 0 else 0
     a = torch.empty(count, dtype=torch.float32, device=x.device)
     q = torch.empty(count, dtype=torch.float32, device=x.device)
-    with torch.cuda.device(x.device):
-        st = _lib.tcr_segmented_moments(x.data_ptr(), a.data_ptr(), q.data_ptr(), n, seg_len, _stream_handle(stream))
-    if st != OK:
-        raise TcrError(st, "tcr_segmented_moments")
+    _run(_lib.tcr_segmented_moments, "tcr_segmented_moments", x, stream, x.data_ptr(), a.data_ptr(), q.data_ptr(), n, seg_len)
     return a, q
 
 
