@@ -925,17 +925,23 @@ inline tcr_status launch_irregular_reduce(const _Float16* in, const uint64_t* of
         st = check_launch("irregular_bounds_kernel");
         if (st != TCR_OK) return st;
     }
+    // (the tables' words are free then: the tiles' own shares of the carried results go there)
+    float* parts = search ? reinterpret_cast<float*>(starts) : nullptr;
+    // (one launch up to 256 tiles: lognormal lengths at n = 2^16 / 2^20 / 2^21 / 2^22 5.8 / 6.2 / 7.3 / 11.2 us against 8.0 /
+    // 8.2 / 8.4 / 8.5 with the finishing kernel -- more counts on one address than that cost more than the launch)
+    uint32_t* counter = search && tiles > 1 && tiles <= kFinishThreads ? finish_counter(ws, capturing) : nullptr;
     if (search) {
         const dim3 grid((unsigned)tiles), block(4 * kWave);
-        if (kind == kBoth) irregular_reduce_kernel<4, 4, false, kBoth, true><<<grid, block, 0, s>>>(in, offsets, out, out2, n, nullptr, nullptr, 0, nseg, shift, pairs, carried);
-        else irregular_reduce_kernel<4, 4, false, kSum, true><<<grid, block, 0, s>>>(in, offsets, out, nullptr, n, nullptr, nullptr, 0, nseg, shift, pairs, carried);
+        if (kind == kBoth) irregular_reduce_kernel<4, 4, false, kBoth, true><<<grid, block, 0, s>>>(in, offsets, out, out2, n, nullptr, nullptr, 0, nseg, shift, pairs, carried, parts, counter);
+        else irregular_reduce_kernel<4, 4, false, kSum, true><<<grid, block, 0, s>>>(in, offsets, out, nullptr, n, nullptr, nullptr, 0, nseg, shift, pairs, carried, parts, counter);
+        if (counter != nullptr) return check_launch("irregular_reduce_kernel");
     } else if (shape == 1) launch_irregular_reduce_shape<4, 8>(regular, kind, in, offsets, out, out2, n, starts, ends, seg_len, nseg, shift, pairs, carried, tiles, s);
     else if (shape == 2) launch_irregular_reduce_shape<2, 8>(regular, kind, in, offsets, out, out2, n, starts, ends, seg_len, nseg, shift, pairs, carried, tiles, s);
     else launch_irregular_reduce_shape<4, 4>(regular, kind, in, offsets, out, out2, n, starts, ends, seg_len, nseg, shift, pairs, carried, tiles, s);
     st = check_launch("irregular_reduce_kernel");
     if (st != TCR_OK || tiles == 1) return st;          // a single tile has nothing in front of it
     irregular_finish_kernel<kFinishThreads, kFinishFar><<<dim3((unsigned)ceil_div(tiles, kFinishThreads), ch), dim3(kFinishThreads), 0, s>>>(
-        pairs, carried, tiles, out, out2);
+        pairs, carried, tiles, out, out2, parts);
     return check_launch("irregular_finish_kernel");
 }
 

@@ -487,7 +487,41 @@ __device__ __forceinline__ uint32_t wave_scan_inclusive_u32(uint32_t x) {
 // follow the first channel's `tiles` pairs, are used for kBoth only).
 // SEARCH (irregular segments): the tile's range of entries is searched here, one edge per wavefront, instead of read from
 // the tables -- before the data is asked for: behind a tile's worth of loads every round of the search would wait for
-// them (arrays of up to 2^22 elements, where a launch in front costs more than the search).
+// them.  Such a tile keeps its share of the carried result apart (parts[tile], behind those of the other channel's tiles for
+// the second) instead of writing it to out, and with `counter` the workgroup that finishes last adds up what reaches
+// every tile (finish_tiles): one launch in all.
+template <int WAVES>
+__device__ __forceinline__ void finish_tiles(const TilePair* __restrict__ pairs, const uint64_t* __restrict__ carried,
+                                             const float* __restrict__ parts, uint32_t tiles, float* __restrict__ out,
+                                             float (&s_value)[WAVES], uint32_t (&s_flag)[WAVES], int wave, int lane) {
+    // device-scope loads: the pairs and parts have been written through by workgroups on other XCDs
+    float into = 0.0f;                                    // what reaches the first tile of the round
+    for (uint32_t first = 0; first < tiles; first += (uint32_t)(WAVES * kWave)) {
+        const uint32_t t = first + threadIdx.x, at = t < tiles ? t : 0u;
+        const unsigned long long word = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(pairs) + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t index = __hip_atomic_load(carried + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const float part = __hip_atomic_load(parts + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        TilePair mine = __builtin_bit_cast(TilePair, word);
+        if (t >= tiles) mine = TilePair{0.0f, 0u};
+        wave_seg_scan_inclusive(mine.flag, mine.value);
+        __syncthreads();                                  // (the round before has been read)
+        if (lane == kWave - 1) {
+            s_value[wave] = mine.value;
+            s_flag[wave] = mine.flag;
+        }
+        __syncthreads();
+        float ext = into;
+#pragma unroll
+        for (int v = 0; v < WAVES; ++v) {
+            if (v < wave) ext = s_flag[v] ? s_value[v] : ext + s_value[v];
+            into = s_flag[v] ? s_value[v] : into + s_value[v];
+        }
+        const uint32_t flag_before = wave_shr1_u32(mine.flag);
+        const float value_before = wave_shr1(mine.value);
+        if (t < tiles && index != kNoSegment) out[index] = part + (flag_before ? value_before : value_before + ext);
+    }
+}
+
 template <int U, int WAVES, bool REGULAR, int KIND = kSum, bool SEARCH = false>
 __global__ __launch_bounds__(WAVES * kWave) void irregular_reduce_kernel(const _Float16* __restrict__ in,
                                                                          const uint64_t* __restrict__ offsets,
@@ -497,7 +531,9 @@ __global__ __launch_bounds__(WAVES * kWave) void irregular_reduce_kernel(const _
                                                                          const uint64_t* __restrict__ ends_below,
                                                                          uint64_t seg_len, uint64_t nseg, uint32_t shift,
                                                                          TilePair* __restrict__ pairs,
-                                                                         uint64_t* __restrict__ carried) {
+                                                                         uint64_t* __restrict__ carried,
+                                                                         float* __restrict__ parts = nullptr,
+                                                                         uint32_t* __restrict__ counter = nullptr) {
     constexpr uint32_t kChunk = (uint32_t)kTile * U;
     constexpr uint32_t kBlockTile = kChunk * WAVES;
     constexpr int kSubs = U * WAVES;
@@ -691,12 +727,21 @@ __global__ __launch_bounds__(WAVES * kWave) void irregular_reduce_kernel(const _
                 break;
             }
         }
-#pragma unroll
-        for (int c = 0; c < CH; ++c) pairs[(uint64_t)c * gridDim.x + tile] = TilePair{total[c], closed};
         // the first segment end of the tile closes a segment begun earlier unless an entry sits on tb itself
-        carried[tile] = (end_lo < end_hi && end_lo == head_lo && end_lo >= 1) ? end_lo - 1 : kNoSegment;
+        const uint64_t open_segment = (end_lo < end_hi && end_lo == head_lo && end_lo >= 1) ? end_lo - 1 : kNoSegment;
+        if constexpr (SEARCH) {
+#pragma unroll
+            for (int c = 0; c < CH; ++c)
+                __hip_atomic_store(reinterpret_cast<unsigned long long*>(pairs) + ((uint64_t)c * gridDim.x + tile),
+                                   __builtin_bit_cast(unsigned long long, TilePair{total[c], closed}), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(carried + tile, open_segment, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+#pragma unroll
+            for (int c = 0; c < CH; ++c) pairs[(uint64_t)c * gridDim.x + tile] = TilePair{total[c], closed};
+            carried[tile] = open_segment;
+        }
     }
-    if (end_lo == end_hi) return;             // no segment ends here: nothing to write
+    if (!SEARCH && end_lo == end_hi) return;  // no segment ends here: nothing to write
 
     float ext[CH];                            // carry from the wavefronts in front, inside this tile only
 #pragma unroll
@@ -763,12 +808,27 @@ __global__ __launch_bounds__(WAVES * kWave) void irregular_reduce_kernel(const _
                 const float* const mine_at = stage + c * kStageFloats;
                 const float from_front = mine_at[kTile + at_lane];
                 const float value = mine_at[(e >> 2) * (kTile / 2) + 4 * at_lane + (e & 3u)] + (heads_upto ? 0.0f : from_front);
-                (c == 0 ? out_from : out2_from)[(int64_t)i - 1] = take ? value : 0.0f;
+                // (entry 0 closes the segment begun in an earlier tile: head_lo == 0 starts with entry 1)
+                if (SEARCH && i == 0u) __hip_atomic_store(parts + ((uint64_t)c * gridDim.x + tile), take ? value : 0.0f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                else (c == 0 ? out_from : out2_from)[(int64_t)i - 1] = take ? value : 0.0f;
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    if constexpr (SEARCH) {
+        if (counter == nullptr) return;
+        __shared__ uint32_t s_last;
+        __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0): this wavefront's stores have been acknowledged
+        __syncthreads();
+        if (threadIdx.x == 0) s_last = atomicInc(counter, gridDim.x - 1u) == gridDim.x - 1u ? 1u : 0u;      // (back to 0 with the last)
+        __syncthreads();
+        if (s_last == 0u) return;
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+            finish_tiles<WAVES>(pairs + (uint64_t)c * gridDim.x, carried, parts + (uint64_t)c * gridDim.x, gridDim.x,
+                                c == 0 ? out : out2, s_wave_value[0], s_wave_flag, wave, lane);
     }
 }
 
@@ -784,7 +844,8 @@ constexpr int kFinishThreads = 256, kFinishFar = 16;
 template <int THREADS, int FAR>
 __global__ __launch_bounds__(THREADS) void irregular_finish_kernel(const TilePair* __restrict__ pairs,
                                                                           const uint64_t* __restrict__ carried, uint64_t tiles,
-                                                                          float* __restrict__ out, float* __restrict__ out2) {
+                                                                          float* __restrict__ out, float* __restrict__ out2,
+                                                                          const float* __restrict__ parts) {
     constexpr int kWaves = THREADS / kWave;
     __shared__ float s_value[kWaves], s_far[kWaves];
     __shared__ uint32_t s_flag[kWaves];
@@ -802,7 +863,8 @@ __global__ __launch_bounds__(THREADS) void irregular_finish_kernel(const TilePai
         mine = pairs[t];
         seg = carried[t];
     }
-    const float had = seg != kNoSegment ? out[seg] : 0.0f;
+    // the tile's own share of the result: kept apart by the tiles that search, else already in its place
+    const float had = seg == kNoSegment ? 0.0f : (parts != nullptr ? parts[(uint64_t)blockIdx.y * tiles + t] : out[seg]);
     wave_seg_scan_inclusive(mine.flag, mine.value);
     if (lane == kWave - 1) {
         s_value[wave] = mine.value;

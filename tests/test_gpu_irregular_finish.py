@@ -74,3 +74,46 @@ def test_searched_and_looked_up_ranges_agree(tcr, oracle, recipe, shift):
         check(tcr, oracle, x, xd, off)
     finally:
         tcr.tuning_import("")
+
+
+def test_recorded_and_on_a_caller_workspace(tcr, oracle):
+    n = 40 * TILE + 77
+    inputs = [workloads.make_input(n, "int1", (3, k)) for k in range(2)]
+    off = workloads.make_offsets(n, "lognormal256", 2).view(np.int64)
+    od = torch.from_numpy(off).cuda()
+    x = torch.from_numpy(inputs[0]).cuda()
+    out = torch.empty(off.size - 1, dtype=torch.float32, device="cuda")
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        tcr.irregular_reduce(x, od, out=out)
+    side.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        tcr.irregular_reduce(x, od, out=out)
+    for k in (1, 0, 1, 1):
+        x.copy_(torch.from_numpy(inputs[k]).cuda())
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy().astype(np.float64), oracle.irregular_reduce(inputs[k], off))
+        with torch.cuda.stream(side):
+            again = tcr.irregular_reduce(x, od)
+        side.synchronize()
+        assert torch.equal(again, out)
+    # arbitrary contents: until a call that chains tiles has cleared the buffer, the count in it means nothing
+    want, moments = oracle.irregular_reduce(inputs[1], off), oracle.irregular_moments(inputs[1], off)
+    need = max(tcr.workspace_bytes(tcr.OP_IRREGULAR_MOMENTS, n, 0), tcr.workspace_bytes(tcr.OP_IRREGULAR_SCAN, n, 0))
+    buf = torch.full((need,), 0x77, dtype=torch.uint8, device="cuda")
+    try:
+        tcr.set_workspace(buf)
+        for _ in range(3):
+            assert np.array_equal(tcr.irregular_reduce(x, od).cpu().numpy().astype(np.float64), want)
+            a, q = tcr.irregular_moments(x, od)
+            assert np.array_equal(a.cpu().numpy().astype(np.float64), moments[0])
+            assert np.array_equal(q.cpu().numpy().astype(np.float64), moments[1])
+            assert np.array_equal(tcr.irregular_scan(x, od).cpu().numpy().astype(np.float64), oracle.irregular_scan(inputs[1], off))
+    finally:
+        torch.cuda.synchronize()
+        tcr.set_workspace(None)
