@@ -878,70 +878,97 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
     return TCR_OK;
 }
 
-// offsets == nullptr: regular segments of seg_len elements (no look-up tables).
-// kind: kSum, kSquares (regular segments only), or kBoth with the sums of squares in out2.  shape: an id of
-// kIrregularReduceShapes.
-template <int U, int W>
-inline void launch_irregular_reduce_shape(bool regular, int kind, const _Float16* in, const uint64_t* offsets, float* out, float* out2,
-                                          uint64_t n, const uint64_t* starts, const uint64_t* ends, uint64_t seg_len, uint64_t nseg,
-                                          uint32_t shift, TilePair* pairs, uint64_t* carried, uint64_t tiles, hipStream_t s) {
-    const dim3 grid((unsigned)tiles), block(W * kWave);
-    if (regular) {
-        if (kind == kBoth) irregular_reduce_kernel<U, W, true, kBoth><<<grid, block, 0, s>>>(in, nullptr, out, out2, n, nullptr, nullptr, seg_len, nseg, shift, pairs, carried);
-        else if (kind == kSquares) irregular_reduce_kernel<U, W, true, kSquares><<<grid, block, 0, s>>>(in, nullptr, out, out2, n, nullptr, nullptr, seg_len, nseg, shift, pairs, carried);
-        else irregular_reduce_kernel<U, W, true, kSum><<<grid, block, 0, s>>>(in, nullptr, out, out2, n, nullptr, nullptr, seg_len, nseg, shift, pairs, carried);
+struct IrregularReduce {
+    const _Float16* in;
+    const uint64_t* offsets;      // nullptr: regular segments of seg_len elements (no look-up tables)
+    float* out;
+    float* out2;
+    uint64_t n;
+    const uint64_t* starts;
+    const uint64_t* ends;
+    uint64_t seg_len, nseg;
+    uint32_t shift;
+    TilePair* pairs;
+    uint64_t* carried;
+    uint64_t tiles;
+    int kind;                     // kSum, kSquares (regular segments only), or kBoth with the sums of squares in out2
+};
+template <int U, int W, bool LINKED, bool REGULAR, int KIND>
+inline void launch_irregular_reduce_kernel(const IrregularReduce& a, const ReduceLink& link, hipStream_t s) {
+    irregular_reduce_kernel<U, W, REGULAR, KIND, LINKED><<<dim3((unsigned)a.tiles), dim3(W * kWave), 0, s>>>(
+        a.in, a.offsets, a.out, a.out2, a.n, a.starts, a.ends, a.seg_len, a.nseg, a.shift, a.pairs, a.carried, link);
+}
+template <int U, int W, bool LINKED>
+inline tcr_status launch_irregular_reduce_shape(const IrregularReduce& a, const ReduceLink& link, hipStream_t s) {
+    if (a.offsets == nullptr) {
+        if (a.kind == kBoth) launch_irregular_reduce_kernel<U, W, LINKED, true, kBoth>(a, link, s);
+        else if (a.kind == kSquares) launch_irregular_reduce_kernel<U, W, LINKED, true, kSquares>(a, link, s);
+        else launch_irregular_reduce_kernel<U, W, LINKED, true, kSum>(a, link, s);
     } else {
-        if (kind == kBoth) irregular_reduce_kernel<U, W, false, kBoth><<<grid, block, 0, s>>>(in, offsets, out, out2, n, starts, ends, 0, nseg, shift, pairs, carried);
-        else irregular_reduce_kernel<U, W, false, kSum><<<grid, block, 0, s>>>(in, offsets, out, nullptr, n, starts, ends, 0, nseg, shift, pairs, carried);
+        if (a.kind == kBoth) launch_irregular_reduce_kernel<U, W, LINKED, false, kBoth>(a, link, s);
+        else launch_irregular_reduce_kernel<U, W, LINKED, false, kSum>(a, link, s);
     }
+    return check_launch("irregular_reduce_kernel");
 }
 
 inline tcr_status launch_irregular_reduce(const _Float16* in, const uint64_t* offsets, float* out, uint64_t n, uint64_t nseg,
                                           uint64_t seg_len, hipStream_t s, int kind = kSum, float* out2 = nullptr, int shape = -1) {
+    const bool untuned = shape < 0 && tuned_id(kTuneIrregular, 0) < 0;
     if (shape < 0) shape = irregular_shape(false);
     const uint64_t elems = irregular_tile_elems(false, shape);
     const uint32_t shift = alignment_shift(in);
     in -= shift;
     n += shift;
     const uint64_t tiles = irregular_tiles(false, n, shape);
-    const bool regular = offsets == nullptr;
     const unsigned ch = kind == kBoth ? 2u : 1u;
     Workspace* ws = nullptr;
     bool capturing = false;
     tcr_status st = get_workspace(s, &ws, &capturing);
     if (st != TCR_OK) return st;
+    // (also where the call does without them: the same call can then be recorded into a graph)
     st = ensure_partials(ws, s, 2 * (irregular_words(false, n, shape) + (ch - 1) * tiles), capturing);
     if (st != TCR_OK) return st;
+    // One launch, whose tiles search the offsets and add what reaches them from in front themselves, out of one descriptor
+    // per tile and channel; against a look-up kernel in front and a finishing kernel behind, us, segments of 16 elements /
+    // lognormal lengths / seven segments: n = 2^20 8.0 / 6.2 / 5.5 -> 5.6 / 5.3 / 5.3, 2^22 10.6 / 9.0 / 8.6 -> 7.4 / 6.2 / 6.2, 2^24
+    // 19.0 / 13.1 / 12.9 -> 17.3 / 11.8 / 10.4, 2^25 29.8 / 20.1 / 19.0 -> 29.3 / 19.6 / 16.1, both moments at 2^24 25.5 / 17.5 / 14.0
+    // -> 22.9 / 16.0 / 12.3.  Beyond, the searches are what the tiles wait for (2^26 43.6 / 29.8 / 28.2 -> 52.0 / 34.2 / 25.4) and
+    // for both moments and regular segments the sums of thousands of tiles behind one result (one segment of 2^26 elements:
+    // 25.9 -> 31.0).  Not where the descriptors cannot be had: a caller's buffer that is too small, a call recorded into a
+    // graph (recording one that uses descriptors leaves their epochs to the device, which costs every later call on the
+    // stream a launch).
+    const bool room = capturing ? ws->device_managed && !ws->dirty && ch * tiles <= ws->desc_capacity
+                                : !ws->caller_owned || ch * tiles <= ws->desc_capacity;
+    const bool linked = room && shape != 1 && tiles <= (offsets != nullptr && kind == kSum ? 4096u : 2048u);
+    // (up to four tiles per compute unit twice the wavefronts per tile: segments of 16 elements, n = 2^20 / 2^22 / 2^23 / 2^24
+    // 7.1 / 8.6 / 12.0 / 17.3 us with 4 wavefronts, 5.6 / 7.4 / 11.2 / 19.3 with 8)
+    if (linked && untuned && tiles <= 4 * (uint64_t)compute_units()) shape = 2;
+    ReduceLink link = {};
+    if (linked) {
+        st = begin_lookback(ws, s, ch * tiles, &link.ws, capturing);
+        if (st != TCR_OK) return st;
+        link.patience = g_variant.scan_wait ? kOncePatience : 0u;
+        const IrregularReduce a = {in, offsets, out, out2, n, nullptr, nullptr, seg_len, nseg, shift, nullptr, nullptr, tiles, kind};
+        st = shape == 2 ? launch_irregular_reduce_shape<2, 8, true>(a, link, s) : launch_irregular_reduce_shape<4, 4, true>(a, link, s);
+        if (st != TCR_OK) ws->dirty = true;
+        return st;
+    }
     uint64_t* starts = reinterpret_cast<uint64_t*>(ws->partials);
     uint64_t* ends = starts + (tiles + 1);
     uint64_t* carried = ends + (tiles + 1);
     TilePair* pairs = reinterpret_cast<TilePair*>(carried + tiles);              // ch * tiles
-    // (tiles that search the offsets themselves: n = 2^20 / 2^24, lognormal lengths, 11.4 / 15.9 us with the look-up kernel
-    // in front, 8.0 / 13.2 without; 2^25 22.0 / 22.2, 2^26 31.1 / 35.0 -- the searches are then what the tiles wait for)
-    const bool search = !regular && shape == 0 && tiles <= 2048;
-    if (!regular && !search) {
+    const IrregularReduce a = {in, offsets, out, out2, n, starts, ends, seg_len, nseg, shift, pairs, carried, tiles, kind};
+    if (offsets != nullptr) {
         irregular_bounds_kernel<<<dim3((unsigned)ceil_div(tiles + 1, kBoundsWaves * kBoundsPerWave)), dim3(kBoundsWaves * kWave), 0, s>>>(
             offsets, nseg + 1, elems, tiles + 1, shift, starts, ends);
         st = check_launch("irregular_bounds_kernel");
         if (st != TCR_OK) return st;
     }
-    // (the tables' words are free then: the tiles' own shares of the carried results go there)
-    float* parts = search ? reinterpret_cast<float*>(starts) : nullptr;
-    // (one launch up to 256 tiles: lognormal lengths at n = 2^16 / 2^20 / 2^21 / 2^22 5.8 / 6.2 / 7.3 / 11.2 us against 8.0 /
-    // 8.2 / 8.4 / 8.5 with the finishing kernel -- more counts on one address than that cost more than the launch)
-    uint32_t* counter = search && tiles > 1 && tiles <= kFinishThreads ? finish_counter(ws, capturing) : nullptr;
-    if (search) {
-        const dim3 grid((unsigned)tiles), block(4 * kWave);
-        if (kind == kBoth) irregular_reduce_kernel<4, 4, false, kBoth, true><<<grid, block, 0, s>>>(in, offsets, out, out2, n, nullptr, nullptr, 0, nseg, shift, pairs, carried, parts, counter);
-        else irregular_reduce_kernel<4, 4, false, kSum, true><<<grid, block, 0, s>>>(in, offsets, out, nullptr, n, nullptr, nullptr, 0, nseg, shift, pairs, carried, parts, counter);
-        if (counter != nullptr) return check_launch("irregular_reduce_kernel");
-    } else if (shape == 1) launch_irregular_reduce_shape<4, 8>(regular, kind, in, offsets, out, out2, n, starts, ends, seg_len, nseg, shift, pairs, carried, tiles, s);
-    else if (shape == 2) launch_irregular_reduce_shape<2, 8>(regular, kind, in, offsets, out, out2, n, starts, ends, seg_len, nseg, shift, pairs, carried, tiles, s);
-    else launch_irregular_reduce_shape<4, 4>(regular, kind, in, offsets, out, out2, n, starts, ends, seg_len, nseg, shift, pairs, carried, tiles, s);
-    st = check_launch("irregular_reduce_kernel");
+    st = shape == 1 ? launch_irregular_reduce_shape<4, 8, false>(a, link, s)
+                    : (shape == 2 ? launch_irregular_reduce_shape<2, 8, false>(a, link, s) : launch_irregular_reduce_shape<4, 4, false>(a, link, s));
     if (st != TCR_OK || tiles == 1) return st;          // a single tile has nothing in front of it
     irregular_finish_kernel<kFinishThreads, kFinishFar><<<dim3((unsigned)ceil_div(tiles, kFinishThreads), ch), dim3(kFinishThreads), 0, s>>>(
-        pairs, carried, tiles, out, out2, parts);
+        pairs, carried, tiles, out, out2);
     return check_launch("irregular_finish_kernel");
 }
 

@@ -12,10 +12,10 @@
 // across a wavefront's sub-tiles in registers and across wavefronts through LDS.  Across tiles the scan
 // uses the descriptor chain of the regular scans -- a tile that contains a segment start publishes the
 // sum since its last start as a finished prefix at once, because no later tile can need more of it --
-// while the reduction, where at most one result per tile depends on earlier tiles, leaves the tiles
-// independent and adds that one carry afterwards (a small kernel over the per-tile sums).
+// while the reduction, where at most one result per tile depends on earlier tiles, either lets each tile add that
+// one part itself or leaves the tiles independent and adds it afterwards (a small kernel over the per-tile sums).
 //
-// What a tile needs from the offsets is found before it starts: irregular_bounds_kernel writes, per
+// What a tile of a large array needs from the offsets is found before it starts: irregular_bounds_kernel writes, per
 // tile boundary, how many offsets lie below it, so a tile reads its range of entries with one look-up
 // instead of searching while its data waits in registers.
 #pragma once
@@ -478,51 +478,94 @@ __device__ __forceinline__ uint32_t wave_scan_inclusive_u32(uint32_t x) {
 // them in LDS as they are, next to the 64 sums that reach its lanes from in front, and its lanes walk the
 // entries that end a segment inside the sub-tile -- the result is the staged sum plus, unless a head lies
 // between the lane's first element and the segment's last, the sum from in front -- so consecutive lanes write
-// consecutive results.  The one result per tile that belongs to a segment begun in an earlier tile is written
-// without that earlier part; the tile records which segment it is (carried[tile], or none) and its own pair
-// (pairs[tile]) for the finishing kernel.
+// consecutive results.  One result per tile may belong to a segment begun in an earlier tile (LINKED, below).
 // REGULAR: entry s is s * seg_len, s = 0 .. nseg, instead of offsets[s] (offsets and the tables are not read).
 // shift: as for irregular_scan_kernel (`in` points that many elements in front of the caller's array).
 // KIND: sums of the elements, of their squares, or both (out2 and the pairs of the second channel, which
 // follow the first channel's `tiles` pairs, are used for kBoth only).
-// SEARCH (irregular segments): the tile's range of entries is searched here, one edge per wavefront, instead of read from
-// the tables -- before the data is asked for: behind a tile's worth of loads every round of the search would wait for
-// them.  Such a tile keeps its share of the carried result apart (parts[tile], behind those of the other channel's tiles for
-// the second) instead of writing it to out, and with `counter` the workgroup that finishes last adds up what reaches
-// every tile (finish_tiles): one launch in all.
-template <int WAVES>
-__device__ __forceinline__ void finish_tiles(const TilePair* __restrict__ pairs, const uint64_t* __restrict__ carried,
-                                             const float* __restrict__ parts, uint32_t tiles, float* __restrict__ out,
-                                             float (&s_value)[WAVES], uint32_t (&s_flag)[WAVES], int wave, int lane) {
-    // device-scope loads: the pairs and parts have been written through by workgroups on other XCDs
-    float into = 0.0f;                                    // what reaches the first tile of the round
-    for (uint32_t first = 0; first < tiles; first += (uint32_t)(WAVES * kWave)) {
-        const uint32_t t = first + threadIdx.x, at = t < tiles ? t : 0u;
-        const unsigned long long word = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(pairs) + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint64_t index = __hip_atomic_load(carried + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const float part = __hip_atomic_load(parts + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        TilePair mine = __builtin_bit_cast(TilePair, word);
-        if (t >= tiles) mine = TilePair{0.0f, 0u};
-        wave_seg_scan_inclusive(mine.flag, mine.value);
-        __syncthreads();                                  // (the round before has been read)
-        if (lane == kWave - 1) {
-            s_value[wave] = mine.value;
-            s_flag[wave] = mine.flag;
-        }
-        __syncthreads();
-        float ext = into;
+// LINKED: the tile adds that part itself.  The segment's start s0 is known from the offsets, so the part is the sum from s0
+// to the tile's start: at most 512 elements per wavefront are added up by the wavefronts while their own data is on its
+// way (a neighbour's data, mostly found in a cache); a longer part is the published sums of the tiles from the one that
+// holds s0 on -- no tile in between has a head -- read by the wavefront whose result it is, after its other results.  A
+// sum that is not there after `patience` looks is added up from the elements, so no wait depends on which workgroups run.
+// The tile's range of entries is then searched here, one edge per wavefront, instead of read from the tables -- before
+// the data is asked for: behind a tile's worth of loads every round of the search would wait for them.
+// Not LINKED: that result is written without its earlier part; the tile records which segment it is (carried[tile], or
+// none) and its own pair (pairs[tile]) for the finishing kernel.
+struct ReduceLink {
+    ScanWorkspace ws;             // desc: one sum per channel and tile, channel after channel
+    uint32_t patience;
+};
+
+// Sum (KIND, channel C) of this wavefront's 512 elements from position `at` on, without those in front of `from`.
+template <int KIND, int C>
+__device__ __forceinline__ float masked_terms(half8 x, uint64_t at, uint64_t from, int lane) {
+    const uint64_t mine = at + 8 * (uint64_t)lane;
+    const half8 kept = drop_leading(x, from > mine ? (int)(from - mine < 8 ? from - mine : 8) : 0);
+    float v = 0.0f;
 #pragma unroll
-        for (int v = 0; v < WAVES; ++v) {
-            if (v < wave) ext = s_flag[v] ? s_value[v] : ext + s_value[v];
-            into = s_flag[v] ? s_value[v] : into + s_value[v];
-        }
-        const uint32_t flag_before = wave_shr1_u32(mine.flag);
-        const float value_before = wave_shr1(mine.value);
-        if (t < tiles && index != kNoSegment) out[index] = part + (flag_before ? value_before : value_before + ext);
-    }
+    for (int e = 0; e < 8; ++e) v += term<KIND, C>(kept[e]);
+    return wave_sum(v);
 }
 
-template <int U, int WAVES, bool REGULAR, int KIND = kSum, bool SEARCH = false>
+// Sum from position s0 to the start of `tile` out of the published sums (whole wavefront).  PER sums per lane and step, all
+// asked for before the first is looked at: a segment of a million elements spans a hundred tiles and more.
+template <int KIND, int C, int PER>
+__device__ __forceinline__ float linked_step(const _Float16* __restrict__ in, const unsigned long long* desc, uint32_t want, uint32_t hi,
+                                             uint32_t span, uint64_t s0, int tile_log2, uint32_t patience, int lane) {
+    float v[PER];
+    for (uint32_t polls = 0;; ++polls) {
+        unsigned long long d[PER];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const uint32_t at = (uint32_t)(k * kWave + lane);
+            d[k] = load_descriptor(&desc[hi - 1u - (at < span ? at : 0u)]);
+        }
+        uint32_t missing = 0u;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const bool counts = (uint32_t)(k * kWave + lane) < span;
+            if (counts && (uint32_t)(d[k] >> 32) != want) missing |= 1u << k;
+            v[k] = counts ? __builtin_bit_cast(float, (uint32_t)d[k]) : 0.0f;
+        }
+        if (__ballot(missing != 0u) == 0ull) break;
+        if (polls >= patience) {
+#pragma unroll
+            for (int k = 0; k < PER; ++k) {
+                for (unsigned long long lanes = __ballot((missing >> k) & 1u); lanes != 0ull; lanes &= lanes - 1ull) {
+                    const int slot = __builtin_ctzll(lanes);
+                    const uint64_t begin = (uint64_t)(hi - 1u - (uint32_t)(k * kWave + slot)) << tile_log2;
+                    float sum = 0.0f;
+                    for (uint64_t at = begin; at < begin + (1ull << tile_log2); at += (uint64_t)kTile)
+                        if (at + (uint64_t)kTile > s0) sum += masked_terms<KIND, C>(load8(in, at + 8 * (uint64_t)lane), at, s0, lane);
+                    if (lane == slot) v[k] = sum;
+                }
+            }
+            break;
+        }
+        __builtin_amdgcn_s_sleep(1);
+    }
+    float sum = 0.0f;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) sum += v[k];
+    return wave_sum(sum);
+}
+template <int KIND, int C>
+__device__ __forceinline__ float linked_sum(const _Float16* __restrict__ in, const unsigned long long* desc, uint32_t epoch, uint32_t tile,
+                                            uint64_t s0, int tile_log2, uint32_t patience, int lane) {
+    const uint32_t first = (uint32_t)(s0 >> tile_log2), want = epoch * 4u + kStatusAggregate;
+    constexpr int kPer = 8;
+    float acc = 0.0f;
+    for (uint32_t hi = tile; hi > first;) {
+        const uint32_t left = hi - first, span = left < (uint32_t)(kPer * kWave) ? left : (uint32_t)(kPer * kWave);
+        if (span <= (uint32_t)kWave) acc += linked_step<KIND, C, 1>(in, desc, want, hi, span, s0, tile_log2, patience, lane);
+        else acc += linked_step<KIND, C, kPer>(in, desc, want, hi, span, s0, tile_log2, patience, lane);
+        hi -= span;
+    }
+    return acc;
+}
+
+template <int U, int WAVES, bool REGULAR, int KIND, bool LINKED>
 __global__ __launch_bounds__(WAVES * kWave) void irregular_reduce_kernel(const _Float16* __restrict__ in,
                                                                          const uint64_t* __restrict__ offsets,
                                                                          float* __restrict__ out, float* __restrict__ out2,
@@ -532,8 +575,9 @@ __global__ __launch_bounds__(WAVES * kWave) void irregular_reduce_kernel(const _
                                                                          uint64_t seg_len, uint64_t nseg, uint32_t shift,
                                                                          TilePair* __restrict__ pairs,
                                                                          uint64_t* __restrict__ carried,
-                                                                         float* __restrict__ parts = nullptr,
-                                                                         uint32_t* __restrict__ counter = nullptr) {
+                                                                         ReduceLink link) {
+    constexpr bool SEARCH = LINKED && !REGULAR;
+    static_assert(!SEARCH || WAVES >= 4, "one wavefront per edge");
     constexpr uint32_t kChunk = (uint32_t)kTile * U;
     constexpr uint32_t kBlockTile = kChunk * WAVES;
     constexpr int kSubs = U * WAVES;
@@ -546,7 +590,10 @@ __global__ __launch_bounds__(WAVES * kWave) void irregular_reduce_kernel(const _
     __shared__ uint64_t s_bound[4];
     static_assert(kBlockTile <= 65535u, "positions are kept in 16 bits");
     constexpr int CH = channels<KIND>();
+    constexpr uint64_t kBackMax = (uint64_t)kTile * WAVES;        // the longest open part that the wavefronts add up themselves
+    constexpr int kTileLog2 = __builtin_ctz(kBlockTile);
     __shared__ float s_wave_value[CH][WAVES];
+    __shared__ float s_back[LINKED ? CH : 1][WAVES];
     __shared__ uint32_t s_wave_flag[WAVES];
     // Per wavefront: first one binary16 value per element of its share, 0 on a head and 1 elsewhere (the factor
     // that continues or restarts a lane's running sum); later, sub-tile by sub-tile, the running sums of 512
@@ -565,7 +612,6 @@ __global__ __launch_bounds__(WAVES * kWave) void irregular_reduce_kernel(const _
     // while the tile's data is still on its way (the barriers below order LDS only and wait for neither)
     uint64_t head_lo = 0, head_hi = 0, end_lo = 0, end_hi = 0;
     if constexpr (SEARCH) {
-        static_assert(!SEARCH || (!REGULAR && WAVES >= 4), "");
         if (wave < 4) {
             // entries below tb, below te, and the same with the entries on the edge added (entry s lies on offsets[s] + shift)
             const uint64_t edge = tb + ((wave & 1) ? (uint64_t)kBlockTile : 0) + (uint64_t)(wave >> 1);
@@ -625,12 +671,30 @@ __global__ __launch_bounds__(WAVES * kWave) void irregular_reduce_kernel(const _
             if (s < end_hi) ahead[k] = offsets[s];
         }
     }
+    uint64_t open_at = 0;                         // the entry that starts the segment open at tb, if there is one
+    if constexpr (SEARCH) open_at = offsets[end_lo > 0 && end_lo <= nseg ? end_lo - 1 : 0];
     lds_barrier();
     if constexpr (REGULAR) {
         head_lo = s_bound[0];
         head_hi = s_bound[1];
         end_lo = s_bound[2];
         end_hi = s_bound[3];
+        if constexpr (LINKED) open_at = end_lo > 0 ? (end_lo - 1) * seg_len : 0;
+    }
+    // How many elements in front of the tile belong to the first result of the tile (0: a segment starts on tb, or none ends
+    // in the tile), and this wavefront's 512 of them.
+    uint64_t back = 0, back_at = 0;
+    half8 back_x = splat_half(0.0f);
+    if constexpr (LINKED) {
+        const uint64_t s0 = open_at + shift;
+        if (tile != 0 && end_lo == head_lo && end_lo >= 1 && end_lo < end_hi && s0 < tb) back = tb - s0;
+        const uint64_t behind = (uint64_t)kTile * (uint64_t)wave;
+        const bool adds = back <= kBackMax && behind < back;
+        back_at = adds ? tb - behind - (uint64_t)kTile : 0;
+        // (only the groups of 8 from s0 on are read: in front of them the offset from `from` wraps out of range)
+        const uint64_t from = !adds ? 0 : (s0 > back_at ? s0 & ~7ull : back_at);
+        const __amdgpu_buffer_rsrc_t back_src = make_rsrc(in + from, adds ? (uint32_t)(back_at + (uint64_t)kTile - from) * 2u : 0u);
+        back_x = buffer_load8(back_src, (uint32_t)(back_at + 8 * (uint64_t)lane - from) * 2u);
     }
     // (the first tile also takes the entries on position 0, which close empty segments in front of everything)
     if (tile == 0) end_lo = 0;
@@ -707,9 +771,22 @@ __global__ __launch_bounds__(WAVES * kWave) void irregular_reduce_kernel(const _
         }
         chunk_flag |= sub_flag;
     }
+    float back_sum[CH];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) back_sum[c] = 0.0f;
+    const bool far = LINKED && back > kBackMax;
+    if constexpr (LINKED) {
+        if (!far && (uint64_t)kTile * (uint64_t)wave < back) {
+            back_sum[0] = masked_terms<KIND, 0>(back_x, back_at, tb - back, lane);
+            if constexpr (CH == 2) back_sum[CH - 1] = masked_terms<KIND, 1>(back_x, back_at, tb - back, lane);
+        }
+    }
     if (lane == 0) {
 #pragma unroll
-        for (int c = 0; c < CH; ++c) s_wave_value[c][wave] = run[c];
+        for (int c = 0; c < CH; ++c) {
+            s_wave_value[c][wave] = run[c];
+            if constexpr (LINKED) s_back[c][wave] = back_sum[c];
+        }
         s_wave_flag[wave] = chunk_flag;
     }
     lds_barrier();
@@ -727,21 +804,21 @@ __global__ __launch_bounds__(WAVES * kWave) void irregular_reduce_kernel(const _
                 break;
             }
         }
-        // the first segment end of the tile closes a segment begun earlier unless an entry sits on tb itself
-        const uint64_t open_segment = (end_lo < end_hi && end_lo == head_lo && end_lo >= 1) ? end_lo - 1 : kNoSegment;
-        if constexpr (SEARCH) {
+        if constexpr (LINKED) {
+            const ScanWorkspace ws = resolve_workspace(link.ws);
+            if (tile == 0 && ws.state != nullptr && !ws.device_managed) ws.state[0] = ws.epoch;
 #pragma unroll
             for (int c = 0; c < CH; ++c)
-                __hip_atomic_store(reinterpret_cast<unsigned long long*>(pairs) + ((uint64_t)c * gridDim.x + tile),
-                                   __builtin_bit_cast(unsigned long long, TilePair{total[c], closed}), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(carried + tile, open_segment, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&ws.desc[(uint64_t)c * gridDim.x + tile], pack_desc(ws.epoch, kStatusAggregate, total[c]),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else {
+            // the first segment end of the tile closes a segment begun earlier unless an entry sits on tb itself
 #pragma unroll
             for (int c = 0; c < CH; ++c) pairs[(uint64_t)c * gridDim.x + tile] = TilePair{total[c], closed};
-            carried[tile] = open_segment;
+            carried[tile] = (end_lo < end_hi && end_lo == head_lo && end_lo >= 1) ? end_lo - 1 : kNoSegment;
         }
     }
-    if (!SEARCH && end_lo == end_hi) return;  // no segment ends here: nothing to write
+    if (end_lo == end_hi) return;             // no segment ends here: nothing to write
 
     float ext[CH];                            // carry from the wavefronts in front, inside this tile only
 #pragma unroll
@@ -765,12 +842,24 @@ __global__ __launch_bounds__(WAVES * kWave) void irregular_reduce_kernel(const _
     const uint32_t i_first = head_lo == 0 ? 1u : 0u;                    // offsets[0] closes nothing
     float* const out_from = out + head_lo;                              // (out_from[i - 1] is never touched for head_lo + i == 0)
     float* const out2_from = CH == 2 ? out2 + head_lo : nullptr;
+    // (entry head_lo closes the segment open at tb, where back != 0: its result gets the part in front of the tile)
+    float in_front[CH], kept[CH];
+    bool owner = false;                                                 // this wavefront adds a far part to that result (lane 0's `kept`)
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        in_front[c] = kept[c] = 0.0f;
+        if (LINKED && back != 0 && !far) {
+#pragma unroll
+            for (int v = 0; v < WAVES; ++v) in_front[c] += s_back[c][v];
+        }
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int sub = wave * U + u;
         const uint32_t count = (uint32_t)__builtin_amdgcn_readlane((int)mine, sub);
         if (count == 0u) continue;
         const uint32_t i0 = (uint32_t)(end_lo - head_lo) + ((uint32_t)__builtin_amdgcn_readlane((int)upto, sub) - count);
+        owner = owner || (far && i0 == 0u);
         // the sub-tile's running sums without what reaches the lane from in front of it, and that sum per lane
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
@@ -808,27 +897,24 @@ __global__ __launch_bounds__(WAVES * kWave) void irregular_reduce_kernel(const _
                 const float* const mine_at = stage + c * kStageFloats;
                 const float from_front = mine_at[kTile + at_lane];
                 const float value = mine_at[(e >> 2) * (kTile / 2) + 4 * at_lane + (e & 3u)] + (heads_upto ? 0.0f : from_front);
-                // (entry 0 closes the segment begun in an earlier tile: head_lo == 0 starts with entry 1)
-                if (SEARCH && i == 0u) __hip_atomic_store(parts + ((uint64_t)c * gridDim.x + tile), take ? value : 0.0f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                else (c == 0 ? out_from : out2_from)[(int64_t)i - 1] = take ? value : 0.0f;
+                if (i == 0u) kept[c] = value + in_front[c];
+                (c == 0 ? out_from : out2_from)[(int64_t)i - 1] = take ? (i == 0u ? kept[c] : value) : 0.0f;
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    if constexpr (SEARCH) {
-        if (counter == nullptr) return;
-        __shared__ uint32_t s_last;
-        __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0): this wavefront's stores have been acknowledged
-        __syncthreads();
-        if (threadIdx.x == 0) s_last = atomicInc(counter, gridDim.x - 1u) == gridDim.x - 1u ? 1u : 0u;      // (back to 0 with the last)
-        __syncthreads();
-        if (s_last == 0u) return;
-#pragma unroll
-        for (int c = 0; c < CH; ++c)
-            finish_tiles<WAVES>(pairs + (uint64_t)c * gridDim.x, carried, parts + (uint64_t)c * gridDim.x, gridDim.x,
-                                c == 0 ? out : out2, s_wave_value[0], s_wave_flag, wave, lane);
+    if constexpr (LINKED) {
+        if (owner) {
+            const ScanWorkspace ws = resolve_workspace(link.ws);
+            const float sum = linked_sum<KIND, 0>(in, ws.desc, ws.epoch, tile, tb - back, kTileLog2, link.patience, lane);
+            if (lane == 0) out_from[-1] = kept[0] + sum;
+            if constexpr (CH == 2) {
+                const float sum2 = linked_sum<KIND, 1>(in, ws.desc + gridDim.x, ws.epoch, tile, tb - back, kTileLog2, link.patience, lane);
+                if (lane == 0) out2_from[-1] = kept[CH - 1] + sum2;
+            }
+        }
     }
 }
 
@@ -844,8 +930,7 @@ constexpr int kFinishThreads = 256, kFinishFar = 16;
 template <int THREADS, int FAR>
 __global__ __launch_bounds__(THREADS) void irregular_finish_kernel(const TilePair* __restrict__ pairs,
                                                                           const uint64_t* __restrict__ carried, uint64_t tiles,
-                                                                          float* __restrict__ out, float* __restrict__ out2,
-                                                                          const float* __restrict__ parts) {
+                                                                          float* __restrict__ out, float* __restrict__ out2) {
     constexpr int kWaves = THREADS / kWave;
     __shared__ float s_value[kWaves], s_far[kWaves];
     __shared__ uint32_t s_flag[kWaves];
@@ -863,8 +948,7 @@ __global__ __launch_bounds__(THREADS) void irregular_finish_kernel(const TilePai
         mine = pairs[t];
         seg = carried[t];
     }
-    // the tile's own share of the result: kept apart by the tiles that search, else already in its place
-    const float had = seg == kNoSegment ? 0.0f : (parts != nullptr ? parts[(uint64_t)blockIdx.y * tiles + t] : out[seg]);
+    const float had = seg == kNoSegment ? 0.0f : out[seg];
     wave_seg_scan_inclusive(mine.flag, mine.value);
     if (lane == kWave - 1) {
         s_value[wave] = mine.value;
