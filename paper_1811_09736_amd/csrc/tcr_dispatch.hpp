@@ -745,12 +745,11 @@ inline tcr_status launch_fill_outside(const uint64_t* offsets, uint64_t nseg, vo
 }
 
 // One tile per workgroup (tcr_once.hpp).  in, out, n: already counted from the 16-byte boundary below the caller's array.
-template <int U, int W, int MODE>
-inline void launch_tile_scan(const TileScan& a, bool local, const ScanWorkspace& dev, hipStream_t s) {
+template <int U, int W, int MODE, bool LOCAL>
+inline void launch_tile_scan(const TileScan& a, const ScanWorkspace& dev, hipStream_t s) {
     const dim3 grid((unsigned)ceil_div(a.n, (uint64_t)(kTile * U * W))), block(W * kWave);
-    if (local) irregular_scan_kernel<U, W, true, MODE, true><<<grid, block, 0, s>>>(a, dev);
-    else if (a.offsets == nullptr) irregular_scan_kernel<U, W, true, MODE, false><<<grid, block, 0, s>>>(a, dev);
-    else irregular_scan_kernel<U, W, false, MODE, false><<<grid, block, 0, s>>>(a, dev);
+    if (LOCAL || a.offsets == nullptr) irregular_scan_kernel<U, W, true, MODE, LOCAL><<<grid, block, 0, s>>>(a, dev);
+    else if constexpr (!LOCAL) irregular_scan_kernel<U, W, false, MODE, false><<<grid, block, 0, s>>>(a, dev);
 }
 template <int MODE>
 inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, void* out, uint64_t n, uint64_t nseg, uint64_t seg_len,
@@ -778,8 +777,8 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
         // 8 wavefronts, so that the open part is a small share of what a workgroup reads -- unless segments are short and
         // the array streams from memory (seg_len 33 at n = 2^24 / 2^26 / 2^28: 23.2 / 74.8 / 285 us with 8, 23.6 / 73.3 /
         // 276 with 16; 2001: 22.7 / 74.4 / 277 and 24.0 / 77.8 / 290), or longer than 8 wavefronts can add up at once
-        if (seg_len > 4096 || (seg_len <= 1024 && n > (1ull << 24))) launch_tile_scan<1, 16, MODE>(a, true, dev, s);
-        else launch_tile_scan<1, 8, MODE>(a, true, dev, s);
+        if (seg_len > 4096 || (seg_len <= 1024 && n > (1ull << 24))) launch_tile_scan<1, 16, MODE, true>(a, dev, s);
+        else launch_tile_scan<1, 8, MODE, true>(a, dev, s);
         return check_launch("irregular_scan_kernel");
     }
     Workspace* ws = nullptr;
@@ -787,16 +786,25 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
     tcr_status st = get_workspace(s, &ws, &capturing);
     if (st != TCR_OK) return st;
     const uint64_t limit = ws->caller_owned || capturing ? ws->desc_capacity : ~0ull;
-    // the smallest tiles of which there are no more than compute units (n = 2^22, seg_len 10001: 8.2 us with 16384-element
-    // tiles, 9.0 with 8192), at most 32768 elements (65536: 2 us slower at n = 2^24, one workgroup per compute unit)
+    // Workgroups of 8 wavefronts, small enough that the compute units get about equally many: with 4096, 8192 and 16384
+    // elements a tile n = 2.2e6 7.6 / 7.2 / 8.4 us, 5.2e6 15.1 / 11.7 / 12.3, 8e6 20.5 / 16.5 / 14.7 (seven segments; lognormal
+    // lengths and regular segments of 10802 and 198163 elements alike), 2^24 - / 31.7 / 27.4.  16 wavefronts, 16384 and
+    // 32768 elements: 2.2e6 7.9 / 11.1, 5.2e6 15.0 / 13.1, 8e6 17.2 / 15.8, 2^24 33.6 / 27.2 -- better where every unit just
+    // gets one (4.1e6: 9.5 us against 10.1), and 32768 where the table has no room for more tiles.
     const uint64_t units = (uint64_t)compute_units();
-    int u = 1;
-    while (u < 4 && (ceil_div(n, (uint64_t)(kTile * 16 * u)) > units || ceil_div(n, (uint64_t)(kTile * 16 * u)) > limit)) u *= 2;
-    st = begin_lookback(ws, s, ceil_div(n, (uint64_t)(kTile * 16 * u)), &dev, capturing);
+    const auto tiles_of = [n](int u, int w) { return ceil_div(n, (uint64_t)(kTile * u * w)); };
+    int u = 4, w = 8;
+    if (tiles_of(1, 8) <= 2 * units) u = 1;
+    else if (tiles_of(2, 16) <= units && 4 * tiles_of(2, 16) > 3 * units) u = 2, w = 16;
+    else if (tiles_of(2, 8) <= 3 * units) u = 2;
+    if (tiles_of(u, w) > limit) u = 4, w = tiles_of(4, 8) > limit ? 16 : 8;
+    st = begin_lookback(ws, s, tiles_of(u, w), &dev, capturing);
     if (st != TCR_OK) return st;
-    if (u == 1) launch_tile_scan<1, 16, MODE>(a, false, dev, s);
-    else if (u == 2) launch_tile_scan<2, 16, MODE>(a, false, dev, s);
-    else launch_tile_scan<4, 16, MODE>(a, false, dev, s);
+    if (u == 1) launch_tile_scan<1, 8, MODE, false>(a, dev, s);
+    else if (u == 2 && w == 8) launch_tile_scan<2, 8, MODE, false>(a, dev, s);
+    else if (u == 2) launch_tile_scan<2, 16, MODE, false>(a, dev, s);
+    else if (w == 8) launch_tile_scan<4, 8, MODE, false>(a, dev, s);
+    else launch_tile_scan<4, 16, MODE, false>(a, dev, s);
     st = check_launch("irregular_scan_kernel");
     if (st != TCR_OK) ws->dirty = true;
     return st;
@@ -817,8 +825,8 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
     // One tile per workgroup with nothing chained: regular segments short enough for a workgroup to add up the open part by
     // itself, at every size of array, and any segments in an array that the chip holds at once (at most a 65536-element
     // share per compute unit).  n = 2^20 / 2^24 / 2^26, us, by ticket and look-back against this: seg_len 1001 8.2 / 27 / 85
-    // against 4.1 / 22.8 / 74; 100003 8.7 / 28 against 6.4 / 23.7; irregular, lognormal lengths 10.9 / 31.8 against 6.6 /
-    // 27.2, seven segments 20 / 40 against 6.9 / 28.
+    // against 4.1 / 22.8 / 74; 100003 8.7 / 28 against 5.1 / 23; irregular, lognormal lengths 10.9 / 31.8 against 5.5 /
+    // 28, seven segments 20 / 40 against 5.3 / 28; without the limit 2^26 91 against 95 and 106.
     if (shape == 0 && g_variant.formulation == kMfma && (regular ? seg_len >= 2 : g_variant.irregular_scan == 0) &&
         ((regular && seg_len <= kLocalMax) || n <= (uint64_t)compute_units() * (uint64_t)(kTile * 16 * 8)))
         return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, s);

@@ -35,7 +35,7 @@ def cut(n, recipe, seed):
 
 
 # several heads in a lane's eight elements (2 to 7), the last lengths whose open part 8 and 16 wavefronts add up, the first
-# that is looked up, and segments of several tiles; tile sizes change at 2^21, 2^22 and 2^23 elements
+# that is looked up, and segments of several tiles; tile sizes change at several sizes from 2^21 elements on
 @pytest.mark.parametrize("seg", [2, 3, 6, 7, 9, 31, 511, 513, 1023, 1025, 4095, 4097, 8191, 8193, 12345, 40001, 300007])
 @pytest.mark.parametrize("n", [70001, (1 << 21) + 4099, (1 << 23) + 70001])
 def test_regular_segments(tcr, oracle, wait, seg, n):
@@ -114,6 +114,21 @@ def test_a_new_result_is_zero_outside_the_segments(tcr, oracle, n, flags):
         assert torch.isnan(out[:shift]).all() and torch.isnan(out[shift + n - 8:]).all()
         assert not torch.isnan(out[shift:shift + n - 8]).any()
         assert not out[shift:shift + 9000].any() and not out[shift + 15001:shift + n - 8].any()
+
+
+# the last and first elements of every tile size: 4096 elements up to 2 tiles per compute unit, 8192 up to 3, 16384 in between
+# where every unit gets one, and beyond
+@pytest.mark.parametrize("n", [4096 * 512, 4096 * 512 + 1, 16384 * 192, 16384 * 192 + 1, 16384 * 256, 16384 * 256 + 1, 8192 * 768, 8192 * 768 + 1,
+                               16384 * 1024 - 1])
+def test_tile_sizes(tcr, oracle, n):
+    x = workloads.make_input(n, "int4", n % 89)
+    xd = torch.from_numpy(x).cuda()
+    for recipe in ("few3", "lognormal256"):
+        off = cut(n, recipe, n % 7)
+        got = tcr.irregular_scan(xd, torch.from_numpy(off).cuda()).cpu().numpy().astype(np.float64)
+        assert np.array_equal(got, oracle.irregular_scan(x, off))
+    m = n // 8195 * 8195
+    assert np.array_equal(tcr.segmented_scan(xd[:m], 8195).cpu().numpy().astype(np.float64), oracle.segmented_scan(x[:m], 8195))
 
 
 def test_a_small_caller_workspace(tcr, oracle):
