@@ -188,12 +188,8 @@ __device__ __forceinline__ void masked_piece(const _Float16* __restrict__ in, fl
         __syncthreads();
         const bool finish = PIECES && fin.counter != nullptr;
         if (threadIdx.x != 0 && !finish) return;
-        a = q = 0.0f;
-#pragma unroll
-        for (int v = 0; v < W; ++v) {
-            a += s_part[0][v];
-            q += s_part[1][v];
-        }
+        a = pairwise_sum(s_part[0]);
+        q = pairwise_sum(s_part[1]);
         if constexpr (PIECES) {
             if (finish) {
                 if (threadIdx.x == 0) {
