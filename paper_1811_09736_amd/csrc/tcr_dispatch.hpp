@@ -546,12 +546,13 @@ tcr_status launch_chain_once(const _Float16* in, void* out, uint64_t n, uint64_t
 }
 
 // The persistent chain (shape 10 or 11) over segments of `seg_len` elements: any multiple of 8 that is at
-// least one tile, or one segment of n elements (n a multiple of 8).
+// least one tile, or one segment of n elements (n a multiple of 8).  With `used` the caller reads the totals of the
+// chain's own tiles out of the table afterwards, so the array is not run as one tile per workgroup, whatever its size.
 template <int FORM, int MODE>
 tcr_status launch_chain(int shape, const _Float16* in, void* out, uint64_t n, uint64_t seg_len, hipStream_t s,
                         ScanWorkspace* used = nullptr, uint32_t* used_tiles = nullptr) {
     if constexpr (FORM == kMfma) {
-        if (shape == 10 && once_share(n, seg_len, ~0ull) != 0) return launch_chain_once<MODE>(in, out, n, seg_len, s);
+        if (shape == 10 && used == nullptr && once_share(n, seg_len, ~0ull) != 0) return launch_chain_once<MODE>(in, out, n, seg_len, s);
     }
     const uint64_t tile = scan_shape_tile(shape);
     const uint64_t per_segment = ceil_div(seg_len, tile);
