@@ -527,10 +527,14 @@ extern "C" tcr_status tcr_check_device_flags(void* stream) {
     auto own = g_caller_workspaces.find(dev);
     if (own != g_caller_workspaces.end()) all.push_back(&own->second);
     if (dev >= 0 && dev < kMaxDevices && g_static_ready[dev]) all.push_back(&g_static_workspace[dev]);
+    std::vector<const uint32_t*> counters;
     for (const Workspace* w : all) {
-        if (w->counters == nullptr || !w->flag_valid) continue;
+        if (w->counters != nullptr && w->flag_valid) counters.push_back(w->counters);
+        for (const Workspace::RecordedTable& t : w->recorded_tables) counters.push_back(t.counters);
+    }
+    for (const uint32_t* c : counters) {
         uint32_t flag = 0;
-        TCR_HIP(hipMemcpy(&flag, w->counters + 1, sizeof(flag), hipMemcpyDeviceToHost));
+        TCR_HIP(hipMemcpy(&flag, c + 1, sizeof(flag), hipMemcpyDeviceToHost));
         if (flag != 0) {
             g_hip_error = "a look-back wait expired";
             return TCR_ERR_HIP;
@@ -600,12 +604,7 @@ extern "C" tcr_status tcr_set_workspace(void* dev_ptr, uint64_t bytes) {
 
 extern "C" void tcr_release(void) {
     std::lock_guard<std::mutex> lock(g_mutex);
-    for (auto& kv : g_workspaces) {
-        Workspace& w = kv.second;
-        if (w.desc) g_parked_tables.push_back({kv.first.first, w.desc, w.desc_capacity});   // uncached: parked, not freed
-        if (w.partials) (void)hipFree(w.partials);
-        if (w.counters) (void)hipFree(w.counters);
-    }
+    for (auto& kv : g_workspaces) release_workspace(kv.first.first, kv.second);
     g_workspaces.clear();
 }
 
@@ -615,10 +614,7 @@ extern "C" tcr_status tcr_release_stream(void* stream) {
     std::lock_guard<std::mutex> lock(g_mutex);
     auto it = g_workspaces.find(std::make_pair(dev, static_cast<hipStream_t>(stream)));
     if (it == g_workspaces.end()) return TCR_OK;
-    Workspace& w = it->second;
-    if (w.desc) g_parked_tables.push_back({dev, w.desc, w.desc_capacity});       // uncached: parked, not freed
-    if (w.partials) (void)hipFree(w.partials);
-    if (w.counters) (void)hipFree(w.counters);
+    release_workspace(dev, it->second);
     g_workspaces.erase(it);
     return TCR_OK;
 }

@@ -81,6 +81,15 @@ struct Workspace {
     // device (advanced by chain_begin_kernel in front of every launch) and the two host mirrors above are
     // no longer used: a replayed graph repeats its kernel arguments.
     bool device_managed = false;
+    // Counters and tables that recorded launches were given before the table was outgrown.  A replay goes on counting
+    // epochs in them and takes any word of its table that carries the epoch for its own, so the pair stays as it is,
+    // together and for nobody else, until the workspace is released.
+    struct RecordedTable {
+        uint32_t* counters;
+        unsigned long long* desc;
+        uint64_t desc_capacity;
+    };
+    std::vector<RecordedTable> recorded_tables;
     bool dirty = true;              // counters / descriptors must be re-zeroed before use
     bool caller_owned = false;      // memory supplied through tcr_set_workspace: never grown, never freed
     bool flag_valid = true;         // false until the first clean-up has written the caller's (uninitialised) flag word
@@ -194,6 +203,17 @@ inline uint32_t* finish_counter(Workspace* ws, bool capturing) {
     return ws->counters + 4;
 }
 
+// Gives back a library-owned workspace's memory, whose work has finished (g_mutex is held).  The uncached tables are parked.
+inline void release_workspace(int device, Workspace& ws) {
+    if (ws.desc) g_parked_tables.push_back({device, ws.desc, ws.desc_capacity});
+    if (ws.partials) (void)hipFree(ws.partials);
+    if (ws.counters) (void)hipFree(ws.counters);
+    for (const Workspace::RecordedTable& t : ws.recorded_tables) {
+        if (t.desc) g_parked_tables.push_back({device, t.desc, t.desc_capacity});
+        (void)hipFree(t.counters);
+    }
+}
+
 // Makes room for `tiles` descriptors and starts a new epoch (tiles == 0: only the running counter is wanted).
 inline tcr_status begin_lookback(Workspace* ws, hipStream_t stream, uint64_t tiles, ScanWorkspace* dev, bool capturing) {
     if (ws->caller_owned && tiles > ws->desc_capacity) return TCR_ERR_WORKSPACE;
@@ -207,9 +227,20 @@ inline tcr_status begin_lookback(Workspace* ws, hipStream_t stream, uint64_t til
         int dev_id = 0;
         TCR_HIP(hipGetDevice(&dev_id));
         std::lock_guard<std::mutex> lock(g_mutex);
-        if (ws->desc) g_parked_tables.push_back({dev_id, ws->desc, ws->desc_capacity});
+        if (ws->device_managed) {
+            // (recorded launches keep the old pair; with a new one the host counts again)
+            ws->recorded_tables.push_back({ws->counters, ws->desc, ws->desc_capacity});
+            ws->counters = nullptr;
+            ws->device_managed = false;
+        } else if (ws->desc) {
+            g_parked_tables.push_back({dev_id, ws->desc, ws->desc_capacity});
+        }
         ws->desc = nullptr;
         ws->desc_capacity = 0;
+        if (ws->counters == nullptr) {
+            const tcr_status st = create_counters(ws);
+            if (st != TCR_OK) return st;
+        }
         const tcr_status st = acquire_table(dev_id, tiles, &ws->desc, &ws->desc_capacity);
         if (st != TCR_OK) return st;
         ws->dirty = true;

@@ -1,0 +1,130 @@
+"""Recorded launches and eager calls that outgrow the workspace they were recorded with: a replay has to find its own tables,
+with nothing in them that an eager call or another stream put there.  Whole numbers: exact."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1811_09736_amd import workloads
+
+pytestmark = pytest.mark.gpu
+
+N, LARGE = (1 << 20) + 8192 * 5, 1 << 24         # the scan that is recorded; arrays of 2048 tiles and more
+
+
+@pytest.fixture(scope="module")
+def tcr():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1811_09736_amd import binding
+    binding.set_variant("reset")
+    binding.tuning_import("")
+    yield binding
+    binding.check_device_flags()
+
+
+@pytest.fixture(scope="module")
+def large(oracle):
+    x = workloads.make_input(LARGE, "int1", 5)
+    off = workloads.make_offsets(LARGE, "few7", 2).view(np.int64)
+    return (torch.from_numpy(x).cuda(), torch.from_numpy(off).cuda(), oracle.irregular_moments(x, off))
+
+
+def same(t, want):
+    return np.array_equal(t.cpu().numpy().astype(np.float64), want)
+
+
+@pytest.mark.parametrize("again", [False, True])
+def test_eager_reductions_outgrow_the_table_of_a_recorded_scan(tcr, oracle, large, again):
+    xl, od, (sums, squares) = large
+    inputs = [workloads.make_input(N, "int4", (31, k)) for k in range(3)]
+    refs = [oracle.scan(h) for h in inputs]
+    x = torch.from_numpy(inputs[0]).cuda()
+    out, second = (torch.empty(N, dtype=torch.float32, device="cuda") for _ in range(2))
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
+
+    def record(dst):
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            tcr.scan(x, out=dst)
+        return graph
+
+    def replay(graph, dst, k):
+        x.copy_(torch.from_numpy(inputs[k]).cuda())
+        dst.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert same(dst, refs[k])
+
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        tcr.scan(x, out=out)
+    torch.cuda.synchronize()
+    graph = record(out)
+    for k in (1, 2):
+        replay(graph, out, k)
+    with torch.cuda.stream(side):                              # 2048 sums, then twice as many: two larger tables
+        assert same(tcr.irregular_reduce(xl, od), sums)
+        a, q = tcr.irregular_moments(xl, od)
+    torch.cuda.synchronize()
+    assert same(a, sums) and same(q, squares)
+    later = record(second) if again else None                  # the new table is recorded, too
+    for k in (0, 1, 2, 0):
+        replay(graph, out, k)
+        with torch.cuda.stream(other):                         # a stream that could be handed the outgrown table
+            assert same(tcr.scan(x), refs[k])
+        with torch.cuda.stream(side):
+            assert same(tcr.scan(x), refs[k])
+            assert same(tcr.irregular_reduce(xl, od), sums)
+        torch.cuda.synchronize()
+        if again:
+            replay(later, second, (k + 1) % 3)
+    tcr.check_device_flags(side)
+    torch.cuda.synchronize()
+    tcr.release_stream(other)
+
+
+def test_a_scan_and_moments_outgrow_tables_with_recorded_scans(tcr, oracle):
+    n = 1 << 18
+    side = torch.cuda.Stream()
+    x = torch.from_numpy(workloads.make_input(n, "int4", 3)).cuda()
+    big = torch.ones((1 << 25) + 100003, dtype=torch.float16, device="cuda")
+    off = torch.tensor([0, 3, 1 << 23, 1 << 24], dtype=torch.int64, device="cuda")
+    lengths = np.array([3.0, (1 << 23) - 3, 1 << 23])
+
+    def nothing():
+        return True
+
+    def scan():                                                # 1028 tiles
+        return float(tcr.scan(big)[(1 << 24) - 1]) == float(1 << 24)
+
+    def moments():                                             # 4096 sums
+        a, q = tcr.irregular_moments(big[:1 << 24], off)
+        return same(a, lengths) and same(q, lengths)
+
+    outs, graphs = [], []
+    torch.cuda.synchronize()
+    for call in (nothing, scan, moments):
+        with torch.cuda.stream(side):
+            assert call()
+            tcr.scan(x)
+        torch.cuda.synchronize()
+        outs.append(torch.empty(n, dtype=torch.float32, device="cuda"))
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1], stream=side):
+            tcr.scan(x, out=outs[-1])
+    for k in range(4):
+        h = workloads.make_input(n, "int4", (4, k))
+        x.copy_(torch.from_numpy(h).cuda())
+        for o in outs:
+            o.fill_(float("nan"))
+        torch.cuda.synchronize()
+        for g in graphs:
+            g.replay()
+        torch.cuda.synchronize()
+        want = oracle.scan(h)
+        assert all(same(o, want) for o in outs)
+        with torch.cuda.stream(side):
+            assert moments() and scan()
+        torch.cuda.synchronize()
+    tcr.check_device_flags(side)
