@@ -38,8 +38,8 @@
  *   with seg_len <= 131072 -- powers of two from 16 on; default variant and tuning) never do.
  *   From the first recorded launch that chains tiles on (scans, and irregular reductions that run as one launch),
  *   the workspace keeps its launch counters on the device and every such launch on it, recorded or not, is preceded
- *   by one small bookkeeping kernel.  A later call that needs more room gets new tables; recorded launches keep
- *   theirs, which live until the workspace is released (tcr_release, tcr_release_stream): no replay after that.
+ *   by one small bookkeeping kernel.  A later call that needs more room gets new memory; recorded launches keep
+ *   theirs, which lives until the workspace is released (tcr_release, tcr_release_stream): no replay after that.
  *   The "fused" reduce_finish variant cannot be recorded.
  *   There is no CPU fallback: without a usable HIP device every call returns TCR_ERR_HIP.
  */

@@ -90,6 +90,9 @@ struct Workspace {
         uint64_t desc_capacity;
     };
     std::vector<RecordedTable> recorded_tables;
+    // The same for the partials: a recorded launch stores them there and reads them back at every replay.
+    bool partials_recorded = false;
+    std::vector<float*> recorded_partials;
     bool dirty = true;              // counters / descriptors must be re-zeroed before use
     bool caller_owned = false;      // memory supplied through tcr_set_workspace: never grown, never freed
     bool flag_valid = true;         // false until the first clean-up has written the caller's (uninitialised) flag word
@@ -161,13 +164,18 @@ inline uint64_t partials_limit(const Workspace* ws, bool capturing) {
 }
 
 inline tcr_status ensure_partials(Workspace* ws, hipStream_t stream, uint64_t floats, bool capturing) {
-    if (floats <= ws->partials_capacity) return TCR_OK;
+    if (floats <= ws->partials_capacity) {
+        if (capturing) ws->partials_recorded = true;
+        return TCR_OK;
+    }
     if (ws->caller_owned) return TCR_ERR_WORKSPACE;
     if (capturing) return TCR_ERR_UNSUPPORTED;
     TCR_HIP(hipStreamSynchronize(stream));
-    if (ws->partials) TCR_HIP(hipFree(ws->partials));
+    if (ws->partials_recorded) ws->recorded_partials.push_back(ws->partials);
+    else if (ws->partials) TCR_HIP(hipFree(ws->partials));
     ws->partials = nullptr;
     ws->partials_capacity = 0;
+    ws->partials_recorded = false;
     uint64_t cap = 1;
     while (cap < floats) cap <<= 1;
     if (hipMalloc(&ws->partials, cap * sizeof(float)) != hipSuccess) {
@@ -208,6 +216,7 @@ inline void release_workspace(int device, Workspace& ws) {
     if (ws.desc) g_parked_tables.push_back({device, ws.desc, ws.desc_capacity});
     if (ws.partials) (void)hipFree(ws.partials);
     if (ws.counters) (void)hipFree(ws.counters);
+    for (float* p : ws.recorded_partials) (void)hipFree(p);
     for (const Workspace::RecordedTable& t : ws.recorded_tables) {
         if (t.desc) g_parked_tables.push_back({device, t.desc, t.desc_capacity});
         (void)hipFree(t.counters);

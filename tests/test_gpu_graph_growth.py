@@ -1,5 +1,5 @@
-"""Recorded launches and eager calls that outgrow the workspace they were recorded with: a replay has to find its own tables,
-with nothing in them that an eager call or another stream put there.  Whole numbers: exact."""
+"""Recorded launches and eager calls that outgrow the workspace they were recorded with: a replay has to find its own memory,
+with nothing in it that an eager call or another stream put there.  Whole numbers: exact."""
 import numpy as np
 import pytest
 import torch
@@ -128,3 +128,47 @@ def test_a_scan_and_moments_outgrow_tables_with_recorded_scans(tcr, oracle):
             assert moments() and scan()
         torch.cuda.synchronize()
     tcr.check_device_flags(side)
+
+
+def test_eager_calls_outgrow_the_partials_of_recorded_reductions(tcr, oracle):
+    # the replays' partials stay theirs: neither handed back to the allocator nor to the later call
+    n, seg = 1 << 24, 1 << 18
+    side = torch.cuda.Stream()
+    x = torch.from_numpy(workloads.make_input(n, "int1", 8)).cuda()
+    off = torch.from_numpy(workloads.make_offsets(n, "lognormal256", 8).view(np.int64)).cuda()
+    total = torch.empty(1, dtype=torch.float32, device="cuda")
+    segs = torch.empty(n // seg, dtype=torch.float32, device="cuda")
+    irregular = torch.empty(off.numel() - 1, dtype=torch.float32, device="cuda")
+    outs = (total, segs, irregular)
+
+    def calls():
+        tcr.reduce(x, out=total)                               # 4096 partials, added by a second kernel
+        tcr.segmented_reduce(x, seg, out=segs)
+        tcr.irregular_reduce(x, off, out=irregular)            # look-up tables and tile sums
+
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        calls()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        calls()
+    big = torch.zeros((1 << 26) + 1, dtype=torch.float16, device="cuda")
+    for k in range(3):
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            assert float(tcr.reduce(big[1:])) == 0.0           # 8192 tiles of an unaligned array
+            assert not torch.any(tcr.segmented_reduce(big[:1 << 26], seg))
+        torch.cuda.synchronize()
+        taken = torch.full((1 << 20,), 3.0, device="cuda")     # whoever gets memory that was freed
+        h = workloads.make_input(n, "int1", (9, k))
+        x.copy_(torch.from_numpy(h).cuda())
+        for o in outs:
+            o.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert float(total) == oracle.reduce(h)
+        assert same(segs, oracle.segmented_reduce(h, seg))
+        assert same(irregular, oracle.irregular_reduce(h, off.cpu().numpy()))
+        assert torch.all(taken == 3.0)
