@@ -143,13 +143,16 @@ tcr_status tcr_scan_ex(const void *in, void *out, uint64_t n, uint32_t flags, vo
  *   tcr_irregular_scan    out[k] = sum of in[offsets[s] .. k] for k in segment s; out is indexed like `in`
  *                         (positions outside [offsets[0], offsets[nseg]) are not written).
  * The work is divided by elements, not by segments: fixed tiles of the array at a speed that hardly depends on
- * the mix of segment lengths.  Both use the workspace (tcr_workspace_bytes, op 4 and 5): one small kernel looks
- * up where the tile boundaries fall among the offsets; the scan chains its tiles like the long regular scans
- * (with fewer segments than a quarter of the tiles it runs as two kernels: the pipelined chain of the long
- * regular scans takes the tiles without a segment start, a second kernel the others); an array that the chip holds at
- * once (up to 2^24 elements) is scanned by one kernel whose tiles search the offsets and look up what they need;
- * the reduction keeps its tiles independent and a small kernel adds the one sum per tile that reaches in
- * from earlier tiles -- plain loads in a fixed order, so the reduction's results are the same from run to run.
+ * the mix of segment lengths.  Both use the workspace (tcr_workspace_bytes, op 4 and 5).
+ *   Arrays of up to 2^24 elements (sums: 2^25) run as one kernel, whose tiles search the offsets and look up, among the
+ * sums that the other tiles publish, what reaches them from in front -- except where the workspace is too small for a
+ * sum per tile, and reductions that are recorded into a graph on a stream where no launch that chains tiles has been.
+ *   In larger ones a small kernel looks up where the tile boundaries fall among the offsets; the scan chains its tiles
+ * like the long regular scans (with fewer segments than a quarter of the tiles it runs as two kernels: the pipelined
+ * chain of the long regular scans takes the tiles without a segment start, a second kernel the others); the reduction
+ * keeps its tiles independent and a small kernel adds the one sum per tile that reaches in from earlier tiles.
+ *   The reduction's results are the same from run to run: the additions of each of its two forms have one order, also
+ * where a tile adds up again what another has not published yet.  (The two forms may round differently.)
  * in and out need only their natural alignment (2 and 4 bytes): the tiles start at the 16-byte boundary at or
  * below `in` (up to 7 elements in front of it are read and ignored), and a scan whose `out` does not sit at the
  * same distance from a 16-byte boundary stores its results one by one (slower).

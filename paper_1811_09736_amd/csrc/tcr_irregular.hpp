@@ -487,7 +487,8 @@ __device__ __forceinline__ uint32_t wave_scan_inclusive_u32(uint32_t x) {
 // to the tile's start: at most 512 elements per wavefront are added up by the wavefronts while their own data is on its
 // way (a neighbour's data, mostly found in a cache); a longer part is the published sums of the tiles from the one that
 // holds s0 on -- no tile in between has a head -- read by the wavefront whose result it is, after its other results.  A
-// sum that is not there after `patience` looks is added up from the elements, so no wait depends on which workgroups run.
+// sum that is not there after `patience` looks is added up from the elements, so no wait depends on which workgroups run
+// (and no bit of a result on how they run: linked_tile_sum).
 // The tile's range of entries is then searched here, one edge per wavefront, instead of read from the tables -- before
 // the data is asked for: behind a tile's worth of loads every round of the search would wait for them.
 // Not LINKED: that result is written without its earlier part; the tile records which segment it is (carried[tile], or
@@ -508,11 +509,29 @@ __device__ __forceinline__ float masked_terms(half8 x, uint64_t at, uint64_t fro
     return wave_sum(v);
 }
 
+// What tile number `t` publishes, from its elements (whole wavefront; s0 is the tile's last head or lies in front of it).
+// Added in the order in which the tile itself adds -- a wavefront's sub-tiles one after another, then the wavefronts from
+// the last one back, and wave_sum's order inside a sub-tile; what lies in front of s0 adds nothing either way -- so
+// that a result has the same bits whether the sum had arrived or not.
+template <int KIND, int C, int U, int WAVES>
+__device__ __forceinline__ float linked_tile_sum(const _Float16* __restrict__ in, uint32_t t, uint64_t s0, int lane) {
+    constexpr uint64_t kChunk = (uint64_t)kTile * U;
+    const uint64_t begin = (uint64_t)t * (kChunk * WAVES);
+    float total = 0.0f;
+    for (int w = WAVES - 1; w >= 0; --w) {
+        float run = 0.0f;
+        for (uint64_t at = begin + (uint64_t)w * kChunk, end = at + kChunk; at < end; at += (uint64_t)kTile)
+            if (at + (uint64_t)kTile > s0) run += masked_terms<KIND, C>(load8(in, at + 8 * (uint64_t)lane), at, s0, lane);
+        total += run;
+    }
+    return total;
+}
+
 // Sum from position s0 to the start of `tile` out of the published sums (whole wavefront).  PER sums per lane and step, all
 // asked for before the first is looked at: a segment of a million elements spans a hundred tiles and more.
-template <int KIND, int C, int PER>
+template <int KIND, int C, int U, int WAVES, int PER>
 __device__ __forceinline__ float linked_step(const _Float16* __restrict__ in, const unsigned long long* desc, uint32_t want, uint32_t hi,
-                                             uint32_t span, uint64_t s0, int tile_log2, uint32_t patience, int lane) {
+                                             uint32_t span, uint64_t s0, uint32_t patience, int lane) {
     float v[PER];
     for (uint32_t polls = 0;; ++polls) {
         unsigned long long d[PER];
@@ -534,10 +553,7 @@ __device__ __forceinline__ float linked_step(const _Float16* __restrict__ in, co
             for (int k = 0; k < PER; ++k) {
                 for (unsigned long long lanes = __ballot((missing >> k) & 1u); lanes != 0ull; lanes &= lanes - 1ull) {
                     const int slot = __builtin_ctzll(lanes);
-                    const uint64_t begin = (uint64_t)(hi - 1u - (uint32_t)(k * kWave + slot)) << tile_log2;
-                    float sum = 0.0f;
-                    for (uint64_t at = begin; at < begin + (1ull << tile_log2); at += (uint64_t)kTile)
-                        if (at + (uint64_t)kTile > s0) sum += masked_terms<KIND, C>(load8(in, at + 8 * (uint64_t)lane), at, s0, lane);
+                    const float sum = linked_tile_sum<KIND, C, U, WAVES>(in, hi - 1u - (uint32_t)(k * kWave + slot), s0, lane);
                     if (lane == slot) v[k] = sum;
                 }
             }
@@ -550,16 +566,16 @@ __device__ __forceinline__ float linked_step(const _Float16* __restrict__ in, co
     for (int k = 0; k < PER; ++k) sum += v[k];
     return wave_sum(sum);
 }
-template <int KIND, int C>
+template <int KIND, int C, int U, int WAVES>
 __device__ __forceinline__ float linked_sum(const _Float16* __restrict__ in, const unsigned long long* desc, uint32_t epoch, uint32_t tile,
-                                            uint64_t s0, int tile_log2, uint32_t patience, int lane) {
-    const uint32_t first = (uint32_t)(s0 >> tile_log2), want = epoch * 4u + kStatusAggregate;
+                                            uint64_t s0, uint32_t patience, int lane) {
+    const uint32_t first = (uint32_t)(s0 / (uint64_t)(kTile * U * WAVES)), want = epoch * 4u + kStatusAggregate;
     constexpr int kPer = 8;
     float acc = 0.0f;
     for (uint32_t hi = tile; hi > first;) {
         const uint32_t left = hi - first, span = left < (uint32_t)(kPer * kWave) ? left : (uint32_t)(kPer * kWave);
-        if (span <= (uint32_t)kWave) acc += linked_step<KIND, C, 1>(in, desc, want, hi, span, s0, tile_log2, patience, lane);
-        else acc += linked_step<KIND, C, kPer>(in, desc, want, hi, span, s0, tile_log2, patience, lane);
+        if (span <= (uint32_t)kWave) acc += linked_step<KIND, C, U, WAVES, 1>(in, desc, want, hi, span, s0, patience, lane);
+        else acc += linked_step<KIND, C, U, WAVES, kPer>(in, desc, want, hi, span, s0, patience, lane);
         hi -= span;
     }
     return acc;
@@ -591,7 +607,6 @@ __global__ __launch_bounds__(WAVES * kWave) void irregular_reduce_kernel(const _
     static_assert(kBlockTile <= 65535u, "positions are kept in 16 bits");
     constexpr int CH = channels<KIND>();
     constexpr uint64_t kBackMax = (uint64_t)kTile * WAVES;        // the longest open part that the wavefronts add up themselves
-    constexpr int kTileLog2 = __builtin_ctz(kBlockTile);
     __shared__ float s_wave_value[CH][WAVES];
     __shared__ float s_back[LINKED ? CH : 1][WAVES];
     __shared__ uint32_t s_wave_flag[WAVES];
@@ -908,10 +923,10 @@ __global__ __launch_bounds__(WAVES * kWave) void irregular_reduce_kernel(const _
     if constexpr (LINKED) {
         if (owner) {
             const ScanWorkspace ws = resolve_workspace(link.ws);
-            const float sum = linked_sum<KIND, 0>(in, ws.desc, ws.epoch, tile, tb - back, kTileLog2, link.patience, lane);
+            const float sum = linked_sum<KIND, 0, U, WAVES>(in, ws.desc, ws.epoch, tile, tb - back, link.patience, lane);
             if (lane == 0) out_from[-1] = kept[0] + sum;
             if constexpr (CH == 2) {
-                const float sum2 = linked_sum<KIND, 1>(in, ws.desc + gridDim.x, ws.epoch, tile, tb - back, kTileLog2, link.patience, lane);
+                const float sum2 = linked_sum<KIND, 1, U, WAVES>(in, ws.desc + gridDim.x, ws.epoch, tile, tb - back, link.patience, lane);
                 if (lane == 0) out2_from[-1] = kept[CH - 1] + sum2;
             }
         }
