@@ -516,13 +516,17 @@ __device__ __forceinline__ float masked_terms(half8 x, uint64_t at, uint64_t fro
 template <int KIND, int C, int U, int WAVES>
 __device__ __forceinline__ float linked_tile_sum(const _Float16* __restrict__ in, uint32_t t, uint64_t s0, int lane) {
     constexpr uint64_t kChunk = (uint64_t)kTile * U;
-    const uint64_t begin = (uint64_t)t * (kChunk * WAVES);
-    float total = 0.0f;
-    for (int w = WAVES - 1; w >= 0; --w) {
-        float run = 0.0f;
-        for (uint64_t at = begin + (uint64_t)w * kChunk, end = at + kChunk; at < end; at += (uint64_t)kTile)
-            if (at + (uint64_t)kTile > s0) run += masked_terms<KIND, C>(load8(in, at + 8 * (uint64_t)lane), at, s0, lane);
-        total += run;
+    const uint64_t tile_begin = (uint64_t)t * (kChunk * WAVES);
+    float total = 0.0f, run = 0.0f;
+    // (one loop, not unrolled: a nest of two costs the whole kernel 8 registers and with them a wavefront per SIMD)
+#pragma unroll 1
+    for (int k = 0; k < U * WAVES; ++k) {
+        const uint64_t at = tile_begin + (uint64_t)((WAVES - 1 - k / U) * U + k % U) * (uint64_t)kTile;
+        if (at + (uint64_t)kTile > s0) run += masked_terms<KIND, C>(load8(in, at + 8 * (uint64_t)lane), at, s0, lane);
+        if (k % U == U - 1) {
+            total += run;
+            run = 0.0f;
+        }
     }
     return total;
 }
@@ -549,12 +553,15 @@ __device__ __forceinline__ float linked_step(const _Float16* __restrict__ in, co
         }
         if (__ballot(missing != 0u) == 0ull) break;
         if (polls >= patience) {
+            // (in one place, not once per k, for the same reason)
+            for (unsigned long long lanes; (lanes = __ballot(missing != 0u)) != 0ull;) {
+                const int slot = __builtin_ctzll(lanes);
+                const int which = __builtin_ctz((uint32_t)__builtin_amdgcn_readlane((int)missing, slot));
+                const float sum = linked_tile_sum<KIND, C, U, WAVES>(in, hi - 1u - (uint32_t)(which * kWave + slot), s0, lane);
+                if (lane == slot) {
+                    missing &= missing - 1u;
 #pragma unroll
-            for (int k = 0; k < PER; ++k) {
-                for (unsigned long long lanes = __ballot((missing >> k) & 1u); lanes != 0ull; lanes &= lanes - 1ull) {
-                    const int slot = __builtin_ctzll(lanes);
-                    const float sum = linked_tile_sum<KIND, C, U, WAVES>(in, hi - 1u - (uint32_t)(k * kWave + slot), s0, lane);
-                    if (lane == slot) v[k] = sum;
+                    for (int k = 0; k < PER; ++k) v[k] = k == which ? sum : v[k];
                 }
             }
             break;
