@@ -195,19 +195,19 @@ struct ReducePlan {
     bool finish;        // the partials are added up by the workgroup that finishes last
 };
 
-// Arrays whose partials the last workgroup adds up: at most 128 of them (one count on one address takes 12 ns), of a
-// workgroup's share each.  Full reduction of 2^18 / 2^20 / 2^22 / 2^23 elements, us back to back: two kernels 6.8 / 6.9 /
+// Arrays whose partials the last workgroup adds up: at most 128 of them, of a workgroup's share each, and one more per
+// segment where segments end inside a share (one count on one address takes 12 ns).  Full reduction of 2^18 / 2^20 / 2^22 / 2^23 elements, us back to back: two kernels 6.8 / 6.9 /
 // 6.7 / 6.7, one launch 4.5 / 4.5 / 5.9 / 7.0 -- and 3.3 us less for the host at every size, which is the longer of the two
 // up to there.  (One workgroup and no partials at all up to 2^17: 3.7 at 2^16, 4.9 at 2^17.)
 constexpr uint64_t kFinishElemsMax = 1ull << 23;
 constexpr uint64_t kFinishSums = 32;                     // results that the last workgroup adds up
+constexpr uint64_t kFinishShares = 128;
+static_assert(kFinishShares + kFinishSums <= kFinishCount, "a launch counts each of its workgroups");
 inline uint64_t finish_share(uint64_t n) {
     uint64_t share = 16384;
-    while (ceil_div(n, share) > 128) share <<= 1;
+    while (ceil_div(n, share) > kFinishShares) share <<= 1;
     return share;
 }
-
-
 
 // How many wavefronts an array is shared among, if its size allows: a wavefront keeps 8 KiB of loads in flight, and 16
 // wavefronts per compute unit is where more of them no longer help.

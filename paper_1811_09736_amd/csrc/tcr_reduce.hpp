@@ -16,6 +16,7 @@
 // FORM selects the arithmetic inside a tile: kMfma (matrix cores) or kDpp (convert, add in
 // binary32, cross-lane DPP adds) -- the wavefront-primitive alternative kept for measurement.
 #pragma once
+#include "tcr_count.hpp"
 #include "tcr_device.hpp"
 
 namespace tcr {
@@ -209,9 +210,9 @@ struct ReduceFinish {
     float* out;            // [nseg]
     float* out2;           // a second set of nseg * per partials behind the first goes there (the sums of squares), or null
     uint32_t* counter;     // count of finished workgroups
-    uint32_t base;         // value of *counter when this launch starts (wrap == 0: a running count that is never reset)
+    uint32_t base;         // weighed == 0: value of *counter when this launch starts (workgroups count one each)
     uint32_t nseg, per;    // dst holds nseg * per partials
-    uint32_t wrap;         // 1: the count returns to 0 with the last workgroup, so a recorded launch can be replayed
+    uint32_t weighed;      // 1: every launch adds kFinishCount in total (tcr_count.hpp), so a recorded launch can be replayed
 };
 
 // Executed by every thread of a workgroup whose partial(s) thread 0 has just stored with device scope.
@@ -225,9 +226,9 @@ __device__ __forceinline__ void finish_partials(const float* __restrict__ dst, c
     if (threadIdx.x == 0) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");       // compiler ordering
         __builtin_amdgcn_s_waitcnt(0x0F70);                          // vmcnt(0): the store has been acknowledged
-        const uint32_t before = fin.wrap ? atomicInc(fin.counter, gridDim.x - 1u)
-                                         : __hip_atomic_fetch_add(fin.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - fin.base;
-        s_last = before == gridDim.x - 1u ? 1u : 0u;
+        const uint32_t weight = fin.weighed ? finish_weight(blockIdx.x, gridDim.x) : 1u;
+        const uint32_t before = __hip_atomic_fetch_add(fin.counter, weight, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_last = (fin.weighed ? finish_is_last(before, weight) : before - fin.base == gridDim.x - 1u) ? 1u : 0u;
     }
     __syncthreads();
     if (s_last == 0u) return;

@@ -74,7 +74,7 @@ struct Workspace {
     float* partials = nullptr;
     uint64_t partials_capacity = 0; // floats
     uint32_t* counters = nullptr;   // [0] = ticket, [1] = gave_up flag, [2] = latest epoch, [3] = ticket base (device-managed),
-                                    // [4] = workgroups of a reduction that have finished (0 between launches)
+                                    // [4] = workgroups of a reduction that have finished (tcr_count.hpp)
     uint32_t tickets_issued = 0;    // host mirror of counters[0] once all enqueued launches finish
     uint32_t epoch = 0;
     // Once a launch that chains tiles has been recorded into a HIP graph, epoch and ticket base live on the
@@ -186,8 +186,8 @@ inline tcr_status ensure_partials(Workspace* ws, hipStream_t stream, uint64_t fl
     return TCR_OK;
 }
 
-// The count of finished workgroups of a one-launch reduction, or nullptr where it is not known to be 0 and cannot be
-// cleared now (a caller's buffer that no call has cleared yet, a workspace that would have to be created in a capture).
+// The count of finished workgroups of a one-launch reduction, or nullptr where it has never been cleared and cannot be
+// now (a caller's buffer that no call has cleared yet, a workspace that would have to be created in a capture).
 constexpr uint64_t kCounterWords = 8;
 inline tcr_status create_counters(Workspace* ws) {
     void* p = nullptr;
