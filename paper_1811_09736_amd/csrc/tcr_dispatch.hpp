@@ -777,8 +777,9 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
         a.magic = (uint32_t)(((1ull << 32) + seg_len - 1) / seg_len);
         // 8 wavefronts, so that the open part is a small share of what a workgroup reads -- unless segments are short and
         // the array streams from memory (seg_len 33 at n = 2^24 / 2^26 / 2^28: 23.2 / 74.8 / 285 us with 8, 23.6 / 73.3 /
-        // 276 with 16; 2001: 22.7 / 74.4 / 277 and 24.0 / 77.8 / 290), or longer than 8 wavefronts can add up at once
-        if (seg_len > 4096 || (seg_len <= 1024 && n > (1ull << 24))) launch_tile_scan<1, 16, MODE, true>(a, dev, s);
+        // 276 with 16; 2001: 22.7 / 74.4 / 277 and 24.0 / 77.8 / 290; binary16 results, 33 at 2^26 / 2^27 / 2^28: 42.2 / 91.9 /
+        // 179 with 8, 43.8 / 100.8 / 196 with 16), or longer than 8 wavefronts can add up at once
+        if (seg_len > 4096 || (!(MODE & 2) && seg_len <= 1024 && n > (1ull << 24))) launch_tile_scan<1, 16, MODE, true>(a, dev, s);
         else launch_tile_scan<1, 8, MODE, true>(a, dev, s);
         return check_launch("irregular_scan_kernel");
     }
@@ -811,6 +812,22 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
     return st;
 }
 
+// Regular segments of up to kLocalMax elements for which chained tiles are the faster form.  The open part that a tile adds
+// up again costs cache bandwidth in proportion to the segment length, and the longer segments take workgroups of 16
+// wavefronts; against that stand the ticket and the look-back, which weigh less the larger the array.  us, chained
+// against this, for segments of 4097 / 6001 / 8001 elements:
+//   binary32 results, n in 2^20: 40  50 / 50 / 49 and 44 / 44 / 45    48  68 / 67 / 67 and 68 / 70 / 71    56  75 / 76 / 76 and 72 / 75 / 78
+//                                64  85 / 85 / 85 and 80 / 82 / 83    80  102 / 102 / 102 and 97 / 99 / 102    128  152 / 152 / 154 and
+//                                151 / 154 / 158    256  287 / 287 / 289 and 294 / 300 / 308
+//   binary16 results:            24  30 / 30 / 30 and 28 / 29 / 30    40  35 / 35 / 35 and 34 / 35 / 37    64  50 / 49 / 50 and 52 / 53 / 56
+//                                128  101 / 101 / 102 and 115 / 118 / 120    256  190 / 190 / 190 and 224 / 228 / 232
+//                                (4001: 48  39 and 39    56  44 and 45    64  49 and 51    2001: 64  48 and 46    256  189 and 188)
+// (Between 2^20 * 44 and 56 an array and its binary32 results just outgrow the 256 MiB of the memory-side cache.)
+inline bool scan_better_chained(uint64_t n, uint64_t seg_len, bool f16) {
+    if (f16) return (seg_len > 4096 && n > (5ull << 23)) || (seg_len > 2048 && n > (3ull << 24));
+    return seg_len > 4096 && n > (11ull << 22) && (n <= (7ull << 23) || n > (seg_len <= 6144 ? 1ull << 27 : 5ull << 24));
+}
+
 template <int MODE>
 inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offsets, void* out, uint64_t n, uint64_t nseg,
                                         uint64_t seg_len, hipStream_t s, int shape = -1, bool fill = false) {
@@ -824,13 +841,22 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
     const uint64_t tiles = irregular_tiles(true, n, shape);
     const bool regular = offsets == nullptr;
     // One tile per workgroup with nothing chained: regular segments short enough for a workgroup to add up the open part by
-    // itself, at every size of array, and any segments in an array that the chip holds at once (at most a 65536-element
+    // itself, at nearly every size of array (scan_better_chained), and any segments in an array that the chip holds at once (at most a 65536-element
     // share per compute unit).  n = 2^20 / 2^24 / 2^26, us, by ticket and look-back against this: seg_len 1001 8.2 / 27 / 85
     // against 4.1 / 22.8 / 74; 100003 8.7 / 28 against 5.1 / 23; irregular, lognormal lengths 10.9 / 31.8 against 5.5 /
     // 28, seven segments 20 / 40 against 5.3 / 28; without the limit 2^26 91 against 95 and 106.
     if (shape == 0 && g_variant.formulation == kMfma && (regular ? seg_len >= 2 : g_variant.irregular_scan == 0) &&
-        ((regular && seg_len <= kLocalMax) || n <= (uint64_t)compute_units() * (uint64_t)(kTile * 16 * 8)))
-        return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, s);
+        ((regular && seg_len <= kLocalMax) || n <= (uint64_t)compute_units() * (uint64_t)(kTile * 16 * 8))) {
+        bool chained = regular && seg_len <= kLocalMax && scan_better_chained(n, seg_len, (MODE & 2) != 0);
+        if (chained) {                       // (and the table is there, or can be had)
+            Workspace* ws = nullptr;
+            bool capturing = false;
+            const tcr_status st = get_workspace(s, &ws, &capturing);
+            if (st != TCR_OK) return st;
+            chained = table_has_room(ws, tiles, capturing);
+        }
+        if (!chained) return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, s);
+    }
     if (fill) {
         const tcr_status filled = launch_fill_outside<(MODE >> 1)>(offsets, nseg, out, n, shift, s);
         if (filled != TCR_OK) return filled;
@@ -943,12 +969,8 @@ inline tcr_status launch_irregular_reduce(const _Float16* in, const uint64_t* of
     // 19.0 / 13.1 / 12.9 -> 17.3 / 11.8 / 10.4, 2^25 29.8 / 20.1 / 19.0 -> 29.3 / 19.6 / 16.1, both moments at 2^24 25.5 / 17.5 / 14.0
     // -> 22.9 / 16.0 / 12.3.  Beyond, the searches are what the tiles wait for (2^26 43.6 / 29.8 / 28.2 -> 52.0 / 34.2 / 25.4) and
     // for both moments and regular segments the sums of thousands of tiles behind one result (one segment of 2^26 elements:
-    // 25.9 -> 31.0).  Not where the descriptors cannot be had: a caller's buffer that is too small, a call recorded into a
-    // graph (recording one that uses descriptors leaves their epochs to the device, which costs every later call on the
-    // stream a launch).
-    const bool room = capturing ? ws->device_managed && !ws->dirty && ch * tiles <= ws->desc_capacity
-                                : !ws->caller_owned || ch * tiles <= ws->desc_capacity;
-    const bool linked = room && shape != 1 && tiles <= (offsets != nullptr && kind == kSum ? 4096u : 2048u);
+    // 25.9 -> 31.0).  Not where the descriptors cannot be had.
+    const bool linked = table_has_room(ws, ch * tiles, capturing) && shape != 1 && tiles <= (offsets != nullptr && kind == kSum ? 4096u : 2048u);
     // (up to four tiles per compute unit twice the wavefronts per tile: segments of 16 elements, n = 2^20 / 2^22 / 2^23 / 2^24
     // 7.1 / 8.6 / 12.0 / 17.3 us with 4 wavefronts, 5.6 / 7.4 / 11.2 / 19.3 with 8)
     if (linked && untuned && tiles <= 4 * (uint64_t)compute_units()) shape = 2;

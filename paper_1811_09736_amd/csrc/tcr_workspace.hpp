@@ -211,6 +211,14 @@ inline uint32_t* finish_counter(Workspace* ws, bool capturing) {
     return ws->counters + 4;
 }
 
+// Whether a call that has another form should take one that needs `tiles` descriptors: not on a caller's buffer that is too
+// small for them, and not recorded into a graph on a workspace whose epochs the host keeps (recording it would leave them to
+// the device, which costs every later call on the stream a launch).
+inline bool table_has_room(const Workspace* ws, uint64_t tiles, bool capturing) {
+    if (capturing) return ws->device_managed && !ws->dirty && tiles <= ws->desc_capacity;
+    return !ws->caller_owned || tiles <= ws->desc_capacity;
+}
+
 // Gives back a library-owned workspace's memory, whose work has finished (g_mutex is held).  The uncached tables are parked.
 inline void release_workspace(int device, Workspace& ws) {
     if (ws.desc) g_parked_tables.push_back({device, ws.desc, ws.desc_capacity});
