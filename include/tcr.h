@@ -151,9 +151,10 @@ tcr_status tcr_scan_ex(const void *in, void *out, uint64_t n, uint32_t flags, vo
  *   In larger ones a small kernel looks up where the tile boundaries fall among the offsets; the scan chains its tiles
  * like the long regular scans (with fewer segments than a quarter of the tiles it runs as two kernels: the pipelined
  * chain of the long regular scans takes the tiles without a segment start, a second kernel the others); the reduction
- * keeps its tiles independent and a small kernel adds the one sum per tile that reaches in from earlier tiles.
- *   The reduction's results are the same from run to run: the additions of each of its two forms have one order, also
- * where a tile adds up again what another has not published yet.  (The two forms may round differently.)
+ * keeps its tiles independent and one or two small kernels (two for few, very long segments) add the one sum per tile
+ * that reaches in from earlier tiles.
+ *   The reduction's results are the same from run to run: the additions of each of its forms have one order, also
+ * where a tile adds up again what another has not published yet.  (The forms may round differently.)
  * in and out need only their natural alignment (2 and 4 bytes): the tiles start at the 16-byte boundary at or
  * below `in` (up to 7 elements in front of it are read and ignored), and a scan whose `out` does not sit at the
  * same distance from a 16-byte boundary stores its results one by one (slower).

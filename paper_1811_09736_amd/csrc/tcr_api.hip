@@ -560,9 +560,10 @@ extern "C" uint64_t tcr_workspace_bytes(int op, uint64_t n, uint64_t seg_len) {
         desc = (irregular ? 2 : 1) * irregular_tiles_max(true, padded);
         if (irregular) words = irregular_words_max(true, padded); // where the tile boundaries fall among the offsets
     } else {
-        // tables, one carried-segment index and one pair per tile; the sums of squares add a second set of pairs
-        const uint64_t tiles = irregular_tiles_max(false, padded);
-        words = irregular_words_max(false, padded) + (moments ? tiles : 0);
+        // tables, one carried-segment index and one pair per tile and per group of 64 tiles; the sums of squares add a
+        // second set of pairs
+        const uint64_t tiles = irregular_tiles_max(false, padded), groups = irregular_groups(tiles);
+        words = irregular_words_max(false, padded) + groups + (moments ? tiles + groups : 0);
     }
     if (!irregular) {
         // Regular calls run the tiled kernels above for some lengths and alignments; otherwise, over every variant

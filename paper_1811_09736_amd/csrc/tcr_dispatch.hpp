@@ -704,12 +704,20 @@ inline uint64_t irregular_tile_elems(bool scan, int shape) {
 }
 inline uint64_t irregular_tiles(bool scan, uint64_t n, int shape) { return ceil_div(n, irregular_tile_elems(scan, shape)); }
 // 8-byte words of the partials area: the look-up table(s) of the tile boundaries, and for the reduction one
-// carried-segment index and one pair per tile.
-inline uint64_t irregular_words(bool scan, uint64_t n, int shape) {
+// carried-segment index and one pair per tile and channel.
+inline uint64_t irregular_words(bool scan, uint64_t n, int shape, uint64_t ch = 1) {
     const uint64_t tiles = irregular_tiles(scan, n, shape);
     // (scan: the look-up table and one TileLink per tile)
-    return scan ? 2 * tiles + 1 : 2 * (tiles + 1) + 2 * tiles;
+    return scan ? 2 * tiles + 1 : 2 * (tiles + 1) + (1 + ch) * tiles;
 }
+// Reductions over segments of thousands of tiles also combine the pairs of every 64 tiles.  Segments of 1024 tiles on
+// average, in arrays that do not run as one launch, us, without / with the combined pairs: one segment of 2^20 * 48 / 64 /
+// 128 / 256 / 511 elements 22.8 / 27.8 / 50.0 / 95.8 / 186.9 against 22.0 / 26.6 / 46.5 / 87.8 / 170.3, two segments 21.8 / 26.3 /
+// 47.1 / 89.5 / 176.4 against 22.0 / 26.4 / 45.7 / 85.7 / 167.7, seven 21.8 / 27.5 / 49.1 / 90.9 / 178.1 against 22.1 / 26.7 / 47.0 /
+// 87.0 / 169.0, forty (818 tiles each at 2^28) 21.7 / 26.8 / 46.1 / 86.4 against 22.4 / 27.4 / 46.8 / 85.8; lognormal lengths
+// 23.7 / 28.3 / 47.5 / 87.3 / 170.1 against 25.6 / 30.1 / 49.3 / 89.0 / 172.8.
+inline uint64_t irregular_groups(uint64_t tiles) { return ceil_div(tiles, kWave); }
+inline bool irregular_far(uint64_t tiles, uint64_t nseg) { return tiles > 4096 && tiles / 1024 >= nseg; }
 // The largest of these over the tile shapes (the smallest tiles): what tcr_workspace_bytes reports.
 inline uint64_t irregular_tiles_max(bool scan, uint64_t n) {
     uint64_t m = 0;
@@ -961,7 +969,9 @@ inline tcr_status launch_irregular_reduce(const _Float16* in, const uint64_t* of
     tcr_status st = get_workspace(s, &ws, &capturing);
     if (st != TCR_OK) return st;
     // (also where the call does without them: the same call can then be recorded into a graph)
-    st = ensure_partials(ws, s, 2 * (irregular_words(false, n, shape) + (ch - 1) * tiles), capturing);
+    const uint64_t words = irregular_words(false, n, shape, ch), groups = irregular_groups(tiles);
+    const bool far = irregular_far(tiles, nseg) && 2 * (words + ch * groups) <= partials_limit(ws, capturing);
+    st = ensure_partials(ws, s, 2 * (words + (far ? ch * groups : 0)), capturing);
     if (st != TCR_OK) return st;
     // One launch, whose tiles search the offsets and add what reaches them from in front themselves, out of one descriptor
     // per tile and channel; against a look-up kernel in front and a finishing kernel behind, us, segments of 16 elements /
@@ -998,6 +1008,15 @@ inline tcr_status launch_irregular_reduce(const _Float16* in, const uint64_t* of
     st = shape == 1 ? launch_irregular_reduce_shape<4, 8, false>(a, link, s)
                     : (shape == 2 ? launch_irregular_reduce_shape<2, 8, false>(a, link, s) : launch_irregular_reduce_shape<4, 4, false>(a, link, s));
     if (st != TCR_OK || tiles == 1) return st;          // a single tile has nothing in front of it
+    if (far) {
+        TilePair* group_pairs = pairs + ch * tiles;
+        const dim3 grid((unsigned)ceil_div(groups, kCarryWaves), ch);
+        irregular_groups_kernel<<<grid, dim3(kCarryWaves * kWave), 0, s>>>(pairs, tiles, group_pairs);
+        st = check_launch("irregular_groups_kernel");
+        if (st != TCR_OK) return st;
+        irregular_carry_kernel<<<grid, dim3(kCarryWaves * kWave), 0, s>>>(pairs, group_pairs, carried, tiles, out, out2);
+        return check_launch("irregular_carry_kernel");
+    }
     irregular_finish_kernel<kFinishThreads, kFinishFar><<<dim3((unsigned)ceil_div(tiles, kFinishThreads), ch), dim3(kFinishThreads), 0, s>>>(
         pairs, carried, tiles, out, out2);
     return check_launch("irregular_finish_kernel");
