@@ -865,10 +865,6 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
         }
         if (!chained) return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, s);
     }
-    if (fill) {
-        const tcr_status filled = launch_fill_outside<(MODE >> 1)>(offsets, nseg, out, n, shift, s);
-        if (filled != TCR_OK) return filled;
-    }
     Workspace* ws = nullptr;
     bool capturing = false;
     tcr_status st = get_workspace(s, &ws, &capturing);
@@ -885,6 +881,10 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
     ScanWorkspace dev = {};
     st = begin_lookback(ws, s, two_kernels ? 2 * tiles : tiles, &dev, capturing);      // (two kernels: a second table behind the first)
     if (st != TCR_OK) return st;
+    if (fill) {                              // (now that the call is not refused)
+        st = launch_fill_outside<(MODE >> 1)>(offsets, nseg, out, n, shift, s);
+        if (st != TCR_OK) return st;
+    }
     uint64_t* starts = reinterpret_cast<uint64_t*>(ws->partials);
     TileLink* links = reinterpret_cast<TileLink*>(starts + (tiles + 1));
     if (!regular) {
