@@ -245,7 +245,8 @@ tcr_status tcr_set_variant(const char *key, const char *value);
  *     small-segment kernels, and the formulation (matrix cores or cross-lane adds);
  *   longer powers of two and the one-segment operations (class 41): the launch shape -- scans: 12 shapes of
  *     share size, ticketed or not, persistent chain or not, plus the two multi-kernel carry strategies of
- *     tcr_set_variant("scan_carry"); reductions: span per wavefront and wavefronts combined -- and the formulation;
+ *     tcr_set_variant("scan_carry"); reductions: span per wavefront and wavefronts combined, or one launch where the
+ *     default is one -- and the formulation;
  *   every other length (class floor(log2(seg_len))): which kernel takes it -- scans: fixed tiles with marked
  *     starts (two tile shapes), one workgroup per segment, the chain on a per-segment tile grid; reductions: rows
  *     of whole segments (two launch shapes), masked row products, fixed tiles (two shapes), one wavefront per

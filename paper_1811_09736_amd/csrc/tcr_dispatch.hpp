@@ -258,7 +258,8 @@ inline ReducePlan plan_reduce(uint64_t n, uint64_t seg_len, bool whole, bool coa
     const int count = reduce_candidates(n, seg_len, whole, cand);
     bool finish = false;
     int pick = tuned_id(kTuneReduce, tuning_class(seg_len, whole));
-    if (pick < 0 || pick >= count) {
+    const bool untuned = pick < 0 || pick >= count;
+    if (untuned) {
         // frozen defaults for an array that fills the chip whatever the split: segments of 8192 .. 32768 elements over
         // 2 or 4 wavefronts; from 2^18 elements on (and for one segment) every wavefront leaves a partial of its own
         // for the second kernel -- combining the wavefronts of a workgroup first holds each back to the slowest
@@ -266,13 +267,16 @@ inline ReducePlan plan_reduce(uint64_t n, uint64_t seg_len, bool whole, bool coa
         // or 2^20 elements one workgroup's and the second kernel unnecessary, 84.1 and 90.8 us)
         if (whole || seg_len >= (1ull << 18)) pick = count > 1 ? 1 : 0;
         else pick = (seg_len < 8192 || seg_len > 32768) ? 0 : (seg_len == 8192 ? 1 : 2);
+    }
+    // (the tuner's first candidate, too, is run in one launch where that is possible: it has to find what untuned calls run)
+    if (untuned || pick == 0) {
         const bool long_one = whole ? count > 1 : seg_len > kOneGroupSegment;
         if (whole && long_one && n <= kOneGroupSegment) {
             cand[pick = 0] = {ceil_div(ceil_div(n, 16), kTile) * kTile, 16};       // one workgroup, no partials
         } else if (long_one && n <= kFinishElemsMax && (whole || n / seg_len <= kFinishSums) && !coarse && !two_kernels && !g_variant.reduce_fused) {
             cand[pick = 0] = {finish_share(n) / 16, 16};
             finish = true;
-        } else if (!whole) {
+        } else if (untuned && !whole) {
             ReduceShape c = cand[pick];
             if (seg_len <= kOneGroupSegment) {
                 // too few wavefronts to fill the chip: halve their shares, up to one workgroup of 16 per segment
