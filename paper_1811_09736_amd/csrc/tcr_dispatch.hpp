@@ -761,8 +761,8 @@ inline tcr_status launch_fill_outside(const uint64_t* offsets, uint64_t nseg, vo
 template <int U, int W, int MODE, bool LOCAL>
 inline void launch_tile_scan(const TileScan& a, const ScanWorkspace& dev, hipStream_t s) {
     const dim3 grid((unsigned)ceil_div(a.n, (uint64_t)(kTile * U * W))), block(W * kWave);
-    if (LOCAL || a.offsets == nullptr) irregular_scan_kernel<U, W, true, MODE, LOCAL><<<grid, block, 0, s>>>(a, dev);
-    else if constexpr (!LOCAL) irregular_scan_kernel<U, W, false, MODE, false><<<grid, block, 0, s>>>(a, dev);
+    if (LOCAL || a.offsets == nullptr) tile_scan_kernel<U, W, true, MODE, LOCAL><<<grid, block, 0, s>>>(a, dev);
+    else if constexpr (!LOCAL) tile_scan_kernel<U, W, false, MODE, false><<<grid, block, 0, s>>>(a, dev);
 }
 template <int MODE>
 inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, void* out, uint64_t n, uint64_t nseg, uint64_t seg_len,
@@ -793,7 +793,7 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
         // 179 with 8, 43.8 / 100.8 / 196 with 16), or longer than 8 wavefronts can add up at once
         if (seg_len > 4096 || (!(MODE & 2) && seg_len <= 1024 && n > (1ull << 24))) launch_tile_scan<1, 16, MODE, true>(a, dev, s);
         else launch_tile_scan<1, 8, MODE, true>(a, dev, s);
-        return check_launch("irregular_scan_kernel");
+        return check_launch("tile_scan_kernel");
     }
     Workspace* ws = nullptr;
     bool capturing = false;
@@ -819,7 +819,7 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
     else if (u == 2) launch_tile_scan<2, 16, MODE, false>(a, dev, s);
     else if (w == 8) launch_tile_scan<4, 8, MODE, false>(a, dev, s);
     else launch_tile_scan<4, 16, MODE, false>(a, dev, s);
-    st = check_launch("irregular_scan_kernel");
+    st = check_launch("tile_scan_kernel");
     if (st != TCR_OK) ws->dirty = true;
     return st;
 }

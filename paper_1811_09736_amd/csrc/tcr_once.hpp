@@ -11,7 +11,7 @@
 //     from the elements, so no wait depends on which workgroups run.
 // Bound: memory for large arrays, the chain of dependent steps for the smaller ones.  The ticket, the look-back and, for
 // regular segments, the bitmap of the starts and its two barriers are what this form does without.
-// (The tile arithmetic is that of the fixed tiles of irregular_scan_kernel: running sums that restart at heads inside a
+// (The tile arithmetic is that of irregular_scan_kernel, the chained form: running sums that restart at heads inside a
 // lane's eight elements, pairs of (head, sum) across lanes and wavefronts.)
 #pragma once
 #include "tcr_irregular.hpp"
@@ -84,7 +84,7 @@ __device__ __forceinline__ float lookup_open_sum(const TileScan& a, const ScanWo
 
 // LOCAL (regular segments of 2 to WAVES * 512 elements): no sum is ever looked up, no workspace.
 template <int U, int WAVES, bool REGULAR, int MODE, bool LOCAL>
-__global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U == 4 ? 8 : 4, 8))) void irregular_scan_kernel(TileScan a, ScanWorkspace ws_arg) {
+__global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U == 4 ? 8 : 4, 8))) void tile_scan_kernel(TileScan a, ScanWorkspace ws_arg) {
     static_assert(!LOCAL || REGULAR, "");
     constexpr int EXCL = MODE & 1, F16 = MODE >> 1;
     constexpr uint32_t kChunk = (uint32_t)kTile * U;          // one wavefront's share

@@ -62,8 +62,10 @@ def short(name: str) -> str:
     m = re.match(r"_ZN3tcr(\d+)([a-z_0-9]+)E", name)
     if m:
         return f"tcr::{m.group(2)}"
-    if name.startswith("tcr::"):
-        return name.split("(")[0]
+    m = re.match(r"(?:void )?(tcr::[a-z_0-9]+)(?:<([^>]*)>)?\(", name)                  # (demangled by the profiler)
+    if m:
+        args = m.group(2)
+        return m.group(1) + ("" if args is None else "<" + args.replace(" ", "").replace("true", "1").replace("false", "0") + ">")
     return name[:70]
 
 
@@ -96,8 +98,8 @@ def _write(name: str, lines) -> None:
 TEMPLATE_NOTE = [
     "Template arguments: reduce_small<FORM,LOG2L,U,W,LOAD>, scan_small<FORM,LOG2L,U,W,MODE,LOAD>, reduce_span<FORM,U,W,COMBINE,FINISH>,",
     "scan_block<FORM,U,W,CARRY,MODE>, scan_chain<FORM,U,W,MODE>, rows_reduce<KIND,U,W>, packed_rows_reduce<KIND,U,W>, scan_half<U,W,CARRY,EXCL>; FORM 0 = MFMA, 1 = DPP;",
-    "CARRY 0 = none, 1 = look-back; irregular_scan<U,W,REGULAR,MODE>, irregular_reduce<U,W,REGULAR,KIND,LINKED> (REGULAR 1: regular segments",
-    "of an untuned length; the context rows mix three offset arrays).",
+    "CARRY 0 = none, 1 = look-back; irregular_scan<U,W,REGULAR,MODE,SECOND>, tile_scan<U,W,REGULAR,MODE,LOCAL>, irregular_reduce<U,W,REGULAR,KIND,LINKED> (REGULAR 1:",
+    "regular segments of an untuned length; the context rows mix three offset arrays).",
 ]
 
 
@@ -256,7 +258,7 @@ def irregular(dirs) -> None:
            "    rocprofv3 --pmc WRITE_SIZE --output-format csv -d <out> -o bench -- python3 bench.py --no-cpu-baseline --steps 1 --warmup 0 --context-filter <mix> --calibration-copy", "",
            "Counters scaled by the three 1 GiB device copies of the same run, as in bench_cfg5_sweep_pmc_traffic.md.",
            "Algorithmic bytes: input 512 MiB, offsets 8 B per entry, results 4 B per segment (reduce) or 1024 MiB (scan).",
-           "irregular_scan_kernel<U,W,REGULAR,MODE>, irregular_reduce_kernel<U,W,REGULAR,KIND>: REGULAR 0 = offsets array.", ""]
+           "irregular_scan_kernel<U,W,REGULAR,MODE,SECOND>, irregular_reduce_kernel<U,W,REGULAR,KIND,LINKED>: REGULAR 0 = offsets array.", ""]
     for i, (label, filt, nseg) in enumerate(IRREGULAR_MIXES):
         kt_dir, fetch_dir, write_dir = dirs[3 * i: 3 * i + 3]
         stats = {short(r["Name"]): r for r in _csv(kt_dir, "kernel_stats.csv")}
