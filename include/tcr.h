@@ -224,8 +224,8 @@ tcr_status tcr_scan(const void *in, float *out, uint64_t n, void *stream);
  *   "irregular_scan" "auto" (default: one kernel or two by the number of segments) | "single" (always the one
  *                  kernel of chained tiles) | "chain" (always two, where the launch allows it: default tile shape,
  *                  16-byte aligned arrays, matrix-core formulation)
- *   "scan_wait"    "bounded" (default: the chained scan of an array that the chip holds at once waits a bounded time for
- *                  the sum of an earlier tile, then adds that tile up again) | "none" (adds up at once what is not there
+ *   "scan_wait"    "bounded" (default: scans and irregular reductions that run as one launch wait a bounded time for the
+ *                  sum of an earlier tile, then add that tile up again) | "none" (add up at once what is not there
  *                  yet; for tests)
  *   "reduce_finish" "second_kernel" (default: the paper's two-kernel device-level reduction, Section 4; arrays of up to 2^23
  *                  elements finish in one launch all the same) |

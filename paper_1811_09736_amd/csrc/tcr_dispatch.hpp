@@ -853,10 +853,15 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
     const uint64_t tiles = irregular_tiles(true, n, shape);
     const bool regular = offsets == nullptr;
     // One tile per workgroup with nothing chained: regular segments short enough for a workgroup to add up the open part by
-    // itself, at nearly every size of array (scan_better_chained), and any segments in an array that the chip holds at once (at most a 65536-element
-    // share per compute unit).  n = 2^20 / 2^24 / 2^26, us, by ticket and look-back against this: seg_len 1001 8.2 / 27 / 85
-    // against 4.1 / 22.8 / 74; 100003 8.7 / 28 against 5.1 / 23; irregular, lognormal lengths 10.9 / 31.8 against 5.5 /
-    // 28, seven segments 20 / 40 against 5.3 / 28; without the limit 2^26 91 against 95 and 106.
+    // itself, at nearly every size of array (scan_better_chained), and any segments in an array of up to 2^24 elements (256
+    // units).  n = 2^20 / 2^24 / 2^26, us, by ticket and look-back against this: seg_len 1001 8.2 / 27 / 85 against 4.1 / 22.8 /
+    // 74; 100003 8.7 / 28 against 5.1 / 20.4; irregular, lognormal lengths 10.9 / 31.8 against 5.5 / 22.5, seven segments 20 / 40
+    // against 5.3 / 25.3.  The limit of the latter dates from workgroups that took 65536 elements, one per unit; no result
+    // depends on it, and with today's tiles the forms cross later.  n = 2^24 + 8 / 2^20 * 20 / 24 / 32 / 40 / 48 / 64 / 96, us, chained
+    // against this beyond the limit: seven segments 40.7 / 43.2 / 41.7 / 46.5 / 53.4 / 68.7 / 91.1 / 126 against 25.5 / 30.9 / 35.7 /
+    // 45.9 / 60.3 / 83.4 / 111 / 171; lognormal lengths 29.8 / 33.7 / 36.9 / 44.6 / 52.0 / 66.6 / 89.9 / 124 against 23.6 / 28.5 / 33.0 / 41.9 /
+    // 56.1 / 68.4 / 89.9 / 128; segments of 16 34.5 / 38.2 / 42.5 / 50.6 / 61.8 / 79.9 / 101 / 139 against 25.4 / 30.8 / 36.4 / 46.5 / 64.9 /
+    // 75.0 / 98.6 / 143; regular 100003 - / 30.9 / 34.3 / 41.9 / 49.7 / 65.7 / 88.7 / 123 against - / 25.3 / 28.8 / 36.3 / 46.0 / 60.0 / 82.3 / 117.
     if (shape == 0 && g_variant.formulation == kMfma && (regular ? seg_len >= 2 : g_variant.irregular_scan == 0) &&
         ((regular && seg_len <= kLocalMax) || n <= (uint64_t)compute_units() * (uint64_t)(kTile * 16 * 8))) {
         bool chained = regular && seg_len <= kLocalMax && scan_better_chained(n, seg_len, (MODE & 2) != 0);

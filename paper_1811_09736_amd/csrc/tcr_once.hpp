@@ -83,6 +83,12 @@ __device__ __forceinline__ float lookup_open_sum(const TileScan& a, const ScanWo
 }
 
 // LOCAL (regular segments of 2 to WAVES * 512 elements): no sum is ever looked up, no workspace.
+// Registers: four sub-tiles per wavefront are held to 64, so that every wavefront slot of a compute unit is taken.  That
+// spills: 10 vector registers, 44 bytes of scratch per lane (exclusive scans 6 and 28), and 44 to 48 scalar ones into
+// lanes.  Without the cap it takes 77 (73), nothing in scratch, and 6 wavefronts per SIMD instead of 8.  us, capped against
+// not, workgroups of 8 wavefronts: n = 2^24, seven segments / lognormal lengths / segments of 16 25.2 / 22.4 / 24.3 against
+// 24.5 / 22.8 / 26.2, binary16 exclusive 17.5 / 15.9 / 17.5 against 18.9 / 18.0 / 18.9; regular 100003 20.4 against 21.5; n = 12 *
+// 2^20 19.8 / 18.4 / 20.5 against 19.0 / 18.0 / 19.8, 13.8 / 14.1 / 14.7 against 13.6 / 13.5 / 14.2.
 template <int U, int WAVES, bool REGULAR, int MODE, bool LOCAL>
 __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U == 4 ? 8 : 4, 8))) void tile_scan_kernel(TileScan a, ScanWorkspace ws_arg) {
     static_assert(!LOCAL || REGULAR, "");
