@@ -6,7 +6,6 @@ using namespace tcr;
 using namespace tcr::host;
 
 // ================================================================================ C ABI
-// ================================================================================ C ABI
 
 extern "C" tcr_status tcr_segmented_reduce(const void* in, float* out, uint64_t n, uint64_t seg_len, void* stream) {
     tcr_status st = validate(in, out, n, seg_len, 4);
@@ -568,9 +567,9 @@ extern "C" uint64_t tcr_workspace_bytes(int op, uint64_t n, uint64_t seg_len) {
     if (!irregular) {
         // Regular calls run the tiled kernels above for some lengths and alignments; otherwise, over every variant
         // and launch shape: one descriptor per 16384-element share (the smallest share handed out by ticket),
-        // and at most one binary32 partial per 4096 elements (the smallest span a wavefront of the one-segment
-        // reduction leaves a partial for; segmented reductions and the multi-kernel scans leave one per 65536, the
-        // moments two).
+        // and at most one binary32 partial per 4096 elements (the smallest span a wavefront of a long reduction leaves a
+        // partial for; the pieces of masked segments, two partials each for the moments, are 16384 elements and more, the
+        // shares of the multi-kernel scans 65536).
         const uint64_t shares = ceil_div(n, 16384);
         if (scan && shares > desc) desc = shares;
         const uint64_t partials = ceil_div(n, 4096);

@@ -13,7 +13,7 @@
 // uses the descriptor chain of the regular scans -- a tile that contains a segment start publishes the
 // sum since its last start as a finished prefix at once, because no later tile can need more of it --
 // while the reduction, where at most one result per tile depends on earlier tiles, either lets each tile add that
-// one part itself or leaves the tiles independent and adds it afterwards (a small kernel over the per-tile sums).
+// one part itself or leaves the tiles independent and adds it afterwards (one or two small kernels over the per-tile sums).
 //
 // What a tile of a large array needs from the offsets is found before it starts: irregular_bounds_kernel writes, per
 // tile boundary, how many offsets lie below it, so a tile reads its range of entries with one look-up
