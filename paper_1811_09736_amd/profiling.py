@@ -5,6 +5,7 @@ Nothing here computes anything of the method: it reads profiler CSV files, avera
 writes text.  Usage (the rocprofv3 commands themselves are quoted in every summary):
 
     python -m paper_1811_09736_amd.profiling kernel-stats  <dir of --kernel-trace --stats run>
+    python -m paper_1811_09736_amd.profiling sizes         <log2 n> <dir of --kernel-trace --stats run> ...
     python -m paper_1811_09736_amd.profiling traffic       <dir of --pmc FETCH_SIZE run> <dir of --pmc WRITE_SIZE run>
     python -m paper_1811_09736_amd.profiling mix           <kernel-stats dir> <dir of SQ counters, mfma> <dir of SQ counters, dpp>
     python -m paper_1811_09736_amd.profiling irregular     <kt dir> <fetch dir> <write dir>  (three times, one per length mix)
@@ -97,7 +98,7 @@ def _write(name: str, lines) -> None:
 
 TEMPLATE_NOTE = [
     "Template arguments: reduce_small<FORM,LOG2L,U,W,LOAD>, scan_small<FORM,LOG2L,U,W,MODE,LOAD>, reduce_span<FORM,U,W,COMBINE,FINISH>,",
-    "scan_block<FORM,U,W,CARRY,MODE>, scan_chain<FORM,U,W,MODE>, rows_reduce<KIND,U,W>, packed_rows_reduce<KIND,U,W>, scan_half<U,W,CARRY,EXCL>; FORM 0 = MFMA, 1 = DPP;",
+    "scan_block<FORM,U,W,CARRY,MODE>, scan_chain<FORM,U,W,MODE,IRREG,ONCE>, rows_reduce<KIND,U,W>, packed_rows_reduce<KIND,U,W>, scan_half<U,W,CARRY,EXCL>; FORM 0 = MFMA, 1 = DPP;",
     "CARRY 0 = none, 1 = look-back; irregular_scan<U,W,REGULAR,MODE,SECOND>, tile_scan<U,W,REGULAR,MODE,LOCAL>, irregular_reduce<U,W,REGULAR,KIND,LINKED> (REGULAR 1:",
     "regular segments of an untuned length; the context rows mix three offset arrays).",
 ]
@@ -115,6 +116,23 @@ def kernel_stats(kt_dir: str) -> None:
         out.append(f"| {short(r['Name'])} | {r['Calls']} | {float(r['AverageNs']) / 1e3:.1f} | {float(r['MinNs']) / 1e3:.1f} | "
                    f"{float(r['MaxNs']) / 1e3:.1f} | {float(r['Percentage']):.2f} |")
     _write("bench_cfg5_sweep_kernel_stats.md", out)
+
+
+def sizes(args) -> None:
+    """Pairs of log2(n) and a kernel-trace folder: the same calls on smaller arrays, one table per size."""
+    out = ["# rocprofv3 kernel statistics: bench.py's calls on smaller arrays", "",
+           f"Sources: csrc stamp {source_stamp()}, commit {_commit()}.",
+           "Command, per size (run from /tmp with TMPDIR=/tmp on the MI355X box):", "",
+           "    rocprofv3 --kernel-trace --stats --output-format csv -d <out> -o bench -- python3 bench.py --no-cpu-baseline --no-small-configs --log2n <log2 n>", "",
+           "The library's own kernels only; a row averages every call that runs the instance (the sweep's segment lengths, the", "context rows, the three mixes of irregular segments).",
+           *TEMPLATE_NOTE]
+    for log2n, directory in zip(args[::2], args[1::2]):
+        out += ["", f"## n = 2^{log2n}", "", "| kernel | calls | avg us | min us | max us |", "|---|---:|---:|---:|---:|"]
+        for r in _csv(directory, "kernel_stats.csv"):
+            if short(r["Name"]).startswith("tcr::"):
+                out.append(f"| {short(r['Name'])} | {r['Calls']} | {float(r['AverageNs']) / 1e3:.1f} | {float(r['MinNs']) / 1e3:.1f} | "
+                           f"{float(r['MaxNs']) / 1e3:.1f} |")
+    _write("bench_smaller_arrays_kernel_stats.md", out)
 
 
 def dispatcher_names(k: str):
@@ -271,8 +289,8 @@ def irregular(dirs) -> None:
                 f"Algorithmic MiB: reduce {512 + off_mib + 4 * nseg / 1048576:.1f}, scan {512 + off_mib + 1024:.1f}.", "",
                 "| kernel | calls | avg us | scaled read MiB | scaled written MiB |", "|---|---:|---:|---:|---:|"]
         for k in sorted(stats):
-            if "irregular" not in k:
-                continue
+            if not k.startswith(("tcr::irregular", "tcr::scan_chain_kernel<0,4,16,0,1")):
+                continue                                          # (the chain over the tiles without a segment start)
             fv = fetch.get(k, {}).get("FETCH_SIZE", [0.0])
             wv = write.get(k, {}).get("WRITE_SIZE", [0.0])
             out.append(f"| {k} | {stats[k]['Calls']} | {float(stats[k]['AverageNs']) / 1e3:.1f} | "
@@ -309,7 +327,7 @@ def chain_gap(kt_dir: str, sq_dir: str, tcc_dir: str) -> None:
                 "    rocprofv3 --pmc SQ_WAVES SQ_WAVE_CYCLES SQ_BUSY_CU_CYCLES SQ_WAIT_ANY SQ_ACTIVE_INST_ANY SQ_WAIT_INST_LDS SQ_INSTS_VMEM_RD SQ_INSTS_VMEM_WR --output-format csv -d <out> -o bench -- python3 bench.py --no-cpu-baseline --steps 2 --warmup 1 --no-context",
                 "    rocprofv3 --pmc TCC_EA0_RDREQ_DRAM_CREDIT_STALL_sum TCC_EA0_WRREQ_STALL_sum TCC_EA0_RD_UNCACHED_32B_sum TCC_ATOMIC --output-format csv -d <out> -o bench -- python3 bench.py --no-cpu-baseline --steps 2 --warmup 1 --no-context", "",
                 *TEMPLATE_NOTE]
-    reading = ["Reading (scan_chain_kernel<0,4,16,0,0>, seg_len 2^16 and 2^20, against scan_block_kernel<0,1,2,0,0> and <0,1,8,0,0>,",
+    reading = ["Reading (scan_chain_kernel<0,4,16,0,0,0>, seg_len 2^16 and 2^20, against scan_block_kernel<0,1,2,0,0> and <0,1,8,0,0>,",
                "seg_len 2^10 and 2^12, same bytes): the chain adds some 57 000 wavefront-level loads per launch (SQ_INSTS_VMEM_RD:",
                "the descriptor reads, one window of aggregates per tile) and 8 960 atomics (TCC_ATOMIC: the tickets) -- a",
                "hundredth of a percent of the traffic.  What differs is how much work is in flight: SQ_WAVE_CYCLES is about",
@@ -333,7 +351,7 @@ def irregular_counters(kt_dir: str, sq1: str, sq2: str, sq3: str) -> None:
                 f"    rocprofv3 --pmc SQ_INSTS_VALU SQ_INSTS_SALU SQ_INSTS_LDS SQ_INSTS_VMEM_RD SQ_INSTS_VMEM_WR SQ_INSTS_SMEM SQ_INSTS_BRANCH SQ_WAIT_INST_ANY --output-format csv -d <out> -o bench -- python3 bench.py --no-cpu-baseline --steps 1 --warmup 0 {flt}",
                 f"    rocprofv3 --pmc SQ_LDS_BANK_CONFLICT SQ_LDS_IDX_ACTIVE SQ_LDS_ADDR_CONFLICT SQ_INST_LEVEL_LDS SQ_INST_LEVEL_VMEM --output-format csv -d <out> -o bench -- python3 bench.py --no-cpu-baseline --steps 1 --warmup 0 {flt}", "",
                 *TEMPLATE_NOTE]
-    reading = ["Reading.  A launch covers 2^28 elements = 524288 sub-tiles of 512; irregular_reduce_kernel<4,4,0,0> runs 131072",
+    reading = ["Reading.  A launch covers 2^28 elements = 524288 sub-tiles of 512; irregular_reduce_kernel<4,4,0,0,0> runs 131072",
                "wavefronts of four sub-tiles.  SQ_INSTS_VALU / 524288 is the vector instructions per 512 elements, all of the",
                "kernel included (marking the segment starts, the sums, the walk over the segment ends); SQ_LDS_IDX_ACTIVE / 256 is",
                "the LDS busy cycles per compute unit, to be held against the launch's duration times the clock.  The same",
@@ -404,6 +422,8 @@ def main(argv) -> int:
     kind, args = argv[1], argv[2:]
     if kind == "kernel-stats":
         kernel_stats(*args)
+    elif kind == "sizes":
+        sizes(args)
     elif kind == "traffic":
         traffic(*args)
     elif kind == "mix":
