@@ -73,7 +73,7 @@ typedef enum {
  * workspace); reductions of 5 to 15 elements from arrays that are not 4-byte aligned run on fixed
  * tiles of the array with the segment starts marked (the kernels of the irregular calls below; they use the
  * workspace); scans run on fixed tiles too, up to 8192 elements per segment with no need of the workspace (a workgroup
- * adds up the part of its open segment in front of its tile by itself; segments of more than 2048 elements in arrays of
+ * adds up the part of its open segment in front of its tile by itself; segments of more than 3072 elements in arrays of
  * more than 2^25 chain their tiles instead where that is faster and the workspace has room), except scans of a multiple of 8 elements from 65536 on (the
  * chained scan) and of a multiple of 64 elements up to 8192 that fills a workgroup's tiles to four fifths (one
  * workgroup per segment; the tuning table can give it every multiple of 8 between 520 and 65528); longer

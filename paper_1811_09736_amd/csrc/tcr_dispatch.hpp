@@ -833,11 +833,14 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
 //                                151 / 154 / 158    256  287 / 287 / 289 and 294 / 300 / 308
 //   binary16 results:            24  30 / 30 / 30 and 28 / 29 / 30    40  35 / 35 / 35 and 34 / 35 / 37    64  50 / 49 / 50 and 52 / 53 / 56
 //                                128  101 / 101 / 102 and 115 / 118 / 120    256  190 / 190 / 190 and 224 / 228 / 232
-//                                (4001: 48  39 and 39    56  44 and 45    64  49 and 51    2001: 64  48 and 46    256  189 and 188)
+//                                2501 / 3001 / 4001:  64  49 / 49 / 49 and 48 / 50 / 52    96  79 / 79 / 79 and 74 / 74 / 77    128  101 / 101 / 101
+//                                and 98 / 98 / 101    256  189 / 189 / 189 and 188 / 192 / 195    (2001: 64  48 and 47    256  189 and 186)
 // (Between 2^20 * 44 and 56 an array and its binary32 results just outgrow the 256 MiB of the memory-side cache.)
 inline bool scan_better_chained(uint64_t n, uint64_t seg_len, bool f16) {
-    if (f16) return (seg_len > 4096 && n > (5ull << 23)) || (seg_len > 2048 && n > (3ull << 24));
-    return seg_len > 4096 && n > (11ull << 22) && (n <= (7ull << 23) || n > (seg_len <= 6144 ? 1ull << 27 : 5ull << 24));
+    if (f16 && seg_len > 4096) return n > (seg_len <= 6144 ? 5ull << 23 : 9ull << 22);
+    if (f16) return seg_len > 3072 && ((n > (3ull << 24) && n <= (5ull << 24)) || n > (3ull << 26));
+    if (seg_len <= 4096 || n <= (11ull << 22)) return false;
+    return seg_len <= 6144 ? n <= (13ull << 22) || n > (1ull << 27) : n <= (7ull << 23) || n > (5ull << 24);
 }
 
 template <int MODE>

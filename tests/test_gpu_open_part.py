@@ -21,7 +21,7 @@ def tcr():
 @pytest.fixture(scope="module")
 def data():
     torch.manual_seed(4)
-    return torch.randint(-1, 2, ((1 << 27) + 16384,), device="cuda", dtype=torch.int8).to(torch.float16)
+    return torch.randint(-1, 2, ((3 << 26) + 16384,), device="cuda", dtype=torch.int8).to(torch.float16)
 
 
 def check(got, x, seg, exclusive):
@@ -31,8 +31,8 @@ def check(got, x, seg, exclusive):
     assert torch.equal(got.view(-1, seg), ref.to(got.dtype))
 
 
-@pytest.mark.parametrize("limit", [5 << 23, 3 << 24, 11 << 22, 7 << 23, 5 << 24, 1 << 27])
-@pytest.mark.parametrize("seg", [2047, 2049, 4095, 4097, 6143, 6145, 8191])
+@pytest.mark.parametrize("limit", [9 << 22, 5 << 23, 3 << 24, 11 << 22, 13 << 22, 7 << 23, 5 << 24, 1 << 27, 3 << 26])
+@pytest.mark.parametrize("seg", [2047, 3071, 3073, 4095, 4097, 6143, 6145, 8191])
 def test_both_sides_of_every_limit(tcr, data, limit, seg):
     for n in (limit // seg * seg, (limit // seg + 1) * seg):
         for shift, flags in ((0, 0), (0, 3), (1, 2)):
