@@ -147,7 +147,8 @@ tcr_status tcr_scan_ex(const void *in, void *out, uint64_t n, uint32_t flags, vo
  * the mix of segment lengths.  Both use the workspace (tcr_workspace_bytes, op 4 and 5).
  *   Arrays of up to 2^24 elements (sums: 2^25) run as one kernel, whose tiles search the offsets and look up, among the
  * sums that the other tiles publish, what reaches them from in front -- except where the workspace is too small for a
- * sum per tile, and reductions that are recorded into a graph on a stream where no launch that chains tiles has been.
+ * sum per tile, and reductions that are recorded into a graph before any launch that chains tiles has been on that
+ * stream.
  *   In larger ones a small kernel looks up where the tile boundaries fall among the offsets; the scan chains its tiles
  * like the long regular scans (with fewer segments than a quarter of the tiles it runs as two kernels: the pipelined
  * chain of the long regular scans takes the tiles without a segment start, a second kernel the others); the reduction
