@@ -1,5 +1,5 @@
 """Reductions that finish in one launch: the workgroup that is done last adds up the partials, and the count of finished
-workgroups is back at 0 for the next launch, recorded or not.  Whole numbers: exact."""
+workgroups serves the next launch, recorded or not.  Whole numbers: exact."""
 import numpy as np
 import pytest
 import torch

@@ -1,6 +1,7 @@
-"""The sums that reach a tile of the irregular reduction from tiles in front of it: from the tile next to it, from within the
-finishing workgroup, from further away than one and than several of its steps; and the tiles that search the offsets
-themselves.  Whole numbers: exact."""
+"""The sums that reach a tile of the irregular reduction from tiles in front of it: from the tile next to it, from further away
+than one and than several steps of the finishing kernel; and the tiles that search the offsets themselves.  (Arrays of up to
+4096 tiles, both moments 2048, run as one launch: the finishing kernel at the edges of its groups of tiles is in
+test_gpu_finish_groups.py.)  Whole numbers: exact."""
 import numpy as np
 import pytest
 import torch
