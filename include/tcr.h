@@ -273,10 +273,11 @@ tcr_status tcr_tuning_import(const char *text);
  * Name of the kernel the dispatcher would launch for (op, n, seg_len) under the current
  * variant settings; op is 0 = segmented_reduce, 1 = segmented_scan, 2 = reduce, 3 = scan,
  * 4 = irregular_reduce, 5 = irregular_scan (seg_len is ignored).  For fixed tiles, irregular and <regular>, the
- * kernels of a large array are named whatever its size: smaller arrays need fewer (their tiles search the offsets
+ * kernels that work on any array are named whatever its size: smaller arrays need fewer (their tiles search the offsets
  * and add what reaches them themselves, so neither irregular_bounds_kernel nor irregular_finish_kernel is launched),
- * scans of smaller arrays and of regular segments of up to 8192 elements are tile_scan_kernel, and sums over segments
- * of thousands of tiles are irregular_groups_kernel and irregular_carry_kernel.  The arrays are taken to be 16-byte
+ * irregular sums and moments of most arrays above 2^22 elements are segments_reduce_kernel alone unless they are
+ * recorded into a graph, scans of smaller arrays and of regular segments of up to 8192 elements are tile_scan_kernel, and
+ * sums over segments of thousands of tiles are irregular_groups_kernel and irregular_carry_kernel.  The arrays are taken to be 16-byte
  * aligned (regular calls on arrays that are not run on the fixed tiles).
  * Returns a static string ("" when nothing would be launched); never NULL.
  */

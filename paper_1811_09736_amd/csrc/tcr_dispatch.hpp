@@ -966,6 +966,49 @@ inline tcr_status launch_irregular_reduce_shape(const IrregularReduce& a, const 
     return check_launch("irregular_reduce_kernel");
 }
 
+// Irregular reductions by workgroups that walk ranges of tiles (tcr_segments.hpp), where that is the faster form.  us, tiles
+// of their own (one launch up to 2^24 or 2^25 elements, three beyond) against ranges, by the mean length of a segment:
+//   sums          n = 2^20 *     4           8           16          32          64          128
+//     2                      16.0/17.0   25.9/27.1   46.5/41.1   94.0/77.0   165/142     305/243
+//     8                       8.7/9.1    12.6/12.7   21.2/18.8   37.0/29.6   54.0/50.4   96.8/98.5
+//     16                      7.5/7.4    11.1/9.4    17.2/13.3   29.2/21.6   43.6/36.2   72.3/66.0
+//     64                      6.9/7.3     9.6/9.7    14.4/13.4   25.2/21.5   38.0/37.0   62.3/64.7
+//     256                     6.9/7.2     8.9/9.2    13.5/12.0   23.6/18.8   35.8/33.4   59.4/57.7
+//     1024                    6.8/7.5     8.4/9.6    12.1/12.7   21.2/19.8   31.6/32.6   53.2/54.5
+//     16384                   6.9/7.2     8.1/8.7    10.5/11.5   17.7/16.6   28.2/28.7   47.3/49.1
+//     262144                  7.0/6.6     7.0/7.6     9.8/9.9    15.6/14.8   27.4/25.8   46.9/44.7
+//   lognormal lengths (1892)  6.8/7.7     8.6/9.7    11.8/12.8   19.6/19.1   29.4/31.4   50.2/53.4
+//   both moments
+//     8                      10.4/9.8    14.8/14.0   27.5/21.2   44.4/33.9   71.4/56.7   134/111
+//     16                      8.5/8.1    12.8/10.3   22.9/14.8   37.1/24.2   57.9/40.2   100/72.2
+//     256                     8.5/8.2    10.3/9.6    18.8/12.9   30.6/20.6   50.1/35.6   87.2/62.9
+//     16384                   8.3/8.1     9.6/9.5    14.2/12.5   21.4/18.2   32.2/31.2   55.4/53.1
+// (2^28 elements, segments of 16 / lognormal / seven: sums 137 / 90 / 88 against 140 / 96 / 81, both moments 195 / 115 / 90 against
+// 154 / 103 / 84.)  With segments of a thousand elements a tile has a handful of ends, and each is a chain of its own.
+inline bool segments_better(uint64_t n, uint64_t nseg, int kind) {
+    if (n <= (1ull << 22)) return false;
+    if (kind == kBoth) return true;
+    const uint64_t mean = n / nseg;
+    if (mean >= (1ull << 15)) return n > (1ull << 24);
+    if (mean >= 384) return n > (1ull << 24) && n <= (1ull << 25);
+    return n > (mean < 8 ? 1ull << 23 : 1ull << 22) && n <= (1ull << 27);
+}
+// Tiles per workgroup: what makes four workgroups per compute unit, up to 11; four in larger arrays (64M elements in segments of
+// 16, us: 4 / 6 / 8 / 9 / 11 / 14 tiles 37.3 / 40.5 / 37.9 / 36.5 / 36.4 / 40.6; 80M 44.5 / 44.8 / 43.8 / 43.0 / 44.4 / 44.5; 128M 66.4 / 67.0 / 67.0 / - /
+// 72.6 / 71.7), and no more than 2^15 workgroups.
+inline uint64_t segments_tiles(uint64_t n) {
+    const uint64_t tiles = ceil_div(n, kSegmentsTile), even = ceil_div(tiles, 4 * (uint64_t)compute_units());
+    const uint64_t most = ceil_div(tiles, 1ull << 15);
+    return even <= 11 ? even : (most > 4 ? most : 4);
+}
+// Distance of the 64 probes with which a workgroup's search starts, as a power of two: they reach four standard deviations of
+// where n / nseg uniform lengths put an entry to either side.
+inline uint32_t segments_grid_log2(uint64_t nseg) {
+    uint32_t log2 = 6;
+    while (log2 < 40 && (64ull << (2 * log2)) < nseg) ++log2;
+    return log2;
+}
+
 inline tcr_status launch_irregular_reduce(const _Float16* in, const uint64_t* offsets, float* out, uint64_t n, uint64_t nseg,
                                           uint64_t seg_len, hipStream_t s, int kind = kSum, float* out2 = nullptr, int shape = -1) {
     const bool untuned = shape < 0 && tuned_id(kTuneIrregular, 0) < 0;
@@ -985,6 +1028,22 @@ inline tcr_status launch_irregular_reduce(const _Float16* in, const uint64_t* of
     const bool far = irregular_far(tiles, nseg) && 2 * (words + ch * groups) <= partials_limit(ws, capturing);
     st = ensure_partials(ws, s, 2 * (words + (far ? ch * groups : 0)), capturing);
     if (st != TCR_OK) return st;
+    if (offsets != nullptr && shape == 0 && segments_better(n, nseg, kind)) {
+        const uint64_t group_tiles = segments_tiles(n), wgs = ceil_div(n, group_tiles * kSegmentsTile);
+        if (table_has_room(ws, ch * wgs, capturing)) {
+            ScanWorkspace dev = {};
+            st = begin_lookback(ws, s, ch * wgs, &dev, capturing);
+            if (st != TCR_OK) return st;
+            const SegmentsReduce a = {in, offsets, out, out2, n, nseg, shift, (double)(nseg + 1) / (double)n, segments_grid_log2(nseg),
+                                      (uint32_t)group_tiles, g_variant.scan_wait ? kOncePatience : 0u};
+            const dim3 grid((unsigned)wgs), block(4 * kWave);
+            if (kind == kBoth) segments_reduce_kernel<kBoth><<<grid, block, 0, s>>>(a, dev);
+            else segments_reduce_kernel<kSum><<<grid, block, 0, s>>>(a, dev);
+            st = check_launch("segments_reduce_kernel");
+            if (st != TCR_OK) ws->dirty = true;
+            return st;
+        }
+    }
     // One launch, whose tiles search the offsets and add what reaches them from in front themselves, out of one descriptor
     // per tile and channel; against a look-up kernel in front and a finishing kernel behind, us, segments of 16 elements /
     // lognormal lengths / seven segments: n = 2^20 8.0 / 6.2 / 5.5 -> 5.6 / 5.3 / 5.3, 2^22 10.6 / 9.0 / 8.6 -> 7.4 / 6.2 / 6.2, 2^24

@@ -18,6 +18,7 @@
 #include "tcr_generic.hpp"
 #include "tcr_irregular.hpp"
 #include "tcr_once.hpp"
+#include "tcr_segments.hpp"
 #include "tcr_rows.hpp"
 #include "tcr_packed.hpp"
 #include "tcr_half.hpp"

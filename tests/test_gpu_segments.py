@@ -1,0 +1,99 @@
+"""Irregular sums and moments by workgroups that walk ranges of tiles (arrays of more than 2^22 elements): numbers of segments
+per tile around the limits between the ways in which a tile is shared out, batches of entries that end with a tile or
+just behind it, segments around the edges of groups, tiles and ranges, parts added from elements and from published sums
+(waited for or not), entries far from where their number alone would put them.  Whole numbers: exact; fractional ones the
+same from run to run and within the rounding of the additions."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1811_09736_amd import workloads
+
+pytestmark = pytest.mark.gpu
+
+TILE = 6144
+N = (1 << 22) + 3 * TILE + 5                    # (two tiles per range from 1025 tiles on: see BIG)
+BIG = (1 << 24) + 4099                          # three tiles per range
+
+
+@pytest.fixture(scope="module")
+def tcr():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1811_09736_amd import binding
+    binding.set_variant("reset")
+    binding.tuning_import("")
+    yield binding
+    binding.set_variant("reset")
+    binding.check_device_flags()
+
+
+def check(tcr, oracle, x, xd, off):
+    off = np.asarray(off, dtype=np.int64)
+    od = torch.from_numpy(off).cuda()
+    a, q = tcr.irregular_moments(xd, od)
+    wa, wq = oracle.irregular_moments(x, off)
+    assert np.max(wq) < 2 ** 24
+    assert np.array_equal(tcr.irregular_reduce(xd, od).cpu().numpy().astype(np.float64), wa)
+    assert np.array_equal(a.cpu().numpy().astype(np.float64), wa) and np.array_equal(q.cpu().numpy().astype(np.float64), wq)
+
+
+@pytest.mark.parametrize("shift", [0, 3])
+@pytest.mark.parametrize("per_tile", [7, 8, 9, 63, 64, 65, 255, 256, 257, 511, 512, 513, 1024, 2000])
+def test_segments_per_tile(tcr, oracle, per_tile, shift):
+    base = workloads.make_input(N + 8, "int1", per_tile)
+    x, xd = base[shift:shift + N].copy(), torch.from_numpy(base).cuda()[shift:shift + N]
+    ends = np.arange(0, N, TILE)[:, None] + np.round(np.linspace(0, TILE, per_tile, endpoint=False)).astype(np.int64)[None, :]
+    check(tcr, oracle, x, xd, np.concatenate([np.unique(np.minimum(ends.ravel(), N)), [N]]))       # one on every tile's start
+    jitter = np.random.default_rng(per_tile).integers(0, max(TILE // per_tile, 2), ends.shape)
+    check(tcr, oracle, x, xd, np.concatenate([[0], np.sort(np.minimum((ends + jitter).ravel(), N)), [N, N, N]]))
+
+
+@pytest.mark.parametrize("wait", ["bounded", "none"])
+@pytest.mark.parametrize("n", [N, BIG])
+def test_parts_in_front_of_a_range(tcr, oracle, n, wait):
+    x = workloads.make_input(n, "int1", 7)
+    xd = torch.from_numpy(x).cuda()
+    tcr.set_variant("scan_wait", wait)
+    try:
+        for reach in (1, 7, 8, 511, TILE - 1, TILE, TILE + 1, 5 * TILE, 300 * TILE + 9):
+            off = [0]
+            for edge in range(302 * TILE, n - TILE, 311 * TILE):                # a segment from `reach` in front of a tile's start
+                off += sorted({max(edge - reach, off[-1]), edge + 5})
+            # (empty segments in front of, between and behind them bring the mean length down to what sums take this way)
+            check(tcr, oracle, x, xd, off + [n] * (n // 64))
+    finally:
+        tcr.set_variant("reset")
+
+
+def test_entries_far_from_their_share(tcr, oracle):
+    x = workloads.make_input(N, "int1", 5)
+    xd = torch.from_numpy(x).cuda()
+    few = np.arange(0, 40000, dtype=np.int64)
+    check(tcr, oracle, x, xd, np.concatenate([few, [N]]))                        # all in the first tiles
+    check(tcr, oracle, x, xd, np.concatenate([[3], N - 40000 + few, [N]]))       # all in the last ones
+    check(tcr, oracle, x, xd, np.concatenate([np.zeros(30000, np.int64), np.full(30000, N // 2 + 1), [N - 9]]))
+    check(tcr, oracle, x, xd, np.concatenate([np.full(100000, 2 * TILE), [N]]))  # hundreds of batches on one edge
+
+
+@pytest.mark.parametrize("recipe", ["uniform16", "lognormal256", "few7"])
+def test_rounding_and_repetition(tcr, oracle, recipe):
+    n = (1 << 24) + 77                           # (every mean length takes this way here)
+    x = workloads.make_input(n, "normal", 3)
+    xd = torch.from_numpy(x).cuda()
+    off = workloads.make_offsets(n, recipe, 3).view(np.int64)
+    od = torch.from_numpy(off).cuda()
+    results = []
+    for wait in ("bounded", "none", "bounded"):
+        tcr.set_variant("scan_wait", wait)
+        results.append((tcr.irregular_reduce(xd, od), *tcr.irregular_moments(xd, od)))
+    tcr.set_variant("reset")
+    for r in results[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(r, results[0]))
+    # additions in a row: 8 in a group, 12 groups of a lane, 6 across lanes, 4 wavefronts, 3 tiles; then 16 published sums in a
+    # lane, 6 across lanes, 4 wavefronts and the one that joins the parts
+    bound = 64 * 2.0 ** -24 * oracle.irregular_reduce(np.abs(x), off) + 1e-30
+    for got in results[0][:2]:
+        assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - oracle.irregular_reduce(x, off)) <= bound)
+    want = oracle.irregular_moments(x, off)[1]
+    assert np.all(np.abs(results[0][2].cpu().numpy().astype(np.float64) - want) <= 64 * 2.0 ** -24 * want + 1e-30)
