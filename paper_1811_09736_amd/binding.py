@@ -344,9 +344,13 @@ def workspace_bytes(op: int, n: int, seg_len: int) -> int:
     return int(_lib.tcr_workspace_bytes(op, n, seg_len))
 
 
+# The tensors in use as workspaces, by device: every call on the device writes there, so they are kept until replaced.
+_workspaces = {}
+
+
 def set_workspace(buffer: Optional[torch.Tensor]) -> None:
-    """tcr_set_workspace: use `buffer` (any contiguous CUDA tensor; the caller keeps it alive) on its device, or
-    return the current device to library-owned workspaces with None."""
+    """tcr_set_workspace: use `buffer` (any contiguous CUDA tensor) on its device, or return the current device to
+    library-owned workspaces with None."""
     if buffer is None:
         st = _lib.tcr_set_workspace(None, 0)
     else:
@@ -356,6 +360,11 @@ def set_workspace(buffer: Optional[torch.Tensor]) -> None:
             st = _lib.tcr_set_workspace(buffer.data_ptr(), buffer.numel() * buffer.element_size())
     if st != OK:
         raise TcrError(st, "tcr_set_workspace")
+    if buffer is None:
+        if _workspaces:                      # (without a device there are none)
+            _workspaces.pop(torch.cuda.current_device(), None)
+    else:
+        _workspaces[buffer.get_device()] = buffer
 
 
 def set_variant(key: str, value: str = "") -> None:
