@@ -13,25 +13,6 @@ __global__ void fill_zero_kernel(float* out, uint64_t count) {
     if (i < count) out[i] = 0.0f;
 }
 
-// Zeros to the positions of [shift, n) outside [offsets[0] + shift, offsets[nseg] + shift).
-template <int F16>
-__global__ __launch_bounds__(256) void fill_outside_kernel(const uint64_t* __restrict__ offsets, uint64_t nseg, void* __restrict__ out,
-                                                           uint64_t n, uint32_t shift) {
-    uint64_t first = offsets[0] + shift, last = offsets[nseg] + shift;
-    if (first > n) first = n;
-    if (last < first) last = first;
-    const uint64_t stride = (uint64_t)gridDim.x * 256;
-    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x + shift; i < n; i += stride) {
-        if (i >= first && i < last) {                     // (jump over the covered part)
-            const uint64_t trips = (last - i + stride - 1) / stride;
-            i += trips * stride;
-            if (i >= n) return;
-        }
-        if constexpr (F16) static_cast<_Float16*>(out)[i] = (_Float16)0.0f;
-        else static_cast<float*>(out)[i] = 0.0f;
-    }
-}
-
 inline bool is_pow2(uint64_t v) { return v != 0 && (v & (v - 1)) == 0; }
 inline int log2u(uint64_t v) {
     int l = 0;
@@ -757,12 +738,45 @@ inline tcr_status launch_fill_outside(const uint64_t* offsets, uint64_t nseg, vo
     return check_launch("fill_outside_kernel");
 }
 
+// Distance of the 64 probes with which a workgroup's search among the offsets starts, as a power of two: they reach four standard deviations of
+// where n / nseg uniform lengths put an entry to either side.
+inline uint32_t search_grid_log2(uint64_t nseg) {
+    uint32_t log2 = 6;
+    while (log2 < 40 && (64ull << (2 * log2)) < nseg) ++log2;
+    return log2;
+}
+
 // One tile per workgroup (tcr_once.hpp).  in, out, n: already counted from the 16-byte boundary below the caller's array.
 template <int U, int W, int MODE, bool LOCAL>
 inline void launch_tile_scan(const TileScan& a, const ScanWorkspace& dev, hipStream_t s) {
     const dim3 grid((unsigned)ceil_div(a.n, (uint64_t)(kTile * U * W))), block(W * kWave);
     if (LOCAL || a.offsets == nullptr) tile_scan_kernel<U, W, true, MODE, LOCAL><<<grid, block, 0, s>>>(a, dev);
     else if constexpr (!LOCAL) tile_scan_kernel<U, W, false, MODE, false><<<grid, block, 0, s>>>(a, dev);
+}
+// The largest array that runs this way when its sums are looked up, by the (mean) length of its segments.  n in 2^20 elements,
+// us, chained tiles (irregular: with a look-up kernel in front, a second kernel behind where most tiles have no start)
+// against this:
+//   binary32     n = 20          24          32          48          64          96          128         256
+//     16, irregular  40.4/28.8   46.7/36.6   59.6/47.6   84.0/73.3   105/93.0    143/129     180/166
+//     lognormal      36.0/26.1   39.5/30.2   52.9/43.9   71.3/63.3   92.6/85.8   127/122     162/159
+//     seven segments 40.8/29.7   43.5/33.7   52.8/52.6   70.7/83.0   93.9/115    128/179     162/245
+//     100003, regular 31.3/25.4  34.6/29.1   48.0/40.4   66.7/58.1   89.3/79.8   123/114     157/148     294/289 (FIT = 8)
+//     300003         31.5/25.9   35.5/29.6   47.4/41.1   68.2/60.3   91.2/82.6   126/119     161/155
+//     1000003        32.3/26.1   36.7/30.8   47.3/43.0   69.7/65.0   93.1/89.2   130/129     166/170
+//     3000003        31.3/25.6   36.9/30.8   47.8/43.5   66.1/62.5   93.2/91.3   131/134     168/177     319/356 (8)
+//   binary16, exclusive (regular: inclusive)
+//     16, irregular  32.5/22.1   35.9/25.0   44.1/32.6   60.4/46.6   73.7/61.5   102/87.3    128/112
+//     lognormal      28.1/20.1   30.8/23.0   36.1/27.8   50.2/40.9   60.6/51.4   86.6/78.8   110/102
+//     seven segments 33.2/22.6   34.7/25.0   39.1/33.9   50.8/53.6   61.5/73.1   86.9/125    110/176
+//     100003, regular 23.4/18.5  25.8/20.9   31.3/26.5   45.2/37.8   55.9/48.2   81.6/74.5   104/96.9    193/187 (8)
+//     3000003        23.8/18.3   27.6/21.8   32.8/29.4   45.2/41.7   58.1/55.8   86.1/86.1   110/113     207/221 (8)
+// (a sum over thousands of tiles takes as many looks as there are 64s of them, and every tile waits for its own)
+constexpr uint64_t kScanOnceHeld = 1ull << 24;           // (256 compute units hold all workgroups at once)
+inline uint64_t scan_once_max(uint64_t mean, bool regular, bool f16) {
+    if (mean > (1ull << 22)) return f16 ? 5ull << 23 : 7ull << 22;
+    if (mean > (1ull << 20)) return 1ull << 26;
+    if (mean > (1ull << 18)) return 3ull << 25;
+    return regular ? 1ull << 28 : 1ull << 27;
 }
 template <int MODE>
 inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, void* out, uint64_t n, uint64_t nseg, uint64_t seg_len,
@@ -783,6 +797,9 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
         a.per_elem = 1.0 / (double)seg_len;
         for (uint32_t i = 0; i < 8; ++i)
             if (i % seg_len == 0) a.pattern |= 1u << i;
+    } else {
+        a.per_elem = (double)(nseg + 1) / (double)n;
+        a.grid_log2 = search_grid_log2(nseg);
     }
     ScanWorkspace dev = {};
     if (local) {
@@ -811,12 +828,20 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
     if (tiles_of(1, 8) <= 2 * units) u = 1;
     else if (tiles_of(2, 16) <= units && 4 * tiles_of(2, 16) > 3 * units) u = 2, w = 16;
     else if (tiles_of(2, 8) <= 3 * units) u = 2;
+    const bool held = n <= kScanOnceHeld;
+    // (irregular: four wavefronts, whose search is the cheaper one from there on; binary16 results only beyond 2^24, n = 2^24
+    // 17.5 / 15.6 / 16.1 us with eight against 17.7 / 15.5 / 17.3)
+    if (offsets != nullptr && n > ((MODE & 2) ? kScanOnceHeld : 12ull << 20)) u = 4, w = 4;
     if (tiles_of(u, w) > limit) u = 4, w = tiles_of(4, 8) > limit ? 16 : 8;
     st = begin_lookback(ws, s, tiles_of(u, w), &dev, capturing);
     if (st != TCR_OK) return st;
+    const dim3 grid((unsigned)tiles_of(u, w)), block(w * kWave);
     if (u == 1) launch_tile_scan<1, 8, MODE, false>(a, dev, s);
     else if (u == 2 && w == 8) launch_tile_scan<2, 8, MODE, false>(a, dev, s);
     else if (u == 2) launch_tile_scan<2, 16, MODE, false>(a, dev, s);
+    else if (w == 4 && held) tile_scan_kernel<4, 4, false, MODE, false><<<grid, block, 0, s>>>(a, dev);
+    else if (w == 4) tile_scan_kernel<4, 4, false, MODE, false, 7><<<grid, block, 0, s>>>(a, dev);
+    else if (w == 8 && offsets == nullptr && !held) tile_scan_kernel<4, 8, true, MODE, false, 6><<<grid, block, 0, s>>>(a, dev);
     else if (w == 8) launch_tile_scan<4, 8, MODE, false>(a, dev, s);
     else launch_tile_scan<4, 16, MODE, false>(a, dev, s);
     st = check_launch("tile_scan_kernel");
@@ -856,17 +881,11 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
     const uint64_t tiles = irregular_tiles(true, n, shape);
     const bool regular = offsets == nullptr;
     // One tile per workgroup with nothing chained: regular segments short enough for a workgroup to add up the open part by
-    // itself, at nearly every size of array (scan_better_chained), and any segments in an array of up to 2^24 elements (256
-    // units).  n = 2^20 / 2^24 / 2^26, us, by ticket and look-back against this: seg_len 1001 8.2 / 27 / 85 against 4.1 / 22.8 /
-    // 74; 100003 8.7 / 28 against 5.1 / 20.4; irregular, lognormal lengths 10.9 / 31.8 against 5.5 / 22.5, seven segments 20 / 40
-    // against 5.3 / 25.3.  The limit of the latter dates from workgroups that took 65536 elements, one per unit; no result
-    // depends on it, and with today's tiles the forms cross later.  n = 2^24 + 8 / 2^20 * 20 / 24 / 32 / 40 / 48 / 64 / 96, us, chained
-    // against this beyond the limit: seven segments 40.7 / 43.2 / 41.7 / 46.5 / 53.4 / 68.7 / 91.1 / 126 against 25.5 / 30.9 / 35.7 /
-    // 45.9 / 60.3 / 83.4 / 111 / 171; lognormal lengths 29.8 / 33.7 / 36.9 / 44.6 / 52.0 / 66.6 / 89.9 / 124 against 23.6 / 28.5 / 33.0 / 41.9 /
-    // 56.1 / 68.4 / 89.9 / 128; segments of 16 34.5 / 38.2 / 42.5 / 50.6 / 61.8 / 79.9 / 101 / 139 against 25.4 / 30.8 / 36.4 / 46.5 / 64.9 /
-    // 75.0 / 98.6 / 143; regular 100003 - / 30.9 / 34.3 / 41.9 / 49.7 / 65.7 / 88.7 / 123 against - / 25.3 / 28.8 / 36.3 / 46.0 / 60.0 / 82.3 / 117.
+    // itself, at nearly every size of array (scan_better_chained), and any segments in an array of up to scan_once_max elements.
+    // n = 2^20 / 2^24 / 2^26, us, by ticket and look-back against this: seg_len 1001 8.2 / 27 / 85 against 4.1 / 22.8 / 74; 100003
+    // 8.7 / 28 / 89 against 5.1 / 20.4 / 80; irregular, lognormal lengths 10.9 / 31.8 / 93 against 5.5 / 21.4 / 86.
     if (shape == 0 && g_variant.formulation == kMfma && (regular ? seg_len >= 2 : g_variant.irregular_scan == 0) &&
-        ((regular && seg_len <= kLocalMax) || n <= (uint64_t)compute_units() * (uint64_t)(kTile * 16 * 8))) {
+        ((regular && seg_len <= kLocalMax) || n <= kScanOnceHeld || n <= scan_once_max(regular ? seg_len : n / nseg, regular, (MODE & 2) != 0))) {
         bool chained = regular && seg_len <= kLocalMax && scan_better_chained(n, seg_len, (MODE & 2) != 0);
         if (chained) {                       // (and the table is there, or can be had)
             Workspace* ws = nullptr;
@@ -893,15 +912,14 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
     ScanWorkspace dev = {};
     st = begin_lookback(ws, s, two_kernels ? 2 * tiles : tiles, &dev, capturing);      // (two kernels: a second table behind the first)
     if (st != TCR_OK) return st;
-    if (fill) {                              // (now that the call is not refused)
-        st = launch_fill_outside<(MODE >> 1)>(offsets, nseg, out, n, shift, s);
-        if (st != TCR_OK) return st;
-    }
     uint64_t* starts = reinterpret_cast<uint64_t*>(ws->partials);
     TileLink* links = reinterpret_cast<TileLink*>(starts + (tiles + 1));
     if (!regular) {
-        irregular_bounds_kernel<<<dim3((unsigned)ceil_div(tiles + 1, kBoundsWaves * kBoundsPerWave)), dim3(kBoundsWaves * kWave), 0, s>>>(
-            offsets, nseg + 1, elems, tiles + 1, shift, starts, nullptr, two_kernels ? links : nullptr);
+        // (with `fill` it also clears what lies outside the segments: a launch of its own for that took 3 us of every call)
+        const uint64_t searching = ceil_div(tiles + 1, kBoundsWaves * kBoundsPerWave), units = (uint64_t)compute_units();
+        const FillOutside outside = {fill ? out : nullptr, n, (MODE >> 1) ? 2u : 4u, (uint32_t)searching};
+        irregular_bounds_kernel<<<dim3((unsigned)(searching + (fill ? units : 0))), dim3(kBoundsWaves * kWave), 0, s>>>(
+            offsets, nseg + 1, elems, tiles + 1, shift, starts, nullptr, two_kernels ? links : nullptr, outside);
         st = check_launch("irregular_bounds_kernel");
         if (st != TCR_OK) return st;
     }
@@ -1001,14 +1019,6 @@ inline uint64_t segments_tiles(uint64_t n) {
     const uint64_t most = ceil_div(tiles, 1ull << 15);
     return even <= 11 ? even : (most > 4 ? most : 4);
 }
-// Distance of the 64 probes with which a workgroup's search starts, as a power of two: they reach four standard deviations of
-// where n / nseg uniform lengths put an entry to either side.
-inline uint32_t segments_grid_log2(uint64_t nseg) {
-    uint32_t log2 = 6;
-    while (log2 < 40 && (64ull << (2 * log2)) < nseg) ++log2;
-    return log2;
-}
-
 inline tcr_status launch_irregular_reduce(const _Float16* in, const uint64_t* offsets, float* out, uint64_t n, uint64_t nseg,
                                           uint64_t seg_len, hipStream_t s, int kind = kSum, float* out2 = nullptr, int shape = -1) {
     const bool untuned = shape < 0 && tuned_id(kTuneIrregular, 0) < 0;
@@ -1034,7 +1044,7 @@ inline tcr_status launch_irregular_reduce(const _Float16* in, const uint64_t* of
             ScanWorkspace dev = {};
             st = begin_lookback(ws, s, ch * wgs, &dev, capturing);
             if (st != TCR_OK) return st;
-            const SegmentsReduce a = {in, offsets, out, out2, n, nseg, shift, (double)(nseg + 1) / (double)n, segments_grid_log2(nseg),
+            const SegmentsReduce a = {in, offsets, out, out2, n, nseg, shift, (double)(nseg + 1) / (double)n, search_grid_log2(nseg),
                                       (uint32_t)group_tiles, g_variant.scan_wait ? kOncePatience : 0u};
             const dim3 grid((unsigned)wgs), block(4 * kWave);
             if (kind == kBoth) segments_reduce_kernel<kBoth><<<grid, block, 0, s>>>(a, dev);

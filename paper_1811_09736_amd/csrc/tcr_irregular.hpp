@@ -149,6 +149,93 @@ __device__ __forceinline__ uint64_t wave_lower_bound(const uint64_t* __restrict_
     return lo;
 }
 
+// Number of entries of the sorted array a[0 .. count) below key, and the last of them (whole wavefront).  64 probes around `guess`
+// -- where the entry lies if the lengths are alike -- on a grid of 2^grid_log2 entries that all workgroups share; what is
+// then left is mostly few enough to be read at once, so a search is two rounds of requests where one over the whole array
+// takes three or four.  `between` is called when the last round's reads have been asked for, then `take` for each of them that
+// is not below key; it says whether it wants the entry.  wanted: how many it did; seen: entries in front of this one are
+// all below key or have been offered to it.
+struct EntryFound {
+    uint64_t below, last, seen;
+    uint32_t wanted;
+};
+template <typename BETWEEN, typename TAKE>
+__device__ __forceinline__ EntryFound find_entry(const uint64_t* __restrict__ a, uint64_t count, uint64_t key, uint64_t guess,
+                                                 uint32_t grid_log2, int lane, BETWEEN between, TAKE take) {
+    constexpr int kLast = 4;                  // entries per lane of the last round
+    uint64_t lo = 0, hi = count;              // a[i] < key for i < lo;  a[i] >= key for i >= hi
+    if (hi > (uint64_t)(kLast * kWave - 2)) {
+        const uint64_t middle = guess >> grid_log2, first = middle > 32 ? middle - 32 : 0;
+        const uint64_t idx = (first + (uint64_t)lane) << grid_log2;
+        const uint64_t probe = a[idx < hi ? idx : 0];
+        const int c = __builtin_popcountll(__ballot(idx < hi && probe < key));
+        if (c > 0) lo = ((first + (uint64_t)(c - 1)) << grid_log2) + 1;
+        const uint64_t above = (first + (uint64_t)c) << grid_log2;
+        if (c < kWave && above < hi) hi = above;
+        while (hi - lo > (uint64_t)(kLast * kWave - 2)) {
+            const uint64_t step = (hi - lo + 63) >> 6;
+            const uint64_t at = lo + step * (uint64_t)(lane + 1) - 1;
+            const uint64_t b = (uint64_t)__builtin_popcountll(__ballot(at < hi && a[at < hi ? at : lo] < key));
+            const uint64_t first_not_below = lo + step * (b + 1) - 1;
+            hi = first_not_below < hi ? first_not_below : hi;
+            lo = lo + step * b;
+        }
+    }
+    const uint64_t from = lo ? lo - 1 : 0, left = count - from;
+    const uint32_t reads = left < (uint64_t)(kLast * kWave) ? (uint32_t)left : (uint32_t)(kLast * kWave);
+    const __amdgpu_buffer_rsrc_t src = make_rsrc(a + from, reads * 8u);
+    uint64_t e[kLast];
+#pragma unroll
+    for (int k = 0; k < kLast; ++k) e[k] = __builtin_bit_cast(uint64_t, __builtin_amdgcn_raw_buffer_load_b64(src, (k * kWave + lane) * 8, 0, 0));
+    __builtin_amdgcn_sched_barrier(0);        // (what is asked for first arrives first)
+    between();
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t below = 0, wanted = 0;
+#pragma unroll
+    for (int k = 0; k < kLast; ++k) {
+        const bool there = (uint32_t)(k * kWave + lane) < reads;
+        below += (uint32_t)__builtin_popcountll(__ballot(there && e[k] < key));
+        wanted += (uint32_t)__builtin_popcountll(__ballot(there && e[k] >= key && take(e[k])));
+    }
+    const uint32_t last = below ? below - 1u : 0u, which = last >> 6;
+    const uint64_t picked = which == 0u ? e[0] : (which == 1u ? e[1] : (which == 2u ? e[2] : e[3]));
+    return {from + below, ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(picked >> 32), (int)(last & 63u)) << 32) |
+                              (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)picked, (int)(last & 63u)),
+            from + reads, wanted};
+}
+
+// Zeros to the positions of [shift, n) outside [offsets[0] + shift, offsets[nseg] + shift), by workgroups 0 .. groups - 1 of 256
+// threads; this thread's workgroup is number `group`.
+template <typename T>
+__device__ __forceinline__ void fill_outside(const uint64_t* __restrict__ offsets, uint64_t nseg, T* __restrict__ out, uint64_t n, uint32_t shift,
+                                             uint64_t group, uint64_t groups) {
+    uint64_t first = offsets[0] + shift, last = offsets[nseg] + shift;
+    if (first > n) first = n;
+    if (last < first) last = first;
+    const uint64_t stride = groups * 256;
+    for (uint64_t i = group * 256 + threadIdx.x + shift; i < n; i += stride) {
+        if (i >= first && i < last) {                     // (jump over the covered part)
+            const uint64_t trips = (last - i + stride - 1) / stride;
+            i += trips * stride;
+            if (i >= n) return;
+        }
+        out[i] = (T)0.0f;
+    }
+}
+template <int F16>
+__global__ __launch_bounds__(256) void fill_outside_kernel(const uint64_t* __restrict__ offsets, uint64_t nseg, void* __restrict__ out,
+                                                           uint64_t n, uint32_t shift) {
+    if constexpr (F16) fill_outside(offsets, nseg, static_cast<_Float16*>(out), n, shift, blockIdx.x, gridDim.x);
+    else fill_outside(offsets, nseg, static_cast<float*>(out), n, shift, blockIdx.x, gridDim.x);
+}
+// The same by the workgroups behind the first `searching` ones of irregular_bounds_kernel (out == nullptr: there are none).
+struct FillOutside {
+    void* out;                    // `shift` elements in front of the caller's array
+    uint64_t n;                   // elements counted from there
+    uint32_t bytes;               // per element: 2 or 4
+    uint32_t searching;
+};
+
 // starts_below[i] = number of entries of offsets[0 .. count) below i * tile_elems, i = 0 .. boundaries - 1;
 // ends_below[i] (optional) = the same for i * tile_elems + 1, i.e. with the entries ON the boundary added,
 // which turns "segment starts in [begin, end)" into "segment ends in (begin, end]".  kBoundsGroup lanes per boundary.
@@ -162,8 +249,16 @@ __global__ __launch_bounds__(kBoundsWaves * kWave) void irregular_bounds_kernel(
                                                                                 uint64_t boundaries, uint32_t shift,
                                                                                 uint64_t* __restrict__ starts_below,
                                                                                 uint64_t* __restrict__ ends_below,
-                                                                                TileLink* __restrict__ links = nullptr) {
+                                                                                TileLink* __restrict__ links = nullptr,
+                                                                                FillOutside fill = {}) {
     constexpr int G = kBoundsGroup;
+    static_assert(kBoundsWaves * kWave == 256, "fill_outside counts workgroups of 256 threads");
+    if (fill.out != nullptr && blockIdx.x >= fill.searching) {
+        const uint64_t group = blockIdx.x - fill.searching, groups = gridDim.x - fill.searching;
+        if (fill.bytes == 2u) fill_outside(offsets, count - 1, static_cast<_Float16*>(fill.out), fill.n, shift, group, groups);
+        else fill_outside(offsets, count - 1, static_cast<float*>(fill.out), fill.n, shift, group, groups);
+        return;
+    }
     const int lane = threadIdx.x & (kWave - 1);
     const int member = lane & (G - 1), first_lane = lane & ~(G - 1);
     const uint64_t wave_first = ((uint64_t)blockIdx.x * kBoundsWaves + (uint64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * kBoundsPerWave;

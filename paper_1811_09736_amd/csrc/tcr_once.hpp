@@ -25,7 +25,8 @@ struct TileScan {
     uint64_t n;                   // elements counted from `in`
     uint64_t nseg;
     uint64_t seg_len;             // regular
-    double per_elem;              // regular: 1 / seg_len
+    double per_elem;              // regular: 1 / seg_len; irregular: (nseg + 1) / n
+    uint32_t grid_log2;           // irregular: distance of a search's first probes among the offsets
     uint32_t magic;               // regular, seg_len <= kLocalMax: ceil(2^32 / seg_len)
     uint32_t pattern;             // regular: bit i set iff i is a multiple of seg_len, i < 8
     uint32_t shift;
@@ -83,22 +84,27 @@ __device__ __forceinline__ float lookup_open_sum(const TileScan& a, const ScanWo
 }
 
 // LOCAL (regular segments of 2 to WAVES * 512 elements): no sum is ever looked up, no workspace.
-// Registers: four sub-tiles per wavefront are held to 64, so that every wavefront slot of a compute unit is taken.  That
-// spills: 10 vector registers, 44 bytes of scratch per lane (exclusive scans 6 and 28), and 44 to 48 scalar ones into
-// lanes.  Without the cap it takes 77 (73), nothing in scratch, and 6 wavefronts per SIMD instead of 8.  us, capped against
-// not, workgroups of 8 wavefronts: n = 2^24, seven segments / lognormal lengths / segments of 16 25.2 / 22.4 / 24.3 against
-// 24.5 / 22.8 / 26.2, binary16 exclusive 17.5 / 15.9 / 17.5 against 18.9 / 18.0 / 18.9; regular 100003 20.4 against 21.5; n = 12 *
-// 2^20 19.8 / 18.4 / 20.5 against 19.0 / 18.0 / 19.8, 13.8 / 14.1 / 14.7 against 13.6 / 13.5 / 14.2.
-template <int U, int WAVES, bool REGULAR, int MODE, bool LOCAL>
-__global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U == 4 ? 8 : 4, 8))) void tile_scan_kernel(TileScan a, ScanWorkspace ws_arg) {
+// FIT: wavefronts per SIMD that the registers are held to.  Four sub-tiles per wavefront take 77 (73 with binary16 exclusive
+// results) and nothing in scratch where they may: 6 wavefronts.  Up to 2^24 elements, where all workgroups run at once, 8 are
+// better in spite of 44 bytes of scratch per lane (7 vector registers to 11, and up to 50 scalar ones into lanes); beyond,
+// workgroups follow each other and 7 (irregular, 16 bytes) or 6 are.  us, FIT = 8 against less: irregular n = 2^24, segments of
+// 16 / lognormal lengths / seven segments 22.9 / 21.4 / 23.2 against 23.6 / 21.9 / 24.2 (7); 2^20 * 24 37.6 / 35.6 / 38.5 against 36.6 / 30.2 /
+// 33.7, 2^26 97.6 / 92.4 / 117 against 93.0 / 85.8 / 115; regular 100003, 2^20 * 24 / 64 / 96 29.8 / 82.4 / 117 against 29.1 / 79.8 / 114 (6).
+// GUIDED (irregular, workgroups of four wavefronts: arrays of more than 12 * 2^20 elements): a tile's entries are found with one
+// search of two rounds around where they are likely to be, not two of four over the whole array (2^24 elements 24.3 / 22.1 / 24.0
+// -> 22.9 / 21.4 / 23.2; in smaller arrays the searches mostly find what they read in a cache: 2^23 16.2 / 14.5 / 15.1 against
+// 15.3 / 14.9 / 15.7).
+template <int U, int WAVES, bool REGULAR, int MODE, bool LOCAL, int FIT = (U == 4 ? 8 : 4)>
+__global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(FIT, 8))) void tile_scan_kernel(TileScan a, ScanWorkspace ws_arg) {
     static_assert(!LOCAL || REGULAR, "");
+    constexpr bool GUIDED = WAVES == 4;       // (irregular: how a tile's entries are found)
     constexpr int EXCL = MODE & 1, F16 = MODE >> 1;
     constexpr uint32_t kChunk = (uint32_t)kTile * U;          // one wavefront's share
     constexpr uint32_t kBlockTile = kChunk * WAVES;           // one workgroup's share
     constexpr uint64_t kBackMax = (uint64_t)kTile * WAVES;    // the open part that the wavefronts add up themselves
     constexpr int kTileLog2 = __builtin_ctz(kBlockTile);
     __shared__ uint32_t s_heads[REGULAR ? 1 : kBlockTile / 32];
-    __shared__ uint64_t s_bound[2];
+    __shared__ uint64_t s_bound[4];
     __shared__ float s_wave_value[WAVES], s_back[WAVES];
     __shared__ uint32_t s_wave_flag[WAVES];
     __shared__ float s_prefix;
@@ -138,27 +144,75 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
         }
     } else {
         for (uint32_t i = threadIdx.x; i < kBlockTile / 32; i += WAVES * kWave) s_heads[i] = 0u;
-        if (wave < 2) {
-            // entry s lies on position offsets[s] + shift
-            const uint64_t edge = tb + (wave ? (uint64_t)kBlockTile : 0);
-            const uint64_t below = wave_lower_bound(a.offsets, a.nseg + 1, edge > a.shift ? edge - a.shift : 0, lane);
-            if (lane == 0) s_bound[wave] = below;
-        }
-        first = a.offsets[0] + a.shift;
-        last = a.offsets[a.nseg] + a.shift;
-        if (last > a.n) last = a.n;
-        __syncthreads();
-        load_share();
-        const uint64_t lo = s_bound[0], hi = s_bound[1];
-        has_heads = lo < hi;
-        for (uint64_t s = lo + threadIdx.x; s < hi; s += (uint64_t)(WAVES * kWave)) {
-            const uint64_t pos = a.offsets[s] + a.shift - tb;
-            if (pos < (uint64_t)kBlockTile) atomicOr(&s_heads[pos >> 5], 1u << (pos & 31u));
-        }
-        // (nothing is open in front of the first entry and behind the last; an entry on tb itself restarts there)
-        if (lo > 0 && lo <= a.nseg) {
-            const uint64_t at = a.offsets[lo - 1] + a.shift;
-            if (at < tb) s0 = at;
+        // entry s lies on position offsets[s] + shift
+        const auto mark = [&](uint64_t entry) {
+            const uint64_t pos = entry + a.shift - tb;
+            const bool in = pos < (uint64_t)kBlockTile;
+            if (in) atomicOr(&s_heads[pos >> 5], 1u << (pos & 31u));
+            return in;
+        };
+        if constexpr (!GUIDED) {
+            if (wave < 2) {
+                const uint64_t edge = tb + (wave ? (uint64_t)kBlockTile : 0);
+                const uint64_t below = wave_lower_bound(a.offsets, a.nseg + 1, edge > a.shift ? edge - a.shift : 0, lane);
+                if (lane == 0) s_bound[wave] = below;
+            }
+            first = a.offsets[0] + a.shift;
+            last = a.offsets[a.nseg] + a.shift;
+            if (last > a.n) last = a.n;
+            __syncthreads();
+            load_share();
+            const uint64_t lo = s_bound[0], hi = s_bound[1];
+            has_heads = lo < hi;
+            for (uint64_t s = lo + threadIdx.x; s < hi; s += (uint64_t)(WAVES * kWave)) mark(a.offsets[s]);
+            // (nothing is open in front of the first entry and behind the last; an entry on tb itself restarts there)
+            if (lo > 0 && lo <= a.nseg) {
+                const uint64_t at = a.offsets[lo - 1] + a.shift;
+                if (at < tb) s0 = at;
+            }
+        } else {
+            // One wavefront finds the entries in front of the tile, the last of them (the start of the segment open there) and, among
+            // those that the search's last round has read, the tile's first ones -- mostly all of them where segments are not
+            // short.  Nothing else is asked for meanwhile: in an array that the chip holds at once all workgroups search at the same
+            // time, and behind everybody's elements every round would wait for them (2^24 elements, seven segments: 24.4 us with
+            // the other wavefronts' elements asked for in front of the search).
+            lds_barrier();                        // (the bits are cleared)
+            if (wave == 0) {
+                const EntryFound found = find_entry(a.offsets, a.nseg + 1, tb > a.shift ? tb - a.shift : 0, (uint64_t)((double)tb * a.per_elem),
+                                                    a.grid_log2, lane, [] {}, mark);
+                if (lane == 0) {
+                    s_bound[0] = found.below;
+                    s_bound[1] = found.last;
+                    s_bound[2] = found.below + found.wanted == found.seen ? found.seen : ~0ull;       // where more may follow
+                    s_bound[3] = found.wanted;
+                }
+            }
+            first = a.offsets[0] + a.shift;
+            last = a.offsets[a.nseg] + a.shift;
+            if (last > a.n) last = a.n;
+            lds_barrier();
+            load_share();
+            const uint64_t lo = s_bound[0], next = s_bound[2];
+            has_heads = s_bound[3] != 0u;
+            // (nothing is open in front of the first entry and behind the last; an entry on tb itself restarts there)
+            if (lo > 0 && lo <= a.nseg && s_bound[1] + a.shift < tb) s0 = s_bound[1] + a.shift;
+            if (next <= a.nseg) {                 // (the same in every wavefront)
+                // 64 entries per wavefront and turn, the first two turns' asked for at once; one that does not fill the turn is the last
+                const uint64_t rest = a.nseg + 1 - next;
+                const uint32_t there = rest < (uint64_t)(2 * WAVES * kWave) ? (uint32_t)rest : (uint32_t)(2 * WAVES * kWave);
+                const __amdgpu_buffer_rsrc_t entries = make_rsrc(a.offsets + next, there * 8u);
+                uint64_t entry[2];
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+                    entry[k] = __builtin_bit_cast(uint64_t, __builtin_amdgcn_raw_buffer_load_b64(entries, (int)((threadIdx.x + (uint32_t)(k * WAVES * kWave)) * 8u), 0, 0));
+                bool filled = true;
+#pragma unroll
+                for (int k = 0; k < 2; ++k) filled = __ballot(threadIdx.x + (uint32_t)(k * WAVES * kWave) < there && mark(entry[k])) == ~0ull;
+                for (uint64_t s = next + threadIdx.x + (uint64_t)(2 * WAVES * kWave); filled; s += (uint64_t)(WAVES * kWave))
+                    filled = __ballot(s <= a.nseg && mark(a.offsets[s])) == ~0ull;
+                has_heads = true;
+                lds_barrier();                    // the heads are marked
+            }
         }
     }
     const uint64_t back = tb - s0;
@@ -169,20 +223,21 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
     const uint64_t back_at = mine ? tb - behind - (uint64_t)kTile : 0;
     const __amdgpu_buffer_rsrc_t back_src = make_rsrc(a.in + back_at, mine ? (uint32_t)kTile * 2u : 0u);
     const half8 back_x = buffer_load8(back_src, 16u * (uint32_t)lane);
-    if constexpr (!REGULAR) __syncthreads();              // the heads are marked
+    if constexpr (!REGULAR && !GUIDED) __syncthreads();   // the heads are marked
 
     if (count != whole) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if ((uint32_t)(kTile * u + 8 * lane) == whole) x[u] = load8_guarded(a.in, base + whole, a.n);
     }
-    uint32_t bits[U];                             // the lane's heads
+    uint32_t heads[(U + 3) / 4] = {};             // the lane's heads: a byte per sub-tile
     uint64_t flag_before[U];                      // bit l: a head in a lane in front of lane l inside the sub-tile
     uint32_t seen_before[U];                      // a head in a sub-tile in front
     float lane_value[U], before[U], run = 0.0f;
     uint32_t chunk_flag = 0u;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
+        uint32_t bits;
         if constexpr (REGULAR) {
             // the lane's first head, counted from its first element (the heads are head, head + seg_len, ...)
             const uint32_t at = (uint32_t)wave * kChunk + (uint32_t)(kTile * u + 8 * lane);
@@ -196,14 +251,15 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
                 while (h < at) h += a.seg_len;
                 c = h - at < 8u ? (uint32_t)(h - at) : 8u;
             }
-            bits[u] = c < 8u ? (a.pattern << c) & 0xffu : 0u;
+            bits = c < 8u ? (a.pattern << c) & 0xffu : 0u;
         } else {
-            bits[u] = has_heads ? (uint32_t)reinterpret_cast<const uint8_t*>(s_heads)[wave * (kChunk / 8) + (kTile / 8) * u + lane] : 0u;
+            bits = has_heads ? (uint32_t)reinterpret_cast<const uint8_t*>(s_heads)[wave * (kChunk / 8) + (kTile / 8) * u + lane] : 0u;
         }
-        uint64_t flags = __ballot(bits[u] != 0u);
+        heads[u / 4] |= bits << (8 * (u % 4));
+        uint64_t flags = __ballot(bits != 0u);
         float v[1] = {0.0f};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[0] = ((bits[u] >> e) & 1u ? 0.0f : v[0]) + (float)x[u][e];
+        for (int e = 0; e < 8; ++e) v[0] = ((bits >> e) & 1u ? 0.0f : v[0]) + (float)x[u][e];
         flags = wave_seg_scan_inclusive_bits<1>(flags, v);
         flag_before[u] = flags << 1;
         const uint32_t sub_flag = (uint32_t)(flags >> 63);
@@ -272,7 +328,7 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
         float p[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float kept = (bits[u] >> e) & 1u ? 0.0f : q;
+            const float kept = (heads[u / 4] >> (8 * (u % 4) + e)) & 1u ? 0.0f : q;
             q = kept + (float)x[u][e];
             p[e] = EXCL ? kept : q;
         }

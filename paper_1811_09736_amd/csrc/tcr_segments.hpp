@@ -189,48 +189,12 @@ __global__ __launch_bounds__(4 * kWave) __attribute__((amdgpu_waves_per_eu(KIND 
         }
     };
     // at_entry: how many entries lie on rb or in front of it; s0: where the last of them, the start of the segment open at
-    // rb, lies
-    uint64_t at_entry = 0, s0 = rb;
-    // 64 entries around where a uniform distribution has it, on a grid that all workgroups share; what is then left is mostly
-    // few enough to be read at once.  (The range's first elements are asked for behind the last round: what is asked for
-    // first arrives first.)
-    constexpr int kLast = 4;
-    const uint64_t key = rb + 1 > a.shift ? rb + 1 - a.shift : 0;
-    uint64_t lo = 0, hi = a.nseg + 1;
-    if (hi > (uint64_t)(kLast * kWave - 2)) {
-        const uint64_t guess = (uint64_t)((double)rb * a.per_elem) >> a.grid_log2;
-        const uint64_t g0 = guess > 32 ? guess - 32 : 0;
-        const uint64_t idx = (g0 + (uint64_t)lane) << a.grid_log2;
-        const uint64_t probe = a.offsets[idx < hi ? idx : 0];
-        const int c = __builtin_popcountll(__ballot(idx < hi && probe < key));
-        if (c > 0) lo = ((g0 + (uint64_t)(c - 1)) << a.grid_log2) + 1;
-        const uint64_t above = (g0 + (uint64_t)c) << a.grid_log2;
-        if (c < kWave && above < hi) hi = above;
-        while (hi - lo > (uint64_t)(kLast * kWave - 2)) {
-            const uint64_t stride = (hi - lo + 63) >> 6;
-            const uint64_t at = lo + stride * (uint64_t)(lane + 1) - 1;
-            const uint64_t b = (uint64_t)__builtin_popcountll(__ballot(at < hi && a.offsets[at < hi ? at : lo] < key));
-            const uint64_t first_not_below = lo + stride * (b + 1) - 1;
-            hi = first_not_below < hi ? first_not_below : hi;
-            lo = lo + stride * b;
-        }
-    }
-    const uint64_t first_read = lo ? lo - 1 : 0, left_of_them = a.nseg + 1 - first_read;
-    const uint32_t reads = left_of_them < (uint64_t)(kLast * kWave) ? (uint32_t)left_of_them : (uint32_t)(kLast * kWave);
-    const __amdgpu_buffer_rsrc_t last_round = make_rsrc(a.offsets + first_read, reads * 8u);
-    uint64_t e[kLast];
-#pragma unroll
-    for (int k = 0; k < kLast; ++k) e[k] = __builtin_bit_cast(uint64_t, __builtin_amdgcn_raw_buffer_load_b64(last_round, (k * kWave + lane) * 8, 0, 0));
-    load_tile(0);
-    uint32_t below = 0;
-#pragma unroll
-    for (int k = 0; k < kLast; ++k) below += (uint32_t)__builtin_popcountll(__ballot((uint32_t)(k * kWave + lane) < reads && e[k] < key));
-    at_entry = first_read + below;
-    const uint32_t last = below ? below - 1u : 0u, which = last >> 6;
-    const uint64_t picked = which == 0u ? e[0] : (which == 1u ? e[1] : (which == 2u ? e[2] : e[3]));
-    if (below)
-        s0 = (((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(picked >> 32), (int)(last & 63u)) << 32) |
-              (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)picked, (int)(last & 63u))) + a.shift;
+    // rb, lies.  (Every wavefront looks for itself: one that looks for all four takes as long.  The range's first elements are
+    // asked for behind the last round: what is asked for first arrives first.)
+    const EntryFound found = find_entry(a.offsets, a.nseg + 1, rb + 1 > a.shift ? rb + 1 - a.shift : 0,
+                                        (uint64_t)((double)rb * a.per_elem), a.grid_log2, lane, [&] { load_tile(0); }, [](uint64_t) { return false; });
+    uint64_t at_entry = found.below;
+    const uint64_t s0 = at_entry ? found.last + a.shift : rb;
     load_entries(at_entry);
     const bool open = at_entry >= 1 && at_entry <= a.nseg && s0 < rb;
     const bool far = open && rb - s0 > (uint64_t)kTileElems;

@@ -1,0 +1,89 @@
+"""Irregular scans of arrays of more than 12 * 2^20 elements, whose tiles find their entries with a search that starts where
+they are likely to be: tiles whose entries the search's last round has read or not, entries far from their share, segments
+that start many tiles in front; and the zeros outside the segments where the look-up kernel of the largest arrays writes
+them.  Whole numbers: exact."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1811_09736_amd import workloads
+
+pytestmark = pytest.mark.gpu
+
+TILE = 8192
+HELD = (12 << 20) + 3 * TILE + 13               # all workgroups at once
+BEYOND = (1 << 24) + 5 * TILE + 3               # workgroups that follow each other; binary16 results too
+
+
+@pytest.fixture(scope="module")
+def tcr():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1811_09736_amd import binding
+    binding.set_variant("reset")
+    binding.tuning_import("")
+    yield binding
+    binding.set_variant("reset")
+    binding.check_device_flags()
+
+
+@pytest.fixture(scope="module")
+def arrays():
+    base = workloads.make_input(BEYOND + 8, "int1", 11)
+    return base, torch.from_numpy(base).cuda()
+
+
+def check(tcr, oracle, x, xd, off, modes=(0,)):
+    off = np.asarray(off, dtype=np.int64)
+    od = torch.from_numpy(off).cuda()
+    for flags in modes:
+        want = oracle.irregular_scan_exclusive(x, off) if flags & tcr.SCAN_EXCLUSIVE else oracle.irregular_scan(x, off)
+        assert np.max(np.abs(want)) <= (2048 if flags & tcr.OUT_F16 else 1 << 24)
+        got = tcr.irregular_scan_ex(xd, od, flags) if flags else tcr.irregular_scan(xd, od)
+        assert np.array_equal(got.cpu().numpy().astype(np.float64), want)         # (0 outside the segments)
+
+
+# the search's last round reads 256 entries, of which the tile's own are marked at once
+@pytest.mark.parametrize("n", [HELD, BEYOND])
+@pytest.mark.parametrize("per_tile", [1, 3, 127, 200, 254, 255, 256, 257, 300, 512, 767, 768, 769, 1500])
+def test_entries_per_tile(tcr, oracle, arrays, n, per_tile):
+    shift = per_tile % 3
+    x, xd = arrays[0][shift:shift + n].copy(), arrays[1][shift:shift + n]
+    ends = np.arange(0, n, TILE)[:, None] + np.round(np.linspace(0, TILE, per_tile, endpoint=False)).astype(np.int64)[None, :]
+    cuts = np.unique(np.minimum(ends.ravel(), n))
+    check(tcr, oracle, x, xd, np.concatenate([cuts[(cuts > 700) & (cuts < n - 9)], [n - 9]]), (0, 1, 2) if per_tile in (3, 257) else (0,))
+
+
+@pytest.mark.parametrize("n", [HELD, BEYOND])
+def test_entries_far_from_their_share(tcr, oracle, arrays, n):
+    x, xd = arrays[0][:n].copy(), arrays[1][:n]
+    few = np.arange(0, 60000, dtype=np.int64)
+    check(tcr, oracle, x, xd, np.concatenate([few, [n]]))
+    check(tcr, oracle, x, xd, np.concatenate([[3], n - 60000 + few, [n]]))
+    check(tcr, oracle, x, xd, np.concatenate([np.zeros(30000, np.int64), np.full(30000, n // 2 + 1), [n - 9]]))
+    check(tcr, oracle, x, xd, np.concatenate([np.full(100000, 2 * TILE), [n]]))
+
+
+@pytest.mark.parametrize("recipe", ["uniform16", "lognormal256", "few7"])
+def test_recipes(tcr, oracle, arrays, recipe):
+    for n in (HELD, BEYOND):
+        x, xd = arrays[0][:n].copy(), arrays[1][:n]
+        check(tcr, oracle, x, xd, workloads.make_offsets(n - 4000, recipe, 3).view(np.int64) + 2000, (0, 1))
+
+
+@pytest.mark.parametrize("flags", [0, 3])
+def test_zeros_outside_the_segments_of_a_large_array(tcr, oracle, flags):
+    n = (5 << 23) + 77                           # chained tiles: seven long segments
+    x = workloads.make_input(n, "int1", 2)
+    xd = torch.from_numpy(x).cuda()
+    for lo, hi in ((0, n), (5, n), (100003, n - 70001), (n // 2, n // 2 + 9), (0, 7)):
+        off = np.sort(np.random.default_rng(lo).integers(lo, hi, 8, endpoint=True))
+        off[0], off[-1] = lo, hi
+        od = torch.from_numpy(off).cuda()
+        torch.full((n,), float("nan"), device="cuda")                              # (what the next allocation may hold)
+        got = tcr.irregular_scan_ex(xd, od, flags) if flags else tcr.irregular_scan(xd, od)
+        got = got.cpu().numpy().astype(np.float64)
+        want = oracle.irregular_scan_exclusive(x, off) if flags else oracle.irregular_scan(x, off)
+        assert not np.any(got[:lo]) and not np.any(got[hi:])
+        if flags == 0 or np.max(np.abs(want)) <= 2048:
+            assert np.array_equal(got[lo:hi], want[lo:hi])
