@@ -77,10 +77,10 @@ __device__ __forceinline__ float lookup_open_sum(const TileScan& a, const ScanWo
             }
             __builtin_amdgcn_s_sleep(1);
         }
-        acc += wave_sum(v);
+        acc += v;
         hi -= span;
     }
-    return acc;
+    return wave_sum(acc);                                // (added per lane first: one chain of roundings of the whole sum's size, not one per look)
 }
 
 // LOCAL (regular segments of 2 to WAVES * 512 elements): no sum is ever looked up, no workspace.
@@ -319,18 +319,30 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(F
     }
     const uint32_t valid_lo = first > base ? (uint32_t)(first - base < kChunk ? first - base : kChunk) : 0u;
     const uint32_t valid_hi = last > base ? (uint32_t)(last - base < kChunk ? last - base : kChunk) : 0u;
+    // LATE: the sum in front may be millions of times an element, and is added once, behind the sums of the tile, not in front of
+    // a lane's eight additions.  Where workgroups follow each other the two more operations per element are free; where all
+    // run at once they cost 5 to 10 % (seven segments in 2^24 elements: 23.5 us, 25.3 with them).
+    constexpr bool LATE = !LOCAL && U == 4 && FIT < 8;
     const bool inside = valid_lo == 0u && valid_hi == kChunk && a.vector_stores != 0u;
     void* const dst = F16 ? static_cast<void*>(static_cast<_Float16*>(a.out) + base) : static_cast<void*>(static_cast<float*>(a.out) + base);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const float into_sub = seen_before[u] ? before[u] : before[u] + ext;
-        float q = __builtin_amdgcn_inverse_ballot_w64(flag_before[u]) ? lane_value[u] : lane_value[u] + into_sub;
+        float carry = !LATE || seen_before[u] ? 0.0f : ext;
+        const float into_sub = LATE || seen_before[u] ? before[u] : before[u] + ext;
+        const bool after_head = __builtin_amdgcn_inverse_ballot_w64(flag_before[u]);
+        float q = after_head ? lane_value[u] : lane_value[u] + into_sub;
+        if constexpr (LATE) carry = after_head ? 0.0f : carry;
         float p[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float kept = (heads[u / 4] >> (8 * (u % 4) + e)) & 1u ? 0.0f : q;
+            const bool head = (heads[u / 4] >> (8 * (u % 4) + e)) & 1u;
+            const float kept = head ? 0.0f : q;
             q = kept + (float)x[u][e];
             p[e] = EXCL ? kept : q;
+            if constexpr (LATE) {
+                carry = head ? 0.0f : carry;
+                p[e] += carry;
+            }
         }
         const uint32_t k = (uint32_t)(kTile * u + 8 * lane);
         if (inside) {

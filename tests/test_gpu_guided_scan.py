@@ -87,3 +87,24 @@ def test_zeros_outside_the_segments_of_a_large_array(tcr, oracle, flags):
         assert not np.any(got[:lo]) and not np.any(got[hi:])
         if flags == 0 or np.max(np.abs(want)) <= 2048:
             assert np.array_equal(got[lo:hi], want[lo:hi])
+
+
+# A float32 rounding is off by at most half a unit of the last place, evenly spread: 2^-24 * sqrt(1/3) of the power of two below
+# the value, rms; relative to values spread evenly over their octave 2^-24 * sqrt(1/3) * sqrt(1/2).  A result of a long segment
+# takes no more than six of its own size (wavefront sum 2 to 3, with the sums of the wavefronts in front, with the element's
+# place, and what the sums of the tiles bring along); eight more would come from a lane that walks its elements on top of it.
+@pytest.mark.parametrize("n,nseg,seg_len", [((1 << 20) * 24, 7, 0), ((1 << 20) * 20 + 77, 40, 0), ((1 << 20) * 24, 0, 100003)])
+def test_roundings_of_long_sums(tcr, n, nseg, seg_len):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    if seg_len:
+        n -= n % seg_len
+        off = torch.arange(0, n + 1, seg_len, device="cuda")
+    else:
+        off = torch.floor(torch.linspace(0, 1, nseg + 1, device="cuda", dtype=torch.float64) ** 1.2 * n).long()
+    x = torch.rand(n, generator=gen, device="cuda").half()
+    got = (tcr.segmented_scan(x, seg_len) if seg_len else tcr.irregular_scan(x, off)).double()
+    sums = torch.cat([torch.zeros(1, device="cuda", dtype=torch.float64), torch.cumsum(x.double(), 0)])
+    want = sums[1:] - torch.repeat_interleave(sums[off[:-1]], off[1:] - off[:-1])
+    error = ((got - want).pow(2).sum() / want.pow(2).sum()).sqrt().item()
+    assert error <= 2.0 ** -24 * (6 / 3 / 2) ** 0.5, error
