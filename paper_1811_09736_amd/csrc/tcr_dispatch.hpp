@@ -289,6 +289,30 @@ inline void launch_reduce_final(const float* partials, float* out, float* out2, 
     else reduce_final_kernel<kFinalThreads><<<grid, dim3(kFinalThreads), 0, s>>>(partials, out, out2, per, nseg * per);
 }
 
+// Partials of one wavefront each that the last workgroup of a segment collects (tcr_reduce.hpp) instead of a second kernel.
+// Several segments: whole workgroups each.  Not on a workspace whose launches a graph has recorded: there the descriptors cost a
+// launch in front of this one, and it would again be two.
+// Up to 2^24 elements, where two launches keep the host longer than one the device (8.6 us at any size up to 2^24; one launch 5.6 to
+// 8.3).  Beyond, the two overlap and the collecting workgroup does not: two against one, n = 2^20 * 24 / 32 / 64 / 128 / 256 11.1 / 13.5 /
+// 23.6 / 44.0 / 81.4 us against 11.2 / 14.5 / 23.9 / 46.0 / 83.6.
+constexpr uint64_t kGatherElemsMax = 1ull << 24;
+inline bool gather_better(const ReducePlan& p, uint64_t n, uint64_t nseg) {
+    return n <= kGatherElemsMax && p.per > 1 && p.combine == 1 && !p.finish && p.span >= (uint64_t)(kGatherTiles * kTile) &&
+           (nseg == 1 || p.per % kGatherWaves == 0);
+}
+template <int FORM>
+inline tcr_status launch_reduce_gather(const _Float16* in, float* out, uint64_t n, const ReducePlan& p, Workspace* ws, hipStream_t s) {
+    ScanWorkspace dev = {};
+    tcr_status st = begin_lookback(ws, s, p.nspans, &dev, false);
+    if (st != TCR_OK) return st;
+    const ReduceGather a = {in, out, n, p.span, (uint32_t)p.per, (uint32_t)p.nspans, g_variant.scan_wait ? kOncePatience : 0u};
+    const dim3 grid((unsigned)ceil_div(p.nspans, (uint64_t)kGatherWaves)), block(kGatherWaves * kWave);
+    reduce_gather_kernel<FORM><<<grid, block, 0, s>>>(a, dev);
+    st = check_launch("reduce_gather_kernel");
+    if (st != TCR_OK) ws->dirty = true;
+    return st;
+}
+
 inline tcr_status reduce_long(const _Float16* in, float* out, uint64_t n, uint64_t seg_len, bool whole, hipStream_t s) {
     ReducePlan p = plan_reduce(n, seg_len, whole);
     const int form = tuned_formulation(kTuneReduce, tuning_class(seg_len, whole));
@@ -311,6 +335,8 @@ inline tcr_status reduce_long(const _Float16* in, float* out, uint64_t n, uint64
                                  : launch_reduce_span<kDpp>(in, dst, n, p.span, p.nspans, p.combine, s, &fin);
         }
     }
+    if (gather_better(p, n, nseg) && !g_variant.reduce_fused && !capturing && !ws->device_managed && table_has_room(ws, p.nspans, capturing))
+        return form == kMfma ? launch_reduce_gather<kMfma>(in, out, n, p, ws, s) : launch_reduce_gather<kDpp>(in, out, n, p, ws, s);
     if (p.per > 1 && g_variant.reduce_fused && nseg * p.per <= kFusedPartialsMax) {
         // one kernel: the workgroup that finishes last adds up the partials
         if (capturing || ws->device_managed) return TCR_ERR_UNSUPPORTED;     // its count base is a kernel argument

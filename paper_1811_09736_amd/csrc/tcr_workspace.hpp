@@ -15,6 +15,7 @@
 #include "../../include/tcr.h"
 #include "tcr_reduce.hpp"
 #include "tcr_scan.hpp"
+#include "tcr_gather.hpp"
 #include "tcr_generic.hpp"
 #include "tcr_irregular.hpp"
 #include "tcr_once.hpp"
