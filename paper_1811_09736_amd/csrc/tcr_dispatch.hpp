@@ -292,8 +292,8 @@ inline void launch_reduce_final(const float* partials, float* out, float* out2, 
 // Partials of one wavefront each that the last workgroup of a segment collects (tcr_reduce.hpp) instead of a second kernel.
 // Several segments: whole workgroups each.  Not on a workspace whose launches a graph has recorded: there the descriptors cost a
 // launch in front of this one, and it would again be two.
-// Up to 2^24 elements, where two launches keep the host longer than one the device (8.6 us at any size up to 2^24; one launch 5.6 to
-// 8.3).  Beyond, the two overlap and the collecting workgroup does not: two against one, n = 2^20 * 24 / 32 / 64 / 128 / 256 11.1 / 13.5 /
+// Up to 2^24 elements, where two launches keep the host longer than one the device (8.9 to 9.4 us at any size up to 2^24; one launch 5.9
+// to 8.1).  Beyond, the two overlap and the collecting workgroup does not: two against one, n = 2^20 * 24 / 32 / 64 / 128 / 256 11.1 / 13.5 /
 // 23.6 / 44.0 / 81.4 us against 11.2 / 14.5 / 23.9 / 46.0 / 83.6.
 constexpr uint64_t kGatherElemsMax = 1ull << 24;
 inline bool gather_better(const ReducePlan& p, uint64_t n, uint64_t nseg) {
@@ -796,6 +796,8 @@ inline void launch_tile_scan(const TileScan& a, const ScanWorkspace& dev, hipStr
 //     seven segments 33.2/22.6   34.7/25.0   39.1/33.9   50.8/53.6   61.5/73.1   86.9/125    110/176
 //     100003, regular 23.4/18.5  25.8/20.9   31.3/26.5   45.2/37.8   55.9/48.2   81.6/74.5   104/96.9    193/187 (8)
 //     3000003        23.8/18.3   27.6/21.8   32.8/29.4   45.2/41.7   58.1/55.8   86.1/86.1   110/113     207/221 (8)
+// (Measured with one shape forced and the sum in front added to every lane's running value.  As it runs, with that sum added once,
+// 16 / lognormal / seven at 24 34.3 / 30.5 / 34.8, 64 94.5 / 82.5 / -, 128 167 / 151 / -; 100003 at 24 / 64 / 128 29.5 / 79.9 / 148.)
 // (a sum over thousands of tiles takes as many looks as there are 64s of them, and every tile waits for its own)
 constexpr uint64_t kScanOnceHeld = 1ull << 24;           // (256 compute units hold all workgroups at once)
 inline uint64_t scan_once_max(uint64_t mean, bool regular, bool f16) {

@@ -7,8 +7,8 @@
 // Bound: memory; at the end one write and one read on the far side of the caches.  Four wavefronts, each with 4
 // descriptors per lane asked for at once: four rounds for 4096 partials (16 at once, or values held from one look to the next, cost
 // the whole kernel its registers: 140 and three wavefronts per SIMD, 2^28 elements 98.9 us).
-// Against reduce_span_kernel with reduce_final_kernel behind, us back to back, full reduction of 2^23 + 3 / 2^20 * 9 / 12 / 16 elements:
-// 8.6 / 8.7 / 8.6 / 8.7 -> 5.6 / 5.9 / 6.7 / 8.3; segments of 2^18 / 2^20 / 2^22, 2^24 in all: 9.2 / 8.8 / 8.9 -> 8.1 / 8.0 / 7.4.
+// Against reduce_span_kernel with reduce_final_kernel behind, us back to back, full reduction of 2^20 * 8.5 / 10 / 12 / 16 elements:
+// 9.2 / 9.1 / 8.9 / 9.0 -> 5.9 / 6.1 / 6.5 / 8.1; segments of 2^18 / 2^20 / 2^22, 2^24 in all: 9.2 / 8.8 / 8.9 -> 8.1 / 7.9 / 7.5.
 #pragma once
 
 #include "tcr_scan.hpp"

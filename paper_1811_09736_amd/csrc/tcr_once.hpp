@@ -86,7 +86,7 @@ __device__ __forceinline__ float lookup_open_sum(const TileScan& a, const ScanWo
 // LOCAL (regular segments of 2 to WAVES * 512 elements): no sum is ever looked up, no workspace.
 // FIT: wavefronts per SIMD that the registers are held to.  Four sub-tiles per wavefront take 77 (73 with binary16 exclusive
 // results) and nothing in scratch where they may: 6 wavefronts.  Up to 2^24 elements, where all workgroups run at once, 8 are
-// better in spite of 44 bytes of scratch per lane (7 vector registers to 11, and up to 50 scalar ones into lanes); beyond,
+// better in spite of 44 or 48 bytes of scratch per lane (7 vector registers to 11, and up to 50 scalar ones into lanes); beyond,
 // workgroups follow each other and 7 (irregular, 16 bytes) or 6 are.  us, FIT = 8 against less: irregular n = 2^24, segments of
 // 16 / lognormal lengths / seven segments 22.9 / 21.4 / 23.2 against 23.6 / 21.9 / 24.2 (7); 2^20 * 24 37.6 / 35.6 / 38.5 against 36.6 / 30.2 /
 // 33.7, 2^26 97.6 / 92.4 / 117 against 93.0 / 85.8 / 115; regular 100003, 2^20 * 24 / 64 / 96 29.8 / 82.4 / 117 against 29.1 / 79.8 / 114 (6).
