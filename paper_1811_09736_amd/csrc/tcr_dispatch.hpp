@@ -779,32 +779,41 @@ inline void launch_tile_scan(const TileScan& a, const ScanWorkspace& dev, hipStr
     if (LOCAL || a.offsets == nullptr) tile_scan_kernel<U, W, true, MODE, LOCAL><<<grid, block, 0, s>>>(a, dev);
     else if constexpr (!LOCAL) tile_scan_kernel<U, W, false, MODE, false><<<grid, block, 0, s>>>(a, dev);
 }
-// The largest array that runs this way when its sums are looked up, by the (mean) length of its segments.  n in 2^20 elements,
-// us, chained tiles (irregular: with a look-up kernel in front, a second kernel behind where most tiles have no start)
-// against this:
+// The largest array that runs this way when its sums are looked up.  n in 2^20 elements, us, chained tiles (irregular: with a look-up
+// kernel in front, a second kernel behind where most tiles have no start) against this.
+// Regular segments, by their length:
 //   binary32     n = 20          24          32          48          64          96          128         256
-//     16, irregular  40.4/28.8   46.7/36.6   59.6/47.6   84.0/73.3   105/93.0    143/129     180/166
-//     lognormal      36.0/26.1   39.5/30.2   52.9/43.9   71.3/63.3   92.6/85.8   127/122     162/159
-//     seven segments 40.8/29.7   43.5/33.7   52.8/52.6   70.7/83.0   93.9/115    128/179     162/245
-//     100003, regular 31.3/25.4  34.6/29.1   48.0/40.4   66.7/58.1   89.3/79.8   123/114     157/148     294/289 (FIT = 8)
-//     300003         31.5/25.9   35.5/29.6   47.4/41.1   68.2/60.3   91.2/82.6   126/119     161/155
-//     1000003        32.3/26.1   36.7/30.8   47.3/43.0   69.7/65.0   93.1/89.2   130/129     166/170
-//     3000003        31.3/25.6   36.9/30.8   47.8/43.5   66.1/62.5   93.2/91.3   131/134     168/177     319/356 (8)
-//   binary16, exclusive (regular: inclusive)
-//     16, irregular  32.5/22.1   35.9/25.0   44.1/32.6   60.4/46.6   73.7/61.5   102/87.3    128/112
-//     lognormal      28.1/20.1   30.8/23.0   36.1/27.8   50.2/40.9   60.6/51.4   86.6/78.8   110/102
-//     seven segments 33.2/22.6   34.7/25.0   39.1/33.9   50.8/53.6   61.5/73.1   86.9/125    110/176
-//     100003, regular 23.4/18.5  25.8/20.9   31.3/26.5   45.2/37.8   55.9/48.2   81.6/74.5   104/96.9    193/187 (8)
-//     3000003        23.8/18.3   27.6/21.8   32.8/29.4   45.2/41.7   58.1/55.8   86.1/86.1   110/113     207/221 (8)
-// (Measured with one shape forced and the sum in front added to every lane's running value.  As it runs, with that sum added once,
-// 16 / lognormal / seven at 24 34.3 / 30.5 / 34.8, 64 94.5 / 82.5 / -, 128 167 / 151 / -; 100003 at 24 / 64 / 128 29.5 / 79.9 / 148.)
-// (a sum over thousands of tiles takes as many looks as there are 64s of them, and every tile waits for its own)
+//     100003       31.3/25.4   34.6/29.1   48.0/40.4   66.7/58.1   89.3/79.8   123/114     157/148     294/289 (FIT = 8)
+//     300003       31.5/25.9   35.5/29.6   47.4/41.1   68.2/60.3   91.2/82.6   126/119     161/155
+//     1000003      32.3/26.1   36.7/30.8   47.3/43.0   69.7/65.0   93.1/89.2   130/129     166/170
+//     3000003      31.3/25.6   36.9/30.8   47.8/43.5   66.1/62.5   93.2/91.3   131/134     168/177     319/356 (8)
+//   binary16
+//     100003       23.4/18.5   25.8/20.9   31.3/26.5   45.2/37.8   55.9/48.2   81.6/74.5   104/96.9    193/187 (8)
+//     3000003      23.8/18.3   27.6/21.8   32.8/29.4   45.2/41.7   58.1/55.8   86.1/86.1   110/113     207/221 (8)
+// (Measured with one shape forced and the sum in front added to every lane's running value; as it runs, with that sum added once,
+// 100003 at 24 / 64 / 128 29.5 / 79.9 / 148.)
+// A sum over thousands of tiles takes looks in proportion, and every tile waits for its own.  Irregular segments may be short on
+// average and one of them most of the array, so for these the limit is where that case crosses, whatever the number of segments:
+//   binary32        n = 16.5        20          24          28          32
+//     16              37.2/23.6   39.8/28.5   44.3/33.4   48.6/37.6   52.3/42.9
+//     lognormal       33.5/22.7   35.7/26.3   39.4/30.4   43.3/33.8   46.9/37.2
+//     seven segments  38.3/27.6   40.8/31.7   43.4/36.5   46.3/41.2   48.5/48.7
+//     one segment     38.4/30.0   40.8/34.6   43.3/40.6   46.4/46.1   48.9/54.1
+//     and 1023 empty  35.5/30.8   39.4/35.5   43.4/41.3   48.3/46.9   52.0/55.2
+//   binary16, exclusive
+//     16              30.7/19.1   32.0/22.4   35.4/25.8   38.8/27.8   40.9/31.2
+//     seven segments  31.2/20.8   32.9/23.4   34.6/26.5   36.6/30.1   38.6/35.5
+//     one segment     31.8/22.2   33.4/25.8   35.0/29.3   36.9/33.5   38.7/40.4
+//     and 1023 empty  28.4/23.5   31.2/26.3   34.2/30.4   36.8/34.5   39.2/42.2
+// (2^26, with the sums looked up by one wavefront of four: 16 / lognormal / one segment and 1023 empty 103/93.0 / 91.5/84.7 / 101/166;
+// 2^27 180/167 / 160/157 / 163/445.)
 constexpr uint64_t kScanOnceHeld = 1ull << 24;           // (256 compute units hold all workgroups at once)
-inline uint64_t scan_once_max(uint64_t mean, bool regular, bool f16) {
-    if (mean > (1ull << 22)) return f16 ? 5ull << 23 : 7ull << 22;
-    if (mean > (1ull << 20)) return 1ull << 26;
-    if (mean > (1ull << 18)) return 3ull << 25;
-    return regular ? 1ull << 28 : 1ull << 27;
+constexpr uint64_t kIrregularOnceMax = 7ull << 22;
+inline uint64_t scan_once_max(uint64_t seg_len, bool f16) {
+    if (seg_len > (1ull << 22)) return f16 ? 5ull << 23 : 7ull << 22;
+    if (seg_len > (1ull << 20)) return 1ull << 26;
+    if (seg_len > (1ull << 18)) return 3ull << 25;
+    return 1ull << 28;
 }
 template <int MODE>
 inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, void* out, uint64_t n, uint64_t nseg, uint64_t seg_len,
@@ -857,9 +866,10 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
     else if (tiles_of(2, 16) <= units && 4 * tiles_of(2, 16) > 3 * units) u = 2, w = 16;
     else if (tiles_of(2, 8) <= 3 * units) u = 2;
     const bool held = n <= kScanOnceHeld;
-    // (irregular: four wavefronts, whose search is the cheaper one from there on; binary16 results only beyond 2^24, n = 2^24
-    // 17.5 / 15.6 / 16.1 us with eight against 17.7 / 15.5 / 17.3)
-    if (offsets != nullptr && n > ((MODE & 2) ? kScanOnceHeld : 12ull << 20)) u = 4, w = 4;
+    // (irregular: four wavefronts, whose search is the cheaper one where workgroups follow each other.  Up to 2^24 elements only with
+    // segments of 16: one segment and 1023 empty ones / 2^20 segments of 16 in front of one / segments of 16, 12.5 * 2^20 and 2^24
+    // elements 21.4 / 23.3 / 21.1 and 24.6 / 24.6 / 22.8 us with eight, 23.9 / 25.3 / 19.8 and 27.5 / 28.7 / 22.8 with four)
+    if (offsets != nullptr && !held) u = 4, w = 4;
     if (tiles_of(u, w) > limit) u = 4, w = tiles_of(4, 8) > limit ? 16 : 8;
     st = begin_lookback(ws, s, tiles_of(u, w), &dev, capturing);
     if (st != TCR_OK) return st;
@@ -867,7 +877,6 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
     if (u == 1) launch_tile_scan<1, 8, MODE, false>(a, dev, s);
     else if (u == 2 && w == 8) launch_tile_scan<2, 8, MODE, false>(a, dev, s);
     else if (u == 2) launch_tile_scan<2, 16, MODE, false>(a, dev, s);
-    else if (w == 4 && held) tile_scan_kernel<4, 4, false, MODE, false><<<grid, block, 0, s>>>(a, dev);
     else if (w == 4) tile_scan_kernel<4, 4, false, MODE, false, 7><<<grid, block, 0, s>>>(a, dev);
     else if (w == 8 && offsets == nullptr && !held) tile_scan_kernel<4, 8, true, MODE, false, 6><<<grid, block, 0, s>>>(a, dev);
     else if (w == 8) launch_tile_scan<4, 8, MODE, false>(a, dev, s);
@@ -909,11 +918,11 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
     const uint64_t tiles = irregular_tiles(true, n, shape);
     const bool regular = offsets == nullptr;
     // One tile per workgroup with nothing chained: regular segments short enough for a workgroup to add up the open part by
-    // itself, at nearly every size of array (scan_better_chained), and any segments in an array of up to scan_once_max elements.
-    // n = 2^20 / 2^24 / 2^26, us, by ticket and look-back against this: seg_len 1001 8.2 / 27 / 85 against 4.1 / 22.8 / 74; 100003
-    // 8.7 / 28 / 89 against 5.1 / 20.4 / 80; irregular, lognormal lengths 10.9 / 31.8 / 93 against 5.5 / 21.4 / 86.
+    // itself, at nearly every size of array (scan_better_chained), and any segments in an array of up to scan_once_max or
+    // kIrregularOnceMax elements.  n = 2^20 / 2^24 / 2^26, us, by ticket and look-back against this: seg_len 1001 8.2 / 27 / 85 against
+    // 4.1 / 22.8 / 74; 100003 8.7 / 28 / 89 against 5.1 / 20.4 / 80; irregular, lognormal lengths 10.9 / 31.8 against 5.5 / 21.4.
     if (shape == 0 && g_variant.formulation == kMfma && (regular ? seg_len >= 2 : g_variant.irregular_scan == 0) &&
-        ((regular && seg_len <= kLocalMax) || n <= kScanOnceHeld || n <= scan_once_max(regular ? seg_len : n / nseg, regular, (MODE & 2) != 0))) {
+        ((regular && seg_len <= kLocalMax) || n <= kScanOnceHeld || n <= (regular ? scan_once_max(seg_len, (MODE & 2) != 0) : kIrregularOnceMax))) {
         bool chained = regular && seg_len <= kLocalMax && scan_better_chained(n, seg_len, (MODE & 2) != 0);
         if (chained) {                       // (and the table is there, or can be had)
             Workspace* ws = nullptr;

@@ -44,12 +44,16 @@ __device__ __forceinline__ float masked_tile_sum(half8 x, uint64_t at, uint64_t 
     return read_lane(row_sum_to_last<16>(mfma(const_ones(), kept, splat(0.0f))[0]), 15);
 }
 
-// The sum from position s0 to the start of `tile` out of what the tiles in between have published (whole wavefront).
-__device__ __forceinline__ float lookup_open_sum(const TileScan& a, const ScanWorkspace& ws, uint32_t tile, uint64_t s0, int tile_log2, int lane) {
+// The sum from position s0 to the start of `tile` out of what the tiles in between have published: number `looker` of LOOKERS
+// wavefronts that take turns at 64 of them, the nearest first.
+template <int LOOKERS>
+__device__ __forceinline__ float lookup_open_sum(const TileScan& a, const ScanWorkspace& ws, uint32_t tile, uint64_t s0, int tile_log2, int looker,
+                                                 int lane) {
     const uint32_t first = (uint32_t)(s0 >> tile_log2);
     const uint32_t want = ws.epoch * 4u + kStatusAggregate;
     float acc = 0.0f;
-    for (uint32_t hi = tile; hi > first;) {
+    const uint32_t skipped = 64u * (uint32_t)looker;
+    for (uint32_t hi = tile - first > skipped ? tile - skipped : first; hi > first;) {
         const uint32_t span = hi - first > 64u ? 64u : hi - first;
         bool need = (uint32_t)lane < span;
         float v = 0.0f;
@@ -78,26 +82,28 @@ __device__ __forceinline__ float lookup_open_sum(const TileScan& a, const ScanWo
             __builtin_amdgcn_s_sleep(1);
         }
         acc += v;
-        hi -= span;
+        if constexpr (LOOKERS == 1) hi -= span;
+        else hi = hi - first > 64u * LOOKERS ? hi - 64u * LOOKERS : first;
     }
     return wave_sum(acc);                                // (added per lane first: one chain of roundings of the whole sum's size, not one per look)
 }
 
 // LOCAL (regular segments of 2 to WAVES * 512 elements): no sum is ever looked up, no workspace.
-// FIT: wavefronts per SIMD that the registers are held to.  Four sub-tiles per wavefront take 77 (73 with binary16 exclusive
-// results) and nothing in scratch where they may: 6 wavefronts.  Up to 2^24 elements, where all workgroups run at once, 8 are
-// better in spite of 44 or 48 bytes of scratch per lane (7 vector registers to 11, and up to 50 scalar ones into lanes); beyond,
-// workgroups follow each other and 7 (irregular, 16 bytes) or 6 are.  us, FIT = 8 against less: irregular n = 2^24, segments of
-// 16 / lognormal lengths / seven segments 22.9 / 21.4 / 23.2 against 23.6 / 21.9 / 24.2 (7); 2^20 * 24 37.6 / 35.6 / 38.5 against 36.6 / 30.2 /
-// 33.7, 2^26 97.6 / 92.4 / 117 against 93.0 / 85.8 / 115; regular 100003, 2^20 * 24 / 64 / 96 29.8 / 82.4 / 117 against 29.1 / 79.8 / 114 (6).
-// GUIDED (irregular, workgroups of four wavefronts: arrays of more than 12 * 2^20 elements): a tile's entries are found with one
-// search of two rounds around where they are likely to be, not two of four over the whole array (2^24 elements 24.3 / 22.1 / 24.0
-// -> 22.9 / 21.4 / 23.2; in smaller arrays the searches mostly find what they read in a cache: 2^23 16.2 / 14.5 / 15.1 against
-// 15.3 / 14.9 / 15.7).
+// FIT: wavefronts per SIMD that the registers are held to.  Four sub-tiles per wavefront take 77 (73 with exclusive results) and
+// nothing in scratch where they may: 6 wavefronts.  Up to 2^24 elements, where all workgroups run at once, 8 are better in
+// spite of 44 (28) bytes of scratch per lane and 44 to 51 scalar registers in lanes; beyond, workgroups follow each other and
+// 7 (irregular, 16 bytes or none) or 6 are.  us, FIT = 8 against less: 2^20 * 24 elements in segments of 16 / lognormal lengths /
+// seven segments 37.6 / 35.6 / 38.5 against 36.6 / 30.2 / 33.7 (7); regular 100003, 2^20 * 24 / 64 / 96 29.8 / 82.4 / 117 against
+// 29.1 / 79.8 / 114 (6).
+// GUIDED (irregular, workgroups of four wavefronts: where they follow each other): a tile's entries are found with one search of two
+// rounds around where they are likely to be, not two of four over the whole array, and all four wavefronts take turns at what is
+// looked up (16.5 * 2^20 / 2^20 * 24 / 2^20 * 28 elements, one segment and 1023 empty ones: by one of them 30.4 / 43.3 / 50.5 us, by all
+// 30.8 / 41.3 / 46.9; binary16 exclusive 25.7 / 35.3 / 41.7 and 23.5 / 30.4 / 34.5).
 template <int U, int WAVES, bool REGULAR, int MODE, bool LOCAL, int FIT = (U == 4 ? 8 : 4)>
 __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(FIT, 8))) void tile_scan_kernel(TileScan a, ScanWorkspace ws_arg) {
     static_assert(!LOCAL || REGULAR, "");
-    constexpr bool GUIDED = WAVES == 4;       // (irregular: how a tile's entries are found)
+    constexpr bool GUIDED = !REGULAR && WAVES == 4;           // (how a tile's entries are found)
+    constexpr int LOOKERS = GUIDED ? WAVES : 1;
     constexpr int EXCL = MODE & 1, F16 = MODE >> 1;
     constexpr uint32_t kChunk = (uint32_t)kTile * U;          // one wavefront's share
     constexpr uint32_t kBlockTile = kChunk * WAVES;           // one workgroup's share
@@ -105,9 +111,8 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(F
     constexpr int kTileLog2 = __builtin_ctz(kBlockTile);
     __shared__ uint32_t s_heads[REGULAR ? 1 : kBlockTile / 32];
     __shared__ uint64_t s_bound[4];
-    __shared__ float s_wave_value[WAVES], s_back[WAVES];
+    __shared__ float s_wave_value[WAVES], s_back[WAVES];      // (s_back: parts of the open sum, added up or looked up)
     __shared__ uint32_t s_wave_flag[WAVES];
-    __shared__ float s_prefix;
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -301,9 +306,15 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(F
                 if (tile == 0 && ws.state != nullptr && !ws.device_managed) ws.state[0] = ws.epoch;
                 __hip_atomic_store(&ws.desc[tile], pack_desc(ws.epoch, kStatusAggregate, total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
+            if (LOOKERS == 1 && far) {
+                const float pre = lookup_open_sum<1>(a, ws, tile, s0, kTileLog2, 0, lane);
+                if (lane == 0) s_back[0] = pre;
+            }
+        }
+        if constexpr (LOOKERS > 1) {
             if (far) {
-                const float pre = lookup_open_sum(a, ws, tile, s0, kTileLog2, lane);
-                if (lane == 0) s_prefix = pre;
+                const float pre = lookup_open_sum<LOOKERS>(a, ws, tile, s0, kTileLog2, wave, lane);
+                if (lane == 0) s_back[wave] = pre;
             }
         }
         if (far) __syncthreads();
@@ -319,14 +330,14 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(F
         }
     }
     if (open && back != 0) {
-        if (far) {
-            ext += s_prefix;
+        float sum = 0.0f;
+        if constexpr (LOOKERS > 1) {
+            sum = pairwise_sum(s_back);           // (sums over thousands of tiles; one after the other 5.3e-8 -> 5.6e-8 off for seven segments)
         } else {
-            float sum = 0.0f;
 #pragma unroll
             for (int v = 0; v < WAVES; ++v) sum += s_back[v];
-            ext += sum;
         }
+        ext += sum;
     }
     const uint32_t valid_lo = first > base ? (uint32_t)(first - base < kChunk ? first - base : kChunk) : 0u;
     const uint32_t valid_hi = last > base ? (uint32_t)(last - base < kChunk ? last - base : kChunk) : 0u;

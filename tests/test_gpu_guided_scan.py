@@ -1,5 +1,5 @@
-"""Irregular scans of arrays of more than 12 * 2^20 elements, whose tiles find their entries with a search that starts where
-they are likely to be: tiles whose entries the search's last round has read or not, entries far from their share, segments
+"""Irregular scans of arrays of more than 2^24 elements, whose tiles find their entries with a search that starts where
+they are likely to be (and of smaller ones, which search the whole array): tiles whose entries the search's last round has read or not, entries far from their share, segments
 that start many tiles in front; and the zeros outside the segments where the look-up kernel of the largest arrays writes
 them.  Whole numbers: exact."""
 import numpy as np
@@ -11,8 +11,8 @@ from paper_1811_09736_amd import workloads
 pytestmark = pytest.mark.gpu
 
 TILE = 8192
-HELD = (12 << 20) + 3 * TILE + 13               # all workgroups at once
-BEYOND = (1 << 24) + 5 * TILE + 3               # workgroups that follow each other; binary16 results too
+HELD = (12 << 20) + 3 * TILE + 13               # all workgroups at once: the other search
+BEYOND = (1 << 24) + 5 * TILE + 3               # workgroups that follow each other
 
 
 @pytest.fixture(scope="module")
