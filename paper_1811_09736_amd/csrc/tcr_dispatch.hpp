@@ -807,8 +807,9 @@ inline void launch_tile_scan(const TileScan& a, const ScanWorkspace& dev, hipStr
 //     and 1023 empty  28.4/23.5   31.2/26.3   34.2/30.4   36.8/34.5   39.2/42.2
 // (2^26, with the sums looked up by one wavefront of four: 16 / lognormal / one segment and 1023 empty 103/93.0 / 91.5/84.7 / 101/166;
 // 2^27 180/167 / 160/157 / 163/445.)
-constexpr uint64_t kScanOnceHeld = 1ull << 24;           // (256 compute units hold all workgroups at once)
 constexpr uint64_t kIrregularOnceMax = 7ull << 22;
+// Up to here the compute units hold all workgroups at once (256 units: 2^24 elements).
+inline uint64_t scan_held_max() { return (uint64_t)compute_units() * (uint64_t)(kTile * 16 * 8); }
 inline uint64_t scan_once_max(uint64_t seg_len, bool f16) {
     if (seg_len > (1ull << 22)) return f16 ? 5ull << 23 : 7ull << 22;
     if (seg_len > (1ull << 20)) return 1ull << 26;
@@ -865,7 +866,7 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
     if (tiles_of(1, 8) <= 2 * units) u = 1;
     else if (tiles_of(2, 16) <= units && 4 * tiles_of(2, 16) > 3 * units) u = 2, w = 16;
     else if (tiles_of(2, 8) <= 3 * units) u = 2;
-    const bool held = n <= kScanOnceHeld;
+    const bool held = n <= scan_held_max();
     // (irregular: four wavefronts, whose search is the cheaper one where workgroups follow each other.  Up to 2^24 elements only with
     // segments of 16: one segment and 1023 empty ones / 2^20 segments of 16 in front of one / segments of 16, 12.5 * 2^20 and 2^24
     // elements 21.4 / 23.3 / 21.1 and 24.6 / 24.6 / 22.8 us with eight, 23.9 / 25.3 / 19.8 and 27.5 / 28.7 / 22.8 with four)
@@ -922,7 +923,7 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
     // kIrregularOnceMax elements.  n = 2^20 / 2^24 / 2^26, us, by ticket and look-back against this: seg_len 1001 8.2 / 27 / 85 against
     // 4.1 / 22.8 / 74; 100003 8.7 / 28 / 89 against 5.1 / 20.4 / 80; irregular, lognormal lengths 10.9 / 31.8 against 5.5 / 21.4.
     if (shape == 0 && g_variant.formulation == kMfma && (regular ? seg_len >= 2 : g_variant.irregular_scan == 0) &&
-        ((regular && seg_len <= kLocalMax) || n <= kScanOnceHeld || n <= (regular ? scan_once_max(seg_len, (MODE & 2) != 0) : kIrregularOnceMax))) {
+        ((regular && seg_len <= kLocalMax) || n <= scan_held_max() || n <= (regular ? scan_once_max(seg_len, (MODE & 2) != 0) : kIrregularOnceMax))) {
         bool chained = regular && seg_len <= kLocalMax && scan_better_chained(n, seg_len, (MODE & 2) != 0);
         if (chained) {                       // (and the table is there, or can be had)
             Workspace* ws = nullptr;
