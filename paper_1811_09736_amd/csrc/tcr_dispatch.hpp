@@ -922,31 +922,35 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
     // itself, at nearly every size of array (scan_better_chained), and any segments in an array of up to scan_once_max or
     // kIrregularOnceMax elements.  n = 2^20 / 2^24 / 2^26, us, by ticket and look-back against this: seg_len 1001 8.2 / 27 / 85 against
     // 4.1 / 22.8 / 74; 100003 8.7 / 28 / 89 against 5.1 / 20.4 / 80; irregular, lognormal lengths 10.9 / 31.8 against 5.5 / 21.4.
-    if (shape == 0 && g_variant.formulation == kMfma && (regular ? seg_len >= 2 : g_variant.irregular_scan == 0) &&
-        ((regular && seg_len <= kLocalMax) || n <= scan_held_max() || n <= (regular ? scan_once_max(seg_len, (MODE & 2) != 0) : kIrregularOnceMax))) {
-        bool chained = regular && seg_len <= kLocalMax && scan_better_chained(n, seg_len, (MODE & 2) != 0);
-        if (chained) {                       // (and the table is there, or can be had)
-            Workspace* ws = nullptr;
-            bool capturing = false;
-            const tcr_status st = get_workspace(s, &ws, &capturing);
-            if (st != TCR_OK) return st;
-            chained = table_has_room(ws, tiles, capturing);
-        }
-        if (!chained) return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, s);
-    }
+    const bool local = regular && seg_len <= kLocalMax, held = n <= scan_held_max();
+    const bool chained = local && scan_better_chained(n, seg_len, (MODE & 2) != 0);
+    const bool once = shape == 0 && g_variant.formulation == kMfma && (regular ? seg_len >= 2 : g_variant.irregular_scan == 0) &&
+                      (local || held || n <= (regular ? scan_once_max(seg_len, (MODE & 2) != 0) : kIrregularOnceMax));
+    if (once && !chained && (local || held)) return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, s);
     Workspace* ws = nullptr;
     bool capturing = false;
     tcr_status st = get_workspace(s, &ws, &capturing);
     if (st != TCR_OK) return st;
-    if (!regular) {
-        st = ensure_partials(ws, s, 2 * irregular_words(true, n, shape), capturing);
-        if (st != TCR_OK) return st;
-    }
     // Long segments -- fewer segments than a quarter of the tiles, so most tiles hold no segment start: the
     // pipelined chain scans the tiles without a start, a second kernel the others.  (Default tile shape, 16-byte
     // aligned arrays.)
     const bool two_kernels = !regular && shape == 0 && shift == 0 && vector_stores != 0 && g_variant.formulation == kMfma &&
                              g_variant.irregular_scan != 1 && (g_variant.irregular_scan == 2 || nseg <= tiles / 4);
+    if (once && chained) {                   // (and the table is there, or can be had)
+        if (!table_has_room(ws, tiles, capturing)) return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, s);
+    } else if (once) {
+        // Without room for a descriptor per tile: chained tiles, as long as there is room for those.  The larger tiles of this form are
+        // faster (seven segments in 2^20 * 24 elements 37.6 us against 42.2), but add a lane's elements to the sum in front (8.0e-8 off
+        // against 7.0e-8).
+        const uint64_t limit = ws->caller_owned || capturing ? ws->desc_capacity : ~0ull;
+        const bool room = ceil_div(n, (uint64_t)(kTile * 4 * (regular ? 8 : 4))) <= limit;
+        const bool room_chained = (two_kernels ? 2 * tiles : tiles) <= limit && (regular || 2 * irregular_words(true, n, shape) <= partials_limit(ws, capturing));
+        if (room || !room_chained) return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, s);
+    }
+    if (!regular) {
+        st = ensure_partials(ws, s, 2 * irregular_words(true, n, shape), capturing);
+        if (st != TCR_OK) return st;
+    }
     ScanWorkspace dev = {};
     st = begin_lookback(ws, s, two_kernels ? 2 * tiles : tiles, &dev, capturing);      // (two kernels: a second table behind the first)
     if (st != TCR_OK) return st;
