@@ -275,7 +275,7 @@ tcr_status tcr_tuning_import(const char *text);
  * 4 = irregular_reduce, 5 = irregular_scan (seg_len is ignored).  For fixed tiles, irregular and <regular>, the
  * kernels that work on any array are named whatever its size: smaller arrays need fewer (their tiles search the offsets
  * and add what reaches them themselves, so neither irregular_bounds_kernel nor irregular_finish_kernel is launched),
- * irregular sums and moments of most arrays above 2^22 elements are segments_reduce_kernel alone unless they are
+ * irregular sums and moments of most arrays above 2^23 elements are segments_reduce_kernel alone unless they are
  * recorded into a graph, scans of smaller arrays and of regular segments of up to 8192 elements are tile_scan_kernel, and
  * sums over segments of thousands of tiles are irregular_groups_kernel and irregular_carry_kernel.
  * reduce_span_kernel<...,wave>+reduce_final_kernel is reduce_gather_kernel alone up to 2^24 elements, unless recorded.

@@ -1026,40 +1026,64 @@ inline tcr_status launch_irregular_reduce_shape(const IrregularReduce& a, const 
     return check_launch("irregular_reduce_kernel");
 }
 
-// Irregular reductions by workgroups that walk ranges of tiles (tcr_segments.hpp), where that is the faster form.  us, tiles
-// of their own (one launch up to 2^24 or 2^25 elements, three beyond) against ranges, by the mean length of a segment:
-//   sums          n = 2^20 *     4           8           16          32          64          128
-//     2                      16.0/17.0   25.9/27.1   46.5/41.1   94.0/77.0   165/142     305/243
-//     8                       8.7/9.1    12.6/12.7   21.2/18.8   37.0/29.6   54.0/50.4   96.8/98.5
-//     16                      7.5/7.4    11.1/9.4    17.2/13.3   29.2/21.6   43.6/36.2   72.3/66.0
-//     64                      6.9/7.3     9.6/9.7    14.4/13.4   25.2/21.5   38.0/37.0   62.3/64.7
-//     256                     6.9/7.2     8.9/9.2    13.5/12.0   23.6/18.8   35.8/33.4   59.4/57.7
-//     1024                    6.8/7.5     8.4/9.6    12.1/12.7   21.2/19.8   31.6/32.6   53.2/54.5
-//     16384                   6.9/7.2     8.1/8.7    10.5/11.5   17.7/16.6   28.2/28.7   47.3/49.1
-//     262144                  7.0/6.6     7.0/7.6     9.8/9.9    15.6/14.8   27.4/25.8   46.9/44.7
-//   lognormal lengths (1892)  6.8/7.7     8.6/9.7    11.8/12.8   19.6/19.1   29.4/31.4   50.2/53.4
-//   both moments
-//     8                      10.4/9.8    14.8/14.0   27.5/21.2   44.4/33.9   71.4/56.7   134/111
-//     16                      8.5/8.1    12.8/10.3   22.9/14.8   37.1/24.2   57.9/40.2   100/72.2
-//     256                     8.5/8.2    10.3/9.6    18.8/12.9   30.6/20.6   50.1/35.6   87.2/62.9
-//     16384                   8.3/8.1     9.6/9.5    14.2/12.5   21.4/18.2   32.2/31.2   55.4/53.1
-// (2^28 elements, segments of 16 / lognormal / seven: sums 137 / 90 / 88 against 140 / 96 / 81, both moments 195 / 115 / 90 against
-// 154 / 103 / 84.)  With segments of a thousand elements a tile has a handful of ends, and each is a chain of its own.
-inline bool segments_better(uint64_t n, uint64_t nseg, int kind) {
-    if (n <= (1ull << 22)) return false;
-    if (kind == kBoth) return true;
-    const uint64_t mean = n / nseg;
-    if (mean >= (1ull << 15)) return n > (1ull << 24);
-    if (mean >= 384) return n > (1ull << 24) && n <= (1ull << 25);
-    return n > (mean < 8 ? 1ull << 23 : 1ull << 22) && n <= (1ull << 27);
+// Irregular reductions by workgroups that walk ranges of tiles (tcr_segments.hpp).
+// Tiles per workgroup: one while that makes no more than five workgroups per compute unit, two up to ten tiles per unit, then what makes
+// four workgroups per unit, up to 11 tiles; four in larger arrays, and no more than 2^15 workgroups.  us, segments of 16 on average, one / two
+// tiles: 2^20 * 7 / 8 / 9 / 12 elements 8.1 / 8.8, 9.1 / 8.8, 9.3 / 8.9, 12.4 / 9.8; two / three, 14 10.9 / 11.7, 16 12.3 / 12.0; 48 by 7 / 8 29.3 /
+// 28.0; 64 by 4 / 6 / 8 / 9 / 11 / 14 37.3 / 40.5 / 37.9 / 36.5 / 36.4 / 40.6; 128 by 4 / 6 / 8 / 11 66.4 / 67.0 / 67.0 / 72.6.
+// Segments of fewer than 8 elements keep their tile busy for so long that workgroups without any wait for the others: one tile up to
+// seven workgroups per unit, sums no more than four.  Half the array in segments of one element and half in one segment, 2^20 * 8 / 32 / 64
+// elements, by one / two / four / eleven tiles 27.1 / 39.1, - / 65.1 / 82.5, - / 115 / 126 / 194.
+inline uint64_t segments_tiles(uint64_t n, uint64_t mean, int kind) {
+    const uint64_t tiles = ceil_div(n, kSegmentsTile), units = (uint64_t)compute_units();
+    if (tiles <= (mean < 8 ? 7 : 5) * units) return 1;
+    const uint64_t most = ceil_div(tiles, 1ull << 15), even = tiles <= 10 * units ? 2 : ceil_div(tiles, 4 * units);
+    return even <= (mean < 8 && kind == kSum ? 4 : 11) ? even : (most > 4 ? most : 4);
 }
-// Tiles per workgroup: what makes four workgroups per compute unit, up to 11; four in larger arrays (64M elements in segments of
-// 16, us: 4 / 6 / 8 / 9 / 11 / 14 tiles 37.3 / 40.5 / 37.9 / 36.5 / 36.4 / 40.6; 80M 44.5 / 44.8 / 43.8 / 43.0 / 44.4 / 44.5; 128M 66.4 / 67.0 / 67.0 / - /
-// 72.6 / 71.7), and no more than 2^15 workgroups.
-inline uint64_t segments_tiles(uint64_t n) {
-    const uint64_t tiles = ceil_div(n, kSegmentsTile), even = ceil_div(tiles, 4 * (uint64_t)compute_units());
-    const uint64_t most = ceil_div(tiles, 1ull << 15);
-    return even <= 11 ? even : (most > 4 ? most : 4);
+// Where that is the faster form, by the mean length of a segment: us, tiles of their own (one launch up to 2^24 or 2^25 elements, on
+// workgroups of eight wavefronts up to 2^23; three beyond) against ranges:
+//   sums      n = 2^20 *  5          8          9          12         16         24         32         64         96         128
+//     2                 19.6/18.3  25.3/23.3  33.0/23.1  38.3/30.0  46.3/40.8  67.9/52.3  81.5/64.8  164/124    233/178    302/235
+//     4                 11.5/12.8  15.0/16.5  20.1/17.1  23.9/20.7  29.8/26.6  43.9/33.6  52.6/41.6  85.3/69.1  128/106    174/143
+//     8                 8.9/8.7    10.7/11.7  13.2/12.4  15.7/14.1  19.8/18.0  29.2/22.6  36.0/29.4  53.9/48.1  72.6/66.3  89.4/84.2
+//     12                8.0/8.7    -          11.3/11.6  -          15.8/17.0  (faster from 2^24 on)
+//     16                7.8/7.3    9.5/8.8    11.1/8.9   12.4/9.8   14.8/12.0  22.7/16.3  28.3/21.2  43.5/36.6  57.9/51.5  72.3/66.2
+//     32                7.4/7.1    8.7/8.6    10.4/8.6   11.5/9.3   13.8/11.3  19.7/13.9  25.2/18.9  39.3/34.6  53.0/49.9  66.3/64.3
+//     64                7.1/7.6    8.5/9.6    9.7/9.7    10.9/10.4  12.8/12.9  18.8/15.6  23.6/20.7  37.0/36.0  49.5/51.0  62.1/65.3
+//     256               7.0/7.2    8.1/8.8    9.4/8.8    10.7/9.4   12.5/11.6  17.6/14.0  22.0/18.4  33.6/30.1  45.5/44.8  57.9/58.1
+//     1024              6.8/7.4    7.6/9.2    8.5/9.2    9.7/9.9    11.2/12.4  16.4/15.0  20.1/19.5  30.1/31.7  40.3/42.7  50.8/54.4
+//     16384             6.8/7.5    7.3/8.3    7.4/8.4    8.4/9.3    9.6/10.9   13.8/12.8  16.8/16.2  27.1/25.9  37.4/38.3  46.4/48.9
+//     262144            6.7/6.5    6.8/7.4    6.8/7.2    8.2/7.8    8.8/9.1    11.9/11.0  14.8/14.0  26.4/24.1  36.0/33.8  45.8/43.4
+//     lognormal (1892)  6.8/7.3    7.8/9.5    8.3/9.5    9.3/10.2   10.8/12.6  15.9/15.7  18.8/19.6  28.3/31.6  37.9/41.9  47.3/53.1
+//   both moments
+//     2                 22.6/21.1  28.0/26.4  35.8/26.2  51.2/34.1  60.9/47.0  84.3/60.5  107/86.6   231/160    340/224    450/291
+//     4                 14.0/15.0  18.2/19.1  23.8/19.5  32.8/23.6  39.3/30.8  54.4/38.7  66.2/53.6  115/90.9   196/130    257/174
+//     8                 10.4/9.8   12.9/13.3  16.3/14.1  22.5/16.1  27.1/21.1  37.9/26.0  44.3/34.3  70.5/56.0  97.2/77.3  125/99.8
+//     16                9.0/7.9    10.9/9.6   13.0/9.8   17.9/11.0  21.3/14.0  30.7/18.2  36.9/24.3  57.5/40.3  78.6/56.6  99.0/73.1
+//     64                8.1/8.3    9.9/10.7   11.5/10.8  14.7/11.8  18.3/15.1  25.5/18.6  30.3/24.9  51.0/42.0  70.5/58.4  89.0/74.7
+//     256               8.2/7.9    9.5/9.3    11.2/9.3   14.2/10.2  17.7/12.7  24.9/15.4  29.3/20.3  47.5/33.7  66.2/49.9  85.6/64.2
+//     1024              8.3/7.9    9.0/9.6    9.9/9.7    13.2/10.7  15.7/13.2  22.1/16.4  25.7/21.4  40.8/35.0  55.9/47.9  71.3/61.3
+//     16384             8.2/8.2    8.8/9.2    9.1/9.4    11.0/10.3  13.4/12.3  18.1/14.3  20.8/18.5  31.5/27.9  42.8/42.7  54.1/54.3
+//     262144            7.9/7.8    8.2/8.2    8.2/8.1    9.4/8.8    11.6/10.5  16.0/12.3  18.4/16.0  27.7/25.6  39.0/37.1  46.9/46.3
+//     lognormal (1892)  8.1/8.4    9.4/10.1   10.1/10.4  12.6/11.3  15.1/13.8  20.1/16.6  23.2/21.6  35.7/34.1  48.4/46.0  61.0/58.4
+// With segments of a thousand elements a tile has a handful of ends, and each is a chain of its own; below 14 (512 entries a tile) it
+// takes more than one batch of entries.  2^20 segments of 16 at the end of an array that one segment fills (a mean of 32 up to 2^23
+// elements): sums at 2^20 * 5 / 8 elements 6.9 / 8.0 against 7.9 / 9.3, both moments at 7 9.0 against 9.6.
+inline bool segments_better(uint64_t n, uint64_t nseg, int kind) {
+    const uint64_t mean = n / nseg;
+    const auto from = [mean](uint64_t lo, uint64_t hi) { return mean >= lo && mean < hi; };
+    if (n <= (1ull << 22)) return false;
+    if (n <= (1ull << 23)) {
+        if (from(14, 28)) return true;
+        if (segments_tiles(n, mean, kind) != 1) return false;
+        return from(8, 10) || (kind == kBoth && (from(0, 3) || from(96, 1500) || mean >= (1ull << 17)));
+    }
+    if (kind == kBoth) return n > (21ull << 19) || mean < 512 || mean >= (1ull << 17);
+    if (mean >= (1ull << 15)) return n > (mean >= (1ull << 17) ? 1ull << 24 : 5ull << 22);
+    if (mean >= 384) return n > (5ull << 22) && n <= (3ull << 23);
+    if (mean >= 192) return n <= (3ull << 25);
+    if (mean >= 64) return n > (21ull << 19) && n <= (5ull << 24);
+    return n > (from(10, 14) ? 1ull << 24 : 1ull << 23) && n <= (1ull << 27);
 }
 inline tcr_status launch_irregular_reduce(const _Float16* in, const uint64_t* offsets, float* out, uint64_t n, uint64_t nseg,
                                           uint64_t seg_len, hipStream_t s, int kind = kSum, float* out2 = nullptr, int shape = -1) {
@@ -1081,7 +1105,7 @@ inline tcr_status launch_irregular_reduce(const _Float16* in, const uint64_t* of
     st = ensure_partials(ws, s, 2 * (words + (far ? ch * groups : 0)), capturing);
     if (st != TCR_OK) return st;
     if (offsets != nullptr && shape == 0 && segments_better(n, nseg, kind)) {
-        const uint64_t group_tiles = segments_tiles(n), wgs = ceil_div(n, group_tiles * kSegmentsTile);
+        const uint64_t group_tiles = segments_tiles(n, n / nseg, kind), wgs = ceil_div(n, group_tiles * kSegmentsTile);
         if (table_has_room(ws, ch * wgs, capturing)) {
             ScanWorkspace dev = {};
             st = begin_lookback(ws, s, ch * wgs, &dev, capturing);

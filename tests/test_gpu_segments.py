@@ -1,4 +1,4 @@
-"""Irregular sums and moments by workgroups that walk ranges of tiles (arrays of more than 2^22 elements): numbers of segments
+"""Irregular sums and moments by workgroups that walk ranges of tiles (most arrays of more than 2^23 elements): numbers of segments
 per tile around the limits between the ways in which a tile is shared out, batches of entries that end with a tile or
 just behind it, segments around the edges of groups, tiles and ranges, parts added from elements and from published sums
 (waited for or not), entries far from where their number alone would put them.  Whole numbers: exact; fractional ones the
@@ -12,8 +12,8 @@ from paper_1811_09736_amd import workloads
 pytestmark = pytest.mark.gpu
 
 TILE = 6144
-N = (1 << 22) + 3 * TILE + 5                    # (two tiles per range from 1025 tiles on: see BIG)
-BIG = (1 << 24) + 4099                          # three tiles per range
+N = (21 << 19) + 3 * TILE + 5                   # two tiles per range; moments of any segments, sums of up to 383 elements each
+BIG = (5 << 22) + 4099                          # four tiles per range; sums of any segments as well
 
 
 @pytest.fixture(scope="module")
@@ -49,6 +49,15 @@ def test_segments_per_tile(tcr, oracle, per_tile, shift):
     check(tcr, oracle, x, xd, np.concatenate([[0], np.sort(np.minimum((ends + jitter).ravel(), N)), [N, N, N]]))
 
 
+# one tile per range: segments of 14 to 27 elements, and moments of one or two, from 2^22 elements on
+@pytest.mark.parametrize("length", [1, 2, 15, 27])
+def test_one_tile_per_range(tcr, oracle, length):
+    n = (1 << 22) + 3 * TILE + 5
+    x = workloads.make_input(n, "int1", length)
+    off = np.sort(np.random.default_rng(length).integers(0, n, n // length))
+    check(tcr, oracle, x, torch.from_numpy(x).cuda(), np.concatenate([[0], off, [n]]))
+
+
 @pytest.mark.parametrize("wait", ["bounded", "none"])
 @pytest.mark.parametrize("n", [N, BIG])
 def test_parts_in_front_of_a_range(tcr, oracle, n, wait):
@@ -78,7 +87,7 @@ def test_entries_far_from_their_share(tcr, oracle):
 
 @pytest.mark.parametrize("recipe", ["uniform16", "lognormal256", "few7"])
 def test_rounding_and_repetition(tcr, oracle, recipe):
-    n = (1 << 24) + 77                           # (every mean length takes this way here)
+    n = (5 << 22) + 77                           # (every mean length takes this way here)
     x = workloads.make_input(n, "normal", 3)
     xd = torch.from_numpy(x).cuda()
     off = workloads.make_offsets(n, recipe, 3).view(np.int64)
@@ -90,7 +99,7 @@ def test_rounding_and_repetition(tcr, oracle, recipe):
     tcr.set_variant("reset")
     for r in results[1:]:
         assert all(torch.equal(a, b) for a, b in zip(r, results[0]))
-    # additions in a row: 8 in a group, 12 groups of a lane, 6 across lanes, 4 wavefronts, 3 tiles; then 16 published sums in a
+    # additions in a row: 8 in a group, 12 groups of a lane, 6 across lanes, 4 wavefronts, 4 tiles; then 16 published sums in a
     # lane, 6 across lanes, 4 wavefronts and the one that joins the parts
     bound = 64 * 2.0 ** -24 * oracle.irregular_reduce(np.abs(x), off) + 1e-30
     for got in results[0][:2]:

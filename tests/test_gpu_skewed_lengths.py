@@ -138,3 +138,23 @@ def test_recorded_with_other_offsets(tcr, oracle, n):
     torch.cuda.synchronize()
     del graph
     tcr.release_stream(side)
+
+
+# Sums and moments at the upper end of the arrays that tiles of their own on workgroups of eight wavefronts are for (the tuner's third
+# shape): segments of 64 on average, and half of the array in segments of one element.  No slower than that form.
+@pytest.mark.parametrize("kind,mix", [("sum", "64"), ("sum", "halves"), ("moments", "64"), ("moments", "halves")])
+def test_time_of_reductions_around_two_to_the_23(tcr, kind, mix):
+    n = 1 << 23
+    x = torch.ones(n, dtype=torch.float16, device="cuda")
+    off = (torch.from_numpy(np.sort(np.random.default_rng(1).integers(0, n, n // 64))).cuda() if mix == "64"
+           else torch.cat([torch.arange(0, n // 2 + 1, device="cuda"), torch.tensor([n], device="cuda")]))
+
+    def calls():
+        for _ in range(30):
+            tcr.irregular_reduce(x, off) if kind == "sum" else tcr.irregular_moments(x, off)
+
+    took = milliseconds(calls)
+    tcr.tuning_import("irregular:0=2;")
+    other = milliseconds(calls)
+    tcr.tuning_import("")
+    assert took <= 1.07 * other, (took, other)
