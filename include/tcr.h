@@ -302,8 +302,8 @@ tcr_status tcr_check_device_flags(void *stream);
  * tcr_set_workspace: from now on every call on the CURRENT device uses [dev_ptr, dev_ptr + bytes) instead of
  *   library-owned memory, whatever its stream, and allocates nothing; a call that needs more returns
  *   TCR_ERR_WORKSPACE.  dev_ptr: device memory, 256-byte aligned, at least 768 bytes, contents arbitrary (the
- *   first call that chains tiles synchronises its stream once and clears it); it stays the caller's and must
- *   outlive the calls that use it.  One buffer serves one stream at a time: calls that use it must be ordered
+ *   first call that passes sums between workgroups synchronises its stream once and clears it); it stays the
+ *   caller's and must outlive the calls that use it, and graphs recorded with it.  One buffer serves one stream at a time: calls that use it must be ordered
  *   by their streams or by the caller.  dev_ptr == NULL returns the device to library-owned workspaces.
  *   TCR_ERR_INVALID_ARG for a misaligned or too small buffer.
  */

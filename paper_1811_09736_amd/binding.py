@@ -344,13 +344,28 @@ def workspace_bytes(op: int, n: int, seg_len: int) -> int:
     return int(_lib.tcr_workspace_bytes(op, n, seg_len))
 
 
-# The tensors in use as workspaces, by device: every call on the device writes there, so they are kept until replaced.
+# The tensors in use as workspaces, by device: every call on the device writes there, so they are kept until replaced; and those
+# that were replaced while a graph was recorded, when nothing can be waited for.
 _workspaces = {}
+_replaced_in_capture = []
+
+
+def _keep_workspace(index: int, buffer: Optional[torch.Tensor]) -> None:
+    old = _workspaces.pop(index, None)
+    if buffer is not None:
+        _workspaces[index] = buffer
+    if old is None or old is buffer:
+        return
+    if torch.cuda.is_current_stream_capturing():
+        _replaced_in_capture.append(old)
+    else:
+        torch.cuda.synchronize(index)        # (calls on any stream may still write to the tensor that is now given up)
 
 
 def set_workspace(buffer: Optional[torch.Tensor]) -> None:
     """tcr_set_workspace: use `buffer` (any contiguous CUDA tensor) on its device, or return the current device to
-    library-owned workspaces with None."""
+    library-owned workspaces with None.  The tensor is kept until it is replaced, and then until the device has finished what
+    runs.  A graph that was recorded with it writes to it at every replay: keep the tensor as long as such a graph."""
     if buffer is None:
         st = _lib.tcr_set_workspace(None, 0)
     else:
@@ -360,11 +375,10 @@ def set_workspace(buffer: Optional[torch.Tensor]) -> None:
             st = _lib.tcr_set_workspace(buffer.data_ptr(), buffer.numel() * buffer.element_size())
     if st != OK:
         raise TcrError(st, "tcr_set_workspace")
-    if buffer is None:
-        if _workspaces:                      # (without a device there are none)
-            _workspaces.pop(torch.cuda.current_device(), None)
-    else:
-        _workspaces[buffer.get_device()] = buffer
+    if buffer is not None:
+        _keep_workspace(buffer.get_device(), buffer)
+    elif _workspaces:                        # (without a device there are none)
+        _keep_workspace(torch.cuda.current_device(), None)
 
 
 def set_variant(key: str, value: str = "") -> None:
