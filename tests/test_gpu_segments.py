@@ -106,3 +106,57 @@ def test_rounding_and_repetition(tcr, oracle, recipe):
         assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - oracle.irregular_reduce(x, off)) <= bound)
     want = oracle.irregular_moments(x, off)[1]
     assert np.all(np.abs(results[0][2].cpu().numpy().astype(np.float64) - want) <= 64 * 2.0 ** -24 * want + 1e-30)
+
+
+def exact_moments(x, off):
+    """Sums and sums of squares of non-empty segments in 64 bits, each from its own elements alone."""
+    starts, ends = off[:-1], off[1:]
+    with np.errstate(invalid="ignore"):
+        v = np.append(x.astype(np.float64), 0.0)
+        cut = np.stack([starts, ends], 1).ravel()
+        return np.add.reduceat(v, cut)[::2], np.add.reduceat(v * v, cut)[::2]
+
+
+def check_special(tcr, x, off):
+    xd, od = torch.from_numpy(x).cuda(), torch.from_numpy(off).cuda()
+    wa, wq = exact_moments(x, off)
+    a, q = tcr.irregular_moments(xd, od)
+    for got, want in ((tcr.irregular_reduce(xd, od), wa), (a, wa), (q, wq)):
+        assert np.array_equal(got.cpu().numpy().astype(np.float64), want, equal_nan=True)
+
+
+# lengths of a tile's segments in each of the ways in which it is shared out: a wavefront, eight lanes and one lane each (and longer
+# ones among them by eight lanes and by the whole wavefront)
+MIXES = {"few": (1500, 9001), "some": (100, 500), "many": (9, 40), "mixed": (2, 3, 5, 130, 700, 11)}
+
+
+def cuts(mix, n, first):
+    lengths = np.random.default_rng(len(mix)).choice(MIXES[mix], n // min(MIXES[mix]))
+    off = first + np.concatenate([[0], np.cumsum(lengths)])
+    return off[off <= n - 5].astype(np.int64)
+
+
+@pytest.mark.parametrize("mix", list(MIXES))
+def test_subnormal_elements(tcr, mix):
+    # every other segment holds binary16 subnormals, k * 2^-24: the sums are whole multiples of 2^-24 (2^-48) below 2^24 of them
+    off = cuts(mix, BIG, 3)
+    x = np.ones(BIG, dtype=np.float16)
+    rng = np.random.default_rng(2)
+    small = (rng.integers(-6, 7, BIG) * 2.0 ** -24).astype(np.float16)
+    which = np.repeat(np.arange(off.size - 1) % 2 == 0, np.diff(off))
+    x[off[0]:off[-1]][which] = small[off[0]:off[-1]][which]
+    assert np.count_nonzero((x != 0) & (np.abs(x) < 2.0 ** -14)) > BIG // 4
+    check_special(tcr, x, off)
+
+
+@pytest.mark.parametrize("mix", list(MIXES))
+def test_infinities_and_nan_stay_in_their_segments(tcr, mix):
+    off = cuts(mix, BIG, 3)
+    x = np.random.default_rng(3).integers(-2, 3, BIG).astype(np.float16)
+    x[:off[0]] = np.nan                                        # (outside the segments)
+    x[off[-1]:] = np.inf
+    special = np.array([np.inf, -np.inf, np.nan], dtype=np.float16)
+    hit = np.arange(1, off.size - 1, 3)                        # the neighbours on both sides stay finite
+    x[off[hit]] = special[hit % 3]                             # its first element; its last one
+    x[off[hit + 1] - 1] = special[(hit // 3) % 3]
+    check_special(tcr, x, off)
