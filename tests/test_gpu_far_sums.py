@@ -1,5 +1,6 @@
-"""Irregular reductions over segments of thousands of tiles: the sums of 64 tiles combined first, the last group ragged, on a
-caller's workspace that has room for the combined sums and on one that has not, and recorded.  Whole numbers: exact."""
+"""Irregular reductions over segments of thousands of tiles: eagerly, on a caller's workspace, and recorded, where the sums of 64 tiles
+are combined first -- or not, on a workspace without room for the combined sums or with segments that are not as long.  Whole
+numbers: exact."""
 import numpy as np
 import pytest
 import torch
@@ -43,7 +44,7 @@ def check(tcr, data, shift, n, off):
         assert torch.equal(a.double(), want) and torch.equal(q.double(), wq)
 
 
-@pytest.mark.parametrize("tiles", [4096, 4097, 4097 + 63, 8192, 12288 + 64, 12400])      # one launch, then single and far sums
+@pytest.mark.parametrize("tiles", [4096, 4097, 4097 + 63, 8192, 12288 + 64, 12400])      # ranges of tiles; unaligned regular ones: one launch, then far sums
 def test_long_segments(tcr, data, tiles):
     n = tiles * TILE - 11
     mid = (tiles // 2) * TILE
@@ -87,3 +88,48 @@ def test_small_workspaces_and_graphs(tcr, data):
         graph.replay()
         torch.cuda.synchronize()
         assert float(out) == sign * float(sums[n] - sums[3])
+
+
+# recorded on a stream that nothing else has been recorded on, so with a look-up kernel in front and kernels behind: combined sums
+# (one and two segments; a ragged last group), single ones (a hundred segments; no room for the combined sums)
+@pytest.mark.parametrize("tiles,nseg,room", [(4097, 1, True), (8200, 2, True), (12400, 1, True), (8200, 100, True), (4100, 1, False), (8200, 2, False),
+                                             (1600, 3, True)])
+def test_recorded_sums_and_moments(tcr, data, tiles, nseg, room):
+    x, sums, squares = data
+    n = tiles * TILE - 11
+    words = 2 * (tiles + 1) + 3 * tiles
+    off = np.sort(np.random.default_rng(tiles).integers(0, n, nseg + 1, endpoint=True))
+    off[0], off[-1] = 7, n - 3
+    od = torch.from_numpy(off).cuda()
+    want, wq = (c[od[1:]] - c[od[:-1]] for c in (sums, squares))
+    xd = x[:n].clone()
+    side = torch.cuda.Stream()
+    out = torch.empty(nseg, device="cuda")
+    torch.cuda.synchronize()
+    if not room:
+        tcr.set_workspace(torch.full((256 + 2 * ((8 * words + 255) // 256 * 256),), 0x55, dtype=torch.uint8, device="cuda"))
+    try:
+        with torch.cuda.stream(side):
+            tcr.irregular_reduce(xd, od, out=out)
+            tcr.irregular_moments(xd, od)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            tcr.irregular_reduce(xd, od, out=out)
+            a, q = tcr.irregular_moments(xd, od)
+        for sign in (-1.0, 1.0, -1.0):
+            xd.copy_(x[:n] * sign)
+            for t in (out, a, q):
+                t.fill_(float("nan"))
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out.double(), sign * want) and torch.equal(a.double(), sign * want) and torch.equal(q.double(), wq)
+            with torch.cuda.stream(side):
+                eager = tcr.irregular_reduce(xd, od)
+            side.synchronize()
+            assert torch.equal(eager, out)
+        del graph
+    finally:
+        torch.cuda.synchronize()
+        tcr.set_workspace(None)

@@ -8,7 +8,11 @@ from paper_1811_09736_amd import workloads
 
 pytestmark = pytest.mark.gpu
 
-N, LARGE = (1 << 20) + 8192 * 5, 1 << 24         # the scan that is recorded; arrays of 2048 tiles and more
+# the scan that is recorded; an array whose sums publish one per tile of 8192 elements; one whose moments publish two per range of
+# four tiles of 6144, more than twice as many
+N, LARGE, HUGE = (1 << 20) + 8192 * 5, 1 << 24, 72 << 20
+SUMS, MOMENTS = LARGE // 8192, 2 * (HUGE // (4 * 6144))
+assert 1024 < SUMS <= 2048 < MOMENTS
 
 
 @pytest.fixture(scope="module")
@@ -26,7 +30,15 @@ def tcr():
 def large(oracle):
     x = workloads.make_input(LARGE, "int1", 5)
     off = workloads.make_offsets(LARGE, "few7", 2).view(np.int64)
-    return (torch.from_numpy(x).cuda(), torch.from_numpy(off).cuda(), oracle.irregular_moments(x, off))
+    return (torch.from_numpy(x).cuda(), torch.from_numpy(off).cuda(), oracle.irregular_reduce(x, off))
+
+
+@pytest.fixture(scope="module")
+def huge():
+    # a one in eight zeros: moments of any segment are whole numbers below 2^24
+    x = torch.zeros(HUGE, dtype=torch.float16, device="cuda")
+    x[::8] = 1.0
+    return x, torch.tensor([0, 24, 1 << 25, HUGE], device="cuda"), np.array([3.0, (1 << 22) - 3, (HUGE - (1 << 25)) / 8])
 
 
 def same(t, want):
@@ -34,8 +46,9 @@ def same(t, want):
 
 
 @pytest.mark.parametrize("again", [False, True])
-def test_eager_reductions_outgrow_the_table_of_a_recorded_scan(tcr, oracle, large, again):
-    xl, od, (sums, squares) = large
+def test_eager_reductions_outgrow_the_table_of_a_recorded_scan(tcr, oracle, large, huge, again):
+    xl, od, sums = large
+    xh, oh, counts = huge
     inputs = [workloads.make_input(N, "int4", (31, k)) for k in range(3)]
     refs = [oracle.scan(h) for h in inputs]
     x = torch.from_numpy(inputs[0]).cuda()
@@ -63,11 +76,11 @@ def test_eager_reductions_outgrow_the_table_of_a_recorded_scan(tcr, oracle, larg
     graph = record(out)
     for k in (1, 2):
         replay(graph, out, k)
-    with torch.cuda.stream(side):                              # 2048 sums, then twice as many: two larger tables
+    with torch.cuda.stream(side):                              # SUMS, then MOMENTS: two larger tables
         assert same(tcr.irregular_reduce(xl, od), sums)
-        a, q = tcr.irregular_moments(xl, od)
+        a, q = tcr.irregular_moments(xh, oh)
     torch.cuda.synchronize()
-    assert same(a, sums) and same(q, squares)
+    assert same(a, counts) and same(q, counts)
     later = record(second) if again else None                  # the new table is recorded, too
     for k in (0, 1, 2, 0):
         replay(graph, out, k)
@@ -84,13 +97,12 @@ def test_eager_reductions_outgrow_the_table_of_a_recorded_scan(tcr, oracle, larg
     tcr.release_stream(other)
 
 
-def test_a_scan_and_moments_outgrow_tables_with_recorded_scans(tcr, oracle):
+def test_a_scan_and_moments_outgrow_tables_with_recorded_scans(tcr, oracle, huge):
     n = 1 << 18
     side = torch.cuda.Stream()
     x = torch.from_numpy(workloads.make_input(n, "int4", 3)).cuda()
     big = torch.ones((1 << 25) + 100003, dtype=torch.float16, device="cuda")
-    off = torch.tensor([0, 3, 1 << 23, 1 << 24], dtype=torch.int64, device="cuda")
-    lengths = np.array([3.0, (1 << 23) - 3, 1 << 23])
+    xh, oh, counts = huge
 
     def nothing():
         return True
@@ -98,9 +110,9 @@ def test_a_scan_and_moments_outgrow_tables_with_recorded_scans(tcr, oracle):
     def scan():                                                # 1028 tiles
         return float(tcr.scan(big)[(1 << 24) - 1]) == float(1 << 24)
 
-    def moments():                                             # 4096 sums
-        a, q = tcr.irregular_moments(big[:1 << 24], off)
-        return same(a, lengths) and same(q, lengths)
+    def moments():                                             # MOMENTS sums
+        a, q = tcr.irregular_moments(xh, oh)
+        return same(a, counts) and same(q, counts)
 
     outs, graphs = [], []
     torch.cuda.synchronize()

@@ -51,7 +51,7 @@ def test_entries_per_tile(tcr, oracle, arrays, n, per_tile):
     x, xd = arrays[0][shift:shift + n].copy(), arrays[1][shift:shift + n]
     ends = np.arange(0, n, TILE)[:, None] + np.round(np.linspace(0, TILE, per_tile, endpoint=False)).astype(np.int64)[None, :]
     cuts = np.unique(np.minimum(ends.ravel(), n))
-    check(tcr, oracle, x, xd, np.concatenate([cuts[(cuts > 700) & (cuts < n - 9)], [n - 9]]), (0, 1, 2) if per_tile in (3, 257) else (0,))
+    check(tcr, oracle, x, xd, np.concatenate([cuts[(cuts > 700) & (cuts < n - 9)], [n - 9]]), (0, 1, 2, 3) if per_tile in (3, 257) else (0,))
 
 
 @pytest.mark.parametrize("n", [HELD, BEYOND])
@@ -87,6 +87,30 @@ def test_zeros_outside_the_segments_of_a_large_array(tcr, oracle, flags):
         assert not np.any(got[:lo]) and not np.any(got[hi:])
         if flags == 0 or np.max(np.abs(want)) <= 2048:
             assert np.array_equal(got[lo:hi], want[lo:hi])
+
+
+# the same in arrays that are not 16-byte aligned, with something in front of the results and behind them
+@pytest.mark.parametrize("flags", [0, 2])
+@pytest.mark.parametrize("shift", [1, 6])
+def test_zeros_outside_the_segments_of_an_unaligned_large_array(tcr, oracle, shift, flags):
+    n = (5 << 23) + 77
+    base = workloads.make_input(n + 8, "int1", 2)
+    x = base[shift:shift + n].copy()
+    xd = torch.from_numpy(base).cuda()
+    dtype = torch.float16 if flags else torch.float32
+    for lo, hi in ((0, n), (5, n), (100003, n - 70001), (n // 2, n // 2 + 9), (0, 7)):
+        off = np.sort(np.random.default_rng(lo + 1).integers(lo, hi, 8, endpoint=True))
+        off[0], off[-1] = lo, hi
+        od = torch.from_numpy(off).cuda()
+        out = torch.full((n + 8,), float("nan"), dtype=dtype, device="cuda")
+        st = tcr.raw().tcr_irregular_scan_filled(xd[shift:].data_ptr(), od.data_ptr(), out[shift:].data_ptr(), n, 7, flags,
+                                                 int(torch.cuda.current_stream().cuda_stream))
+        assert st == tcr.OK
+        got = out.cpu().numpy()
+        want = np.zeros(n)
+        want[lo:hi] = oracle.irregular_scan(x, off)[lo:hi]
+        assert np.array_equal(got[shift:shift + n], want.astype(got.dtype))
+        assert np.all(np.isnan(got[:shift])) and np.all(np.isnan(got[shift + n:]))
 
 
 # A float32 rounding is off by at most half a unit of the last place, evenly spread: 2^-24 * sqrt(1/3) of the power of two below

@@ -63,6 +63,29 @@ def test_regular_segments_in_an_array_that_streams(tcr, oracle):
         assert np.array_equal(got, oracle.segmented_scan(x, seg))
 
 
+# beyond 2^24 elements the sum in front is added once, behind the sums of the tile
+@pytest.mark.parametrize("seg", [8193, 100003, 3000003])
+@pytest.mark.parametrize("n,wait_for", [((1 << 24) + 3, "bounded"), ((1 << 24) + 3, "none"), ((1 << 25) - 70001, "bounded")])
+def test_regular_segments_of_workgroups_that_follow_each_other(tcr, oracle, seg, n, wait_for):
+    n = (n // seg + 1) * seg
+    base = workloads.make_input(n + 8, "int1", seg % 97)
+    bd = torch.from_numpy(base).cuda()
+    tcr.set_variant("scan_wait", wait_for)
+    try:
+        for shift in (0, 3):
+            x, xd = base[shift:shift + n], bd[shift:shift + n]
+            incl = oracle.segmented_scan(x.copy(), seg)
+            for flags in range(4):
+                want = incl - x if flags & tcr.SCAN_EXCLUSIVE else incl
+                out = torch.full((n + 16,), -3.0, dtype=torch.float16 if flags & tcr.OUT_F16 else torch.float32, device="cuda")
+                tcr.segmented_scan_ex(xd, seg, flags, out=out[8:n + 8])
+                got = out.cpu().numpy()
+                assert np.array_equal(got[8:n + 8], want.astype(got.dtype)), (shift, flags)
+                assert np.all(got[:8] == -3.0) and np.all(got[n + 8:] == -3.0)
+    finally:
+        tcr.set_variant("reset")
+
+
 @pytest.mark.parametrize("recipe", ["uniform1", "uniform16", "uniform5000", "lognormal256", "few3"])
 @pytest.mark.parametrize("n,shift", [(1, 0), (8191, 0), (8193, 3), (70001, 0), ((1 << 21) + 5, 5), ((1 << 22) + 9, 0)])
 def test_irregular_segments(tcr, oracle, wait, recipe, n, shift):
@@ -92,7 +115,7 @@ def test_offsets_on_the_edges_of_tiles(tcr, oracle, wait):
 @pytest.mark.parametrize("flags", [0, 1, 2])
 @pytest.mark.parametrize("n", [20000, (1 << 24) + 40000])
 def test_a_new_result_is_zero_outside_the_segments(tcr, oracle, n, flags):
-    # memory that the allocator hands out again, full of something else; above 2^24 elements a kernel of its own clears
+    # memory that the allocator hands out again, full of something else (2^24 elements and more: workgroups of four wavefronts)
     x = workloads.make_input(n, "int4", 4)
     xd = torch.from_numpy(x).cuda()
     dtype = torch.float16 if flags & 2 else torch.float32
