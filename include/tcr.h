@@ -276,7 +276,8 @@ tcr_status tcr_tuning_import(const char *text);
  * kernels that work on any array are named whatever its size: smaller arrays need fewer (their tiles search the offsets
  * and add what reaches them themselves, so neither irregular_bounds_kernel nor irregular_finish_kernel is launched),
  * irregular sums and moments of most arrays above 2^23 elements are segments_reduce_kernel alone unless they are
- * recorded into a graph, scans of smaller arrays and of regular segments of up to 8192 elements are tile_scan_kernel, and
+ * recorded into a graph, irregular scans of up to 7 * 2^22 elements and regular ones of up to 8192 elements per segment, or
+ * of smaller arrays, are tile_scan_kernel, and
  * sums over segments of thousands of tiles are irregular_groups_kernel and irregular_carry_kernel.
  * reduce_span_kernel<...,wave>+reduce_final_kernel is reduce_gather_kernel alone up to 2^24 elements, unless recorded.
  * The arrays are taken to be 16-byte aligned (regular calls on arrays that are not run on the fixed tiles).

@@ -289,11 +289,11 @@ inline void launch_reduce_final(const float* partials, float* out, float* out2, 
     else reduce_final_kernel<kFinalThreads><<<grid, dim3(kFinalThreads), 0, s>>>(partials, out, out2, per, nseg * per);
 }
 
-// Partials of one wavefront each that the last workgroup of a segment collects (tcr_reduce.hpp) instead of a second kernel.
+// Partials of one wavefront each that the last workgroup of a segment collects (tcr_gather.hpp) instead of a second kernel.
 // Several segments: whole workgroups each.  Not on a workspace whose launches a graph has recorded: there the descriptors cost a
 // launch in front of this one, and it would again be two.
-// Up to 2^24 elements, where two launches keep the host longer than one the device (8.9 to 9.4 us at any size up to 2^24; one launch 5.9
-// to 8.1).  Beyond, the two overlap and the collecting workgroup does not: two against one, n = 2^20 * 24 / 32 / 64 / 128 / 256 11.1 / 13.5 /
+// Up to 2^24 elements, where two launches keep the host longer than one the device (8.0 to 9.4 us at any size up to 2^24; one launch 5.4
+// to 6.1, 8.1 in some runs at 2^24).  Beyond, the two overlap and the collecting workgroup does not: two against one, n = 2^20 * 24 / 32 / 64 / 128 / 256 11.1 / 13.5 /
 // 23.6 / 44.0 / 81.4 us against 11.2 / 14.5 / 23.9 / 46.0 / 83.6.
 constexpr uint64_t kGatherElemsMax = 1ull << 24;
 inline bool gather_better(const ReducePlan& p, uint64_t n, uint64_t nseg) {

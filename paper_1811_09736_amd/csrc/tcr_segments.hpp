@@ -1,4 +1,4 @@
-// Sums (and sums of squares) of irregular segments in one launch, for arrays of more than a few million elements.
+// Sums (and sums of squares) of irregular segments in one launch, mostly for arrays of more than 2^23 elements.
 //
 // A workgroup of four wavefronts takes a range of consecutive tiles of 6144 elements.  It searches the offsets once, for the
 // range's start, and from there on only reads entries: 512 at a time, each once, those of the next tile -- and its
@@ -20,8 +20,10 @@
 // Bound: memory, and in front of it a range's start (two rounds of requests for the search, one for the entries): with one
 // tile per workgroup those are half of a workgroup's time (64M elements, segments of 16: 51 us).  Against a look-up
 // kernel, irregular_reduce_kernel and a finishing kernel, or up to 2^24 elements irregular_reduce_kernel with four
-// searches per tile, us, n = 2^20 * 8 / 16 / 32 / 64 / 128: segments of 16 11.1 / 17.2 / 29.2 / 43.6 / 72.3 -> 9.4 / 13.3 / 21.6 / 36.2 /
-// 66.0, both moments 12.8 / 22.9 / 37.1 / 57.9 / 100 -> 10.3 / 14.8 / 24.2 / 40.2 / 72.2.
+// searches per tile, us, n = 2^20 * 9 / 16 / 32 / 64 / 128: segments of 16 11.1 / 14.8 / 28.3 / 43.5 / 72.3 -> 8.9 / 12.0 / 21.2 / 36.6 /
+// 66.2, both moments 13.0 / 21.3 / 36.9 / 57.5 / 99.0 -> 9.8 / 14.0 / 24.3 / 40.3 / 73.1.
+// Registers: held to what seven workgroups per compute unit leave (both moments: six): 71 (77), with 48 (37) scalar ones spilled to
+// lanes and nothing (20 bytes per lane) in scratch.
 #pragma once
 #include "tcr_irregular.hpp"
 
@@ -41,8 +43,8 @@ struct SegmentsReduce {
     uint32_t patience;
 };
 
-// Tiles of 6144 elements: 18.9 KiB of LDS (23.1 for both moments) leave room for the 7 (6) workgroups per compute unit that 72
-// (80) registers do.  8192 elements, 24.6 KiB: 5 workgroups, 64M elements in segments of 16 42 us against 38; 4096: 45.
+// Tiles of 6144 elements: 18.9 KiB of LDS (23.1 for both moments) leave room for the 7 (6) workgroups per compute unit that the
+// registers do.  8192 elements, 24.6 KiB: 5 workgroups, 64M elements in segments of 16 42 us against 38; 4096: 45.
 constexpr int kSegmentsU = 3, kSegmentsBatch = 2;        // 512-element sub-tiles per wavefront; entries per thread and batch
 constexpr uint64_t kSegmentsTile = (uint64_t)kTile * kSegmentsU * 4;
 // How a tile's segments are shared out, by their number m.  Segments of 512 / 128 / 64 elements (12 / 48 / 96 in a tile) at 64M
