@@ -952,7 +952,10 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
         if (st != TCR_OK) return st;
     }
     ScanWorkspace dev = {};
-    st = begin_lookback(ws, s, two_kernels ? 2 * tiles : tiles, &dev, capturing);      // (two kernels: a second table behind the first)
+    // (two kernels: a second table behind the first; asked for also where one kernel does, so that the same call can be recorded
+    // with other offsets)
+    const bool second_table = two_kernels || (!regular && !ws->caller_owned && !capturing);
+    st = begin_lookback(ws, s, second_table ? 2 * tiles : tiles, &dev, capturing);
     if (st != TCR_OK) return st;
     uint64_t* starts = reinterpret_cast<uint64_t*>(ws->partials);
     TileLink* links = reinterpret_cast<TileLink*>(starts + (tiles + 1));

@@ -117,6 +117,11 @@ def test_recorded_with_other_offsets(tcr, oracle, n):
     out = torch.empty(n, dtype=torch.float32, device="cuda")
     side = torch.cuda.Stream()
     torch.cuda.synchronize()
+    holders = [torch.cuda.Stream() for _ in range(8)]          # (tables that earlier calls left behind are in use elsewhere)
+    for s in holders:
+        with torch.cuda.stream(s):
+            tcr.scan(xd[:1 << 24])
+    torch.cuda.synchronize()
     with torch.cuda.stream(side):
         tcr.irregular_scan(xd, first, out=out)
     torch.cuda.synchronize()
@@ -137,7 +142,8 @@ def test_recorded_with_other_offsets(tcr, oracle, n):
     tcr.check_device_flags(side)
     torch.cuda.synchronize()
     del graph
-    tcr.release_stream(side)
+    for s in holders + [side]:
+        tcr.release_stream(s)
 
 
 # Sums and moments at the upper end of the arrays that tiles of their own on workgroups of eight wavefronts are for (the tuner's third
