@@ -160,3 +160,47 @@ def test_infinities_and_nan_stay_in_their_segments(tcr, mix):
     x[off[hit]] = special[hit % 3]                             # its first element; its last one
     x[off[hit + 1] - 1] = special[(hit // 3) % 3]
     check_special(tcr, x, off)
+
+
+def test_recorded_on_a_stream_whose_epochs_the_device_keeps(tcr, oracle):
+    # a recorded scan leaves the stream's epochs to the device; ranges of tiles then run recorded and eagerly, with sums that other
+    # ranges look up
+    inputs = [workloads.make_input(BIG, "int1", (12, k)) for k in range(2)]
+    off = np.concatenate([[5], np.sort(np.random.default_rng(3).integers(5, BIG // 2, BIG // 64)), [BIG // 2, BIG - 70001, BIG - 2]]).astype(np.int64)
+    od = torch.from_numpy(off).cuda()
+    x = torch.from_numpy(inputs[0]).cuda()
+    scanned = torch.empty(BIG, dtype=torch.float32, device="cuda")
+    out = torch.empty(off.size - 1, dtype=torch.float32, device="cuda")
+    side = torch.cuda.Stream()
+
+    def calls():
+        tcr.scan(x, out=scanned)
+        tcr.irregular_reduce(x, od, out=out)
+        return tcr.irregular_moments(x, od)
+
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        calls()
+    side.synchronize()
+    for _ in range(2):                                            # the second recording finds them on the device
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            a, q = calls()
+        for k in (1, 0, 1):
+            x.copy_(torch.from_numpy(inputs[k]).cuda())
+            for t in (scanned, out, a, q):
+                t.fill_(float("nan"))
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            wa, wq = oracle.irregular_moments(inputs[k], off)
+            for got, want in ((out, wa), (a, wa), (q, wq), (scanned, oracle.scan(inputs[k]))):
+                assert np.array_equal(got.cpu().numpy().astype(np.float64), want)
+            with torch.cuda.stream(side):
+                eager = tcr.irregular_reduce(x, od)
+            side.synchronize()
+            assert torch.equal(eager, out)
+    del graph
+    tcr.check_device_flags(side)
+    torch.cuda.synchronize()
+    tcr.release_stream(side)
