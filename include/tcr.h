@@ -276,8 +276,7 @@ tcr_status tcr_tuning_import(const char *text);
  * kernels that work on any array are named whatever its size: smaller arrays need fewer (their tiles search the offsets
  * and add what reaches them themselves, so neither irregular_bounds_kernel nor irregular_finish_kernel is launched),
  * irregular sums and moments of most arrays above 2^23 elements are segments_reduce_kernel alone unless they are
- * recorded into a graph, irregular scans of up to 7 * 2^22 elements and regular ones of up to 8192 elements per segment, or
- * of smaller arrays, are tile_scan_kernel, and
+ * recorded into a graph, irregular scans of up to 9 * 2^24 elements and regular ones in fixed tiles are tile_scan_kernel, and
  * sums over segments of thousands of tiles are irregular_groups_kernel and irregular_carry_kernel.
  * reduce_span_kernel<...,wave>+reduce_final_kernel is reduce_gather_kernel alone up to 2^24 elements, unless recorded.
  * The arrays are taken to be 16-byte aligned (regular calls on arrays that are not run on the fixed tiles).
@@ -299,7 +298,8 @@ tcr_status tcr_check_device_flags(void *stream);
  * Caller-supplied workspace, for callers that manage device memory themselves.
  * tcr_workspace_bytes: an upper bound, over every variant, launch shape and pointer alignment, of the workspace a
  *   call with these arguments can need (op as for tcr_kernel_name, and 6 = segmented_moments,
- *   7 = irregular_moments; 0 for arguments no call accepts).
+ *   7 = irregular_moments; 0 for arguments no call accepts).  Regular scans of more than 2^27 elements run a faster form on
+ *   library-owned memory, and on a buffer with room for two 8-byte words per 8192 elements in either half.
  * tcr_set_workspace: from now on every call on the CURRENT device uses [dev_ptr, dev_ptr + bytes) instead of
  *   library-owned memory, whatever its stream, and allocates nothing; a call that needs more returns
  *   TCR_ERR_WORKSPACE.  dev_ptr: device memory, 256-byte aligned, at least 768 bytes, contents arbitrary (the

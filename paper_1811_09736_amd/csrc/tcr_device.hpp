@@ -19,6 +19,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace tcr {
 
@@ -86,8 +87,58 @@ __device__ __forceinline__ float read_lane(float x, int lane) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), lane));
 }
 
+__device__ __forceinline__ double read_lane(double x, int lane) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane), hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
 // Sum over all 64 lanes, returned uniformly.
 __device__ __forceinline__ float wave_sum(float x) { return read_lane(wave_scan_inclusive(x), 63); }
+
+// Value of the previous lane of the wavefront (0 for lane 0).
+__device__ __forceinline__ float wave_shr1(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x138, 0xf, 0xf, true));
+}
+
+// Segmented inclusive scan over all 64 lanes, sums restarting at flagged lanes, with the flags as one bit per lane in a scalar
+// register pair: the shifts of the flags are then
+// scalar instructions and a step costs the vector unit one cross-lane addition and one select.  Returns the
+// inclusive flags (bit l: a flag in lanes 0 .. l).
+template <int CTRL, int ROW_MASK, bool BOUND>
+__device__ __forceinline__ float dpp_move(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, ROW_MASK, 0xf, BOUND));
+}
+template <int CTRL, int ROW_MASK, bool BOUND>
+__device__ __forceinline__ double dpp_move(double x) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROW_MASK, 0xf, BOUND);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROW_MASK, 0xf, BOUND);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+template <int CH, typename T>
+__device__ __forceinline__ uint64_t wave_seg_scan_inclusive_bits(uint64_t flags, T (&v)[CH]) {
+    auto step = [&](auto ctrl, auto row_mask, auto bound, uint64_t from_left) {
+        const bool f = __builtin_amdgcn_inverse_ballot_w64(flags);
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const T vl = dpp_move<decltype(ctrl)::value, decltype(row_mask)::value, decltype(bound)::value>(v[c]);
+            v[c] = f ? v[c] : v[c] + vl;
+        }
+        flags |= from_left;
+    };
+    using std::integral_constant;
+    step(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{}, integral_constant<bool, true>{}, (flags << 1) & 0xfffefffefffefffeull);
+    step(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{}, integral_constant<bool, true>{}, (flags << 2) & 0xfffcfffcfffcfffcull);
+    step(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{}, integral_constant<bool, true>{}, (flags << 4) & 0xfff0fff0fff0fff0ull);
+    step(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{}, integral_constant<bool, true>{}, (flags << 8) & 0xff00ff00ff00ff00ull);
+    // lane 15 of rows 0 and 2 -> every lane of rows 1 and 3; lane 31 -> every lane of rows 2 and 3
+    step(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{}, integral_constant<bool, false>{},
+         ((flags >> 15) & 1ull ? 0x00000000ffff0000ull : 0ull) | ((flags >> 47) & 1ull ? 0xffff000000000000ull : 0ull));
+    step(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{}, integral_constant<bool, false>{},
+         (flags >> 31) & 1ull ? 0xffffffff00000000ull : 0ull);
+    return flags;
+}
 
 // A workgroup barrier that orders LDS accesses only: unlike __syncthreads() it does not wait for the wavefront's
 // outstanding loads from memory, so data requested before it keeps arriving while the workgroup works on LDS.

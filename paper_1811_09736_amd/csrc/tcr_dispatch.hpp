@@ -541,16 +541,43 @@ tcr_status launch_chain_once(const _Float16* in, void* out, uint64_t n, uint64_t
     bool capturing = false;
     tcr_status st = get_workspace(s, &ws, &capturing);
     if (st != TCR_OK) return st;
-    const int u = once_share(n, seg_len, ws->caller_owned || capturing ? ws->desc_capacity : ~0ull);
+    const int u = once_share(n, seg_len, table_limit(ws, capturing));
     const uint64_t tiles = once_tiles(n, seg_len, u);
     st = begin_lookback(ws, s, tiles, &dev, capturing);
     if (st != TCR_OK) return st;
     const ChainGrid grid = {seg_len, (uint32_t)(tiles / (n / seg_len)), (uint32_t)tiles, g_variant.scan_wait ? kOncePatience : 0u};
     const dim3 blocks((unsigned)tiles), block(16 * kWave);
-    if (u == 1) scan_chain_kernel<kMfma, 1, 16, MODE, false, true><<<blocks, block, 0, s>>>(in, out, grid, dev, nullptr);
-    else if (u == 2) scan_chain_kernel<kMfma, 2, 16, MODE, false, true><<<blocks, block, 0, s>>>(in, out, grid, dev, nullptr);
-    else if (u == 4) scan_chain_kernel<kMfma, 4, 16, MODE, false, true><<<blocks, block, 0, s>>>(in, out, grid, dev, nullptr);
-    else scan_chain_kernel<kMfma, 8, 16, MODE, false, true><<<blocks, block, 0, s>>>(in, out, grid, dev, nullptr);
+    if (u == 1) scan_chain_kernel<kMfma, 1, 16, MODE, false, kChainOnce><<<blocks, block, 0, s>>>(in, out, grid, dev, nullptr);
+    else if (u == 2) scan_chain_kernel<kMfma, 2, 16, MODE, false, kChainOnce><<<blocks, block, 0, s>>>(in, out, grid, dev, nullptr);
+    else if (u == 4) scan_chain_kernel<kMfma, 4, 16, MODE, false, kChainOnce><<<blocks, block, 0, s>>>(in, out, grid, dev, nullptr);
+    else scan_chain_kernel<kMfma, 8, 16, MODE, false, kChainOnce><<<blocks, block, 0, s>>>(in, out, grid, dev, nullptr);
+    st = check_launch("scan_chain_kernel");
+    if (st != TCR_OK) ws->dirty = true;
+    return st;
+}
+
+// The chain with carries from the relay (tcr_relay.hpp), in tiles of 8192 elements, for arrays larger than the chip holds at once: two
+// words of the table per tile.  us, the persistent chain against this, n in 2^20, full scan:
+//   binary32   n = 16.001  26.8/21.0   20  30.5/25.1   24  39.5/33.2   32  46.0/42.5   64  81.2/74.8   128  148/140   256  281/270   512  546/531
+//   binary16       16.001  21.0/17.2   20  22.9/18.7   24  24.4/20.7   32  30.9/26.8   64  53.2/50.0   128  96.6/96.5   160  117/118   256  181/183
+// (segments of 65536: 20 30.0/25.3, 256 276/271; of 65544: 24 44.2/34, 64 89.1/78.6, 128 160/148.)  And where one tile per compute unit would
+// have to be one of 65536 elements (kChainOnce) and segments are long, full scan of 8.001 / 9 / 10 / 11 / 12 15.5/13.4, 15.7/14.3, 16.0/14.8, 16.3/15.8,
+// 16.6/16.5; segments of 262144 9 / 11 15.1/14.3, 15.7/15.8; of 65536 9 14.2/14.3; binary16 10 9.8/12.5.
+constexpr uint64_t kRelayTile = (uint64_t)(kTile * 4 * kRelayWaves);
+inline uint64_t relay_tiles(uint64_t n, uint64_t seg_len) { return (n / seg_len) * ceil_div(seg_len, kRelayTile); }
+inline bool chain_relayed(uint64_t n, uint64_t seg_len, bool f16) {
+    const int once = once_share(n, seg_len, ~0ull);
+    if (once != 0) return once == 8 && !f16 && seg_len >= (1ull << 18) && n <= (21ull << 19);
+    return !f16 || n <= (3ull << 25);
+}
+template <int MODE>
+tcr_status launch_chain_relay(Workspace* ws, bool capturing, const _Float16* in, void* out, uint64_t n, uint64_t seg_len, hipStream_t s) {
+    const uint64_t tiles = relay_tiles(n, seg_len);
+    ScanWorkspace dev = {};
+    tcr_status st = begin_lookback(ws, s, 2 * tiles, &dev, capturing);
+    if (st != TCR_OK) return st;
+    const ChainGrid grid = {seg_len, (uint32_t)(tiles / (n / seg_len)), (uint32_t)tiles, g_variant.scan_wait ? kOncePatience : 0u};
+    scan_chain_kernel<kMfma, 4, kRelayWaves, MODE, false, kChainRelay><<<dim3((unsigned)tiles + 1), dim3(kRelayWaves * kWave), 0, s>>>(in, out, grid, dev, nullptr);
     st = check_launch("scan_chain_kernel");
     if (st != TCR_OK) ws->dirty = true;
     return st;
@@ -562,8 +589,10 @@ tcr_status launch_chain_once(const _Float16* in, void* out, uint64_t n, uint64_t
 template <int FORM, int MODE>
 tcr_status launch_chain(int shape, const _Float16* in, void* out, uint64_t n, uint64_t seg_len, hipStream_t s,
                         ScanWorkspace* used = nullptr, uint32_t* used_tiles = nullptr) {
+    const bool held = shape == 10 && used == nullptr && once_share(n, seg_len, ~0ull) != 0;
+    const bool alone = shape == 10 && used == nullptr && chain_relayed(n, seg_len, (MODE & 2) != 0);
     if constexpr (FORM == kMfma) {
-        if (shape == 10 && used == nullptr && once_share(n, seg_len, ~0ull) != 0) return launch_chain_once<MODE>(in, out, n, seg_len, s);
+        if (held && !alone) return launch_chain_once<MODE>(in, out, n, seg_len, s);
     }
     const uint64_t tile = scan_shape_tile(shape);
     const uint64_t per_segment = ceil_div(seg_len, tile);
@@ -573,6 +602,12 @@ tcr_status launch_chain(int shape, const _Float16* in, void* out, uint64_t n, ui
     bool capturing = false;
     tcr_status st = get_workspace(s, &ws, &capturing);
     if (st != TCR_OK) return st;
+    if constexpr (FORM == kMfma) {
+        if (alone) {
+            if (2 * relay_tiles(n, seg_len) <= table_limit(ws, capturing)) return launch_chain_relay<MODE>(ws, capturing, in, out, n, seg_len, s);
+            if (held) return launch_chain_once<MODE>(in, out, n, seg_len, s);
+        }
+    }
     st = begin_lookback(ws, s, tiles, &dev, capturing);
     if (st != TCR_OK) return st;
     const uint64_t resident = (uint64_t)compute_units() * (uint64_t)kScanShapes[shape].persistent;
@@ -595,7 +630,16 @@ tcr_status launch_chain(int shape, const _Float16* in, void* out, uint64_t n, ui
 template <int FORM, int MODE>
 tcr_status launch_chain_tail(const _Float16* in, void* out, uint64_t n, hipStream_t s) {
     if constexpr (FORM == kMfma) {
-        if (once_share(n, n, ~0ull) != 0) return launch_chain_once<MODE>(in, out, n, n, s);      // (cuts its last group itself)
+        // (these cut the last group themselves)
+        const bool held = once_share(n, n, ~0ull) != 0;
+        if (chain_relayed(n, n, (MODE & 2) != 0)) {
+            Workspace* ws = nullptr;
+            bool capturing = false;
+            const tcr_status st = get_workspace(s, &ws, &capturing);
+            if (st != TCR_OK) return st;
+            if (2 * relay_tiles(n, n) <= table_limit(ws, capturing)) return launch_chain_relay<MODE>(ws, capturing, in, out, n, n, s);
+        }
+        if (held) return launch_chain_once<MODE>(in, out, n, n, s);
     }
     const uint64_t n8 = n & ~7ull;
     ScanWorkspace dev = {};
@@ -773,52 +817,17 @@ inline uint32_t search_grid_log2(uint64_t nseg) {
 }
 
 // One tile per workgroup (tcr_once.hpp).  in, out, n: already counted from the 16-byte boundary below the caller's array.
-template <int U, int W, int MODE, bool LOCAL>
+template <int U, int W, int MODE, bool LOCAL, bool RELAY = false>
 inline void launch_tile_scan(const TileScan& a, const ScanWorkspace& dev, hipStream_t s) {
-    const dim3 grid((unsigned)ceil_div(a.n, (uint64_t)(kTile * U * W))), block(W * kWave);
-    if (LOCAL || a.offsets == nullptr) tile_scan_kernel<U, W, true, MODE, LOCAL><<<grid, block, 0, s>>>(a, dev);
-    else if constexpr (!LOCAL) tile_scan_kernel<U, W, false, MODE, false><<<grid, block, 0, s>>>(a, dev);
+    const dim3 grid((unsigned)ceil_div(a.n, (uint64_t)(kTile * U * W)) + (RELAY ? 1u : 0u)), block(W * kWave);
+    if (LOCAL || a.offsets == nullptr) tile_scan_kernel<U, W, true, MODE, LOCAL, RELAY><<<grid, block, 0, s>>>(a, dev);
+    else if constexpr (!LOCAL) tile_scan_kernel<U, W, false, MODE, false, RELAY><<<grid, block, 0, s>>>(a, dev);
 }
-// The largest array that runs this way when its sums are looked up.  n in 2^20 elements, us, chained tiles (irregular: with a look-up
-// kernel in front, a second kernel behind where most tiles have no start) against this.
-// Regular segments, by their length:
-//   binary32     n = 20          24          32          48          64          96          128         256
-//     100003       31.3/25.4   34.6/29.1   48.0/40.4   66.7/58.1   89.3/79.8   123/114     157/148     294/289 (FIT = 8)
-//     300003       31.5/25.9   35.5/29.6   47.4/41.1   68.2/60.3   91.2/82.6   126/119     161/155
-//     1000003      32.3/26.1   36.7/30.8   47.3/43.0   69.7/65.0   93.1/89.2   130/129     166/170
-//     3000003      31.3/25.6   36.9/30.8   47.8/43.5   66.1/62.5   93.2/91.3   131/134     168/177     319/356 (8)
-//   binary16
-//     100003       23.4/18.5   25.8/20.9   31.3/26.5   45.2/37.8   55.9/48.2   81.6/74.5   104/96.9    193/187 (8)
-//     3000003      23.8/18.3   27.6/21.8   32.8/29.4   45.2/41.7   58.1/55.8   86.1/86.1   110/113     207/221 (8)
-// (Measured with one shape forced and the sum in front added to every lane's running value; as it runs, with that sum added once,
-// 100003 at 24 / 64 / 128 29.5 / 79.9 / 148.)
-// A sum over thousands of tiles takes looks in proportion, and every tile waits for its own.  Irregular segments may be short on
-// average and one of them most of the array, so for these the limit is where that case crosses, whatever the number of segments:
-//   binary32        n = 16.5        20          24          28          32
-//     16              37.2/23.6   39.8/28.5   44.3/33.4   48.6/37.6   52.3/42.9
-//     lognormal       33.5/22.7   35.7/26.3   39.4/30.4   43.3/33.8   46.9/37.2
-//     seven segments  38.3/27.6   40.8/31.7   43.4/36.5   46.3/41.2   48.5/48.7
-//     one segment     38.4/30.0   40.8/34.6   43.3/40.6   46.4/46.1   48.9/54.1
-//     and 1023 empty  35.5/30.8   39.4/35.5   43.4/41.3   48.3/46.9   52.0/55.2
-//   binary16, exclusive
-//     16              30.7/19.1   32.0/22.4   35.4/25.8   38.8/27.8   40.9/31.2
-//     seven segments  31.2/20.8   32.9/23.4   34.6/26.5   36.6/30.1   38.6/35.5
-//     one segment     31.8/22.2   33.4/25.8   35.0/29.3   36.9/33.5   38.7/40.4
-//     and 1023 empty  28.4/23.5   31.2/26.3   34.2/30.4   36.8/34.5   39.2/42.2
-// (2^26, with the sums looked up by one wavefront of four: 16 / lognormal / one segment and 1023 empty 103/93.0 / 91.5/84.7 / 101/166;
-// 2^27 180/167 / 160/157 / 163/445.)
-constexpr uint64_t kIrregularOnceMax = 7ull << 22;
 // Up to here the compute units hold all workgroups at once (256 units: 2^24 elements).
 inline uint64_t scan_held_max() { return (uint64_t)compute_units() * (uint64_t)(kTile * 16 * 8); }
-inline uint64_t scan_once_max(uint64_t seg_len, bool f16) {
-    if (seg_len > (1ull << 22)) return f16 ? 5ull << 23 : 7ull << 22;
-    if (seg_len > (1ull << 20)) return 1ull << 26;
-    if (seg_len > (1ull << 18)) return 3ull << 25;
-    return 1ull << 28;
-}
 template <int MODE>
 inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, void* out, uint64_t n, uint64_t nseg, uint64_t seg_len,
-                                   uint32_t shift, bool fill, hipStream_t s) {
+                                   uint32_t shift, bool fill, bool relay, hipStream_t s) {
     TileScan a = {};
     a.in = in;
     a.offsets = offsets;
@@ -840,7 +849,7 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
         a.grid_log2 = search_grid_log2(nseg);
     }
     ScanWorkspace dev = {};
-    if (local) {
+    if (local && !relay) {
         a.magic = (uint32_t)(((1ull << 32) + seg_len - 1) / seg_len);
         // 8 wavefronts, so that the open part is a small share of what a workgroup reads -- unless segments are short and
         // the array streams from memory (seg_len 33 at n = 2^24 / 2^26 / 2^28: 23.2 / 74.8 / 285 us with 8, 23.6 / 73.3 /
@@ -854,7 +863,15 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
     bool capturing = false;
     tcr_status st = get_workspace(s, &ws, &capturing);
     if (st != TCR_OK) return st;
-    const uint64_t limit = ws->caller_owned || capturing ? ws->desc_capacity : ~0ull;
+    const uint64_t limit = table_limit(ws, capturing);
+    if (relay) {
+        st = begin_lookback(ws, s, 2 * ceil_div(n, kRelayTile), &dev, capturing);
+        if (st != TCR_OK) return st;
+        launch_tile_scan<4, kRelayWaves, MODE, false, true>(a, dev, s);
+        st = check_launch("tile_scan_kernel");
+        if (st != TCR_OK) ws->dirty = true;
+        return st;
+    }
     // Workgroups of 8 wavefronts, small enough that the compute units get about equally many: with 4096, 8192 and 16384
     // elements a tile n = 2.2e6 7.6 / 7.2 / 8.4 us, 5.2e6 15.1 / 11.7 / 12.3, 8e6 20.5 / 16.5 / 14.7 (seven segments; lognormal
     // lengths and regular segments of 10802 and 198163 elements alike), 2^24 - / 31.7 / 27.4.  16 wavefronts, 16384 and
@@ -866,20 +883,15 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
     if (tiles_of(1, 8) <= 2 * units) u = 1;
     else if (tiles_of(2, 16) <= units && 4 * tiles_of(2, 16) > 3 * units) u = 2, w = 16;
     else if (tiles_of(2, 8) <= 3 * units) u = 2;
-    const bool held = n <= scan_held_max();
-    // (irregular: four wavefronts, whose search is the cheaper one where workgroups follow each other.  Up to 2^24 elements only with
-    // segments of 16: one segment and 1023 empty ones / 2^20 segments of 16 in front of one / segments of 16, 12.5 * 2^20 and 2^24
-    // elements 21.4 / 23.3 / 21.1 and 24.6 / 24.6 / 22.8 us with eight, 23.9 / 25.3 / 19.8 and 27.5 / 28.7 / 22.8 with four)
-    if (offsets != nullptr && !held) u = 4, w = 4;
     if (tiles_of(u, w) > limit) u = 4, w = tiles_of(4, 8) > limit ? 16 : 8;
     st = begin_lookback(ws, s, tiles_of(u, w), &dev, capturing);
     if (st != TCR_OK) return st;
-    const dim3 grid((unsigned)tiles_of(u, w)), block(w * kWave);
+    // (regular segments where workgroups follow each other: six wavefronts per SIMD in place of eight.  9001 / 30003 elements, n = 2^26 76.3 / 77.9 against
+    // 79.0 / 78.4 us, 2^28 275 / 278 against 287 / 279)
     if (u == 1) launch_tile_scan<1, 8, MODE, false>(a, dev, s);
     else if (u == 2 && w == 8) launch_tile_scan<2, 8, MODE, false>(a, dev, s);
     else if (u == 2) launch_tile_scan<2, 16, MODE, false>(a, dev, s);
-    else if (w == 4) tile_scan_kernel<4, 4, false, MODE, false, 7><<<grid, block, 0, s>>>(a, dev);
-    else if (w == 8 && offsets == nullptr && !held) tile_scan_kernel<4, 8, true, MODE, false, 6><<<grid, block, 0, s>>>(a, dev);
+    else if (w == 8 && offsets == nullptr && n > scan_held_max()) tile_scan_kernel<4, 8, true, MODE, false, false, 6><<<dim3((unsigned)tiles_of(4, 8)), dim3(8 * kWave), 0, s>>>(a, dev);
     else if (w == 8) launch_tile_scan<4, 8, MODE, false>(a, dev, s);
     else launch_tile_scan<4, 16, MODE, false>(a, dev, s);
     st = check_launch("tile_scan_kernel");
@@ -887,23 +899,38 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
     return st;
 }
 
-// Regular segments of up to kLocalMax elements for which chained tiles are the faster form.  The open part that a tile adds
-// up again costs cache bandwidth in proportion to the segment length, and the longer segments take workgroups of 16
-// wavefronts; against that stand the ticket and the look-back, which weigh less the larger the array.  us, chained
-// against this, for segments of 4097 / 6001 / 8001 elements:
-//   binary32 results, n in 2^20: 40  50 / 50 / 49 and 44 / 44 / 45    48  68 / 67 / 67 and 68 / 70 / 71    56  75 / 76 / 76 and 72 / 75 / 78
-//                                64  85 / 85 / 85 and 80 / 82 / 83    80  102 / 102 / 102 and 97 / 99 / 102    128  152 / 152 / 154 and
-//                                151 / 154 / 158    256  287 / 287 / 289 and 294 / 300 / 308
-//   binary16 results:            24  30 / 30 / 30 and 28 / 29 / 30    40  35 / 35 / 35 and 34 / 35 / 37    64  50 / 49 / 50 and 52 / 53 / 56
-//                                128  101 / 101 / 102 and 115 / 118 / 120    256  190 / 190 / 190 and 224 / 228 / 232
-//                                2501 / 3001 / 4001:  64  49 / 49 / 49 and 48 / 50 / 52    96  79 / 79 / 79 and 74 / 74 / 77    128  101 / 101 / 101
-//                                and 98 / 98 / 101    256  189 / 189 / 189 and 188 / 192 / 195    (2001: 64  48 and 47    256  189 and 186)
-// (Between 2^20 * 44 and 56 an array and its binary32 results just outgrow the 256 MiB of the memory-side cache.)
-inline bool scan_better_chained(uint64_t n, uint64_t seg_len, bool f16) {
-    if (f16 && seg_len > 4096) return n > (seg_len <= 6144 ? 5ull << 23 : 9ull << 22);
-    if (f16) return seg_len > 3072 && ((n > (3ull << 24) && n <= (5ull << 24)) || n > (3ull << 26));
-    if (seg_len <= 4096 || n <= (11ull << 22)) return false;
-    return seg_len <= 6144 ? n <= (13ull << 22) || n > (1ull << 27) : n <= (7ull << 23) || n > (5ull << 24);
+// Scans in fixed tiles whose carries come from the relay: us, the other forms (the wavefronts add the open part up themselves or
+// look up what tiles in front have published, or chained tiles) against this, n in 2^20.
+// Irregular segments: beyond what the chip holds at once, up to 9 * 2^24 elements.  What the others cost there goes by the longest segment,
+// which the host does not know; the relay's does not.
+//   binary32        n = 17          20          24          32          64          128         256
+//     2              49.9/53.5   53.6/57.0   62.3/61.6   94.8/87.2   164.6/150.9
+//     16             26.2/26.3   32.0/32.0   39.6/40.2   63.0/54.1   103.1/95.0  178.5/168.4 328/322
+//     lognormal      24.0/24.2   30.2/30.5   38.2/36.8   55.1/48.0   90.3/83.6   158.9/155.3 294/299
+//     seven          28.0/23.0        -      42.4/36.5   55.2/46.4   91.0/81.8   159.1/151.6 292/293
+//     one, 1023 empty 32.7/23.5  37.7/29.7   48.7/37.1        -      98.8/84.9        -      293/302
+//   binary16, exclusive
+//     16             19.5/19.6   22.8/22.7   26.6/27.2   44.9/37.0   73.3/64.0   124.8/113.7 228/214
+//     lognormal      18.6/19.3   20.9/20.9   23.7/23.9        -      61.1/56.6   107.2/106.1 197/202
+//     seven          21.0/18.7   23.0/20.7   26.7/23.2        -      62.3/55.3   107.0/104.5 191/199
+//   (the largest loss of those with more than a few elements, lognormal at 18: 26.5/27.6)
+// Regular segments and seven irregular ones, of more than 2^20 elements on average: binary32 from 12 * 2^20 elements on (3000003 at 14.3: 21.7/19.4, 22.9: 32.6/30.8, 62.9:
+// 91.3/76.7, 126: 167.9/143.8; seven at 12 / 14 / 16 18.6/18.4, 21.6/19.9, 22.8/21.5).
+// Other regular ones, beyond 2^24, by length and type (chained tiles, which took some lengths of 4097 to 8191 elements: 64 85, 128 152, 256 287; binary16
+// 64 50, 128 102, 256 190):
+//   binary32   5001: 20 27.7/26.6, 24 33.2/34.3, 32 43.0/44.4, 48 61.0/61.8, 56 70.2/69.4, 128 151/146, 256 296/281; 8001: 17 23.2/22.9, 24 34.7/34.3,
+//              64 81.8/78.2, 128 157/146, 256 306/281; 9001 (looked up): 24 33.0/33.7, 64 76.3/78.0, 256 275/281; 30003: 20 26.3/26.3, 64 77.9/77.7,
+//              256 278/281; 50003: 17 22.9/22.3, 64 78.8/78.0; 100003: 17 23.1/22.3, 64 80.0/78.0, 128 148.2/145.2
+//   binary16   2001: 64 49.8/50.3, 256 187/181; 3001: 48 39.8/41.9, 64 51.2/50.1, 128 97.9/94.5, 256 191/181; 5001: 17 17.0/18.1, 24 21.7/21.7, 28 26.9/25.1,
+//              64 60.3/50.6; 8001: 17 18.2/18.1, 20 20.5/19.4, 64 62.4/50.4; 30003: 17 16.9/18.1, 32 26.8/28.3; 500003: 17 17.9/18.9, 28 24.9/25.9, 32 29.2/27.5,
+//              48 44.3/42.6; 3000003: 17 18.8/18.9, 23 22.5/21.6, 26 25.0/23.7
+inline bool tiles_relayed(uint64_t n, uint64_t nseg, uint64_t seg_len, bool regular, bool f16) {
+    const bool far = nseg << 20 < n;                     // more than 2^20 elements a segment
+    if (n <= scan_held_max()) return far && !f16 && n > (3ull << 22);
+    if (!regular) return n <= (9ull << 24);
+    if (far) return true;
+    if (f16) return seg_len > 2048 && n > (seg_len > kLocalMax ? 5ull << 23 : seg_len > 4096 ? 3ull << 23 : 15ull << 22);
+    return seg_len > 32768 || (seg_len > 4096 && seg_len <= kLocalMax && (seg_len > 6144 || n > (13ull << 22)));
 }
 
 template <int MODE>
@@ -918,15 +945,12 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
     const uint32_t vector_stores = aligned(out, 16) ? 1u : 0u;
     const uint64_t tiles = irregular_tiles(true, n, shape);
     const bool regular = offsets == nullptr;
-    // One tile per workgroup with nothing chained: regular segments short enough for a workgroup to add up the open part by
-    // itself, at nearly every size of array (scan_better_chained), and any segments in an array of up to scan_once_max or
-    // kIrregularOnceMax elements.  n = 2^20 / 2^24 / 2^26, us, by ticket and look-back against this: seg_len 1001 8.2 / 27 / 85 against
-    // 4.1 / 22.8 / 74; 100003 8.7 / 28 / 89 against 5.1 / 20.4 / 80; irregular, lognormal lengths 10.9 / 31.8 against 5.5 / 21.4.
-    const bool local = regular && seg_len <= kLocalMax, held = n <= scan_held_max();
-    const bool chained = local && scan_better_chained(n, seg_len, (MODE & 2) != 0);
-    const bool once = shape == 0 && g_variant.formulation == kMfma && (regular ? seg_len >= 2 : g_variant.irregular_scan == 0) &&
-                      (local || held || n <= (regular ? scan_once_max(seg_len, (MODE & 2) != 0) : kIrregularOnceMax));
-    if (once && !chained && (local || held)) return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, s);
+    // One tile per workgroup: with carries from the relay (tiles_relayed), else regular segments of any length and, up to what the chip
+    // holds at once, irregular ones.  n = 2^20 / 2^24 / 2^26, us, by ticket and look-back against this: seg_len 1001 8.2 / 27 / 85 against
+    // 4.1 / 22.8 / 74; 100003 8.7 / 28 / 89 against 5.1 / 20.4 / 78; irregular, lognormal lengths 10.9 / 31.8 against 5.5 / 21.0.
+    const bool alone = shape == 0 && g_variant.formulation == kMfma && (regular ? seg_len >= 2 : g_variant.irregular_scan == 0);
+    const bool relay = alone && tiles_relayed(n, nseg, seg_len, regular, (MODE & 2) != 0);
+    if (alone && !relay && (regular || n <= scan_held_max())) return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, false, s);
     Workspace* ws = nullptr;
     bool capturing = false;
     tcr_status st = get_workspace(s, &ws, &capturing);
@@ -936,16 +960,13 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
     // aligned arrays.)
     const bool two_kernels = !regular && shape == 0 && shift == 0 && vector_stores != 0 && g_variant.formulation == kMfma &&
                              g_variant.irregular_scan != 1 && (g_variant.irregular_scan == 2 || nseg <= tiles / 4);
-    if (once && chained) {                   // (and the table is there, or can be had)
-        if (!table_has_room(ws, tiles, capturing)) return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, s);
-    } else if (once) {
-        // Without room for a descriptor per tile: chained tiles, as long as there is room for those.  The larger tiles of this form are
-        // faster (seven segments in 2^20 * 24 elements 37.6 us against 42.2), but add a lane's elements to the sum in front (8.0e-8 off
-        // against 7.0e-8).
-        const uint64_t limit = ws->caller_owned || capturing ? ws->desc_capacity : ~0ull;
-        const bool room = ceil_div(n, (uint64_t)(kTile * 4 * (regular ? 8 : 4))) <= limit;
+    if (relay) {
+        // without room for its two words per tile: regular segments look up or add up what is in front of a tile, others are chained
+        const uint64_t limit = table_limit(ws, capturing);
+        const bool room = 2 * ceil_div(n, kRelayTile) <= limit;
+        const bool room_once = regular && (seg_len <= kLocalMax || ceil_div(n, (uint64_t)(kTile * 4 * 8)) <= limit);
         const bool room_chained = (two_kernels ? 2 * tiles : tiles) <= limit && (regular || 2 * irregular_words(true, n, shape) <= partials_limit(ws, capturing));
-        if (room || !room_chained) return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, s);
+        if (room || room_once || !room_chained || n <= scan_held_max()) return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, room, s);
     }
     if (!regular) {
         st = ensure_partials(ws, s, 2 * irregular_words(true, n, shape), capturing);

@@ -57,34 +57,6 @@ __device__ __forceinline__ void wave_seg_scan_inclusive(uint32_t& f, float& v) {
     v = one[0];
 }
 
-// The same scan with the flags as one bit per lane in a scalar register pair: the shifts of the flags are then
-// scalar instructions and a step costs the vector unit one cross-lane addition and one select.  Returns the
-// inclusive flags (bit l: a flag in lanes 0 .. l).
-template <int CH>
-__device__ __forceinline__ uint64_t wave_seg_scan_inclusive_bits(uint64_t flags, float (&v)[CH]) {
-    auto step = [&](auto ctrl, auto row_mask, auto bound, uint64_t from_left) {
-        const bool f = __builtin_amdgcn_inverse_ballot_w64(flags);
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            const float vl = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v[c]), decltype(ctrl)::value,
-                                                                                   decltype(row_mask)::value, 0xf, decltype(bound)::value));
-            v[c] = f ? v[c] : v[c] + vl;
-        }
-        flags |= from_left;
-    };
-    using std::integral_constant;
-    step(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{}, integral_constant<bool, true>{}, (flags << 1) & 0xfffefffefffefffeull);
-    step(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{}, integral_constant<bool, true>{}, (flags << 2) & 0xfffcfffcfffcfffcull);
-    step(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{}, integral_constant<bool, true>{}, (flags << 4) & 0xfff0fff0fff0fff0ull);
-    step(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{}, integral_constant<bool, true>{}, (flags << 8) & 0xff00ff00ff00ff00ull);
-    // lane 15 of rows 0 and 2 -> every lane of rows 1 and 3; lane 31 -> every lane of rows 2 and 3
-    step(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{}, integral_constant<bool, false>{},
-         ((flags >> 15) & 1ull ? 0x00000000ffff0000ull : 0ull) | ((flags >> 47) & 1ull ? 0xffff000000000000ull : 0ull));
-    step(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{}, integral_constant<bool, false>{},
-         (flags >> 31) & 1ull ? 0xffffffff00000000ull : 0ull);
-    return flags;
-}
-
 // What is summed (KIND): 0 the elements, 1 their squares (exact in binary32), 2 both at once, as two
 // channels that share the segment starts.
 constexpr int kSum = 0, kSquares = 1, kBoth = 2;

@@ -6,9 +6,9 @@
 // entry in front of the tile for irregular ones -- and so is the way the sum is found:
 //   * s0 at most a tile or so in front: the workgroup adds those elements up itself, 512 to a wavefront, while its own
 //     data is on its way (they are a neighbour's data, mostly found in a cache);
-//   * further away: the published sums of the tiles from the one that holds s0 on, read in one round trip.  As in the
-//     chained scan of arrays that the chip holds at once, a sum that is not there after `patience` looks is added up
-//     from the elements, so no wait depends on which workgroups run.
+//   * further away: the published sums of the tiles from the one that holds s0 on, read in one round trip, or, in larger
+//     arrays, the carry that the relay makes of them (tcr_relay.hpp).  As in the chained scan of arrays that the chip holds at
+//     once, what is not there after `patience` looks is added up from the elements, so no wait depends on which workgroups run.
 // Bound: memory for large arrays, the chain of dependent steps for the smaller ones.  The ticket, the look-back and, for
 // regular segments, the bitmap of the starts and its two barriers are what this form does without.
 // (The tile arithmetic is that of irregular_scan_kernel, the chained form: running sums that restart at heads inside a
@@ -44,16 +44,22 @@ __device__ __forceinline__ float masked_tile_sum(half8 x, uint64_t at, uint64_t 
     return read_lane(row_sum_to_last<16>(mfma(const_ones(), kept, splat(0.0f))[0]), 15);
 }
 
-// The sum from position s0 to the start of `tile` out of what the tiles in between have published: number `looker` of LOOKERS
-// wavefronts that take turns at 64 of them, the nearest first.
-template <int LOOKERS>
-__device__ __forceinline__ float lookup_open_sum(const TileScan& a, const ScanWorkspace& ws, uint32_t tile, uint64_t s0, int tile_log2, int looker,
-                                                 int lane) {
+// The elements of tile t from position s0 on: their sum, by one wavefront.
+__device__ __forceinline__ float open_tile_sum(const TileScan& a, uint32_t t, uint64_t s0, int tile_log2, int lane) {
+    const uint64_t begin = (uint64_t)t << tile_log2;
+    float sum = 0.0f;
+    for (uint64_t at = begin; at < begin + (1ull << tile_log2); at += (uint64_t)kTile)
+        if (at + (uint64_t)kTile > s0) sum += masked_tile_sum(load8(a.in, at + 8 * (uint64_t)lane), at, s0, lane);
+    return sum;
+}
+
+// One wavefront: the sum from position s0 to the start of `tile` out of what the tiles in between have published, 64 at a time, the
+// nearest first; false if one of them is not there after `patience` looks.
+__device__ __forceinline__ bool lookup_open_sum(const TileScan& a, const ScanWorkspace& ws, uint32_t tile, uint64_t s0, int tile_log2, int lane,
+                                                float& sum) {
     const uint32_t first = (uint32_t)(s0 >> tile_log2);
-    const uint32_t want = ws.epoch * 4u + kStatusAggregate;
     float acc = 0.0f;
-    const uint32_t skipped = 64u * (uint32_t)looker;
-    for (uint32_t hi = tile - first > skipped ? tile - skipped : first; hi > first;) {
+    for (uint32_t hi = tile; hi > first;) {
         const uint32_t span = hi - first > 64u ? 64u : hi - first;
         bool need = (uint32_t)lane < span;
         float v = 0.0f;
@@ -61,49 +67,37 @@ __device__ __forceinline__ float lookup_open_sum(const TileScan& a, const ScanWo
         while (true) {
             if (need) {
                 const unsigned long long d = load_descriptor(&ws.desc[hi - 1u - (uint32_t)lane]);
-                if ((uint32_t)(d >> 32) == want) {
+                if ((uint32_t)(d >> 34) == ws.epoch) {
                     v = __builtin_bit_cast(float, (uint32_t)d);
                     need = false;
                 }
             }
-            unsigned long long missing = __ballot(need);
-            if (missing == 0ull) break;
-            if (++polls > a.patience) {
-                for (; missing != 0ull; missing &= missing - 1ull) {
-                    const int slot = __builtin_ctzll(missing);
-                    const uint64_t begin = (uint64_t)(hi - 1u - (uint32_t)slot) << tile_log2;
-                    float sum = 0.0f;
-                    for (uint64_t at = begin; at < begin + (1ull << tile_log2); at += (uint64_t)kTile)
-                        if (at + (uint64_t)kTile > s0) sum += masked_tile_sum(load8(a.in, at + 8 * (uint64_t)lane), at, s0, lane);
-                    if (lane == slot) v = sum;
-                }
-                break;
-            }
+            if (__ballot(need) == 0ull) break;
+            if (__builtin_expect(++polls > a.patience, 0)) return false;
             __builtin_amdgcn_s_sleep(1);
         }
         acc += v;
-        if constexpr (LOOKERS == 1) hi -= span;
-        else hi = hi - first > 64u * LOOKERS ? hi - 64u * LOOKERS : first;
+        hi -= span;
     }
-    return wave_sum(acc);                                // (added per lane first: one chain of roundings of the whole sum's size, not one per look)
+    sum = wave_sum(acc);                                 // (added per lane first: one chain of roundings of the whole sum's size, not one per look)
+    return true;
 }
 
 // LOCAL (regular segments of 2 to WAVES * 512 elements): no sum is ever looked up, no workspace.
-// FIT: wavefronts per SIMD that the registers are held to.  Four sub-tiles per wavefront take 77 (73 with exclusive results) and
-// nothing in scratch where they may: 6 wavefronts.  Up to 2^24 elements, where all workgroups run at once, 8 are better in
-// spite of 44 (28) bytes of scratch per lane and 44 to 51 scalar registers in lanes; beyond, workgroups follow each other and
-// 7 (irregular, 16 bytes or none) or 6 are.  us, FIT = 8 against less: 2^20 * 24 elements in segments of 16 / lognormal lengths /
-// seven segments 37.6 / 35.6 / 38.5 against 36.6 / 30.2 / 33.7 (7); regular 100003, 2^20 * 24 / 64 / 96 29.8 / 82.4 / 117 against
-// 29.1 / 79.8 / 114 (6).
-// GUIDED (irregular, workgroups of four wavefronts: where they follow each other): a tile's entries are found with one search of two
-// rounds around where they are likely to be, not two of four over the whole array, and all four wavefronts take turns at what is
-// looked up (16.5 * 2^20 / 2^20 * 24 / 2^20 * 28 elements, one segment and 1023 empty ones: by one of them 30.4 / 43.3 / 50.5 us, by all
-// 30.8 / 41.3 / 46.9; binary16 exclusive 25.7 / 35.3 / 41.7 and 23.5 / 30.4 / 34.5).
-template <int U, int WAVES, bool REGULAR, int MODE, bool LOCAL, int FIT = (U == 4 ? 8 : 4)>
-__global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(FIT, 8))) void tile_scan_kernel(TileScan a, ScanWorkspace ws_arg) {
+// RELAY (workgroups of four wavefronts, in arrays whose workgroups follow each other): the sum in front comes from the relay
+// (tcr_relay.hpp).  Regular tiles all wait for it, in the order of the array; irregular ones only where it is more than the four
+// wavefronts add up themselves (segments of 16 in 2^27 elements 165 us, 174 where all wait; seven segments 151 and 149).  Their
+// entries are found with one search of two rounds around where they are likely to be (GUIDED), not two of four over the whole array.
+// Registers: at most 64, so that 8 wavefronts per SIMD run.  A wavefront that has waited in vain loads its elements again behind the
+// additions, so that they need not be held across them: 45 to 47 registers where four sub-tiles took 64 and 44 bytes of scratch
+// (lognormal lengths / segments of 16 / seven segments in 2^24 elements 21.7 / 23.9 / 23.6 -> 21.0 / 23.5 / 22.7 us).  Not with fewer
+// sub-tiles, which lose 2 to 5 %, nor with binary16 results (15.7 -> 16.0): 64 registers, 20 to 64 bytes.
+// MOST: wavefronts per SIMD at most.
+template <int U, int WAVES, bool REGULAR, int MODE, bool LOCAL, bool RELAY = false, int MOST = 8>
+__global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U < 4 ? 4 : MOST, MOST))) void tile_scan_kernel(TileScan a, ScanWorkspace ws_arg) {
     static_assert(!LOCAL || REGULAR, "");
-    constexpr bool GUIDED = !REGULAR && WAVES == 4;           // (how a tile's entries are found)
-    constexpr int LOOKERS = GUIDED ? WAVES : 1;
+    static_assert(!RELAY || (WAVES == kRelayWaves && !LOCAL), "");
+    constexpr bool GUIDED = !REGULAR && RELAY;                // (how a tile's entries are found)
     constexpr int EXCL = MODE & 1, F16 = MODE >> 1;
     constexpr uint32_t kChunk = (uint32_t)kTile * U;          // one wavefront's share
     constexpr uint32_t kBlockTile = kChunk * WAVES;           // one workgroup's share
@@ -116,7 +110,14 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(F
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t tile = blockIdx.x;
+    if constexpr (RELAY) {
+        __shared__ RelayShared relay;
+        if (blockIdx.x == 0u) {
+            relay_carries(resolve_workspace(ws_arg), gridDim.x - 1u, relay, wave, lane);
+            return;
+        }
+    }
+    const uint32_t tile = blockIdx.x - (RELAY ? 1u : 0u);
     const uint64_t tb = (uint64_t)tile * kBlockTile;
     const uint64_t base = tb + (uint64_t)wave * kChunk;
     // the wavefront's share: whole groups of 8 through the range check, the group that the array's end cuts by element
@@ -127,6 +128,13 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(F
     const auto load_share = [&] {
 #pragma unroll
         for (int u = 0; u < U; ++u) x[u] = buffer_load8(src, (uint32_t)(kTile * u + 8 * lane) * 2u);
+    };
+    const auto load_cut_group = [&] {
+        if (count != whole) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if ((uint32_t)(kTile * u + 8 * lane) == whole) x[u] = load8_guarded(a.in, base + whole, a.n);
+        }
     };
     if constexpr (REGULAR) load_share();
 
@@ -232,20 +240,19 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(F
         }
     }
     const uint64_t back = tb - s0;
-    const bool far = !LOCAL && back > kBackMax;
+    const bool far = RELAY && REGULAR ? true : !LOCAL && back > kBackMax;
     // the wavefront's 512 elements of the open part, counted back from the tile's start
     const uint64_t behind = (uint64_t)kTile * (uint64_t)wave;
     const bool mine = !far && behind < back;
     const uint64_t back_at = mine ? tb - behind - (uint64_t)kTile : 0;
-    const __amdgpu_buffer_rsrc_t back_src = make_rsrc(a.in + back_at, mine ? (uint32_t)kTile * 2u : 0u);
-    const half8 back_x = buffer_load8(back_src, 16u * (uint32_t)lane);
+    half8 back_x = {};
+    if constexpr (!(RELAY && REGULAR)) {
+        const __amdgpu_buffer_rsrc_t back_src = make_rsrc(a.in + back_at, mine ? (uint32_t)kTile * 2u : 0u);
+        back_x = buffer_load8(back_src, 16u * (uint32_t)lane);
+    }
     if constexpr (!REGULAR && !GUIDED) __syncthreads();   // the heads are marked
 
-    if (count != whole) {
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if ((uint32_t)(kTile * u + 8 * lane) == whole) x[u] = load8_guarded(a.in, base + whole, a.n);
-    }
+    load_cut_group();
     uint32_t heads[(U + 3) / 4] = {};             // the lane's heads: a byte per sub-tile
     uint64_t flag_before[U];                      // bit l: a head in a lane in front of lane l inside the sub-tile
     uint32_t seen_before[U];                      // a head in a sub-tile in front
@@ -298,23 +305,30 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(F
         if (wave == 0) {
             // what later tiles may need of this one: the sum behind its last head
             float total = 0.0f;
-            for (int v = WAVES - 1; v >= 0; --v) {
+            bool tail = false;
+            for (int v = WAVES - 1; v >= 0 && !tail; --v) {
                 total += s_wave_value[v];
-                if (s_wave_flag[v]) break;
+                tail = s_wave_flag[v] != 0u;
             }
             if (lane == 0) {
-                if (tile == 0 && ws.state != nullptr && !ws.device_managed) ws.state[0] = ws.epoch;
-                __hip_atomic_store(&ws.desc[tile], pack_desc(ws.epoch, kStatusAggregate, total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (!RELAY && tile == 0 && ws.state != nullptr && !ws.device_managed) ws.state[0] = ws.epoch;
+                __hip_atomic_store(&ws.desc[tile], pack_desc(ws.epoch, RELAY && tail ? kStatusTail : kStatusAggregate, total), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
             }
-            if (LOOKERS == 1 && far) {
-                const float pre = lookup_open_sum<1>(a, ws, tile, s0, kTileLog2, 0, lane);
-                if (lane == 0) s_back[0] = pre;
-            }
-        }
-        if constexpr (LOOKERS > 1) {
             if (far) {
-                const float pre = lookup_open_sum<LOOKERS>(a, ws, tile, s0, kTileLog2, wave, lane);
-                if (lane == 0) s_back[wave] = pre;
+                float pre = 0.0f;
+                bool got;
+                if constexpr (RELAY) got = relay_wait(ws, gridDim.x - 1u, tile, a.patience, pre);
+                else got = lookup_open_sum(a, ws, tile, s0, kTileLog2, lane, pre);
+                if (__builtin_expect(!got, 0)) {
+                    pre = add_up_in_front<RELAY>(ws, gridDim.x - 1u, (uint32_t)(s0 >> kTileLog2), tile,
+                                                 [&](uint32_t t) { return open_tile_sum(a, t, s0, kTileLog2, lane); });
+                    if constexpr (U >= 4 && !F16) {
+                        load_share();
+                        load_cut_group();
+                    }
+                }
+                if (lane == 0) s_back[0] = pre;
             }
         }
         if (far) __syncthreads();
@@ -331,12 +345,8 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(F
     }
     if (open && back != 0) {
         float sum = 0.0f;
-        if constexpr (LOOKERS > 1) {
-            sum = pairwise_sum(s_back);           // (sums over thousands of tiles; one after the other 5.3e-8 -> 5.6e-8 off for seven segments)
-        } else {
 #pragma unroll
-            for (int v = 0; v < WAVES; ++v) sum += s_back[v];
-        }
+        for (int v = 0; v < WAVES; ++v) sum += s_back[v];
         ext += sum;
     }
     const uint32_t valid_lo = first > base ? (uint32_t)(first - base < kChunk ? first - base : kChunk) : 0u;
@@ -344,7 +354,7 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(F
     // LATE: the sum in front may be millions of times an element, and is added once, behind the sums of the tile, not in front of
     // a lane's eight additions.  Where workgroups follow each other the two more operations per element are free; where all
     // run at once they cost 5 to 10 % (seven segments in 2^24 elements: 23.5 us, 25.3 with them).
-    constexpr bool LATE = !LOCAL && U == 4 && FIT < 8;
+    constexpr bool LATE = RELAY;
     const bool inside = valid_lo == 0u && valid_hi == kChunk && a.vector_stores != 0u;
     void* const dst = F16 ? static_cast<void*>(static_cast<_Float16*>(a.out) + base) : static_cast<void*>(static_cast<float*>(a.out) + base);
 #pragma unroll

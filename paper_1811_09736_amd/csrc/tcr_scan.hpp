@@ -26,6 +26,7 @@
 //                         the paper's scan-then-propagate).
 #pragma once
 #include "tcr_device.hpp"
+#include "tcr_relay.hpp"
 #include "tcr_reduce.hpp"
 
 namespace tcr {
@@ -44,11 +45,6 @@ __device__ __forceinline__ float lanes_scan_inclusive(float x, int lane) {
     if constexpr (GROUP > 32)
         x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x143, 0xc, 0xf, false));
     return x;
-}
-
-// Value of the previous lane of the wavefront (0 for lane 0).
-__device__ __forceinline__ float wave_shr1(float x) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x138, 0xf, 0xf, true));
 }
 
 // In-lane scan of 8 values, binary32: inclusive (EXCL = 0) or exclusive (EXCL = 1).  Returns the
@@ -137,36 +133,7 @@ __global__ __launch_bounds__(WAVES * kWave) void scan_small_kernel(const _Float1
     }
 }
 
-// ------------------------------------------------------------------------------ look-back state
-// One 64-bit word per workgroup tile: high half = tag, low half = binary32 value.
-// tag = epoch * 4 + status; a word whose epoch differs from the launch's is "not yet written",
-// so the table never needs clearing between launches.
-constexpr uint32_t kStatusAggregate = 1;   // value = total of this tile only
-constexpr uint32_t kStatusPrefix = 2;      // value = total of this tile and all earlier tiles of its segment
-constexpr int kSpinLimit = 1 << 20;        // polls of one look-back window before giving up
-
-struct ScanWorkspace {
-    unsigned long long* desc;   // [tiles]
-    uint32_t* ticket;           // running count of tiles handed out since the workspace was created
-    uint32_t* gave_up;          // set to 1 if a bounded wait expired
-    uint32_t ticket_base;       // value of *ticket when this launch starts
-    uint32_t epoch;
-    // state[0]: epoch of the latest launch, state[1]: *ticket at its start.  Host-managed workspaces
-    // (device_managed == 0) pass epoch and ticket_base above and the launch only records its epoch in
-    // state[0]; device-managed ones (launches recorded into HIP graphs, whose arguments are frozen)
-    // take both from state[], which chain_begin_kernel advances in front of every launch.
-    uint32_t* state;
-    uint32_t device_managed;
-};
-
-__device__ __forceinline__ ScanWorkspace resolve_workspace(ScanWorkspace w) {
-    if (w.state != nullptr && w.device_managed) {
-        w.epoch = w.state[0];
-        w.ticket_base = w.state[1];
-    }
-    return w;
-}
-
+// ------------------------------------------------------------------------------ look-back state (tcr_relay.hpp), kept up
 // Device-managed workspaces: one workgroup, enqueued in front of every launch that chains tiles.  Starts a
 // new epoch (clearing the descriptor table when the 30-bit epoch wraps) and records the ticket count the
 // launch starts from -- every earlier launch on the stream has finished drawing by now.
@@ -202,17 +169,6 @@ __global__ __launch_bounds__(kClearThreads) void workspace_clear_kernel(uint32_t
         counters[3] = 0u;
         counters[4] = 0u;
     }
-}
-
-__device__ __forceinline__ unsigned long long pack_desc(uint32_t epoch, uint32_t status, float v) {
-    return ((unsigned long long)(epoch * 4u + status) << 32) | (unsigned long long)__builtin_bit_cast(uint32_t, v);
-}
-
-// Descriptor words live in uncached device memory and are read with agent scope: the tiles of
-// one chain run on different XCDs, whose L2 caches are not coherent with each other.  (A read
-// that only bypasses the first-level cache was tried and does see stale words.)
-__device__ __forceinline__ unsigned long long load_descriptor(const unsigned long long* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Executed by one whole wavefront.  Returns (uniformly) the sum of the totals of all earlier
@@ -523,7 +479,7 @@ struct ChainGrid {
     uint64_t seg_len;
     uint32_t per_segment;
     uint32_t tiles;
-    uint32_t patience;       // ONCE: looks at an aggregate before its tile is added up here
+    uint32_t patience;       // one tile per workgroup: looks at a descriptor before elements are added up here
 };
 
 // Stage C: request the data of ticket `tile`.
@@ -670,7 +626,7 @@ __device__ __forceinline__ uint32_t chain_finish(ChainTile<U>& t, void* __restri
     return fresh;
 }
 
-// ONCE: the chain for arrays that the chip holds all at once.  Every workgroup takes one tile, that of its blockIdx, and
+// kChainOnce: the chain for arrays that the chip holds all at once.  Every workgroup takes one tile, that of its blockIdx, and
 // nothing is drawn: its tile's aggregate is published as soon as its totals are known, the aggregates of the segment's
 // earlier tiles are read in one round trip, and the results go out.  Such arrays are bound by latency: the pipeline
 // above starts with three draws one after another and the loads between them, 9 us before the first store.  Nothing
@@ -741,7 +697,8 @@ __device__ __forceinline__ float once_sum_totals(const ScanWorkspace& ws, uint32
     return acc;
 }
 
-template <int U, int WAVES, int MODE>
+// RELAY: the same with carries from the relay (tcr_relay.hpp), for arrays whose workgroups follow each other.
+template <int U, int WAVES, int MODE, bool RELAY>
 __device__ __forceinline__ void chain_once(const _Float16* __restrict__ in, void* __restrict__ out, const ChainGrid& grid,
                                            const ScanWorkspace& ws, ChainShared& sh) {
     constexpr int EXCL = MODE & 1, F16 = MODE >> 1;
@@ -749,8 +706,8 @@ __device__ __forceinline__ void chain_once(const _Float16* __restrict__ in, void
     constexpr uint32_t kBlockTile = kChunk * WAVES;
     const LaneId id;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t tile = blockIdx.x;
-    if (tile == 0 && threadIdx.x == 0 && ws.state != nullptr && !ws.device_managed) ws.state[0] = ws.epoch;
+    const uint32_t tile = blockIdx.x - (RELAY ? 1u : 0u);
+    if (!RELAY && tile == 0 && threadIdx.x == 0 && ws.state != nullptr && !ws.device_managed) ws.state[0] = ws.epoch;
     const uint32_t seg = tile / grid.per_segment, pos = tile - seg * grid.per_segment;
     const uint64_t seg_begin = (uint64_t)seg * grid.seg_len, seg_end = seg_begin + grid.seg_len;
     const uint64_t base = seg_begin + (uint64_t)pos * kBlockTile + (uint64_t)wave * kChunk;
@@ -760,13 +717,16 @@ __device__ __forceinline__ void chain_once(const _Float16* __restrict__ in, void
     const uint32_t lane_off = (uint32_t)(kRow * id.j + 8 * id.g);
     const __amdgpu_buffer_rsrc_t src = make_rsrc(in + (count ? base : 0), whole * 2u);
     half8 x[U];
+    const auto load_share = [&] {
 #pragma unroll
-    for (int u = 0; u < U; ++u) x[u] = buffer_load8(src, ((uint32_t)(kTile * u) + lane_off) * 2u);
-    if (count != whole) {
+        for (int u = 0; u < U; ++u) x[u] = buffer_load8(src, ((uint32_t)(kTile * u) + lane_off) * 2u);
+        if (count != whole) {
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if ((uint32_t)(kTile * u) + lane_off == whole) x[u] = load8_guarded(in, base + whole, seg_end);
-    }
+            for (int u = 0; u < U; ++u)
+                if ((uint32_t)(kTile * u) + lane_off == whole) x[u] = load8_guarded(in, base + whole, seg_end);
+        }
+    };
+    load_share();
     float pre[U], run = 0.0f;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -784,15 +744,33 @@ __device__ __forceinline__ void chain_once(const _Float16* __restrict__ in, void
         if (w < wave) ext += t;
         total += t;
     }
-    if (pos + 1u < grid.per_segment && wave == 0 && id.lane == 0)      // (the segment's last tile is nobody's predecessor)
-        __hip_atomic_store(&ws.desc[tile], pack_desc(ws.epoch, kStatusAggregate, total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (pos != 0u) {
+    if constexpr (RELAY) {
         if (wave == 0) {
-            const float before = once_sum_totals<U, WAVES>(ws, tile - pos, tile, in, grid, id);
+            // (of the segment's last tile nothing reaches the next one)
+            const bool tail = pos + 1u == grid.per_segment;
+            if (id.lane == 0)
+                __hip_atomic_store(&ws.desc[tile], pack_desc(ws.epoch, tail ? kStatusTail : kStatusAggregate, tail ? 0.0f : total), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            float before = 0.0f;
+            if (!relay_wait(ws, grid.tiles, tile, grid.patience, before)) {
+                before = add_up_in_front<true>(ws, grid.tiles, tile - pos, tile, [&](uint32_t t) { return once_tile_total<U, WAVES>(t, in, grid, id); });
+                load_share();
+            }
             if (id.lane == 0) sh.prefix = before;
         }
         __syncthreads();
         ext += sh.prefix;
+    } else {
+        if (pos + 1u < grid.per_segment && wave == 0 && id.lane == 0)      // (the segment's last tile is nobody's predecessor)
+            __hip_atomic_store(&ws.desc[tile], pack_desc(ws.epoch, kStatusAggregate, total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (pos != 0u) {
+            if (wave == 0) {
+                const float before = once_sum_totals<U, WAVES>(ws, tile - pos, tile, in, grid, id);
+                if (id.lane == 0) sh.prefix = before;
+            }
+            __syncthreads();
+            ext += sh.prefix;
+        }
     }
     const __amdgpu_buffer_rsrc_t dst = make_rsrc(static_cast<char*>(out) + (count ? base : 0) * (F16 ? 2u : 4u), whole * (F16 ? 2u : 4u));
 #pragma unroll
@@ -820,17 +798,28 @@ __device__ __forceinline__ void chain_once(const _Float16* __restrict__ in, void
     }
 }
 
-template <int FORM, int U, int WAVES, int MODE, bool IRREG = false, bool ONCE = false>
-__global__ __launch_bounds__(WAVES * kWave) void scan_chain_kernel(const _Float16* __restrict__ in,
+// How the tiles are taken: by persistent workgroups in a pipeline, or one per workgroup that looks its carry up itself or gets it
+// from the relay.
+enum ChainKind { kChainPipeline = 0, kChainOnce = 1, kChainRelay = 2 };
+template <int FORM, int U, int WAVES, int MODE, bool IRREG = false, int KIND = kChainPipeline>
+__global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(KIND == kChainRelay ? 8 : 1, 8))) void scan_chain_kernel(const _Float16* __restrict__ in,
                                                                    void* __restrict__ out, ChainGrid grid,
                                                                    ScanWorkspace ws_arg, const TileLink* __restrict__ links) {
     static_assert(WAVES <= 16, "");
-    static_assert(!ONCE || (FORM == kMfma && !IRREG), "");
+    static_assert(KIND == kChainPipeline || (FORM == kMfma && !IRREG), "");
+    static_assert(KIND != kChainRelay || WAVES == kRelayWaves, "");
     const uint32_t tiles = grid.tiles;
     const ScanWorkspace ws = resolve_workspace(ws_arg);
     __shared__ ChainShared sh;
-    if constexpr (ONCE) {
-        chain_once<U, WAVES, MODE>(in, out, grid, ws, sh);
+    if constexpr (KIND != kChainPipeline) {
+        if constexpr (KIND == kChainRelay) {
+            __shared__ RelayShared relay;
+            if (blockIdx.x == 0u) {
+                relay_carries(ws, tiles, relay, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), threadIdx.x & (kWave - 1));
+                return;
+            }
+        }
+        chain_once<U, WAVES, MODE, KIND == kChainRelay>(in, out, grid, ws, sh);
         return;
     }
     __shared__ uint32_t s_draw;

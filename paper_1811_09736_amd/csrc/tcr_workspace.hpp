@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "../../include/tcr.h"
+#include "tcr_relay.hpp"
 #include "tcr_reduce.hpp"
 #include "tcr_scan.hpp"
 #include "tcr_gather.hpp"
@@ -163,6 +164,11 @@ inline tcr_status get_workspace(hipStream_t stream, Workspace** out, bool* captu
 // How many partials a call may plan for: what is there, where that cannot be grown (the caller's buffer, a capture).
 inline uint64_t partials_limit(const Workspace* ws, bool capturing) {
     return (ws->caller_owned || capturing) ? ws->partials_capacity : ~0ull;
+}
+
+// The same for descriptors.
+inline uint64_t table_limit(const Workspace* ws, bool capturing) {
+    return (ws->caller_owned || capturing) ? ws->desc_capacity : ~0ull;
 }
 
 inline tcr_status ensure_partials(Workspace* ws, hipStream_t stream, uint64_t floats, bool capturing) {
