@@ -1,9 +1,13 @@
-"""Thin ctypes binding over the C ABI of libtcr.so (include/tcr.h).
+"""Thin binding over the C ABI of libtcr.so (include/tcr.h): ctypes, and an extension module for the ordinary calls.
 
 Argument marshalling only: device pointers, sizes and the stream handle are passed
 through; every step of the computation runs in the HIP kernels.  PyTorch supplies
 device memory and streams, nothing else.  If the library has not been built the
 import of this module fails -- there is no CPU fallback.
+
+An operation on plain tensors of the current device and on the current stream goes through _native (csrc/tcr_native.cpp), which
+makes the same checks and the same call in less time; for everything else _native gives None, before it has done anything,
+and the call goes on here.
 """
 from __future__ import annotations
 
@@ -13,7 +17,7 @@ from typing import Optional
 
 import torch
 
-from .build import LIB_PATH
+from .build import LIB_PATH, NATIVE_PATH
 
 OK, ERR_INVALID_ARG, ERR_UNSUPPORTED, ERR_WORKSPACE, ERR_HIP = range(5)
 OP_SEGMENTED_REDUCE, OP_SEGMENTED_SCAN, OP_REDUCE, OP_SCAN, OP_IRREGULAR_REDUCE, OP_IRREGULAR_SCAN = range(6)
@@ -102,6 +106,20 @@ def _load() -> ctypes.CDLL:
 _lib = _load()
 
 
+def _load_native():
+    if not os.path.exists(NATIVE_PATH):
+        raise ImportError(
+            f"{NATIVE_PATH} is missing: build it with `python -c 'import __graft_entry__ as g; g.build()'`")
+    from . import _native
+    _native.bind(TcrError, *(ctypes.cast(getattr(_lib, name), ctypes.c_void_p).value for name in (
+        "tcr_segmented_reduce", "tcr_segmented_scan_ex", "tcr_scan_ex", "tcr_reduce", "tcr_segmented_moments", "tcr_irregular_reduce",
+        "tcr_irregular_scan_ex", "tcr_irregular_scan_filled", "tcr_irregular_moments")))
+    return _native
+
+
+_native = _load_native()
+
+
 # A call's own work on the host is a few microseconds, of which the launch is three; the public ways to ask for the current
 # device and stream (a guard object, a Stream object) cost more than that, so the plain integers are asked for instead.
 _current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
@@ -140,6 +158,10 @@ def _check_output(out: torch.Tensor, numel: int, like: torch.Tensor) -> None:
 def segmented_reduce(x: torch.Tensor, seg_len: int, out: Optional[torch.Tensor] = None,
                      stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
     """tcr_segmented_reduce: out[s] = sum of x[s*seg_len : (s+1)*seg_len]."""
+    if stream is None:
+        got = _native.segmented_reduce(x, seg_len, out)
+        if got is not None:
+            return got
     _check_input(x)
     n = x.numel()
     if seg_len <= 0 or n % seg_len:
@@ -155,6 +177,10 @@ def segmented_reduce(x: torch.Tensor, seg_len: int, out: Optional[torch.Tensor] 
 def segmented_scan(x: torch.Tensor, seg_len: int, out: Optional[torch.Tensor] = None,
                    stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
     """tcr_segmented_scan: inclusive running sums restarting every seg_len elements."""
+    if stream is None:
+        got = _native.segmented_scan(x, seg_len, 0, out, "tcr_segmented_scan")
+        if got is not None:
+            return got
     _check_input(x)
     n = x.numel()
     if seg_len <= 0 or n % seg_len:
@@ -182,6 +208,10 @@ def segmented_scan_noalloc(x: torch.Tensor, seg_len: int, out: torch.Tensor,
 def segmented_scan_ex(x: torch.Tensor, seg_len: int, flags: int, out: Optional[torch.Tensor] = None,
                       stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
     """tcr_segmented_scan_ex: flags = SCAN_EXCLUSIVE | OUT_F16 (float16 output tensor when OUT_F16 is set)."""
+    if stream is None:
+        got = _native.segmented_scan(x, seg_len, flags, out, "tcr_segmented_scan_ex")
+        if got is not None:
+            return got
     _check_input(x)
     n = x.numel()
     if seg_len <= 0 or n % seg_len:
@@ -198,6 +228,10 @@ def segmented_scan_ex(x: torch.Tensor, seg_len: int, flags: int, out: Optional[t
 def scan_ex(x: torch.Tensor, flags: int, out: Optional[torch.Tensor] = None,
             stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
     """tcr_scan_ex: the full scan with flags = SCAN_EXCLUSIVE | OUT_F16."""
+    if stream is None:
+        got = _native.scan(x, flags, out, "tcr_scan_ex")
+        if got is not None:
+            return got
     _check_input(x)
     n = x.numel()
     dtype = torch.float16 if flags & OUT_F16 else torch.float32
@@ -219,6 +253,10 @@ def _check_offsets(x: torch.Tensor, offsets: torch.Tensor) -> int:
 def irregular_reduce(x: torch.Tensor, offsets: torch.Tensor, out: Optional[torch.Tensor] = None,
                      stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
     """tcr_irregular_reduce: out[s] = sum of x[offsets[s]:offsets[s+1]]."""
+    if stream is None:
+        got = _native.irregular_reduce(x, offsets, out)
+        if got is not None:
+            return got
     if not (x.is_cuda and x.dtype == torch.float16 and x.dim() == 1 and x.is_contiguous()):
         raise TypeError("input must be a contiguous 1-D float16 CUDA tensor")
     nseg = _check_offsets(x, offsets)
@@ -240,6 +278,10 @@ def irregular_scan(x: torch.Tensor, offsets: torch.Tensor, out: Optional[torch.T
 
 def irregular_moments(x: torch.Tensor, offsets: torch.Tensor, stream: Optional[torch.cuda.Stream] = None):
     """tcr_irregular_moments: (sum, sum of squares) of x[offsets[s]:offsets[s+1]] for every s."""
+    if stream is None:
+        got = _native.irregular_moments(x, offsets)
+        if got is not None:
+            return got
     if not (x.is_cuda and x.dtype == torch.float16 and x.dim() == 1 and x.is_contiguous()):
         raise TypeError("input must be a contiguous 1-D float16 CUDA tensor")
     nseg = _check_offsets(x, offsets)
@@ -253,6 +295,10 @@ def irregular_moments(x: torch.Tensor, offsets: torch.Tensor, stream: Optional[t
 def irregular_scan_ex(x: torch.Tensor, offsets: torch.Tensor, flags: int, out: Optional[torch.Tensor] = None,
                       stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
     """tcr_irregular_scan_ex: the irregular scan with SCAN_EXCLUSIVE / OUT_F16 flags."""
+    if stream is None:
+        got = _native.irregular_scan(x, offsets, flags, out, "tcr_irregular_scan_ex" if flags else "tcr_irregular_scan")
+        if got is not None:
+            return got
     if not (x.is_cuda and x.dtype == torch.float16 and x.dim() == 1 and x.is_contiguous()):
         raise TypeError("input must be a contiguous 1-D float16 CUDA tensor")
     nseg = _check_offsets(x, offsets)
@@ -271,6 +317,10 @@ def irregular_scan_ex(x: torch.Tensor, offsets: torch.Tensor, flags: int, out: O
 def reduce(x: torch.Tensor, out: Optional[torch.Tensor] = None,
            stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
     """tcr_reduce: one-element tensor holding the sum of x."""
+    if stream is None:
+        got = _native.reduce(x, out)
+        if got is not None:
+            return got
     _check_input(x)
     if out is None:
         out = torch.empty(1, dtype=torch.float32, device=x.device)
@@ -283,6 +333,10 @@ def reduce(x: torch.Tensor, out: Optional[torch.Tensor] = None,
 def scan(x: torch.Tensor, out: Optional[torch.Tensor] = None,
          stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
     """tcr_scan: inclusive running sums of x."""
+    if stream is None:
+        got = _native.scan(x, 0, out, "tcr_scan")
+        if got is not None:
+            return got
     _check_input(x)
     if out is None:
         out = torch.empty(x.numel(), dtype=torch.float32, device=x.device)
@@ -331,6 +385,10 @@ def tuning_import(text: str) -> None:
 
 def segmented_moments(x: torch.Tensor, seg_len: int, stream: Optional[torch.cuda.Stream] = None):
     """tcr_segmented_moments: (sum, sum of squares) of every segment, two float32 tensors."""
+    if stream is None:
+        got = _native.segmented_moments(x, seg_len)
+        if got is not None:
+            return got
     _check_input(x)
     n = x.numel()
     count = n // seg_len if seg_len > 0 else 0
