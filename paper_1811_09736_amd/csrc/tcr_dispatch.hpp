@@ -1207,24 +1207,43 @@ inline bool rows_reduce_takes(uint64_t seg_len, int kind = kSum) {
     return g_variant.rows_reduce && seg_len >= (kind == kBoth ? kRowsMomentsMin : kRowsReduceMin) &&
            seg_len <= (kind == kBoth ? kRowsMomentsMax : kRowsReduceMax);
 }
+// A workgroup's share: 16320 elements by eight wavefronts, or, in arrays that do not give every compute unit several such workgroups, 8128 by
+// eight (1) or 4032 by four (2); in all of them whole segments.  us, the first against these, n in 2^20:
+//   both moments, 8128   25: 4 6.3/5.0, 16 12.7/11.8, 64 37.3/36.6, 128 68.9/68.8, 256 131.7/133.9; 33: 4 5.1/4.3, 16 9.6/9.1, 24 12.6/12.4, 32 15.9/16.1;
+//                        100: 1 3.9/3.5, 6 5.4/5.0, 20 10.7/10.4, 24 12.0/11.9, 32 14.8/15.0; 784: 2 3.9/3.6, 4 5.1/4.2, 6 5.4/4.9, 8 6.5/5.8,
+//                        20 10.3/10.1, 32 14.2/14.5; 1999: 8 6.3/5.9, 20 10.0/10.0; 2500: 8 6.4/5.9, 16 8.8/8.6, 20 10.0/10.1;
+//                        2999 (two segments): 8 6.4/6.4, 12 7.5/8.4
+//   sums, 4032           17: 1 3.7/3.6, 4 4.9/4.0, 8 6.5/5.7, 12 7.9/7.3, 14 8.3/8.2; 100: 2 3.6/3.8, 4 4.1/3.9, 8 5.2/5.0, 10 5.6/5.6, 12 6.4/6.2,
+//                        14 6.9/6.6; 784: 4 4.1/3.9, 12 6.5/6.1, 14 6.6/6.9; 2000: 4 4.0/3.9, 8 5.2/4.7, 12 6.3/6.0; 2500 (one): 6 4.3/5.0
+inline int rows_shape(uint64_t n, uint64_t seg_len, int kind) {
+    if (kind == kBoth) return seg_len <= 2709 && n <= (seg_len < 32 ? 1ull << 26 : seg_len <= 2032 ? 5ull << 22 : 1ull << 24) ? 1 : 0;
+    return seg_len <= 2016 && n <= (seg_len < 32 ? 7ull << 21 : 13ull << 20) && (seg_len < 32 || n > (3ull << 20)) ? 2 : 0;
+}
+template <int U, int W>
+inline void launch_rows_shape(const _Float16* in, float* out, float* out2, RowsGrid grid, int kind, hipStream_t s) {
+    grid.per_group = (uint32_t)((U * W * kTile - 64) / grid.seg_len);
+    const dim3 blocks((unsigned)ceil_div(grid.nseg, grid.per_group)), block(W * kWave);
+    if (grid.seg_len < 32) {             // 17 .. 31: two boundaries per row and a whole segment between them
+        if (kind == kBoth) rows_reduce_kernel<kBoth, U, W, 1><<<blocks, block, 0, s>>>(in, out, out2, grid);
+        else rows_reduce_kernel<kSum, U, W, 1><<<blocks, block, 0, s>>>(in, out, nullptr, grid);
+    } else {
+        if (kind == kBoth) rows_reduce_kernel<kBoth, U, W><<<blocks, block, 0, s>>>(in, out, out2, grid);
+        else rows_reduce_kernel<kSum, U, W><<<blocks, block, 0, s>>>(in, out, nullptr, grid);
+    }
+}
 inline tcr_status launch_rows_reduce(const _Float16* in, float* out, float* out2, uint64_t n, uint64_t seg_len, int kind,
                                      hipStream_t s) {
-    constexpr int U = 4, W = 8;
     const uint32_t shift = alignment_shift(in);
     RowsGrid grid;
     grid.seg_len = seg_len;
     grid.nseg = n / seg_len;
     grid.n = n + shift;
     grid.shift = shift;
-    grid.per_group = (uint32_t)(kRowsGroupElems / seg_len);
     grid.magic = (uint32_t)(((1ull << 32) + seg_len - 1) / seg_len);
-    const dim3 blocks((unsigned)ceil_div(grid.nseg, grid.per_group)), block(W * kWave);
-    if (seg_len < 32) {              // 17 .. 31: two boundaries per row and a whole segment between them
-        if (kind == kBoth) rows_reduce_kernel<kBoth, U, W, 1><<<blocks, block, 0, s>>>(in - shift, out, out2, grid);
-        else rows_reduce_kernel<kSum, U, W, 1><<<blocks, block, 0, s>>>(in - shift, out, nullptr, grid);
-    } else {
-        if (kind == kBoth) rows_reduce_kernel<kBoth, U, W><<<blocks, block, 0, s>>>(in - shift, out, out2, grid);
-        else rows_reduce_kernel<kSum, U, W><<<blocks, block, 0, s>>>(in - shift, out, nullptr, grid);
+    switch (rows_shape(n, seg_len, kind)) {
+        case 1: launch_rows_shape<2, 8>(in - shift, out, out2, grid, kind, s); break;
+        case 2: launch_rows_shape<2, 4>(in - shift, out, out2, grid, kind, s); break;
+        default: launch_rows_shape<4, 8>(in - shift, out, out2, grid, kind, s); break;
     }
     return check_launch("rows_reduce_kernel");
 }

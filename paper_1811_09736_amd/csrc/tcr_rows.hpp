@@ -19,7 +19,7 @@
 // product each, whose row sum is that segment's result as it stands (dispatched from 17 elements on: one whole
 // segment per row at most; with two or three, 9 to 15 elements, the kernel is no faster than the fixed tiles).
 //
-// A workgroup owns WHOLE segments (as many as fit into 16320 elements), so no sum crosses workgroups: one
+// A workgroup owns WHOLE segments (as many as fit into its sub-tiles but two rows), so no sum crosses workgroups: one
 // launch, no workspace, the same order of additions in every run.  Its rows are rows of the ARRAY (aligned 64-byte
 // pieces from the 16-byte boundary at or below `in`), so every load is an aligned 128-bit load in the operand
 // layout; the pieces of its first and last row that belong to a neighbour's segments are masked away like any
@@ -40,8 +40,7 @@ struct RowsGrid {
     uint32_t magic;         // ceil(2^32 / seg_len): x / seg_len == umulhi(x, magic) for x * seg_len < 2^32
 };
 
-constexpr uint32_t kRowsGroupElems = 16320;       // a workgroup's segments span at most 512 rows of 32 elements
-constexpr uint64_t kRowsMaxSegLen = 8160;         // at least two segments per workgroup
+constexpr uint64_t kRowsMaxSegLen = 8160;         // at least two segments per workgroup of 32 sub-tiles
 
 // Inclusive segmented scan over the 16 lanes of each row of lanes (the 16 data rows of a sub-tile, held
 // redundantly by the four lane rows).
@@ -61,8 +60,8 @@ template <int KIND, int U, int WAVES, int WHOLES = 0>
 __global__ __launch_bounds__(WAVES * kWave) void rows_reduce_kernel(const _Float16* __restrict__ in,
                                                                     float* __restrict__ out, float* __restrict__ out2,
                                                                     RowsGrid grid) {
+    // (a workgroup's segments span at most its U * WAVES * 16 rows: all its elements but two rows of them)
     static_assert(KIND == kSum || KIND == kBoth, "");
-    static_assert(U * WAVES * 16 >= 512, "a workgroup's rows must fit its sub-tiles");
     constexpr int CH = channels<KIND>();
     __shared__ float s_wave_value[CH][WAVES];
     __shared__ uint32_t s_wave_flag[WAVES];
@@ -76,7 +75,7 @@ __global__ __launch_bounds__(WAVES * kWave) void rows_reduce_kernel(const _Float
     const uint64_t begin = s0 * grid.seg_len + grid.shift;                       // positions count from the aligned base
     const uint64_t end = begin + (uint64_t)count * L;
     const uint64_t row_lo = begin >> 5;
-    const uint32_t nrows = (uint32_t)(((end + 31) >> 5) - row_lo);               // <= 512
+    const uint32_t nrows = (uint32_t)(((end + 31) >> 5) - row_lo);               // <= 16 U WAVES
     const int d0 = (int)(begin & 31);                                            // the first segment starts at column d0 of row 0
 
     // the workgroup's rows as a buffer: rows beyond them (and elements beyond the array) read as zero
