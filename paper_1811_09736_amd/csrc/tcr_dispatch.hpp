@@ -1270,16 +1270,42 @@ inline void launch_packed_shape(const _Float16* in, float* out, float* out2, con
     const size_t staging = (size_t)W * channels<KIND>() * 16 * U * grid.per_row * sizeof(float);      // at most 40 KiB
     packed_rows_reduce_kernel<KIND, U, W><<<dim3((unsigned)ceil_div(rows, (uint64_t)(16 * U * W))), dim3(W * kWave), staging, s>>>(in, out, out2, grid);
 }
+// Fewer tiles per wavefront in smaller arrays, where rows of no multiple of 8 elements take eight: a wavefront's tiles follow each other, and for the
+// squares each is a product per segment of the row.  us, eight against fewer, n in 2^20:
+//   both moments   one    3: 1/16 11.5/4.2, 1 12.0/5.7; 7: 1/16 6.6/3.5, 1 6.7/3.7, 2 7.0/5.0 (two 4.9)
+//                  two    3: 3 12.7/8.8; 7: 2 7.0/4.9, 4 8.6/6.2; 15: 4 6.4/4.9; 22: 4 5.4/4.6
+//                  four   3: 5 15.6/11.9, 12 21.8/20.0, 64 82.1/72.0, 128 145/133; 5: 8 14.3/12.4, 24 25.2/23.4, 32 30.4/29.6, 64 48.2/49.1; 7: 8 10.8/9.6,
+//                         12 14.2/12.9, 24 19.8/20.5; 9: 8 9.0/8.6, 12 12.0/12.1, 16 14.3/14.6; 15: 12 10.0/9.3; 22: 12 9.1/8.6, 16 9.8/10.8
+//   sums           two    3: 3 4.4/3.8; 7: 1 3.8/3.4, 4 4.7/3.7; 15: 4 4.6/3.7; 22: 3 4.3/3.8
+//                  four   3: 6 6.2/5.5, 12 9.8/9.1, 16 11.4/12.2; 7: 8 6.0/5.3, 12 7.6/7.0; 15: 10 6.0/5.7; 22: 8 5.3/5.0, 12 6.8/7.2
+inline int packed_tiles(uint64_t n, uint32_t per_row, int kind) {
+    if (kind == kBoth && n <= (5ull << 18)) return 1;
+    if (n <= (9ull << 19)) return 2;
+    if (kind == kBoth) return n <= (3ull << 22) || per_row >= 10 || (per_row >= 6 && n <= (1ull << 25)) ? 4 : 8;
+    return n <= (11ull << 20) ? 4 : 8;
+}
+// Both moments of 4 and 8 elements: whole segments inside a lane's eight.  us, packed rows against this, n in 2^20: 4 elements 1/16 5.8/3.7, 4 8.0/3.8,
+// 8 12.5/7.3, 16 18.0/13.2, 64 51.1/42.9, 256 192/167 (two groups of eight per lane: 64 40.7 against 41.7 with one, 256 185 against 171); 8 elements 1
+// 4.4/3.9, 8 8.0/5.1, 16 12.8/10.4, 64 36/34.6, 256 138/131 (one group: 8 5.1 against 4.7, 256 132 against 130).
+inline tcr_status launch_tiny_moments(const _Float16* in, float* sum, float* sumsq, uint64_t n, uint64_t seg_len, hipStream_t s) {
+    if (seg_len == 4) tiny_moments_kernel<2, 1><<<dim3((unsigned)ceil_div(n, 8 * kGenericThreads)), dim3(kGenericThreads), 0, s>>>(in, sum, sumsq, n);
+    else tiny_moments_kernel<3, 2><<<dim3((unsigned)ceil_div(n, 16 * kGenericThreads)), dim3(kGenericThreads), 0, s>>>(in, sum, sumsq, n);
+    return check_launch("tiny_moments_kernel");
+}
 // alt: the other launch shape than the one the row width calls for.
 inline tcr_status launch_packed_reduce(const _Float16* in, float* out, float* out2, uint64_t n, uint64_t seg_len, int kind,
                                        hipStream_t s, bool alt = false) {
     const PackedGrid grid = {n, n / seg_len, (uint32_t)seg_len, packed_per_row(seg_len)};
     const bool four = ((grid.seg_len * grid.per_row) % 8u == 0) != alt;
+    const int tiles = four ? 4 : (alt ? 8 : packed_tiles(n, grid.per_row, kind));
     if (kind == kBoth) {
-        if (four) launch_packed_shape<kBoth, 4, 4>(in, out, out2, grid, s);
+        if (tiles == 1) launch_packed_shape<kBoth, 1, 4>(in, out, out2, grid, s);
+        else if (tiles == 2) launch_packed_shape<kBoth, 2, 4>(in, out, out2, grid, s);
+        else if (tiles == 4) launch_packed_shape<kBoth, 4, 4>(in, out, out2, grid, s);
         else launch_packed_shape<kBoth, 8, 4>(in, out, out2, grid, s);
     } else {
-        if (four) launch_packed_shape<kSum, 4, 4>(in, out, nullptr, grid, s);
+        if (tiles == 2) launch_packed_shape<kSum, 2, 4>(in, out, nullptr, grid, s);
+        else if (tiles == 4) launch_packed_shape<kSum, 4, 4>(in, out, nullptr, grid, s);
         else launch_packed_shape<kSum, 8, 4>(in, out, nullptr, grid, s);
     }
     return check_launch("packed_rows_reduce_kernel");
@@ -1474,6 +1500,7 @@ inline tcr_status launch_moments(const _Float16* in, float* sum, float* sumsq, u
         }
         return check_launch("moments_small_kernel");
     }
+    if ((seg_len == 4 || seg_len == 8) && aligned(in, 16)) return launch_tiny_moments(in, sum, sumsq, n, seg_len, s);
     if (packed_reduce_takes(seg_len) && aligned(in, 4)) return launch_packed_reduce(in, sum, sumsq, n, seg_len, kBoth, s);
     if (rows_reduce_takes(seg_len, kBoth)) return launch_rows_reduce(in, sum, sumsq, n, seg_len, kBoth, s);
     if (seg_len >= kTiledMomentsMin && seg_len < kTiledReduceMax) {

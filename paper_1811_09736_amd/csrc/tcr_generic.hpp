@@ -80,6 +80,50 @@ __global__ __launch_bounds__(kGenericThreads) void tiny_reduce_kernel(const _Flo
     }
 }
 
+// Both moments of segments of 4 or 8 elements, whole inside a lane's 8, U groups of 8 per lane.  Added in binary64, which is free here and
+// rounds once (in binary32, two elements per v_dot2_f32_f16: squares of 8 elements 3.4e-8 off, one rounding 2.5e-8, the packed rows 2.6e-8).
+// Bound: memory (64 * 2^20 elements in segments of 4, 268 MB, 43 us).
+template <int LOG2L, int U>
+__global__ __launch_bounds__(kGenericThreads) void tiny_moments_kernel(const _Float16* __restrict__ in, float* __restrict__ sum,
+                                                                       float* __restrict__ sumsq, uint64_t n) {
+    static_assert(LOG2L == 2 || LOG2L == 3, "");
+    constexpr int kResults = 8 >> LOG2L;
+    const uint64_t first = ((uint64_t)blockIdx.x * U * kGenericThreads + threadIdx.x) * 8;
+    half8 x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = load8_guarded<true>(in, first + (uint64_t)(u * 8 * kGenericThreads), n);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint64_t g = first + (uint64_t)(u * 8 * kGenericThreads);
+        float a[kResults], q[kResults];
+#pragma unroll
+        for (int i = 0; i < kResults; ++i) {
+            double sum64 = 0.0, squares64 = 0.0;
+#pragma unroll
+            for (int e = 0; e < (1 << LOG2L); ++e) {
+                const double v = (double)(float)x[u][(i << LOG2L) + e];
+                sum64 += v;
+                squares64 = __builtin_fma(v, v, squares64);
+            }
+            a[i] = (float)sum64;
+            q[i] = (float)squares64;
+        }
+        if (g + 8 <= n) {
+            if constexpr (kResults == 2) {
+                typedef float pair __attribute__((ext_vector_type(2), aligned(4)));       // (results are aligned to their size only)
+                *reinterpret_cast<pair*>(sum + (g >> LOG2L)) = (pair){a[0], a[1]};
+                *reinterpret_cast<pair*>(sumsq + (g >> LOG2L)) = (pair){q[0], q[1]};
+            } else {
+                sum[g >> LOG2L] = a[0];
+                sumsq[g >> LOG2L] = q[0];
+            }
+        } else if (kResults == 2 && g + 4 <= n) {
+            sum[g >> LOG2L] = a[0];
+            sumsq[g >> LOG2L] = q[0];
+        }
+    }
+}
+
 // The inclusive scan of segments of 1, 2, 4 or 8 elements: running sums inside a lane's 8 elements, restarted
 // every 1 << LOG2L of them (seg_len 1: the conversion again).
 template <int LOG2L>
