@@ -54,7 +54,8 @@ __device__ __forceinline__ float open_tile_sum(const TileScan& a, uint32_t t, ui
 }
 
 // One wavefront: the sum from position s0 to the start of `tile` out of what the tiles in between have published, 64 at a time, the
-// nearest first; false if one of them is not there after `patience` looks.
+// nearest first.  What is not there after `patience` looks is added up from the elements, or (GIVE_UP) the result is false.
+template <bool GIVE_UP>
 __device__ __forceinline__ bool lookup_open_sum(const TileScan& a, const ScanWorkspace& ws, uint32_t tile, uint64_t s0, int tile_log2, int lane,
                                                 float& sum) {
     const uint32_t first = (uint32_t)(s0 >> tile_log2);
@@ -72,8 +73,17 @@ __device__ __forceinline__ bool lookup_open_sum(const TileScan& a, const ScanWor
                     need = false;
                 }
             }
-            if (__ballot(need) == 0ull) break;
-            if (__builtin_expect(++polls > a.patience, 0)) return false;
+            unsigned long long missing = __ballot(need);
+            if (missing == 0ull) break;
+            if (++polls > a.patience) {
+                if constexpr (GIVE_UP) return false;
+                for (; missing != 0ull; missing &= missing - 1ull) {
+                    const int slot = __builtin_ctzll(missing);
+                    const float elements = open_tile_sum(a, hi - 1u - (uint32_t)slot, s0, tile_log2, lane);
+                    if (lane == slot) v = elements;
+                }
+                break;
+            }
             __builtin_amdgcn_s_sleep(1);
         }
         acc += v;
@@ -137,6 +147,14 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
         }
     };
     if constexpr (REGULAR) load_share();
+    // Irregular tiles that search for themselves, all at the same time: what every wavefront asked for in front of the search each of its rounds
+    // would wait behind (lognormal lengths in 2^24 elements 24.4 us), and behind it memory idles during the search.  So in every other
+    // workgroup of an XCD (they follow each other in eights) the wavefronts that do not search ask for their elements first: lognormal lengths / segments of 16 / of 200
+    // / one segment, 2^24 elements, 21.2 / 23.6 / 21.5 / 25.0 -> 20.4 / 23.1 / 20.5 / 24.3; in every workgroup 21.5, in three of four 21.0,
+    // in every other one all wavefronts 20.8.
+    constexpr bool STAGGERED = !REGULAR && !GUIDED && U == 4 && WAVES == 8;
+    const bool early = STAGGERED && wave >= 2 && (blockIdx.x & 8u) != 0u;
+    if (early) load_share();
 
     // where the open segment starts (tb: nothing reaches into the tile), and which part of the array lies in a segment
     uint64_t s0 = tb, first = a.shift, last = a.n;
@@ -173,8 +191,8 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
             first = a.offsets[0] + a.shift;
             last = a.offsets[a.nseg] + a.shift;
             if (last > a.n) last = a.n;
-            __syncthreads();
-            load_share();
+            lds_barrier();
+            if (!early) load_share();
             const uint64_t lo = s_bound[0], hi = s_bound[1];
             has_heads = lo < hi;
             for (uint64_t s = lo + threadIdx.x; s < hi; s += (uint64_t)(WAVES * kWave)) mark(a.offsets[s]);
@@ -317,15 +335,18 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
             }
             if (far) {
                 float pre = 0.0f;
+                constexpr bool AGAIN = RELAY || (U == 4 && !F16);      // (elements asked for again by a wavefront that has waited in vain)
                 bool got;
                 if constexpr (RELAY) got = relay_wait(ws, gridDim.x - 1u, tile, a.patience, pre);
-                else got = lookup_open_sum(a, ws, tile, s0, kTileLog2, lane, pre);
-                if (__builtin_expect(!got, 0)) {
-                    pre = add_up_in_front<RELAY>(ws, gridDim.x - 1u, (uint32_t)(s0 >> kTileLog2), tile,
-                                                 [&](uint32_t t) { return open_tile_sum(a, t, s0, kTileLog2, lane); });
-                    if constexpr (U >= 4 && !F16) {
-                        load_share();
-                        load_cut_group();
+                else got = lookup_open_sum<AGAIN>(a, ws, tile, s0, kTileLog2, lane, pre);
+                if constexpr (AGAIN) {
+                    if (__builtin_expect(!got, 0)) {
+                        pre = add_up_in_front<RELAY>(ws, gridDim.x - 1u, (uint32_t)(s0 >> kTileLog2), tile,
+                                                     [&](uint32_t t) { return open_tile_sum(a, t, s0, kTileLog2, lane); });
+                        if constexpr (U >= 4 && !F16) {
+                            load_share();
+                            load_cut_group();
+                        }
                     }
                 }
                 if (lane == 0) s_back[0] = pre;
