@@ -426,7 +426,8 @@ inline void launch_scan_block(const _Float16* in, void* out, uint64_t n, uint64_
 // Ids 10 and 11 are scan_chain_kernel: persistent workgroups (one per compute unit) that take
 // 32768-element tiles by ticket in a loop and keep three in flight (loading, aggregate published,
 // carry looked up and stored); for segments of at least one tile and the one-segment scan,
-// n a multiple of 8.  Id 10 runs arrays that the chip holds all at once as one tile per workgroup (once_share).
+// n a multiple of 8.  Id 10 runs most arrays as one tile per workgroup: those that the chip holds all at once (once_share) and, with
+// carries from the relay, larger ones (chain_relayed).
 struct ScanShape { int u, w; bool ticket; int persistent; };      // persistent: workgroups per compute unit (0: one per tile)
 constexpr ScanShape kScanShapes[] = {{1, 2, false, 0}, {1, 4, false, 0}, {1, 8, false, 0}, {1, 16, false, 0},
                                      {2, 16, false, 0}, {4, 16, false, 0}, {8, 16, false, 0}, {2, 16, true, 0},
@@ -475,7 +476,7 @@ inline int default_scan_shape(uint64_t n, uint64_t len, bool whole, int form) {
     // the pipelined chain: segments of 32768 and more, one segment with n % 8 == 0.  (16 wavefronts of 4 tiles
     // for the matrix cores; the DPP arithmetic needs more registers and takes 8 wavefronts of 8 tiles.)
     if (scan_shape_valid(10, len, whole)) return form == kMfma ? 10 : 11;
-    // n not a multiple of 8: the chain over the whole groups of 8 and a second, tiny kernel for the rest (measured
+    // n not a multiple of 8: one tile per workgroup where id 10 has that, else the chain over the whole groups of 8 and a second, tiny kernel for the rest (measured
     // at n = 2^28 - 3: 297 us against 307-323 us for scan_block_kernel with decoupled look-back, which short arrays keep)
     if (scan_shape_valid(kScanIdChainTail, len, whole)) return kScanIdChainTail;
     if (whole && len < (1u << 16)) return 7;       // a few shares (n = 2^15: 5.2 us against 7.4 with one large share)
@@ -560,7 +561,7 @@ tcr_status launch_chain_once(const _Float16* in, void* out, uint64_t n, uint64_t
 // words of the table per tile.  us, the persistent chain against this, n in 2^20, full scan:
 //   binary32   n = 16.001  26.8/21.0   20  30.5/25.1   24  39.5/33.2   32  46.0/42.5   64  81.2/74.8   128  148/140   256  281/270   512  546/531
 //   binary16       16.001  21.0/17.2   20  22.9/18.7   24  24.4/20.7   32  30.9/26.8   64  53.2/50.0   128  96.6/96.5   160  117/118   256  181/183
-// (segments of 65536: 20 30.0/25.3, 256 276/271; of 65544: 24 44.2/34, 64 89.1/78.6, 128 160/148.)  And where one tile per compute unit would
+// (segments of 65536: 20 30.0/25.3, 256 276/271; of 65544: 24 44.2/36.4, 64 89.1/78.6, 128 160/148.)  And where one tile per compute unit would
 // have to be one of 65536 elements (kChainOnce) and segments are long, full scan of 8.001 / 9 / 10 / 11 / 12 15.5/13.4, 15.7/14.3, 16.0/14.8, 16.3/15.8,
 // 16.6/16.5; segments of 262144 9 / 11 15.1/14.3, 15.7/15.8; of 65536 9 14.2/14.3; binary16 10 9.8/12.5.
 constexpr uint64_t kRelayTile = (uint64_t)(kTile * 4 * kRelayWaves);

@@ -18,9 +18,10 @@
 //                         from earlier workgroups either by single-pass decoupled look-back
 //                         (CARRY == kLookback) or from a precomputed table of exclusive prefixes
 //                         (CARRY == kTable, the reduce-then-scan alternative).
-//   scan_chain_kernel     the same single pass for segments of 32768 elements and more as a
-//                         persistent three-stage pipeline (the dispatched device-level scan,
-//                         Section 5, for the matrix-core formulation).
+//   scan_chain_kernel     the same single pass for segments of 32768 elements and more (the dispatched
+//                         device-level scan, Section 5, for the matrix-core formulation): one tile
+//                         per workgroup, which looks its carry up or gets it from the relay
+//                         (tcr_relay.hpp), or a persistent three-stage pipeline.
 //   scan_partials_kernel, gather_totals_kernel, uniform_add_kernel
 //                         the small kernels of the multi-kernel strategies (reduce-then-scan, and
 //                         the paper's scan-then-propagate).
