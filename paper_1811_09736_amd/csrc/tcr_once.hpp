@@ -373,9 +373,10 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
     const uint32_t valid_lo = first > base ? (uint32_t)(first - base < kChunk ? first - base : kChunk) : 0u;
     const uint32_t valid_hi = last > base ? (uint32_t)(last - base < kChunk ? last - base : kChunk) : 0u;
     // LATE: the sum in front may be millions of times an element, and is added once, behind the sums of the tile, not in front of
-    // a lane's eight additions.  Where workgroups follow each other the two more operations per element are free; where all
-    // run at once they cost 5 to 10 % (seven segments in 2^24 elements: 23.5 us, 25.3 with them).
-    constexpr bool LATE = RELAY;
+    // a lane's eight additions.  Where workgroups follow each other (the relay, and regular tiles beyond what the chip holds at once,
+    // MOST < 8) the two more operations per element are free; where all run at once they cost 5 to 10 % (seven segments in 2^24
+    // elements: 23.5 us, 25.3 with them).
+    constexpr bool LATE = RELAY || (!LOCAL && MOST < 8);
     const bool inside = valid_lo == 0u && valid_hi == kChunk && a.vector_stores != 0u;
     void* const dst = F16 ? static_cast<void*>(static_cast<_Float16*>(a.out) + base) : static_cast<void*>(static_cast<float*>(a.out) + base);
 #pragma unroll
