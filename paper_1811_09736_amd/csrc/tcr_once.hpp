@@ -99,9 +99,9 @@ __device__ __forceinline__ bool lookup_open_sum(const TileScan& a, const ScanWor
 // wavefronts add up themselves (segments of 16 in 2^27 elements 165 us, 174 where all wait; seven segments 151 and 149).  Their
 // entries are found with one search of two rounds around where they are likely to be (GUIDED), not two of four over the whole array.
 // Registers: at most 64, so that 8 wavefronts per SIMD run.  A wavefront that has waited in vain loads its elements again behind the
-// additions, so that they need not be held across them: 45 to 47 registers where four sub-tiles took 64 and 44 bytes of scratch
+// additions, so that they need not be held across them: 43 to 49 registers where four sub-tiles took 64 and 44 bytes of scratch
 // (lognormal lengths / segments of 16 / seven segments in 2^24 elements 21.7 / 23.9 / 23.6 -> 21.0 / 23.5 / 22.7 us).  Not with fewer
-// sub-tiles, which lose 2 to 5 %, nor with binary16 results (15.7 -> 16.0): 64 registers, 20 to 64 bytes.
+// sub-tiles, which lose 2 to 5 %, nor with binary16 results (15.7 -> 16.0): 64 registers, 20 to 68 bytes.
 // MOST: wavefronts per SIMD at most.
 template <int U, int WAVES, bool REGULAR, int MODE, bool LOCAL, bool RELAY = false, int MOST = 8>
 __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U < 4 ? 4 : MOST, MOST))) void tile_scan_kernel(TileScan a, ScanWorkspace ws_arg) {

@@ -1,7 +1,10 @@
 """Rounding of scans of fractions against 64 bits, counted in roundings of a result's size: the error's 2-norm over the one that a single rounding of
 every result leaves, squared.  Whole numbers, which most tests use, are exact in any order of additions; these limits lie between two orders."""
+import numpy as np
 import pytest
 import torch
+
+from paper_1811_09736_amd import workloads
 
 pytestmark = pytest.mark.gpu
 
@@ -45,4 +48,29 @@ def test_the_sum_in_front_is_added_once(tcr, seg, limit, flags):
     if flags & tcr.SCAN_EXCLUSIVE:
         want -= x.double().view(-1, seg)
     got = tcr.segmented_scan_ex(x, seg, flags).view(-1, seg)
+    assert roundings(got, want) < limit
+
+
+# A tile that has waited in vain adds up what is in front of it by itself (the look-up of arrays that the chip holds at once, the relay of larger
+# ones), and which tiles do is a matter of time: no more roundings than where all wait.  Waiting / adding up here: 9.5 / 8.5, 9.4 / 8.5, 5.3 / 6.2, 2.8 /
+# 3.7, 2.8 / 2.9; with the sums of the tiles added one after the other in binary32 156, 56, 6.2, 3.9, 3.8.
+@pytest.mark.parametrize("call,n,limit", [("one", 7 << 20, 11.0), ("one", 11 << 20, 11.0), ("scan", 3 << 24, 7.5), ("seven", 3 << 24, 4.5), ("rows", 3 << 24, 4.0)])
+@pytest.mark.parametrize("wait", ["bounded", "none"])
+def test_tiles_that_help_themselves(tcr, call, n, limit, wait):
+    x = fractions(n)
+    sums = torch.cumsum(x.double(), 0)
+    tcr.set_variant("scan_wait", wait)
+    try:
+        if call == "scan":
+            got, want = tcr.scan(x), sums
+        elif call == "rows":
+            m = n - n % 1000003
+            got, want = tcr.segmented_scan(x[:m], 1000003), torch.cumsum(x[:m].double().view(-1, 1000003), 1).view(-1)
+        else:
+            off = torch.tensor([0, n]) if call == "one" else torch.from_numpy(workloads.make_offsets(n, "few7", 5).view(np.int64))
+            off = off.cuda()
+            got = tcr.irregular_scan(x, off)
+            want = sums - torch.repeat_interleave(torch.cat([sums.new_zeros(1), sums])[off[:-1]], off[1:] - off[:-1])
+    finally:
+        tcr.set_variant("reset")
     assert roundings(got, want) < limit
