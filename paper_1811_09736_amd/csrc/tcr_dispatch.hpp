@@ -917,21 +917,35 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
 //   (the largest loss of those with more than a few elements, lognormal at 18: 26.5/27.6)
 // Regular segments and seven irregular ones, of more than 2^20 elements on average: binary32 from 12 * 2^20 elements on (3000003 at 14.3: 21.7/19.4, 22.9: 32.6/30.8, 62.9:
 // 91.3/76.7, 126: 167.9/143.8; seven at 12 / 14 / 16 18.6/18.4, 21.6/19.9, 22.8/21.5).
-// Other regular ones, beyond 2^24, by length and type (chained tiles, which took some lengths of 4097 to 8191 elements: 64 85, 128 152, 256 287; binary16
-// 64 50, 128 102, 256 190):
-//   binary32   5001: 20 27.7/26.6, 24 33.2/34.3, 32 43.0/44.4, 48 61.0/61.8, 56 70.2/69.4, 128 151/146, 256 296/281; 8001: 17 23.2/22.9, 24 34.7/34.3,
-//              64 81.8/78.2, 128 157/146, 256 306/281; 9001 (looked up): 24 33.0/33.7, 64 76.3/78.0, 256 275/281; 30003: 20 26.3/26.3, 64 77.9/77.7,
-//              256 278/281; 50003: 17 22.9/22.3, 64 78.8/78.0; 100003: 17 23.1/22.3, 64 80.0/78.0, 128 148.2/145.2
+// Other regular ones, beyond 2^24, by length, type and alignment (chained tiles, which took some lengths of 4097 to 8191 elements: 64 85, 128 152, 256 287;
+// binary16 64 50, 128 102, 256 190):
+//   binary32   5001: 32 43.0/44.4, 48 61.0/61.8, 56 70.2/69.4, 128 151/146, 256 296/281; 8191: 18 28.4/28.9, 24 35.1/37.0 (from the memory-side cache 17
+//              20.6/22.1), 28 equal, 64 81.8/78.2, 128 159/146, 256 313/281; 9001 (looked up): 24 33.0/33.7, 64 76.3/78.0, 256 275/281; 30003: 20 26.3/26.3,
+//              64 77.9/77.7, 256 278/281; 50003: 17 22.9/22.3, 64 78.8/78.0; 100003: 17 23.1/22.3, 64 80.0/78.0, 128 148.2/145.2
 //   binary16   2001: 64 49.8/50.3, 256 187/181; 3001: 48 39.8/41.9, 64 51.2/50.1, 128 97.9/94.5, 256 191/181; 5001: 17 17.0/18.1, 24 21.7/21.7, 28 26.9/25.1,
-//              64 60.3/50.6; 8001: 17 18.2/18.1, 20 20.5/19.4, 64 62.4/50.4; 30003: 17 16.9/18.1, 32 26.8/28.3; 500003: 17 17.9/18.9, 28 24.9/25.9, 32 29.2/27.5,
-//              48 44.3/42.6; 3000003: 17 18.8/18.9, 23 22.5/21.6, 26 25.0/23.7
-inline bool tiles_relayed(uint64_t n, uint64_t nseg, uint64_t seg_len, bool regular, bool f16) {
+//              64 60.3/50.6; 8001: 17 18.2/18.1, 20 20.5/19.4, 64 62.4/50.4; 9001: 48 34.2/36.9, 128 92.5/97.1, 256 179/184; 40000: 128 95.1/97.6, 256 184/187;
+//              100003: 48 3 % less, 128 97.7/98.5, 256 187/186; 500003: 17 17.9/18.9, 28 24.9/25.9, 32 29.2/27.5, 48 44.3/42.6; 3000003: 17 18.8/18.9,
+//              23 22.5/21.6, 26 25.0/23.7
+// Where input or results lie off a 16-byte boundary, results are stored by element, twice the time, and tiles that store in the order of the array are in each other's
+// way:  binary32  5001: 64 6 % less, 256 701/735; 8191: 18 57.2/60.5, 24 73.4/78.8, 128 356/374, 256 702/734; 40000: 18 63.5/60.0, 24 78.3/78.4, 48 5 % less, 128
+//                 363/374; 100003: 18 64.7/60.7, 128 366/374; 500003: 64 5 % more, 256 7 % more
+//       binary16  3001: 128 194/211, 256 385/412; 5001: 28 51.7/54.2, 36 65.5/66.7, 48 85.4/85.3, 64 112/108, (chained tiles) 96 159/160, 128 205/210,
+//                 256 393/411; 9001: 48 8 % less, 256 379/408; 262168: 48 4 % less, 256 8 % less; 1000003: equal
+inline bool tiles_relayed(uint64_t n, uint64_t nseg, uint64_t seg_len, bool regular, bool f16, bool vector_stores) {
     const bool far = nseg << 20 < n;                     // more than 2^20 elements a segment
     if (n <= scan_held_max()) return far && !f16 && n > (3ull << 22);
     if (!regular) return n <= (9ull << 24);
     if (far) return true;
-    if (f16) return seg_len > 2048 && n > (seg_len > kLocalMax ? 5ull << 23 : seg_len > 4096 ? 3ull << 23 : 15ull << 22);
-    return seg_len > 32768 || (seg_len > 4096 && seg_len <= kLocalMax && (seg_len > 6144 || n > (13ull << 22)));
+    if (!vector_stores && f16) return seg_len > 4096 && seg_len <= kLocalMax && n > (5ull << 23) && n <= (3ull << 25);
+    if (!vector_stores) return seg_len > (1ull << 18) || (seg_len > 32768 && n <= (5ull << 23));
+    if (f16 && seg_len > kLocalMax) return seg_len > (1ull << 18) && n > (5ull << 23);
+    if (f16) return seg_len > 2048 && n > (seg_len > 4096 ? 3ull << 23 : 15ull << 22);
+    return seg_len > 32768 || (seg_len > 4096 && seg_len <= kLocalMax && n > (seg_len > 6144 ? 13ull << 21 : 13ull << 22));
+}
+// And the only regular ones that are chained: binary16 results by element, where the open part costs more cache bandwidth to add up again than a look-back costs
+// (above: 205 us, 216 where each tile adds it up).
+inline bool tiles_chained(uint64_t n, uint64_t seg_len, bool f16, bool vector_stores) {
+    return f16 && !vector_stores && seg_len > 4096 && seg_len <= kLocalMax && n > (3ull << 25);
 }
 
 template <int MODE>
@@ -950,8 +964,9 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
     // holds at once, irregular ones.  n = 2^20 / 2^24 / 2^26, us, by ticket and look-back against this: seg_len 1001 8.2 / 27 / 85 against
     // 4.1 / 22.8 / 74; 100003 8.7 / 28 / 89 against 5.1 / 20.4 / 78; irregular, lognormal lengths 10.9 / 31.8 against 5.5 / 21.0.
     const bool alone = shape == 0 && g_variant.formulation == kMfma && (regular ? seg_len >= 2 : g_variant.irregular_scan == 0);
-    const bool relay = alone && tiles_relayed(n, nseg, seg_len, regular, (MODE & 2) != 0);
-    if (alone && !relay && (regular || n <= scan_held_max())) return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, false, s);
+    const bool relay = alone && tiles_relayed(n, nseg, seg_len, regular, (MODE & 2) != 0, vector_stores != 0);
+    const bool chained = alone && !relay && regular && tiles_chained(n, seg_len, (MODE & 2) != 0, vector_stores != 0);
+    if (alone && !relay && !chained && (regular || n <= scan_held_max())) return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, false, s);
     Workspace* ws = nullptr;
     bool capturing = false;
     tcr_status st = get_workspace(s, &ws, &capturing);
@@ -969,6 +984,7 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
         const bool room_chained = (two_kernels ? 2 * tiles : tiles) <= limit && (regular || 2 * irregular_words(true, n, shape) <= partials_limit(ws, capturing));
         if (room || room_once || !room_chained || n <= scan_held_max()) return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, room, s);
     }
+    if (chained && !table_has_room(ws, tiles, capturing)) return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, false, s);
     if (!regular) {
         st = ensure_partials(ws, s, 2 * irregular_words(true, n, shape), capturing);
         if (st != TCR_OK) return st;
