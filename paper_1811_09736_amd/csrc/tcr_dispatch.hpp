@@ -818,17 +818,17 @@ inline uint32_t search_grid_log2(uint64_t nseg) {
 }
 
 // One tile per workgroup (tcr_once.hpp).  in, out, n: already counted from the 16-byte boundary below the caller's array.
-template <int U, int W, int MODE, bool LOCAL, bool RELAY = false>
+template <int U, int W, int MODE, bool LOCAL, int SUMS = kSumsWide>
 inline void launch_tile_scan(const TileScan& a, const ScanWorkspace& dev, hipStream_t s) {
-    const dim3 grid((unsigned)ceil_div(a.n, (uint64_t)(kTile * U * W)) + (RELAY ? 1u : 0u)), block(W * kWave);
-    if (LOCAL || a.offsets == nullptr) tile_scan_kernel<U, W, true, MODE, LOCAL, RELAY><<<grid, block, 0, s>>>(a, dev);
-    else if constexpr (!LOCAL) tile_scan_kernel<U, W, false, MODE, false, RELAY><<<grid, block, 0, s>>>(a, dev);
+    const dim3 grid((unsigned)ceil_div(a.n, (uint64_t)(kTile * U * W)) + (SUMS == kSumsRelayed ? 1u : 0u)), block(W * kWave);
+    if (LOCAL || a.offsets == nullptr) tile_scan_kernel<U, W, true, MODE, LOCAL, SUMS><<<grid, block, 0, s>>>(a, dev);
+    else if constexpr (!LOCAL) tile_scan_kernel<U, W, false, MODE, false, SUMS><<<grid, block, 0, s>>>(a, dev);
 }
 // Up to here the compute units hold all workgroups at once (256 units: 2^24 elements).
 inline uint64_t scan_held_max() { return (uint64_t)compute_units() * (uint64_t)(kTile * 16 * 8); }
 template <int MODE>
 inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, void* out, uint64_t n, uint64_t nseg, uint64_t seg_len,
-                                   uint32_t shift, bool fill, bool relay, hipStream_t s) {
+                                   uint32_t shift, bool fill, TileSums sums, hipStream_t s) {
     TileScan a = {};
     a.in = in;
     a.offsets = offsets;
@@ -850,7 +850,7 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
         a.grid_log2 = search_grid_log2(nseg);
     }
     ScanWorkspace dev = {};
-    if (local && !relay) {
+    if (local && sums == kSumsWide) {
         a.magic = (uint32_t)(((1ull << 32) + seg_len - 1) / seg_len);
         // 8 wavefronts, so that the open part is a small share of what a workgroup reads -- unless segments are short and
         // the array streams from memory (seg_len 33 at n = 2^24 / 2^26 / 2^28: 23.2 / 74.8 / 285 us with 8, 23.6 / 73.3 /
@@ -865,10 +865,16 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
     tcr_status st = get_workspace(s, &ws, &capturing);
     if (st != TCR_OK) return st;
     const uint64_t limit = table_limit(ws, capturing);
-    if (relay) {
-        st = begin_lookback(ws, s, 2 * ceil_div(n, kRelayTile), &dev, capturing);
+    if (sums != kSumsWide) {
+        const uint64_t tiles = ceil_div(n, kRelayTile);
+        // (looked-up sums need one; asked for where it can be had, so that the same call can be recorded with other offsets)
+        st = begin_lookback(ws, s, sums == kSumsLookedUp && 2 * tiles > limit ? tiles : 2 * tiles, &dev, capturing);
         if (st != TCR_OK) return st;
-        launch_tile_scan<4, kRelayWaves, MODE, false, true>(a, dev, s);
+        // (7 wavefronts per SIMD: up to 72 registers where the relay alone, with binary32 results, takes 49; 16, or with binary16 results 28, bytes of scratch
+        // per lane or none, up to 60 with 64 registers)
+        if (sums == kSumsLookedUp) tile_scan_kernel<4, kRelayWaves, false, MODE, false, kSumsLookedUp, 7><<<dim3((unsigned)tiles), dim3(kRelayWaves * kWave), 0, s>>>(a, dev);
+        else if (sums == kSumsNear) tile_scan_kernel<4, kRelayWaves, false, MODE, false, kSumsNear, 7><<<dim3((unsigned)tiles + 1), dim3(kRelayWaves * kWave), 0, s>>>(a, dev);
+        else launch_tile_scan<4, kRelayWaves, MODE, false, kSumsRelayed>(a, dev, s);
         st = check_launch("tile_scan_kernel");
         if (st != TCR_OK) ws->dirty = true;
         return st;
@@ -892,7 +898,7 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
     if (u == 1) launch_tile_scan<1, 8, MODE, false>(a, dev, s);
     else if (u == 2 && w == 8) launch_tile_scan<2, 8, MODE, false>(a, dev, s);
     else if (u == 2) launch_tile_scan<2, 16, MODE, false>(a, dev, s);
-    else if (w == 8 && offsets == nullptr && n > scan_held_max()) tile_scan_kernel<4, 8, true, MODE, false, false, 6><<<dim3((unsigned)tiles_of(4, 8)), dim3(8 * kWave), 0, s>>>(a, dev);
+    else if (w == 8 && offsets == nullptr && n > scan_held_max()) tile_scan_kernel<4, 8, true, MODE, false, kSumsWide, 6><<<dim3((unsigned)tiles_of(4, 8)), dim3(8 * kWave), 0, s>>>(a, dev);
     else if (w == 8) launch_tile_scan<4, 8, MODE, false>(a, dev, s);
     else launch_tile_scan<4, 16, MODE, false>(a, dev, s);
     st = check_launch("tile_scan_kernel");
@@ -902,19 +908,18 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
 
 // Scans in fixed tiles whose carries come from the relay: us, the other forms (the wavefronts add the open part up themselves or
 // look up what tiles in front have published, or chained tiles) against this, n in 2^20.
-// Irregular segments: beyond what the chip holds at once, up to 9 * 2^24 elements.  What the others cost there goes by the longest segment,
-// which the host does not know; the relay's does not.
-//   binary32        n = 17          20          24          32          64          128         256
-//     2              49.9/53.5   53.6/57.0   62.3/61.6   94.8/87.2   164.6/150.9
-//     16             26.2/26.3   32.0/32.0   39.6/40.2   63.0/54.1   103.1/95.0  178.5/168.4 328/322
-//     lognormal      24.0/24.2   30.2/30.5   38.2/36.8   55.1/48.0   90.3/83.6   158.9/155.3 294/299
-//     seven          28.0/23.0        -      42.4/36.5   55.2/46.4   91.0/81.8   159.1/151.6 292/293
-//     one, 1023 empty 32.7/23.5  37.7/29.7   48.7/37.1        -      98.8/84.9        -      293/302
+// Irregular segments: beyond what the chip holds at once, up to 9 * 2^24 elements (below: irregular_sums).  What the others cost there goes by the longest
+// segment, which the host does not know; the relay's does not.
+//   binary32        n = 32          64          128         256
+//     2              94.8/87.2   164.6/150.9
+//     16             63.0/54.1   103.1/95.0  178.5/168.4 328/322
+//     lognormal      55.1/48.0   90.3/83.6   158.9/155.3 294/299
+//     seven          55.2/46.4   91.0/81.8   159.1/151.6 292/293
+//     one, 1023 empty   -        98.8/84.9        -      293/302
 //   binary16, exclusive
-//     16             19.5/19.6   22.8/22.7   26.6/27.2   44.9/37.0   73.3/64.0   124.8/113.7 228/214
-//     lognormal      18.6/19.3   20.9/20.9   23.7/23.9        -      61.1/56.6   107.2/106.1 197/202
-//     seven          21.0/18.7   23.0/20.7   26.7/23.2        -      62.3/55.3   107.0/104.5 191/199
-//   (the largest loss of those with more than a few elements, lognormal at 18: 26.5/27.6)
+//     16             44.9/37.0   73.3/64.0   124.8/113.7 228/214
+//     lognormal         -        61.1/56.6   107.2/106.1 197/202
+//     seven             -        62.3/55.3   107.0/104.5 191/199
 // Regular segments and seven irregular ones, of more than 2^20 elements on average: binary32 from 12 * 2^20 elements on (3000003 at 14.3: 21.7/19.4, 22.9: 32.6/30.8, 62.9:
 // 91.3/76.7, 126: 167.9/143.8; seven at 12 / 14 / 16 18.6/18.4, 21.6/19.9, 22.8/21.5).
 // Other regular ones, beyond 2^24, by length, type and alignment (chained tiles, which took some lengths of 4097 to 8191 elements: 64 85, 128 152, 256 287;
@@ -948,6 +953,28 @@ inline bool tiles_chained(uint64_t n, uint64_t seg_len, bool f16, bool vector_st
     return f16 && !vector_stores && seg_len > 4096 && seg_len <= kLocalMax && n > (3ull << 25);
 }
 
+// Where the irregular tiles that tiles_relayed names get the sum in front of them (TileSums).  Up to 7 * 2^22 elements the order in which the relay hands carries out
+// costs more than it gives unless most elements lie in a few segments: a tile that takes long -- thousands of short segments, a million empty ones -- holds up all
+// behind it.  So where most tiles hold many starts the four wavefronts look sums up, and where there is one for every few tiles at most those of the tiles near by;
+// only for fewer segments, which are long whatever the offsets, all goes through the relay.  us, looked up / near by / relay, n = 2^20 * 17, 20, 28:
+//   binary32   16             27.9/28.4/28.3   32.8/33.0/31.7   43.1/43.6/43.9      lognormal  29.2/29.1/29.7   33.0/32.8/32.7   43.1/43.5/41.7
+//              3000           28.7/28.7/30.9   33.2/33.2/33.7   41.3/41.7/43.2      20000      29.2/29.0/31.7   32.8/32.4/33.2   43.0/43.5/41.6
+//              half ones, half one segment  55.0/55.6/56.9   64.8/63.0/60.5   89.0/80.1/77.6     a hundredth of 16, one  37.6/33.6/32.9   41.8/36.0/34.8   56.0/44.7/43.7
+//              100000         29.3/29.4/29.9   32.5/32.7/31.8   44.2/44.3/41.3      seven      34.3/35.0/29.3   38.1/37.7/31.3   53.1/48.5/40.5
+//   binary16,  16             22.0/22.5/22.7   24.8/25.2/24.8   31.5/32.0/32.6      lognormal  22.3/22.3/22.9   24.1/24.2/25.3   30.1/30.0/31.3
+//   exclusive  3000           21.2/21.3/22.7   23.0/23.2/25.0   28.8/29.1/31.1      20000      22.2/22.2/23.1   24.2/24.1/25.7   30.2/30.3/32.2
+//              half ones, half one segment  46.6/52.5/54.0   54.0/55.4/56.0   72.8/71.3/71.3     a hundredth of 16, one  28.0/26.0/24.9   31.1/28.8/27.7   40.3/35.5/34.8
+//              100000         22.2/22.0/21.8   24.0/23.9/24.4   30.8/31.0/32.0      seven      24.7/24.8/21.9   27.0/27.3/24.3   36.0/35.0/31.4
+//              1000, and 2^20 * 0.17 empty ones in a row  24.8/28.0/28.8   26.0/30.2/29.9   32.9/38.3/37.0
+// (results stored by element, 18 and 24: lognormal 59.7/60.2/63.5 and 77.4/77.2/79.3, binary16 38.0/38.0/40.6 and 47.7/48.2/48.5; 100000 38.9/38.7/41.6 and
+// 48.5/48.5/51.4.)
+constexpr uint64_t kIrregularLookedUpMax = 7ull << 22;
+inline TileSums irregular_sums(uint64_t n, uint64_t nseg, bool f16, bool vector_stores) {
+    if (n > (!vector_stores ? 27ull << 20 : f16 ? kIrregularLookedUpMax : 37ull << 19)) return kSumsRelayed;
+    if (nseg >= n >> 9) return kSumsLookedUp;
+    return nseg >= n >> (!vector_stores ? 20 : f16 ? 18 : 16) ? kSumsNear : kSumsRelayed;
+}
+
 template <int MODE>
 inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offsets, void* out, uint64_t n, uint64_t nseg,
                                         uint64_t seg_len, hipStream_t s, int shape = -1, bool fill = false) {
@@ -966,7 +993,7 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
     const bool alone = shape == 0 && g_variant.formulation == kMfma && (regular ? seg_len >= 2 : g_variant.irregular_scan == 0);
     const bool relay = alone && tiles_relayed(n, nseg, seg_len, regular, (MODE & 2) != 0, vector_stores != 0);
     const bool chained = alone && !relay && regular && tiles_chained(n, seg_len, (MODE & 2) != 0, vector_stores != 0);
-    if (alone && !relay && !chained && (regular || n <= scan_held_max())) return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, false, s);
+    if (alone && !relay && !chained && (regular || n <= scan_held_max())) return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, kSumsWide, s);
     Workspace* ws = nullptr;
     bool capturing = false;
     tcr_status st = get_workspace(s, &ws, &capturing);
@@ -977,14 +1004,18 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
     const bool two_kernels = !regular && shape == 0 && shift == 0 && vector_stores != 0 && g_variant.formulation == kMfma &&
                              g_variant.irregular_scan != 1 && (g_variant.irregular_scan == 2 || nseg <= tiles / 4);
     if (relay) {
-        // without room for its two words per tile: regular segments look up or add up what is in front of a tile, others are chained
-        const uint64_t limit = table_limit(ws, capturing);
-        const bool room = 2 * ceil_div(n, kRelayTile) <= limit;
+        // without room for the relay's two words per tile: regular segments look up or add up what is in front of a tile; others look it up where that is as fast, in
+        // one word, or are chained
+        const uint64_t limit = table_limit(ws, capturing), words = ceil_div(n, kRelayTile);
+        TileSums sums = regular || n <= scan_held_max() ? kSumsRelayed : irregular_sums(n, nseg, (MODE & 2) != 0, vector_stores != 0);
+        if (!regular && n <= kIrregularLookedUpMax && n > scan_held_max() && 2 * words > limit) sums = kSumsLookedUp;
+        const bool room = (sums == kSumsLookedUp ? words : 2 * words) <= limit;
         const bool room_once = regular && (seg_len <= kLocalMax || ceil_div(n, (uint64_t)(kTile * 4 * 8)) <= limit);
         const bool room_chained = (two_kernels ? 2 * tiles : tiles) <= limit && (regular || 2 * irregular_words(true, n, shape) <= partials_limit(ws, capturing));
-        if (room || room_once || !room_chained || n <= scan_held_max()) return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, room, s);
+        if (room || room_once || !room_chained || n <= scan_held_max())
+            return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, room ? sums : kSumsWide, s);
     }
-    if (chained && !table_has_room(ws, tiles, capturing)) return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, false, s);
+    if (chained && !table_has_room(ws, tiles, capturing)) return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, kSumsWide, s);
     if (!regular) {
         st = ensure_partials(ws, s, 2 * irregular_words(true, n, shape), capturing);
         if (st != TCR_OK) return st;

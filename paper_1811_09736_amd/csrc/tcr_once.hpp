@@ -6,7 +6,7 @@
 // entry in front of the tile for irregular ones -- and so is the way the sum is found:
 //   * s0 at most a tile or so in front: the workgroup adds those elements up itself, 512 to a wavefront, while its own
 //     data is on its way (they are a neighbour's data, mostly found in a cache);
-//   * further away: the published sums of the tiles from the one that holds s0 on, read in one round trip, or, in larger
+//   * further away: the published sums of the tiles from the one that holds s0 on, read in one round trip, or, in most larger
 //     arrays, the carry that the relay makes of them (tcr_relay.hpp).  As in the chained scan of arrays that the chip holds at
 //     once, what is not there after `patience` looks is added up from the elements, so no wait depends on which workgroups run.
 // Bound: memory for large arrays, the chain of dependent steps for the smaller ones.  The ticket, the look-back and, for
@@ -54,13 +54,15 @@ __device__ __forceinline__ float open_tile_sum(const TileScan& a, uint32_t t, ui
 }
 
 // One wavefront: the sum from position s0 to the start of `tile` out of what the tiles in between have published, 64 at a time, the
-// nearest first.  What is not there after `patience` looks is added up from the elements, or (GIVE_UP) the result is false.
-template <bool GIVE_UP>
+// nearest first; number `looker` of LOOKERS that take turns.  What is not there after `patience` looks is added up from the elements, or (GIVE_UP)
+// the result is false.
+template <bool GIVE_UP, int LOOKERS = 1>
 __device__ __forceinline__ bool lookup_open_sum(const TileScan& a, const ScanWorkspace& ws, uint32_t tile, uint64_t s0, int tile_log2, int lane,
-                                                float& sum) {
+                                                float& sum, int looker = 0) {
     const uint32_t first = (uint32_t)(s0 >> tile_log2);
     float acc = 0.0f;
-    for (uint32_t hi = tile; hi > first;) {
+    const uint32_t skipped = 64u * (uint32_t)looker;
+    for (uint32_t hi = tile - first > skipped ? tile - skipped : first; hi > first;) {
         const uint32_t span = hi - first > 64u ? 64u : hi - first;
         bool need = (uint32_t)lane < span;
         float v = 0.0f;
@@ -87,27 +89,36 @@ __device__ __forceinline__ bool lookup_open_sum(const TileScan& a, const ScanWor
             __builtin_amdgcn_s_sleep(1);
         }
         acc += v;
-        hi -= span;
+        if constexpr (LOOKERS == 1) hi -= span;
+        else hi = hi - first > 64u * LOOKERS ? hi - 64u * LOOKERS : first;
     }
     sum = wave_sum(acc);                                 // (added per lane first: one chain of roundings of the whole sum's size, not one per look)
     return true;
 }
 
+// Where the sum in front of a tile comes from if it is more than the tile's wavefronts add up themselves.  kSumsWide: arrays whose workgroups run all
+// at once, and regular segments; one wavefront looks it up.  The others are for arrays whose workgroups follow each other, in workgroups of four
+// wavefronts: they take turns at looking it up (kSumsLookedUp), the relay hands it out (kSumsRelayed, tcr_relay.hpp), or they look up the sums of up to
+// kNearTiles tiles, one look each, and wait for the relay only further away from the segment's start (kSumsNear).
+enum TileSums { kSumsWide = 0, kSumsLookedUp = 1, kSumsNear = 2, kSumsRelayed = 3 };
+constexpr uint32_t kNearTiles = 64 * kRelayWaves;
+
 // LOCAL (regular segments of 2 to WAVES * 512 elements): no sum is ever looked up, no workspace.
-// RELAY (workgroups of four wavefronts, in arrays whose workgroups follow each other): the sum in front comes from the relay
-// (tcr_relay.hpp).  Regular tiles all wait for it, in the order of the array; irregular ones only where it is more than the four
-// wavefronts add up themselves (segments of 16 in 2^27 elements 165 us, 174 where all wait; seven segments 151 and 149).  Their
-// entries are found with one search of two rounds around where they are likely to be (GUIDED), not two of four over the whole array.
+// Relayed regular tiles all wait for the relay, in the order of the array; irregular ones only where it is more than the four
+// wavefronts add up themselves (segments of 16 in 2^27 elements 165 us, 174 where all wait; seven segments 151 and 149).  The
+// entries of tiles of four wavefronts are found with one search of two rounds around where they are likely to be (GUIDED), not two of four over the whole array.
 // Registers: at most 64, so that 8 wavefronts per SIMD run.  A wavefront that has waited in vain loads its elements again behind the
 // additions, so that they need not be held across them: 43 to 49 registers where four sub-tiles took 64 and 44 bytes of scratch
 // (lognormal lengths / segments of 16 / seven segments in 2^24 elements 21.7 / 23.9 / 23.6 -> 21.0 / 23.5 / 22.7 us).  Not with fewer
 // sub-tiles, which lose 2 to 5 %, nor with binary16 results (15.7 -> 16.0): 64 registers, 20 to 68 bytes.
 // MOST: wavefronts per SIMD at most.
-template <int U, int WAVES, bool REGULAR, int MODE, bool LOCAL, bool RELAY = false, int MOST = 8>
+template <int U, int WAVES, bool REGULAR, int MODE, bool LOCAL, int SUMS = kSumsWide, int MOST = 8>
 __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U < 4 ? 4 : MOST, MOST))) void tile_scan_kernel(TileScan a, ScanWorkspace ws_arg) {
     static_assert(!LOCAL || REGULAR, "");
-    static_assert(!RELAY || (WAVES == kRelayWaves && !LOCAL), "");
-    constexpr bool GUIDED = !REGULAR && RELAY;                // (how a tile's entries are found)
+    static_assert(SUMS == kSumsWide || (WAVES == kRelayWaves && !LOCAL), "");
+    constexpr bool RELAY = SUMS == kSumsNear || SUMS == kSumsRelayed;
+    constexpr bool GUIDED = !REGULAR && SUMS != kSumsWide;    // (how a tile's entries are found)
+    constexpr int LOOKERS = SUMS == kSumsLookedUp || SUMS == kSumsNear ? WAVES : 1;
     constexpr int EXCL = MODE & 1, F16 = MODE >> 1;
     constexpr uint32_t kChunk = (uint32_t)kTile * U;          // one wavefront's share
     constexpr uint32_t kBlockTile = kChunk * WAVES;           // one workgroup's share
@@ -259,6 +270,7 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
     }
     const uint64_t back = tb - s0;
     const bool far = RELAY && REGULAR ? true : !LOCAL && back > kBackMax;
+    const bool looks = LOOKERS > 1 && far && (!RELAY || tile - (uint32_t)(s0 >> kTileLog2) <= kNearTiles);     // (all four wavefronts do)
     // the wavefront's 512 elements of the open part, counted back from the tile's start
     const uint64_t behind = (uint64_t)kTile * (uint64_t)wave;
     const bool mine = !far && behind < back;
@@ -333,7 +345,7 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
                 __hip_atomic_store(&ws.desc[tile], pack_desc(ws.epoch, RELAY && tail ? kStatusTail : kStatusAggregate, total), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
             }
-            if (far) {
+            if ((RELAY || LOOKERS == 1) && far && !looks) {
                 float pre = 0.0f;
                 constexpr bool AGAIN = RELAY || (U == 4 && !F16);      // (elements asked for again by a wavefront that has waited in vain)
                 bool got;
@@ -352,6 +364,13 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
                 if (lane == 0) s_back[0] = pre;
             }
         }
+        if constexpr (LOOKERS > 1) {
+            if (looks) {
+                float pre = 0.0f;
+                lookup_open_sum<false, LOOKERS>(a, ws, tile, s0, kTileLog2, lane, pre, wave);
+                if (lane == 0) s_back[wave] = pre;
+            }
+        }
         if (far) __syncthreads();
     }
     // carry from the wavefronts in front, back to the nearest one that holds a head, else from in front of the tile
@@ -366,17 +385,21 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
     }
     if (open && back != 0) {
         float sum = 0.0f;
+        if constexpr (LOOKERS > 1) {
+            sum = pairwise_sum(s_back);           // (sums over thousands of tiles)
+        } else {
 #pragma unroll
-        for (int v = 0; v < WAVES; ++v) sum += s_back[v];
+            for (int v = 0; v < WAVES; ++v) sum += s_back[v];
+        }
         ext += sum;
     }
     const uint32_t valid_lo = first > base ? (uint32_t)(first - base < kChunk ? first - base : kChunk) : 0u;
     const uint32_t valid_hi = last > base ? (uint32_t)(last - base < kChunk ? last - base : kChunk) : 0u;
     // LATE: the sum in front may be millions of times an element, and is added once, behind the sums of the tile, not in front of
-    // a lane's eight additions.  Where workgroups follow each other (the relay, and regular tiles beyond what the chip holds at once,
+    // a lane's eight additions.  Where workgroups follow each other (tiles of four wavefronts, and regular ones beyond what the chip holds at once,
     // MOST < 8) the two more operations per element are free; where all run at once they cost 5 to 10 % (seven segments in 2^24
     // elements: 23.5 us, 25.3 with them).
-    constexpr bool LATE = RELAY || (!LOCAL && MOST < 8);
+    constexpr bool LATE = SUMS != kSumsWide || (!LOCAL && MOST < 8);
     const bool inside = valid_lo == 0u && valid_hi == kChunk && a.vector_stores != 0u;
     void* const dst = F16 ? static_cast<void*>(static_cast<_Float16*>(a.out) + base) : static_cast<void*>(static_cast<float*>(a.out) + base);
 #pragma unroll

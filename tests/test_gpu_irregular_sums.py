@@ -1,0 +1,116 @@
+"""Irregular scans just beyond 2^24 elements: tiles whose wavefronts look sums up, whose sums near by are looked up, and whose sums all come from one
+workgroup -- which of them goes by the number of segments -- in every mode, against the oracle; and the same offsets at the limits between them."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1811_09736_amd import workloads
+
+pytestmark = pytest.mark.gpu
+
+M, TILE = 1 << 20, 8192
+N = 17 * M + 5
+
+
+@pytest.fixture(scope="module")
+def tcr():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1811_09736_amd import binding
+    binding.set_variant("reset")
+    binding.tuning_import("")
+    yield binding
+    binding.set_variant("reset")
+    binding.set_workspace(None)
+    binding.check_device_flags()
+
+
+def check(tcr, oracle, off, flags, n=N, shift=0, dist="int1"):
+    x = workloads.make_input(n, dist, 7)
+    buffer = torch.zeros(n + shift, dtype=torch.float16, device="cuda")
+    buffer[shift:] = torch.from_numpy(x).cuda()
+    want = oracle.irregular_scan_exclusive(x, off) if flags & 1 else oracle.irregular_scan(x, off)
+    got = tcr.irregular_scan_ex(buffer[shift:], torch.from_numpy(off).cuda(), flags)
+    lo, hi = int(off[0]), int(off[-1])
+    want = torch.from_numpy(want).cuda().to(got.dtype)
+    assert not got[:lo].any() and not got[hi:].any()
+    assert torch.equal(got[lo:hi], want[lo:hi])          # (the sums are exact, so each is rounded once)
+    return buffer[shift:], want
+
+
+def ends(nseg, long_from, n=N):
+    """nseg segments in front of position `long_from`, which is in the middle of the last one: short ones up to it and one from there to the end."""
+    return np.concatenate([np.linspace(0, long_from, nseg).astype(np.int64), [n]])
+
+
+# as many segments as the limits between the three forms, one more and one fewer; the last is longer than 64, 256 and 1024 tiles
+@pytest.mark.parametrize("nseg", [(N >> 9) + 1, N >> 9, (N >> 9) - 1, (N >> 16) + 1, N >> 16, (N >> 16) - 1, (N >> 18) - 1])
+@pytest.mark.parametrize("flags", [0, 3])
+@pytest.mark.parametrize("tiles", [70, 1500])
+def test_limits(tcr, oracle, nseg, flags, tiles):
+    check(tcr, oracle, ends(nseg, N - tiles * TILE - 100), flags)
+
+
+# a segment's start 63 to 258 tiles in front of tiles that look its sums up, and on the edges of tiles; modes and alignments
+@pytest.mark.parametrize("flags,shift", [(0, 0), (1, 3), (2, 5), (3, 0)])
+@pytest.mark.parametrize("per", [300, 20000])
+def test_distances(tcr, oracle, flags, shift, per):
+    long = [63 * TILE, 64 * TILE + 1, 65 * TILE - 1, 256 * TILE, 257 * TILE, 258 * TILE + 7, 5 * TILE]
+    cuts, at = [0], 0
+    for l in long:
+        short = at + per * np.arange(1, 60)
+        cuts += list(short) + [int(short[-1]) + l]
+        at = cuts[-1]
+    cuts += list(range(at + per, N, per)) + [N]
+    check(tcr, oracle, np.array(cuts, dtype=np.int64), flags, shift=shift)
+
+
+# elements in no segment, empty segments, and no tile that waits: what is not there yet is added up from the elements
+@pytest.mark.parametrize("per", [16, 3000])
+@pytest.mark.parametrize("wait", ["bounded", "none"])
+def test_outside_and_unpublished(tcr, oracle, per, wait):
+    inner = np.arange(3 * TILE + 77, N - 300 * TILE, per)
+    off = np.concatenate([inner, np.repeat(inner[-1:], 40000), [N - 9000]]).astype(np.int64)
+    tcr.set_variant("scan_wait", wait)
+    try:
+        check(tcr, oracle, off, 0)
+        check(tcr, oracle, off, 3, shift=1)
+    finally:
+        tcr.set_variant("reset")
+
+
+# buffers with room for one word per tile, for two, and for the chained tiles alone; and a recorded launch with other offsets than the first call's
+@pytest.mark.parametrize("words", [2 * (N // TILE + 1) + 32, N // TILE + 33, N // TILE - 64])
+@pytest.mark.parametrize("recipe", ["uniform16", "lognormal256", "few7"])
+def test_short_buffers(tcr, oracle, words, recipe):
+    tcr.set_workspace(torch.full((256 + 16 * ((words + 31) // 32 * 32),), 0x5A, dtype=torch.uint8, device="cuda"))
+    try:
+        check(tcr, oracle, workloads.make_offsets(N, recipe, 3).view(np.int64), 0)
+    except tcr.TcrError as e:
+        # (too small for any form: chained tiles need tables of the starts)
+        assert e.status == tcr.ERR_WORKSPACE and words < N // TILE
+    finally:
+        tcr.set_workspace(None)
+
+
+def test_recorded_with_other_offsets(tcr, oracle):
+    mixes = [torch.from_numpy(workloads.make_offsets(N, r, 3).view(np.int64)).cuda() for r in ("uniform16", "lognormal256", "few7")]
+    x = torch.from_numpy(workloads.make_input(N, "int1", 5)).cuda()
+    outs = [torch.zeros(N, device="cuda") for _ in mixes]
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        tcr.irregular_scan(x, mixes[0], outs[0])
+    stream.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        for off, out in zip(mixes, outs):
+            tcr.irregular_scan(x, off, out)
+    for turn in range(3):
+        x.copy_(torch.from_numpy(workloads.make_input(N, "int1", 20 + turn)))
+        for out in outs:
+            out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        for off, out in zip(mixes, outs):
+            assert torch.equal(out, tcr.irregular_scan(x, off)), turn
+    assert np.array_equal(outs[1].cpu().numpy().astype(np.float64), oracle.irregular_scan(x.cpu().numpy(), mixes[1].cpu().numpy()))
