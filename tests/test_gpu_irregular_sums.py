@@ -114,3 +114,18 @@ def test_recorded_with_other_offsets(tcr, oracle):
         for off, out in zip(mixes, outs):
             assert torch.equal(out, tcr.irregular_scan(x, off)), turn
     assert np.array_equal(outs[1].cpu().numpy().astype(np.float64), oracle.irregular_scan(x.cpu().numpy(), mixes[1].cpu().numpy()))
+
+
+# whole shares of wavefronts in no segment, in front of the first and behind the last, cleared where results are new and left alone where they are given;
+# the first share of an array off a boundary is no whole one
+@pytest.mark.parametrize("n", [3 * M + 5, 13 * M, N, 33 * M + 8])
+@pytest.mark.parametrize("flags,shift", [(0, 0), (3, 0), (0, 8), (1, 5)])
+def test_shares_in_no_segment(tcr, oracle, n, flags, shift):
+    off = np.arange(n // 3, n - n // 3, 37).astype(np.int64)
+    x, want = check(tcr, oracle, off, flags, n, shift)
+    given = torch.full((n,), 77, dtype=want.dtype, device="cuda")
+    tcr.irregular_scan_ex(x, torch.from_numpy(off).cuda(), flags, out=given)
+    lo, hi = int(off[0]), int(off[-1])
+    assert torch.equal(given[lo:hi], want[lo:hi]) and (given[:lo] == 77).all() and (given[hi:] == 77).all()
+    many = np.array([n // 2, n // 2 + 1])                       # (few segments: the other forms)
+    check(tcr, oracle, many, flags, n, shift)
