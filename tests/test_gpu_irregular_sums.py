@@ -129,3 +129,16 @@ def test_shares_in_no_segment(tcr, oracle, n, flags, shift):
     assert torch.equal(given[lo:hi], want[lo:hi]) and (given[:lo] == 77).all() and (given[hi:] == 77).all()
     many = np.array([n // 2, n // 2 + 1])                       # (few segments: the other forms)
     check(tcr, oracle, many, flags, n, shift)
+
+
+# runs of empty segments that start in the tile's first turns of entries and end on, next to and far from a turn's end: left behind by whole turns of 512
+@pytest.mark.parametrize("n", [N, 29 * M])
+@pytest.mark.parametrize("front", [3, 700, 1300])
+def test_runs_of_empty_segments(tcr, oracle, n, front):
+    parts, at = [np.arange(0, 40 * TILE, 16)], 40 * TILE
+    for run in (511, 512, 64 * 512 - 1, 64 * 512, 65 * 512 + 1, 66 * 512 + 255, 300000):
+        parts += [at + np.arange(front), np.full(run, at + front), at + front + np.arange(1, 200, 3)]
+        at += 9 * TILE + 5
+    off = np.concatenate(parts + [np.arange(at, n, 1000), [n]]).astype(np.int64)
+    check(tcr, oracle, off, 0, n)
+    check(tcr, oracle, off, 3, n, 3)
