@@ -1263,9 +1263,21 @@ inline bool rows_reduce_takes(uint64_t seg_len, int kind = kSum) {
 //                        2999 (two segments): 8 6.4/6.4, 12 7.5/8.4
 //   sums, 4032           17: 1 3.7/3.6, 4 4.9/4.0, 8 6.5/5.7, 12 7.9/7.3, 14 8.3/8.2; 100: 2 3.6/3.8, 4 4.1/3.9, 8 5.2/5.0, 10 5.6/5.6, 12 6.4/6.2,
 //                        14 6.9/6.6; 784: 4 4.1/3.9, 12 6.5/6.1, 14 6.6/6.9; 2000: 4 4.0/3.9, 8 5.2/4.7, 12 6.3/6.0; 2500 (one): 6 4.3/5.0
+// (inputs read from memory; from the memory-side cache the gains up to 2^20 * 6 are hidden behind the call.)  How many segments a smaller share holds matters: 1355
+// elements fill 83 % of 8128 and all of 16320, 2035 75 %.  moments  1200 (89 %): 8 6 % less, 14 3 % more, 18 4 to 8 % more; 1355: 8 6 % less, 11 3 to 7 % more;
+// 1640 (81 %): 8 8 % less, 10 3 % more, 13 6 to 8 % more; 2035: 5 9 % less, 6 4 % more, 11 14 to 18 % more; 1500, 2500 (92 %): 12 7 % less, 14 3 to 6 % more; 1999
+// (98 %): 16 4 % less, 18 1 to 6 % more.  sums  784: 8 5 to 8 % less, 10 and 11 5 % more, 12 4 % less; 1355 (67 %): 8 even, 12 6 to 9 % more; 1700 (84 %): 12 6 % less.
 inline int rows_shape(uint64_t n, uint64_t seg_len, int kind) {
-    if (kind == kBoth) return seg_len <= 2709 && n <= (seg_len < 32 ? 1ull << 26 : seg_len <= 2032 ? 5ull << 22 : 1ull << 24) ? 1 : 0;
-    return seg_len <= 2016 && n <= (seg_len < 32 ? 7ull << 21 : 13ull << 20) && (seg_len < 32 || n > (3ull << 20)) ? 2 : 0;
+    if (kind == kBoth) {
+        if (seg_len > 2709) return 0;
+        const uint64_t filled = 8128 / seg_len * seg_len;
+        if (seg_len < 32) return n <= (1ull << 26) ? 1 : 0;
+        if (filled > 7720) return n <= (seg_len <= 1625 ? 5ull << 22 : 1ull << 24) ? 1 : 0;
+        return n <= (filled > 7315 ? 13ull << 20 : filled > 6340 ? 1ull << 23 : 5ull << 20) ? 1 : 0;
+    }
+    if (seg_len > 2016) return 0;
+    if (seg_len < 32) return n <= (7ull << 21) ? 2 : 0;
+    return n > (3ull << 20) && (n <= (9ull << 20) || (n > (23ull << 19) && n <= (13ull << 20) && 4032 / seg_len * seg_len > 3350)) ? 2 : 0;
 }
 template <int U, int W>
 inline void launch_rows_shape(const _Float16* in, float* out, float* out2, RowsGrid grid, int kind, hipStream_t s) {
@@ -1326,11 +1338,14 @@ inline void launch_packed_shape(const _Float16* in, float* out, float* out2, con
 //                         12 14.2/12.9, 24 19.8/20.5; 9: 8 9.0/8.6, 12 12.0/12.1, 16 14.3/14.6; 15: 12 10.0/9.3; 22: 12 9.1/8.6, 16 9.8/10.8
 //   sums           two    3: 3 4.4/3.8; 7: 1 3.8/3.4, 4 4.7/3.7; 15: 4 4.6/3.7; 22: 3 4.3/3.8
 //                  four   3: 6 6.2/5.5, 12 9.8/9.1, 16 11.4/12.2; 7: 8 6.0/5.3, 12 7.6/7.0; 15: 10 6.0/5.7; 22: 8 5.3/5.0, 12 6.8/7.2
-inline int packed_tiles(uint64_t n, uint32_t per_row, int kind) {
+// Narrow rows fill less of a tile: rows of 18 (9 elements): moments 10 and 11 2 to 7 % more, sums 4 % more; of 20: moments 11 to 13 2 to 9 % more, sums 11 7 % more;
+// of 22: moments 12 2 %; 30: none up to 12.
+inline int packed_tiles(uint64_t n, uint32_t width, uint32_t per_row, int kind) {
     if (kind == kBoth && n <= (5ull << 18)) return 1;
     if (n <= (9ull << 19)) return 2;
-    if (kind == kBoth) return n <= (3ull << 22) || per_row >= 10 || (per_row >= 6 && n <= (1ull << 25)) ? 4 : 8;
-    return n <= (11ull << 20) ? 4 : 8;
+    const uint64_t few = (uint64_t)width << 19;
+    if (kind == kBoth) return (n <= few && n <= (3ull << 22)) || per_row >= 10 || (per_row >= 6 && n <= (1ull << 25)) ? 4 : 8;
+    return n <= few && n <= (11ull << 20) ? 4 : 8;
 }
 // Both moments of 4 and 8 elements: whole segments inside a lane's eight.  us, packed rows against this, n in 2^20: 4 elements 1/16 5.8/3.7, 4 8.0/3.8,
 // 8 12.5/7.3, 16 18.0/13.2, 64 51.1/42.9, 256 192/167 (two groups of eight per lane: 64 40.7 against 41.7 with one, 256 185 against 171); 8 elements 1
@@ -1345,7 +1360,7 @@ inline tcr_status launch_packed_reduce(const _Float16* in, float* out, float* ou
                                        hipStream_t s, bool alt = false) {
     const PackedGrid grid = {n, n / seg_len, (uint32_t)seg_len, packed_per_row(seg_len)};
     const bool four = ((grid.seg_len * grid.per_row) % 8u == 0) != alt;
-    const int tiles = four ? 4 : (alt ? 8 : packed_tiles(n, grid.per_row, kind));
+    const int tiles = four ? 4 : (alt ? 8 : packed_tiles(n, grid.seg_len * grid.per_row, grid.per_row, kind));
     if (kind == kBoth) {
         if (tiles == 1) launch_packed_shape<kBoth, 1, 4>(in, out, out2, grid, s);
         else if (tiles == 2) launch_packed_shape<kBoth, 2, 4>(in, out, out2, grid, s);

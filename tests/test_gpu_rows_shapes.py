@@ -49,3 +49,10 @@ def test_where_the_share_changes(tcr, seg, edge, moments):
     for n in (edge - seg, edge, edge + 2 * seg):
         check(tcr, seg, n // seg, moments, 0)
         check(tcr, seg, n // seg, moments, 7)
+
+
+# and where it changes with how much of it whole segments fill
+@pytest.mark.parametrize("seg,edge,moments", [(1200, 1 << 23, True), (1355, 1 << 23, True), (2035, 5 << 20, True), (2500, 13 << 20, True), (1999, 1 << 24, True),
+                                              (784, 9 << 20, False), (784, 23 << 19, False), (1355, 9 << 20, False), (1700, 13 << 20, False)])
+def test_where_the_filled_share_changes(tcr, seg, edge, moments):
+    test_where_the_share_changes(tcr, seg, edge, moments)

@@ -60,3 +60,10 @@ def test_fractions_subnormals_and_results_off_a_boundary(tcr, seg):
     st = tcr.raw().tcr_segmented_moments(x.data_ptr(), out.data_ptr() + 4, out.data_ptr() + 4 * (4099 + 2), x.numel(), seg, torch.cuda.current_stream().cuda_stream)
     assert st == tcr.OK
     assert torch.equal(out[1:4100], s) and torch.equal(out[4101:8200], q) and out[0] == -1 and out[4100] == -1 and out[8200] == -1
+
+
+# and with the width of a row: 9, 20 and 22 elements make rows of 18, 20 and 22
+@pytest.mark.parametrize("seg,edge", [(9, 9 << 20), (20, 10 << 20), (22, 11 << 20), (7, 11 << 20), (7, 3 << 22)])
+def test_where_the_width_of_a_row_counts(tcr, seg, edge):
+    for n in (edge - seg, edge, edge + seg):
+        check(tcr, seg, n // seg, 0)
