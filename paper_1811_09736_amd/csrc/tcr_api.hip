@@ -349,8 +349,12 @@ extern "C" tcr_status tcr_autotune(int op, const void* in, float* out, uint64_t 
     if (!whole && (!is_pow2(seg_len) || seg_len < 16)) {
         // lengths without a tuned path: which kernel takes them
         if (is_pow2(seg_len) && seg_len <= 8 && (is_scan || seg_len < 4)) return TCR_OK;     // (a single kernel)
-        for (int id = 0; id < (is_scan ? (int)kScanAnyCount : (int)kReduceAnyCount); ++id)
-            if (is_scan ? scan_any_valid(id, seg_len) : reduce_any_valid(id, seg_len)) cand.push_back(id);
+        for (int id = 0; id < (is_scan ? (int)kScanAnyCount : (int)kReduceAnyCount); ++id) {
+            if (!(is_scan ? scan_any_valid(id, seg_len) : reduce_any_valid(id, seg_len))) continue;
+            // (at some sizes the default is the same launch)
+            if (!is_scan && id == kReduceAnyPackedAlt && packed_shape(n, seg_len, kSum, true) == packed_shape(n, seg_len, kSum, false)) continue;
+            cand.push_back(id);
+        }
         return tune_entry(is_scan ? kTuneScanAny : kTuneReduceAny, floor_log2(seg_len), cand, call, s);
     }
     const int cls = tuning_class(seg_len, whole);

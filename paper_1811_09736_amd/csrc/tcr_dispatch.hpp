@@ -1355,12 +1355,17 @@ inline tcr_status launch_tiny_moments(const _Float16* in, float* sum, float* sum
     else tiny_moments_kernel<3, 2><<<dim3((unsigned)ceil_div(n, 16 * kGenericThreads)), dim3(kGenericThreads), 0, s>>>(in, sum, sumsq, n);
     return check_launch("tiny_moments_kernel");
 }
-// alt: the other launch shape than the one the row width calls for.
+// Tiles per wavefront.  alt (a choice of the tuning table, whose meaning does not go by n): eight for rows of a multiple of 8 elements, which take four, four for
+// others.
+inline int packed_shape(uint64_t n, uint64_t seg_len, int kind, bool alt) {
+    const uint32_t per_row = packed_per_row(seg_len), width = (uint32_t)seg_len * per_row;
+    if ((width % 8u == 0) != alt) return 4;
+    return alt ? 8 : packed_tiles(n, width, per_row, kind);
+}
 inline tcr_status launch_packed_reduce(const _Float16* in, float* out, float* out2, uint64_t n, uint64_t seg_len, int kind,
                                        hipStream_t s, bool alt = false) {
     const PackedGrid grid = {n, n / seg_len, (uint32_t)seg_len, packed_per_row(seg_len)};
-    const bool four = ((grid.seg_len * grid.per_row) % 8u == 0) != alt;
-    const int tiles = four ? 4 : (alt ? 8 : packed_tiles(n, grid.seg_len * grid.per_row, grid.per_row, kind));
+    const int tiles = packed_shape(n, seg_len, kind, alt);
     if (kind == kBoth) {
         if (tiles == 1) launch_packed_shape<kBoth, 1, 4>(in, out, out2, grid, s);
         else if (tiles == 2) launch_packed_shape<kBoth, 2, 4>(in, out, out2, grid, s);

@@ -250,3 +250,19 @@ def test_autotune_picks_valid_shapes_and_results_stay_exact(tcr, oracle, data):
         tcr.check_device_flags()
     finally:
         tcr.tuning_import("")
+
+
+# rows of whole segments with four tiles per wavefront: the default of this size and the other choice are one launch, which is no choice
+def test_a_launch_is_no_choice_against_itself(tcr, oracle, data):
+    x, _ = data
+    n = (8 << 20) // 6 * 6
+    xd = torch.from_numpy(np.resize(x, n)).cuda()
+    out = torch.empty(n // 6, dtype=torch.float32, device="cuda")
+    try:
+        for _ in range(12):
+            tcr.autotune(tcr.OP_SEGMENTED_REDUCE, xd, out, 6)
+            assert int(dict(item.split("=") for item in tcr.tuning_export().split(";") if item)["reduce_any:2"]) in (1, 2, 4)
+        tcr.tuning_import("reduce_any:2=5;")                         # (a saved choice keeps its meaning)
+        assert np.array_equal(tcr.segmented_reduce(xd, 6).cpu().numpy().astype(np.float64), oracle.segmented_reduce(np.resize(x, n), 6))
+    finally:
+        tcr.tuning_import("")
