@@ -62,6 +62,13 @@ bool number(PyObject* o, uint64_t least, uint64_t most, uint64_t& v) {
     return true;
 }
 
+// Gives the interpreter up, as torch.empty does around the allocation: one that grows, or frees what is cached, may wait for the device, and the
+// device for Python.
+struct WithoutInterpreter {
+    PyThreadState* const state = PyEval_SaveThread();
+    ~WithoutInterpreter() { PyEval_RestoreThread(state); }
+};
+
 // The results: new, or given and then of the right size.
 struct Results {
     at::Tensor made;
@@ -69,6 +76,7 @@ struct Results {
     void* data = nullptr;
     bool set(PyObject* out, uint64_t count, at::ScalarType type, const at::Tensor& x) {
         if (out == Py_None) {
+            const WithoutInterpreter released;
             made = at::empty({(int64_t)count}, x.options().dtype(type).requires_grad(false));
             data = made.data_ptr();
             return true;

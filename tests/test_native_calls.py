@@ -150,3 +150,44 @@ def test_the_current_stream(data):
         got = binding.scan(y[:N])
     side.synchronize()
     assert torch.equal(got, want)
+
+
+# An allocation that has to free what is cached waits for the device; other threads of Python run meanwhile.  (The device is kept busy for a while, and the
+# process is allowed no more memory than it has.)
+@pytest.mark.gpu
+def test_allocations_give_the_interpreter_up(data):
+    import threading
+    import time
+
+    x = torch.ones(1 << 28, dtype=torch.float16, device="cuda")
+    binding.scan(x)                                                      # (so that the library has what it needs)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    parked = torch.empty(1 << 29, dtype=torch.uint8, device="cuda")      # (half of what the call asks for: no use to it, but cached)
+    total = torch.cuda.get_device_properties(x.device).total_memory
+    calls, ticks, stop = [], [], threading.Event()
+
+    def tick():
+        while not stop.is_set():
+            ticks.append(time.perf_counter())
+            time.sleep(0.0005)
+
+    thread = threading.Thread(target=tick)
+    try:
+        del parked
+        torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (768 << 20)) / total)
+        thread.start()
+        busy = x[:1 << 26]
+        for _ in range(4000):
+            busy.mul_(1.0)
+        begin = time.perf_counter()
+        got = binding._native.scan(x, 0, None, "tcr_scan")
+        calls = [begin, time.perf_counter()]
+    finally:
+        stop.set()
+        thread.join()
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert torch.equal(got[:1 << 24], torch.arange(1, (1 << 24) + 1, device="cuda").float())
+    during = [t for t in ticks if calls[0] < t < calls[1]]
+    assert calls[1] - calls[0] > 0.02, "the call did not wait"
+    assert len(during) > (calls[1] - calls[0]) / 0.02
