@@ -7,7 +7,7 @@ import of this module fails -- there is no CPU fallback.
 
 An operation on plain tensors of the current device and on the current stream goes through _native (csrc/tcr_native.cpp), which
 makes the same checks and the same call in less time; for everything else _native gives None, before it has done anything,
-and the call goes on here.
+and the call goes on here, as all do where the module is missing or was built for another torch.
 """
 from __future__ import annotations
 
@@ -17,7 +17,7 @@ from typing import Optional
 
 import torch
 
-from .build import LIB_PATH, NATIVE_PATH
+from .build import LIB_PATH
 
 OK, ERR_INVALID_ARG, ERR_UNSUPPORTED, ERR_WORKSPACE, ERR_HIP = range(5)
 OP_SEGMENTED_REDUCE, OP_SEGMENTED_SCAN, OP_REDUCE, OP_SCAN, OP_IRREGULAR_REDUCE, OP_IRREGULAR_SCAN = range(6)
@@ -106,11 +106,19 @@ def _load() -> ctypes.CDLL:
 _lib = _load()
 
 
+class _NoNative:
+    """Leaves every call to ctypes."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 def _load_native():
-    if not os.path.exists(NATIVE_PATH):
-        raise ImportError(
-            f"{NATIVE_PATH} is missing: build it with `python -c 'import __graft_entry__ as g; g.build()'`")
-    from . import _native
+    """_native, or what does without it where it was not built, or for another torch or Python: only time is lost."""
+    try:
+        from . import _native
+    except ImportError:
+        return _NoNative()
     _native.bind(TcrError, *(ctypes.cast(getattr(_lib, name), ctypes.c_void_p).value for name in (
         "tcr_segmented_reduce", "tcr_segmented_scan_ex", "tcr_scan_ex", "tcr_reduce", "tcr_segmented_moments", "tcr_irregular_reduce",
         "tcr_irregular_scan_ex", "tcr_irregular_scan_filled", "tcr_irregular_moments")))

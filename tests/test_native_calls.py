@@ -191,3 +191,23 @@ def test_allocations_give_the_interpreter_up(data):
     during = [t for t in ticks if calls[0] < t < calls[1]]
     assert calls[1] - calls[0] > 0.02, "the call did not wait"
     assert len(during) > (calls[1] - calls[0]) / 0.02
+
+
+@pytest.mark.parametrize("missing", [True, False])
+def test_binding_without_the_module(missing):
+    """Where _native cannot be imported the calls take ctypes; where it can, it is used."""
+    import subprocess
+    import sys
+
+    code = ("import sys, torch\n"
+            + ("sys.modules['paper_1811_09736_amd._native'] = None\n" if missing else "")
+            + "from paper_1811_09736_amd import binding\n"
+            "assert (type(binding._native).__name__ == '_NoNative') is %s\n"
+            "assert binding.kernel_name(binding.OP_SCAN, 1 << 20, 1 << 20)\n"
+            "for call in (lambda x: binding.scan(x), lambda x: binding.segmented_moments(x, 8)):\n"
+            "    try: call(torch.zeros(8, dtype=torch.float16))\n"
+            "    except TypeError as e: assert 'input must be' in str(e)\n"
+            "    else: raise AssertionError('accepted')\n"
+            "print('ok')\n") % missing
+    run = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300)
+    assert run.returncode == 0 and run.stdout.strip().endswith("ok"), run.stderr
