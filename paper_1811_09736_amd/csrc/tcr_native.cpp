@@ -62,30 +62,34 @@ bool number(PyObject* o, uint64_t least, uint64_t most, uint64_t& v) {
     return true;
 }
 
-// Gives the interpreter up, as torch.empty does around the allocation: one that grows, or frees what is cached, may wait for the device, and the
-// device for Python.
+// Gives the interpreter up, as torch.empty does around the allocation too: one that grows, or frees what is cached, may wait for the device, and
+// the device for Python.
 struct WithoutInterpreter {
     PyThreadState* const state = PyEval_SaveThread();
     ~WithoutInterpreter() { PyEval_RestoreThread(state); }
 };
 
-// The results: new, or given and then of the right size.
+// The results: given and then of the right size, or new, which is for later (ready).
 struct Results {
     at::Tensor made;
     PyObject* given = nullptr;
     void* data = nullptr;
-    bool set(PyObject* out, uint64_t count, at::ScalarType type, const at::Tensor& x) {
-        if (out == Py_None) {
-            const WithoutInterpreter released;
-            made = at::empty({(int64_t)count}, x.options().dtype(type).requires_grad(false));
-            data = made.data_ptr();
-            return true;
-        }
+    int64_t count = 0;
+    at::ScalarType type = at::kFloat;
+    bool set(PyObject* out, uint64_t size, at::ScalarType dtype, const at::Tensor& x) {
+        count = (int64_t)size;
+        type = dtype;
+        if (out == Py_None) return true;
         const at::Tensor* t = plain(out, type);
-        if (t == nullptr || (uint64_t)t->numel() != count || t->device() != x.device()) return false;
+        if (t == nullptr || (uint64_t)t->numel() != size || t->device() != x.device()) return false;
         given = out;
         data = t->data_ptr();
         return true;
+    }
+    void ready(const at::Tensor& x) {
+        if (given != nullptr) return;
+        made = at::empty({count}, x.options().dtype(type).requires_grad(false));
+        data = made.data_ptr();
     }
     PyObject* take() {
         if (given == nullptr) return THPVariable_Wrap(std::move(made));
@@ -104,11 +108,14 @@ PyObject* failed(tcr_status st, const char* where) {
     }
     return nullptr;
 }
-#define TCR_CALL(expression)     \
-    tcr_status st;               \
-    Py_BEGIN_ALLOW_THREADS       \
-    st = (expression);           \
-    Py_END_ALLOW_THREADS
+// Allocation and call, with the interpreter given up once for both.
+#define TCR_CALL(allocate, expression)      \
+    tcr_status st;                          \
+    {                                       \
+        const WithoutInterpreter released;  \
+        allocate;                           \
+        st = (expression);                  \
+    }
 
 // segmented_reduce(x, seg_len, out)
 PyObject* segmented_reduce(PyObject*, PyObject* const* args, Py_ssize_t count) {
@@ -121,7 +128,7 @@ PyObject* segmented_reduce(PyObject*, PyObject* const* args, Py_ssize_t count) {
     if (n % seg_len != 0 || !out.set(args[2], n / seg_len, at::kFloat, *x)) Py_RETURN_NONE;
     const void* in = x->data_ptr();
     void* const stream = stream_of(*x);
-    TCR_CALL(g_segmented_reduce(in, static_cast<float*>(out.data), n, seg_len, stream))
+    TCR_CALL(out.ready(*x), g_segmented_reduce(in, static_cast<float*>(out.data), n, seg_len, stream))
     return st == TCR_OK ? out.take() : failed(st, "tcr_segmented_reduce");
     END_HANDLE_TH_ERRORS
 }
@@ -133,7 +140,7 @@ PyObject* scan_in(const at::Tensor& x, uint64_t seg_len, uint64_t flags, PyObjec
     if ((seg_len != 0 && n % seg_len != 0) || !out.set(given, n, flags & TCR_OUT_F16 ? at::kHalf : at::kFloat, x)) Py_RETURN_NONE;
     const void* in = x.data_ptr();
     void* const stream = stream_of(x);
-    TCR_CALL(seg_len != 0 ? g_segmented_scan_ex(in, out.data, n, seg_len, (uint32_t)flags, stream) : g_scan_ex(in, out.data, n, (uint32_t)flags, stream))
+    TCR_CALL(out.ready(x), seg_len != 0 ? g_segmented_scan_ex(in, out.data, n, seg_len, (uint32_t)flags, stream) : g_scan_ex(in, out.data, n, (uint32_t)flags, stream))
     return st == TCR_OK ? out.take() : failed(st, PyUnicode_AsUTF8(where));
 }
 // segmented_scan(x, seg_len, flags, out, where)
@@ -164,7 +171,7 @@ PyObject* reduce(PyObject*, PyObject* const* args, Py_ssize_t count) {
     const void* in = x->data_ptr();
     const uint64_t n = (uint64_t)x->numel();
     void* const stream = stream_of(*x);
-    TCR_CALL(g_reduce(in, static_cast<float*>(out.data), n, stream))
+    TCR_CALL(out.ready(*x), g_reduce(in, static_cast<float*>(out.data), n, stream))
     return st == TCR_OK ? out.take() : failed(st, "tcr_reduce");
     END_HANDLE_TH_ERRORS
 }
@@ -181,7 +188,7 @@ PyObject* segmented_moments(PyObject*, PyObject* const* args, Py_ssize_t count) 
     q.set(Py_None, n / seg_len, at::kFloat, *x);
     const void* in = x->data_ptr();
     void* const stream = stream_of(*x);
-    TCR_CALL(g_segmented_moments(in, static_cast<float*>(a.data), static_cast<float*>(q.data), n, seg_len, stream))
+    TCR_CALL((a.ready(*x), q.ready(*x)), g_segmented_moments(in, static_cast<float*>(a.data), static_cast<float*>(q.data), n, seg_len, stream))
     return st == TCR_OK ? Py_BuildValue("NN", a.take(), q.take()) : failed(st, "tcr_segmented_moments");
     END_HANDLE_TH_ERRORS
 }
@@ -197,7 +204,7 @@ PyObject* irregular_reduce(PyObject*, PyObject* const* args, Py_ssize_t count) {
     const uint64_t* off = static_cast<const uint64_t*>(offsets->data_ptr());
     const uint64_t n = (uint64_t)x->numel(), nseg = (uint64_t)offsets->numel() - 1;
     void* const stream = stream_of(*x);
-    TCR_CALL(g_irregular_reduce(in, off, static_cast<float*>(out.data), n, nseg, stream))
+    TCR_CALL(out.ready(*x), g_irregular_reduce(in, off, static_cast<float*>(out.data), n, nseg, stream))
     return st == TCR_OK ? out.take() : failed(st, "tcr_irregular_reduce");
     END_HANDLE_TH_ERRORS
 }
@@ -215,7 +222,7 @@ PyObject* irregular_moments(PyObject*, PyObject* const* args, Py_ssize_t count) 
     const void* in = x->data_ptr();
     const uint64_t* off = static_cast<const uint64_t*>(offsets->data_ptr());
     void* const stream = stream_of(*x);
-    TCR_CALL(g_irregular_moments(in, off, static_cast<float*>(a.data), static_cast<float*>(q.data), n, nseg, stream))
+    TCR_CALL((a.ready(*x), q.ready(*x)), g_irregular_moments(in, off, static_cast<float*>(a.data), static_cast<float*>(q.data), n, nseg, stream))
     return st == TCR_OK ? Py_BuildValue("NN", a.take(), q.take()) : failed(st, "tcr_irregular_moments");
     END_HANDLE_TH_ERRORS
 }
@@ -233,7 +240,7 @@ PyObject* irregular_scan(PyObject*, PyObject* const* args, Py_ssize_t count) {
     const void* in = x->data_ptr();
     const uint64_t* off = static_cast<const uint64_t*>(offsets->data_ptr());
     void* const stream = stream_of(*x);
-    TCR_CALL((out.given == nullptr ? g_irregular_scan_filled : g_irregular_scan_ex)(in, off, out.data, n, nseg, (uint32_t)flags, stream))
+    TCR_CALL(out.ready(*x), (out.given == nullptr ? g_irregular_scan_filled : g_irregular_scan_ex)(in, off, out.data, n, nseg, (uint32_t)flags, stream))
     return st == TCR_OK ? out.take() : failed(st, PyUnicode_AsUTF8(args[4]));
     END_HANDLE_TH_ERRORS
 }
