@@ -571,6 +571,11 @@ inline bool chain_relayed(uint64_t n, uint64_t seg_len, bool f16) {
     if (once != 0) return once == 8 && !f16 && seg_len >= (1ull << 18) && n <= (21ull << 19);
     return !f16 || n <= (3ull << 25);
 }
+// On a caller's buffer, which is ordinary memory, the relay costs more (2^20 * 80 / 96 elements, binary16: 7 and 8 % more than the persistent chain; none more up to 64
+// and with binary32 results).
+inline bool chain_relay_room(const Workspace* ws, bool capturing, uint64_t n, uint64_t seg_len, bool f16) {
+    return !(ws->caller_owned && f16 && n > (1ull << 26)) && 2 * relay_tiles(n, seg_len) <= table_limit(ws, capturing);
+}
 template <int MODE>
 tcr_status launch_chain_relay(Workspace* ws, bool capturing, const _Float16* in, void* out, uint64_t n, uint64_t seg_len, hipStream_t s) {
     const uint64_t tiles = relay_tiles(n, seg_len);
@@ -604,10 +609,8 @@ tcr_status launch_chain(int shape, const _Float16* in, void* out, uint64_t n, ui
     tcr_status st = get_workspace(s, &ws, &capturing);
     if (st != TCR_OK) return st;
     if constexpr (FORM == kMfma) {
-        if (alone) {
-            if (2 * relay_tiles(n, seg_len) <= table_limit(ws, capturing)) return launch_chain_relay<MODE>(ws, capturing, in, out, n, seg_len, s);
-            if (held) return launch_chain_once<MODE>(in, out, n, seg_len, s);
-        }
+        if (alone && chain_relay_room(ws, capturing, n, seg_len, (MODE & 2) != 0)) return launch_chain_relay<MODE>(ws, capturing, in, out, n, seg_len, s);
+        if (alone && held) return launch_chain_once<MODE>(in, out, n, seg_len, s);
     }
     st = begin_lookback(ws, s, tiles, &dev, capturing);
     if (st != TCR_OK) return st;
@@ -638,7 +641,7 @@ tcr_status launch_chain_tail(const _Float16* in, void* out, uint64_t n, hipStrea
             bool capturing = false;
             const tcr_status st = get_workspace(s, &ws, &capturing);
             if (st != TCR_OK) return st;
-            if (2 * relay_tiles(n, n) <= table_limit(ws, capturing)) return launch_chain_relay<MODE>(ws, capturing, in, out, n, n, s);
+            if (chain_relay_room(ws, capturing, n, n, (MODE & 2) != 0)) return launch_chain_relay<MODE>(ws, capturing, in, out, n, n, s);
         }
         if (held) return launch_chain_once<MODE>(in, out, n, n, s);
     }
@@ -975,6 +978,20 @@ inline TileSums irregular_sums(uint64_t n, uint64_t nseg, bool f16, bool vector_
     return nseg >= n >> (!vector_stores ? 20 : f16 ? 18 : 16) ? kSumsNear : kSumsRelayed;
 }
 
+// The same on a caller's buffer, which is ordinary memory where the library's own tables are uncached: everybody's looks at the relay's carries cost
+// more there.  us, n = 2^20 * 48, 64, 112, the relay against adding up or looking up: binary32, 5001 elements 61/61, 82/86, 131/136; 40000 60/65, 80/86, 132/141;
+// 200003 equal up to 64, 112 4 % more; 300003 and more no more; binary16, 2501 (80) 60/66; 300003 (80, 96) 8 and 6 % more.
+inline bool tiles_relayed_callers(uint64_t n, uint64_t seg_len, bool f16) {
+    if (f16) return seg_len > 4096 && (seg_len <= kLocalMax || seg_len > (1ull << 20) || n <= (1ull << 26));
+    return seg_len > (1ull << 18) || (seg_len > kLocalMax && n <= (5ull << 23));
+}
+// Beyond 2^27 elements, for which such a buffer has no room for the relay's words: chained tiles for lengths whose open part is much to add up or to look up
+// (2^20 * 136 / 256 elements, that / chained, binary16: 5001 elements 11 / 16 % less, 8191 16 / 21; binary32: 8191 even / 4, 2000003 2 / 6, one segment off a
+// boundary 28 / 66, with binary16 results 41 / 90; 100003 and less are looked up).
+inline bool tiles_chained_callers(uint64_t n, uint64_t seg_len) {
+    return n > (1ull << 27) && ((seg_len > 4096 && seg_len <= kLocalMax) || seg_len > (1ull << 18));
+}
+
 template <int MODE>
 inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offsets, void* out, uint64_t n, uint64_t nseg,
                                         uint64_t seg_len, hipStream_t s, int shape = -1, bool fill = false) {
@@ -991,8 +1008,8 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
     // holds at once, irregular ones.  n = 2^20 / 2^24 / 2^26, us, by ticket and look-back against this: seg_len 1001 8.2 / 27 / 85 against
     // 4.1 / 22.8 / 74; 100003 8.7 / 28 / 89 against 5.1 / 20.4 / 78; irregular, lognormal lengths 10.9 / 31.8 against 5.5 / 21.0.
     const bool alone = shape == 0 && g_variant.formulation == kMfma && (regular ? seg_len >= 2 : g_variant.irregular_scan == 0);
-    const bool relay = alone && tiles_relayed(n, nseg, seg_len, regular, (MODE & 2) != 0, vector_stores != 0);
-    const bool chained = alone && !relay && regular && tiles_chained(n, seg_len, (MODE & 2) != 0, vector_stores != 0);
+    bool relay = alone && tiles_relayed(n, nseg, seg_len, regular, (MODE & 2) != 0, vector_stores != 0);
+    bool chained = alone && !relay && regular && tiles_chained(n, seg_len, (MODE & 2) != 0, vector_stores != 0);
     if (alone && !relay && !chained && (regular || n <= scan_held_max())) return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, kSumsWide, s);
     Workspace* ws = nullptr;
     bool capturing = false;
@@ -1009,8 +1026,10 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
         const uint64_t limit = table_limit(ws, capturing), words = ceil_div(n, kRelayTile);
         TileSums sums = regular || n <= scan_held_max() ? kSumsRelayed : irregular_sums(n, nseg, (MODE & 2) != 0, vector_stores != 0);
         if (!regular && n <= kIrregularLookedUpMax && n > scan_held_max() && 2 * words > limit) sums = kSumsLookedUp;
-        const bool room = (sums == kSumsLookedUp ? words : 2 * words) <= limit;
-        const bool room_once = regular && (seg_len <= kLocalMax || ceil_div(n, (uint64_t)(kTile * 4 * 8)) <= limit);
+        const bool slower = regular && n > scan_held_max() && ws->caller_owned && !tiles_relayed_callers(n, seg_len, (MODE & 2) != 0);
+        const bool room = !slower && (sums == kSumsLookedUp ? words : 2 * words) <= limit;
+        chained = regular && !room && tiles_chained_callers(n, seg_len);
+        const bool room_once = regular && !chained && (seg_len <= kLocalMax || ceil_div(n, (uint64_t)(kTile * 4 * 8)) <= limit);
         const bool room_chained = (two_kernels ? 2 * tiles : tiles) <= limit && (regular || 2 * irregular_words(true, n, shape) <= partials_limit(ws, capturing));
         if (room || room_once || !room_chained || n <= scan_held_max())
             return launch_scan_once<MODE>(in, offsets, out, n, nseg, seg_len, shift, fill, room ? sums : kSumsWide, s);

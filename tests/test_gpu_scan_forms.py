@@ -62,3 +62,15 @@ def test_chained_without_room(tcr, oracle):
         check(tcr, oracle, 97 * M, 4099, 2, 3, 0)
     finally:
         tcr.set_workspace(None)
+
+
+# a caller's buffer of the size that is said to do: adding and looking up where the library's own memory has carries handed out, chained tiles beyond 2^27
+@pytest.mark.parametrize("seg,flags,n,shift", [(4099, 0, 60 * M, 0), (40001, 1, 39 * M, 0), (40001, 0, 41 * M, 0), (2051, 3, 61 * M, 0), (300007, 2, 63 * M, 0), (300007, 3, 65 * M, 0),
+                                               (65536, 2, 63 * M, 0), (65536, 3, 65 * M, 0), (4099, 2, 129 * M, 0), (8191, 1, 129 * M, 0), (300007, 0, 129 * M, 0),
+                                               (129 * M - 3, 2, 129 * M, 1), (129 * M - 3, 0, 129 * M, 0), (50021, 0, 129 * M, 3)])
+def test_callers_buffer(tcr, oracle, seg, flags, n, shift):
+    tcr.set_workspace(torch.full((tcr.workspace_bytes(tcr.OP_SEGMENTED_SCAN, n - n % seg, seg),), 0x5A, dtype=torch.uint8, device="cuda"))
+    try:
+        check(tcr, oracle, n, seg, flags, shift)
+    finally:
+        tcr.set_workspace(None)
