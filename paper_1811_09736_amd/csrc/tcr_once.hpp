@@ -54,12 +54,13 @@ __device__ __forceinline__ float open_tile_sum(const TileScan& a, uint32_t t, ui
 }
 
 // One wavefront: the sum from position s0 to the start of `tile` out of what the tiles in between have published, 64 at a time, the
-// nearest first; number `looker` of LOOKERS that take turns.  What is not there after `patience` looks is added up from the elements, or (GIVE_UP)
+// nearest first; number `looker` of LOOKERS that take turns.  TAILS: tiles publish either status (with a relay).  What is not there after `patience` looks is added up from the elements, or (GIVE_UP)
 // the result is false.
-template <bool GIVE_UP, int LOOKERS = 1>
+template <bool GIVE_UP, int LOOKERS = 1, bool TAILS = false>
 __device__ __forceinline__ bool lookup_open_sum(const TileScan& a, const ScanWorkspace& ws, uint32_t tile, uint64_t s0, int tile_log2, int lane,
                                                 float& sum, int looker = 0) {
     const uint32_t first = (uint32_t)(s0 >> tile_log2);
+    const uint32_t want = ws.epoch * 4u + kStatusAggregate;
     float acc = 0.0f;
     const uint32_t skipped = 64u * (uint32_t)looker;
     for (uint32_t hi = tile - first > skipped ? tile - skipped : first; hi > first;) {
@@ -70,7 +71,7 @@ __device__ __forceinline__ bool lookup_open_sum(const TileScan& a, const ScanWor
         while (true) {
             if (need) {
                 const unsigned long long d = load_descriptor(&ws.desc[hi - 1u - (uint32_t)lane]);
-                if ((uint32_t)(d >> 34) == ws.epoch) {
+                if (TAILS ? (uint32_t)(d >> 34) == ws.epoch : (uint32_t)(d >> 32) == want) {
                     v = __builtin_bit_cast(float, (uint32_t)d);
                     need = false;
                 }
@@ -341,9 +342,12 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
             // what later tiles may need of this one: the sum behind its last head
             float total = 0.0f;
             bool tail = false;
-            for (int v = WAVES - 1; v >= 0 && !tail; --v) {
+            for (int v = WAVES - 1; v >= 0; --v) {
                 total += s_wave_value[v];
-                tail = s_wave_flag[v] != 0u;
+                if (s_wave_flag[v]) {
+                    tail = true;
+                    break;
+                }
             }
             if (lane == 0) {
                 if (!RELAY && tile == 0 && ws.state != nullptr && !ws.device_managed) ws.state[0] = ws.epoch;
@@ -372,7 +376,7 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
         if constexpr (LOOKERS > 1) {
             if (looks) {
                 float pre = 0.0f;
-                lookup_open_sum<false, LOOKERS>(a, ws, tile, s0, kTileLog2, lane, pre, wave);
+                lookup_open_sum<false, LOOKERS, RELAY>(a, ws, tile, s0, kTileLog2, lane, pre, wave);
                 if (lane == 0) s_back[wave] = pre;
             }
         }
