@@ -275,6 +275,8 @@ tcr_status tcr_tuning_import(const char *text);
  * 4 = irregular_reduce, 5 = irregular_scan (seg_len is ignored).  For fixed tiles, irregular and <regular>, the
  * kernels that work on any array are named whatever its size: smaller arrays need fewer (their tiles search the offsets
  * and add what reaches them themselves, so neither irregular_bounds_kernel nor irregular_finish_kernel is launched),
+ * scan_chain_kernel<mfma>+scan_tail_kernel is scan_chain_kernel alone with binary32 results, and with binary16 ones up to 3 * 2^25
+ * elements, where the buffer has room for it (tcr_workspace_bytes);
  * irregular sums and moments of most arrays above 2^23 elements are segments_reduce_kernel alone unless they are
  * recorded into a graph, irregular scans of up to 9 * 2^24 elements and regular ones in fixed tiles are tile_scan_kernel, and
  * sums over segments of thousands of tiles are irregular_groups_kernel and irregular_carry_kernel.

@@ -562,7 +562,7 @@ extern "C" uint64_t tcr_workspace_bytes(int op, uint64_t n, uint64_t seg_len) {
         // chained tiles (of the smallest tile shape); two tables of them for the two-kernel scan of irregular segments
         desc = (irregular ? 2 : 1) * irregular_tiles_max(true, padded);
         // two words per tile of the relay (regular calls beyond 2^27 elements and irregular ones beyond 9 * 2^24 do not ask for them: on a
-        // buffer of this size they run chained tiles)
+        // buffer of this size sums are looked up or tiles chained)
         const uint64_t relay = 2 * ceil_div(padded, kRelayTile), grid = irregular ? 0 : 2 * relay_tiles(n, seg_len);
         if (n > (1ull << 23) && n <= (irregular ? 9ull << 24 : 1ull << 27)) {
             if (relay > desc) desc = relay;

@@ -1004,8 +1004,8 @@ inline tcr_status launch_irregular_scan(const _Float16* in, const uint64_t* offs
     const uint32_t vector_stores = aligned(out, 16) ? 1u : 0u;
     const uint64_t tiles = irregular_tiles(true, n, shape);
     const bool regular = offsets == nullptr;
-    // One tile per workgroup: with carries from the relay (tiles_relayed), else regular segments of any length and, up to what the chip
-    // holds at once, irregular ones.  n = 2^20 / 2^24 / 2^26, us, by ticket and look-back against this: seg_len 1001 8.2 / 27 / 85 against
+    // One tile per workgroup: with carries from the relay (tiles_relayed; irregular_sums says which irregular tiles look sums up instead), else regular
+    // segments of nearly any length (tiles_chained) and, up to what the chip holds at once, irregular ones.  n = 2^20 / 2^24 / 2^26, us, by ticket and look-back against this: seg_len 1001 8.2 / 27 / 85 against
     // 4.1 / 22.8 / 74; 100003 8.7 / 28 / 89 against 5.1 / 20.4 / 78; irregular, lognormal lengths 10.9 / 31.8 against 5.5 / 21.0.
     const bool alone = shape == 0 && g_variant.formulation == kMfma && (regular ? seg_len >= 2 : g_variant.irregular_scan == 0);
     bool relay = alone && tiles_relayed(n, nseg, seg_len, regular, (MODE & 2) != 0, vector_stores != 0);

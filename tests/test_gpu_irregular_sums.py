@@ -142,3 +142,28 @@ def test_runs_of_empty_segments(tcr, oracle, n, front):
     off = np.concatenate(parts + [np.arange(at, n, 1000), [n]]).astype(np.int64)
     check(tcr, oracle, off, 0, n)
     check(tcr, oracle, off, 3, n, 3)
+
+
+# infinities and NaN stay in their segments, whichever way the sums in front of a tile come: what follows is what it is without them
+@pytest.mark.parametrize("call", ["uniform16", "lognormal256", "few7", 65536, 100003, 5001])
+@pytest.mark.parametrize("flags", [0, 1])
+def test_infinities_and_nan_stay_in_their_segments(tcr, call, flags):
+    n = 65 * M if call == 5001 else N
+    clean = torch.from_numpy(workloads.make_input(n, "int1", 9)).cuda()
+    if isinstance(call, str):
+        off = torch.from_numpy(workloads.make_offsets(n, call, 3).view(np.int64)).cuda()
+        run = lambda x: tcr.irregular_scan_ex(x, off, flags)
+    else:
+        clean = clean[:n - n % call]
+        n = clean.numel()
+        off = torch.arange(0, n + 1, call, device="cuda")
+        run = lambda x: tcr.segmented_scan_ex(x, call, flags)
+    dirty, segments, behind = clean.clone(), torch.zeros(n, dtype=torch.bool, device="cuda"), torch.zeros(n, dtype=torch.bool, device="cuda")
+    for at, value in ((TILE - 1, float("nan")), (5 * TILE, float("inf")), (n // 3, float("-inf")), (n // 2 + 77, float("nan")), (n - 2 * TILE - 1, float("inf"))):
+        dirty[at] = value
+        after = int(torch.searchsorted(off, at, right=True))
+        behind[at + (flags & 1):int(off[after])] = True
+        segments[int(off[after - 1]):int(off[after])] = True         # (in front of it products with zeros may be NaN too)
+    got, want = run(dirty), run(clean)
+    assert torch.equal(got[~segments], want[~segments])
+    assert not got[behind].isfinite().any()
