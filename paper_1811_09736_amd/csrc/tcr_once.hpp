@@ -412,8 +412,8 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
     const bool inside = valid_lo == 0u && valid_hi == kChunk && a.vector_stores != 0u;
     void* const dst = F16 ? static_cast<void*>(static_cast<_Float16*>(a.out) + base) : static_cast<void*>(static_cast<float*>(a.out) + base);
     // A whole share that lies in no segment (the middle third of 2^20 * 24 / 64 / 128 elements in segments of 37, the rest in none: 66 / 150 / 293 us ->
-    // 38 / 83 / 157).  Not with kSumsNear and binary16 results, whose other shares lose 2 %.
-    if constexpr (!REGULAR && !(F16 && SUMS == kSumsNear)) {
+    // 38 / 83 / 157).  Not with kSumsNear and binary16 results, whose other shares lose 2 %, nor with kSumsWide (lognormal lengths in 2^24 elements 20.4 -> 20.5).
+    if constexpr (!REGULAR && SUMS != kSumsWide && !(F16 && SUMS == kSumsNear)) {
         if (a.fill != 0u && a.vector_stores != 0u && count == kChunk && base >= a.shift && (valid_lo == kChunk || valid_hi == 0u)) {
 #pragma unroll
             for (int u = 0; u < U; ++u) store8_t<F16>(dst, (uint32_t)(kTile * u + 8 * lane), splat(0.0f), splat(0.0f));
