@@ -54,8 +54,8 @@ __device__ __forceinline__ float open_tile_sum(const TileScan& a, uint32_t t, ui
 }
 
 // One wavefront: the sum from position s0 to the start of `tile` out of what the tiles in between have published, 64 at a time, the
-// nearest first; number `looker` of LOOKERS that take turns.  TAILS: tiles publish either status (with a relay).  What is not there after `patience` looks is added up from the elements, or (GIVE_UP)
-// the result is false.
+// nearest first; number `looker` of LOOKERS that take turns.  TAILS: tiles publish either status (with a relay).  What is not there after
+// `patience` looks is added up from the elements, or (GIVE_UP) the result is false.
 template <bool GIVE_UP, int LOOKERS = 1, bool TAILS = false>
 __device__ __forceinline__ bool lookup_open_sum(const TileScan& a, const ScanWorkspace& ws, uint32_t tile, uint64_t s0, int tile_log2, int lane,
                                                 float& sum, int looker = 0) {
@@ -259,9 +259,9 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
                     if (!filled) break;
                     // Empty segments.  Where a run of them goes on for long this turn has
                     // marked their position; on with the turn in which they end, the same one for every wavefront (a million of them between
-                    // segments of 16 in 2^20 * 13 / 64 elements: 1340 / 1975 us -> 29 / 99; looked for from the second turn on and not only behind as many entries
+                    // segments of 16 in 2^26 elements: 1975 us -> 99; looked for from the second turn on and not only behind as many entries
                     // as the tile has elements, since all tiles behind this one wait: segments of 1000 and 2^20 * 0.24 empty ones in a row in 2^20 * 24 elements
-                    // 44.1 -> 38.7).
+                    // 44.1 -> 38.7.  Tiles of kSumsWide take every entry: 2^20 * 3 empty ones in 2^20 * 12 elements 2630).
                     uint64_t turns = 1;
                     if (ahead && here == further && here == a.offsets[at + 64 * kTurn]) {
                         const uint64_t behind = wave_lower_bound(a.offsets, a.nseg + 1, here + 1, lane);
