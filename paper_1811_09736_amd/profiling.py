@@ -12,6 +12,7 @@ writes text.  Usage (the rocprofv3 commands themselves are quoted in every summa
     python -m paper_1811_09736_amd.profiling counters      <name> <title> <kernel-stats dir> <pmc dir> [<pmc dir> ...]
     python -m paper_1811_09736_amd.profiling chain-gap     <kernel-stats dir> <SQ counters dir> <TCC counters dir>
     python -m paper_1811_09736_amd.profiling irregular-counters <kernel-stats dir of the mix> <three SQ counter dirs>
+    python -m paper_1811_09736_amd.profiling relay         <kernel-stats dir> <SQ, TCC, FETCH_SIZE and WRITE_SIZE dirs>
     python -m paper_1811_09736_amd.profiling repeatability <bench JSON line file> ...
     python -m paper_1811_09736_amd.profiling tile-load     <five bench JSON line files>
 """
@@ -99,7 +100,7 @@ def _write(name: str, lines) -> None:
 TEMPLATE_NOTE = [
     "Template arguments: reduce_small<FORM,LOG2L,U,W,LOAD>, scan_small<FORM,LOG2L,U,W,MODE,LOAD>, reduce_span<FORM,U,W,COMBINE,FINISH>,",
     "scan_block<FORM,U,W,CARRY,MODE>, scan_chain<FORM,U,W,MODE,IRREG,KIND>, rows_reduce<KIND,U,W>, packed_rows_reduce<KIND,U,W>, scan_half<U,W,CARRY,EXCL>; FORM 0 = MFMA, 1 = DPP;",
-    "CARRY 0 = none, 1 = look-back; irregular_scan<U,W,REGULAR,MODE,SECOND>, tile_scan<U,W,REGULAR,MODE,LOCAL,RELAY,MOST>, irregular_reduce<U,W,REGULAR,KIND,LINKED>, segments_reduce<KIND>, reduce_gather<FORM> (REGULAR 1:",
+    "CARRY 0 = none, 1 = look-back; irregular_scan<U,W,REGULAR,MODE,SECOND>, tile_scan<U,W,REGULAR,MODE,LOCAL,SUMS,MOST>, irregular_reduce<U,W,REGULAR,KIND,LINKED>, segments_reduce<KIND>, reduce_gather<FORM> (REGULAR 1:",
     "regular segments of an untuned length; the context rows mix three offset arrays).",
 ]
 
@@ -342,6 +343,46 @@ def chain_gap(kt_dir: str, sq_dir: str, tcc_dir: str) -> None:
              [sq_dir, tcc_dir], commands, reading)
 
 
+RELAY_PROGRAM = '''import torch
+from paper_1811_09736_amd import binding as b
+n = 1 << 28
+x, out = torch.rand(n, device="cuda").half(), torch.empty(n, device="cuda")
+def four(call):
+    for _ in range(4): call()
+    torch.cuda.synchronize()
+four(lambda: b.scan(x, out))                                        # the relay: scan_chain<0,4,4,0,0,2>
+four(lambda: b.segmented_scan(x, 4096, out))                        # no carries: scan_block<0,1,8,0,0>
+m = n - n % 100003
+four(lambda: b.segmented_scan(x[:m], 100003, out[:m]))              # the relay in tiles of the array: tile_scan<4,4,1,0,0,3,8>
+b.set_workspace(torch.zeros(1 << 19, dtype=torch.uint8, device="cuda"))
+four(lambda: b.scan(x, out))                                        # no room for the relay's words: the persistent chain, scan_chain<0,4,16,0,0,0>
+b.set_workspace(None)
+'''
+
+
+def relay(kt_dir: str, sq_dir: str, tcc_dir: str, fetch_dir: str, write_dir: str) -> None:
+    """The relay beside the persistent chain and a scan without carries: waits, wavefronts in flight, bytes."""
+    program = ["    " + line for line in RELAY_PROGRAM.splitlines()]
+    commands = ["Commands (each its own run, from /tmp with TMPDIR=/tmp and PYTHONPATH at the repository; counters are sums over the chip per launch,",
+                "averaged over launches; FETCH_SIZE and WRITE_SIZE in KiB, of which the first counts half of what is read, see",
+                "bench_cfg5_sweep_pmc_traffic.md):", "",
+                "    rocprofv3 --kernel-trace --stats --output-format csv -d <out> -o bench -- python3 <program>",
+                "    rocprofv3 --pmc SQ_WAVES SQ_WAVE_CYCLES SQ_BUSY_CU_CYCLES SQ_WAIT_ANY SQ_ACTIVE_INST_ANY SQ_WAIT_INST_LDS SQ_INSTS_VMEM_RD SQ_INSTS_VMEM_WR --output-format csv -d <out> -o bench -- python3 <program>",
+                "    rocprofv3 --pmc TCC_EA0_RDREQ_DRAM_CREDIT_STALL_sum TCC_EA0_WRREQ_STALL_sum TCC_EA0_RD_UNCACHED_32B_sum TCC_ATOMIC --output-format csv -d <out> -o bench -- python3 <program>",
+                "    rocprofv3 --pmc FETCH_SIZE --output-format csv -d <out> -o bench -- python3 <program>      (and WRITE_SIZE)", "",
+                "The program:", "", *program, "", *TEMPLATE_NOTE]
+    counters("scan_relay_counters_n2^28.md", "Scans of 2^28 elements with carries from the relay, from the persistent chain and without carries: counters per launch",
+             kt_dir, [sq_dir, tcc_dir, fetch_dir, write_dir], commands, RELAY_READING, only="scan")
+
+
+RELAY_READING = ["Reading.  The same bytes move in all four; what differs is how much waits and how much is in flight.  SQ_WAVE_CYCLES is 1.20e9 with the relay and 1.00e9",
+                 "without carries against 0.64e9 with the chain, at 1.49e8 to 1.62e8 busy cycles of the compute units: 30.5, 27.0 and 15.9 wavefronts per compute unit (the",
+                 "counter counts in fours).  Of these, 78, 67 and 56 % of the cycles are waits (SQ_WAIT_ANY): the relay's wavefronts wait longer, for a carry and not for",
+                 "memory alone, and enough others run meanwhile -- the read-credit stalls are above those of the scan without carries, 13 times the chain's, which cannot press",
+                 "on the memory system.  The polls are 2.3e5 loads beside 5.2e5 of elements (SQ_INSTS_VMEM_RD) and 1 % of the bytes read; no atomics (the chain draws 8960",
+                 "tickets).  That tiles write in the order of the array is not to be seen here: the write-request stalls are nearly three times those of the scan without carries."]
+
+
 def irregular_counters(kt_dir: str, sq1: str, sq2: str, sq3: str) -> None:
     """SQ counters of the irregular kernels on the mix with 16 elements per segment on average."""
     flt = '--context-filter "uniform on 0..32"'
@@ -436,6 +477,8 @@ def main(argv) -> int:
         irregular_counters(*args)
     elif kind == "chain-gap":
         chain_gap(*args)
+    elif kind == "relay":
+        relay(*args)
     elif kind == "repeatability":
         repeatability(args)
     elif kind == "tile-load":
