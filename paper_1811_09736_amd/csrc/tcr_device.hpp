@@ -140,6 +140,13 @@ __device__ __forceinline__ uint64_t wave_seg_scan_inclusive_bits(uint64_t flags,
     return flags;
 }
 
+// Sum over all 64 lanes in binary64, returned uniformly.
+__device__ __forceinline__ double wave_sum(double x) {
+    double v[1] = {x};
+    (void)wave_seg_scan_inclusive_bits<1>(0ull, v);
+    return read_lane(v[0], 63);
+}
+
 // A workgroup barrier that orders LDS accesses only: unlike __syncthreads() it does not wait for the wavefront's
 // outstanding loads from memory, so data requested before it keeps arriving while the workgroup works on LDS.
 __device__ __forceinline__ void lds_barrier() {

@@ -56,12 +56,13 @@ __device__ __forceinline__ float open_tile_sum(const TileScan& a, uint32_t t, ui
 // One wavefront: the sum from position s0 to the start of `tile` out of what the tiles in between have published, 64 at a time, the
 // nearest first; number `looker` of LOOKERS that take turns.  TAILS: tiles publish either status (with a relay).  What is not there after
 // `patience` looks is added up from the elements, or (GIVE_UP) the result is false.
-template <bool GIVE_UP, int LOOKERS = 1, bool TAILS = false>
+// T: what the sums are added in.
+template <bool GIVE_UP, int LOOKERS = 1, bool TAILS = false, typename T>
 __device__ __forceinline__ bool lookup_open_sum(const TileScan& a, const ScanWorkspace& ws, uint32_t tile, uint64_t s0, int tile_log2, int lane,
-                                                float& sum, int looker = 0) {
+                                                T& sum, int looker = 0) {
     const uint32_t first = (uint32_t)(s0 >> tile_log2);
     const uint32_t want = ws.epoch * 4u + kStatusAggregate;
-    float acc = 0.0f;
+    T acc = 0;
     const uint32_t skipped = 64u * (uint32_t)looker;
     for (uint32_t hi = tile - first > skipped ? tile - skipped : first; hi > first;) {
         const uint32_t span = hi - first > 64u ? 64u : hi - first;
@@ -89,7 +90,7 @@ __device__ __forceinline__ bool lookup_open_sum(const TileScan& a, const ScanWor
             }
             __builtin_amdgcn_s_sleep(1);
         }
-        acc += v;
+        acc += (T)v;
         if constexpr (LOOKERS == 1) hi -= span;
         else hi = hi - first > 64u * LOOKERS ? hi - 64u * LOOKERS : first;
     }
@@ -109,9 +110,9 @@ constexpr uint32_t kNearTiles = 64 * kRelayWaves;
 // wavefronts add up themselves (segments of 16 in 2^27 elements 165 us, 174 where all wait; seven segments 151 and 149).  The
 // entries of tiles of four wavefronts are found with one search of two rounds around where they are likely to be (GUIDED), not two of four over the whole array.
 // Registers: at most 64, so that 8 wavefronts per SIMD run.  A wavefront that has waited in vain loads its elements again behind the
-// additions, so that they need not be held across them: 43 to 49 registers where four sub-tiles took 64 and 44 bytes of scratch
+// additions, so that they need not be held across them: 43 to 55 registers where four sub-tiles took 64 and 44 bytes of scratch
 // (lognormal lengths / segments of 16 / seven segments in 2^24 elements 21.7 / 23.9 / 23.6 -> 21.0 / 23.5 / 22.7 us).  Not with fewer
-// sub-tiles, which lose 2 to 5 %, nor with binary16 results (15.7 -> 16.0): 64 registers, 20 to 68 bytes.
+// sub-tiles, which lose 2 to 5 %, nor with binary16 results (15.7 -> 16.0): 64 registers, 28 to 76 bytes.
 // MOST: wavefronts per SIMD at most.
 template <int U, int WAVES, bool REGULAR, int MODE, bool LOCAL, int SUMS = kSumsWide, int MOST = 8>
 __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U < 4 ? 4 : MOST, MOST))) void tile_scan_kernel(TileScan a, ScanWorkspace ws_arg) {
@@ -128,6 +129,10 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
     __shared__ uint32_t s_heads[REGULAR ? 1 : kBlockTile / 32];
     __shared__ uint64_t s_bound[4];
     __shared__ float s_wave_value[WAVES], s_back[WAVES];      // (s_back: parts of the open sum, added up or looked up)
+    // Sums looked up by all, added as the relay adds, in binary64 (lognormal lengths in 2^20 * 17 / 24 elements 5.1e-8 / 6.5e-8 off 64 bits in binary32,
+    // 4.5e-8 / 4.6e-8 so, in the same time; with binary16 results, which don't show it, 1 % more).
+    using Far = std::conditional_t<F16 != 0, float, double>;
+    __shared__ Far s_far[LOOKERS > 1 ? WAVES : 1];
     __shared__ uint32_t s_wave_flag[WAVES];
 
     const int lane = threadIdx.x & (kWave - 1);
@@ -375,9 +380,9 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
         }
         if constexpr (LOOKERS > 1) {
             if (looks) {
-                float pre = 0.0f;
+                Far pre = 0;
                 lookup_open_sum<false, LOOKERS, RELAY>(a, ws, tile, s0, kTileLog2, lane, pre, wave);
-                if (lane == 0) s_back[wave] = pre;
+                if (lane == 0) s_far[wave] = pre;
             }
         }
         if (far) __syncthreads();
@@ -395,7 +400,7 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
     if (open && back != 0) {
         float sum = 0.0f;
         if constexpr (LOOKERS > 1) {
-            sum = pairwise_sum(s_back);           // (sums over thousands of tiles)
+            sum = looks ? (float)((s_far[0] + s_far[1]) + (s_far[2] + s_far[3])) : pairwise_sum(s_back);
         } else {
 #pragma unroll
             for (int v = 0; v < WAVES; ++v) sum += s_back[v];

@@ -135,7 +135,7 @@ __device__ __forceinline__ bool relay_wait(const ScanWorkspace& ws, uint32_t til
 template <bool RELAY, typename TOTAL>
 __device__ __forceinline__ float add_up_in_front(const ScanWorkspace& ws, uint32_t tiles, uint32_t first, uint32_t tile, TOTAL total_of) {
     const uint32_t lane = threadIdx.x & (uint32_t)(kWave - 1);
-    double sum[1] = {0.0};
+    double sum = 0.0;
     for (uint32_t hi = tile; hi > first;) {
         const uint32_t span = hi - first > (uint32_t)kWave ? (uint32_t)kWave : hi - first;
         const uint32_t t = hi - 1u - (lane < span ? lane : 0u);
@@ -150,15 +150,14 @@ __device__ __forceinline__ float add_up_in_front(const ScanWorkspace& ws, uint32
             const float elements = total_of(hi - 1u - slot);
             if (lane == slot) v = elements;
         }
-        if (lane <= last) sum[0] += (double)v;
+        if (lane <= last) sum += (double)v;
         if (carries != 0ull) {
-            if (lane == last) sum[0] += (double)__builtin_bit_cast(float, (uint32_t)c);
+            if (lane == last) sum += (double)__builtin_bit_cast(float, (uint32_t)c);
             break;
         }
         hi -= span;
     }
-    (void)wave_seg_scan_inclusive_bits<1>(0ull, sum);
-    return (float)read_lane(sum[0], kWave - 1);
+    return (float)wave_sum(sum);
 }
 
 }  // namespace tcr

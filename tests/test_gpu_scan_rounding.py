@@ -51,6 +51,21 @@ def test_the_sum_in_front_is_added_once(tcr, seg, limit, flags):
     assert roundings(got, want) < limit
 
 
+# Irregular segments whose sum in front all four wavefronts of a tile look up, from a table or near by, or get from the relay: 2.6 to 3.1 roundings
+# whichever it is; with looked-up sums added in binary32 3.9 to 6.1.
+@pytest.mark.parametrize("recipe,n", [("lognormal100", 17 << 20), ("lognormal20", 17 << 20), ("half", 17 << 20), ("lognormal100", 21 << 20), ("lognormal100", 24 << 20)])
+@pytest.mark.parametrize("flags", [0, 1])
+def test_looked_up_sums(tcr, recipe, n, flags):
+    x = fractions(n)
+    sums = torch.cumsum(x.double(), 0)
+    off = torch.cat([torch.arange(n // 2 + 1), torch.tensor([n])]) if recipe == "half" else torch.from_numpy(workloads.make_offsets(n, recipe, 5).view(np.int64))
+    off = off.cuda()
+    want = sums - torch.repeat_interleave(torch.cat([sums.new_zeros(1), sums])[off[:-1]], off[1:] - off[:-1])
+    if flags & tcr.SCAN_EXCLUSIVE:
+        want -= x.double()
+    assert roundings(tcr.irregular_scan_ex(x, off, flags), want) < 3.5
+
+
 # A tile that has waited in vain adds up what is in front of it by itself (the look-up of arrays that the chip holds at once, the relay of larger
 # ones), and which tiles do is a matter of time: no more roundings than where all wait.  Waiting / adding up here: 9.5 / 8.5, 9.4 / 8.5, 5.3 / 6.2, 2.8 /
 # 3.7, 2.8 / 2.9; with the sums of the tiles added one after the other in binary32 156, 56, 6.2, 3.9, 3.8.
