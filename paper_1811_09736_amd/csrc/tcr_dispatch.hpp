@@ -829,6 +829,7 @@ inline void launch_tile_scan(const TileScan& a, const ScanWorkspace& dev, hipStr
 }
 // Up to here the compute units hold all workgroups at once (256 units: 2^24 elements).
 inline uint64_t scan_held_max() { return (uint64_t)compute_units() * (uint64_t)(kTile * 16 * 8); }
+constexpr uint64_t kNearSevenMax = 39ull << 19;       // (irregular_sums)
 template <int MODE>
 inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, void* out, uint64_t n, uint64_t nseg, uint64_t seg_len,
                                    uint32_t shift, bool fill, TileSums sums, hipStream_t s) {
@@ -873,10 +874,14 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
         // (looked-up sums need one; asked for where it can be had, so that the same call can be recorded with other offsets)
         st = begin_lookback(ws, s, sums == kSumsLookedUp && 2 * tiles > limit ? tiles : 2 * tiles, &dev, capturing);
         if (st != TCR_OK) return st;
-        // (7 wavefronts per SIMD: up to 72 registers where the relay alone, with binary32 results, takes 49; 16, or with binary16 results 28, bytes of scratch
-        // per lane or none, up to 60 with 64 registers)
+        // (7 wavefronts per SIMD: up to 72 registers where the relay alone, with binary32 results, takes 49; none to 24 bytes of scratch
+        // per lane, with binary16 results up to 76 with 64 registers)
         if (sums == kSumsLookedUp) tile_scan_kernel<4, kRelayWaves, false, MODE, false, kSumsLookedUp, 7><<<dim3((unsigned)tiles), dim3(kRelayWaves * kWave), 0, s>>>(a, dev);
-        else if (sums == kSumsNear) tile_scan_kernel<4, kRelayWaves, false, MODE, false, kSumsNear, 7><<<dim3((unsigned)tiles + 1), dim3(kRelayWaves * kWave), 0, s>>>(a, dev);
+        else if (sums == kSumsNear) {
+            constexpr int MOST = MODE < 2 ? 8 : 7;
+            if (n > kNearSevenMax) tile_scan_kernel<4, kRelayWaves, false, MODE, false, kSumsNear, MOST><<<dim3((unsigned)tiles + 1), dim3(kRelayWaves * kWave), 0, s>>>(a, dev);
+            else tile_scan_kernel<4, kRelayWaves, false, MODE, false, kSumsNear, 7><<<dim3((unsigned)tiles + 1), dim3(kRelayWaves * kWave), 0, s>>>(a, dev);
+        }
         else launch_tile_scan<4, kRelayWaves, MODE, false, kSumsRelayed>(a, dev, s);
         st = check_launch("tile_scan_kernel");
         if (st != TCR_OK) ws->dirty = true;
@@ -971,9 +976,18 @@ inline bool tiles_chained(uint64_t n, uint64_t seg_len, bool f16, bool vector_st
 //              1000, and 2^20 * 0.17 empty ones in a row  24.8/28.0/28.8   26.0/30.2/29.9   32.9/38.3/37.0
 // (results stored by element, 18 and 24: lognormal 59.7/60.2/63.5 and 77.4/77.2/79.3, binary16 38.0/38.0/40.6 and 47.7/48.2/48.5; 100000 38.9/38.7/41.6 and
 // 48.5/48.5/51.4.)
+// Binary32 results beyond 2^20 * 19.5: the relay for segments of up to 32 elements and long ones, those near by in between, where the relay lost; without scratch, so that
+// 8 wavefronts per SIMD run (below 2^20 * 19.5 7 are faster: lognormal of mean 756 32.5/31.6).  us, before the relay / relay / near by, lognormal of mean 35, 147, 756, 1000
+// (narrow), 3000 elements each, a tenth in 64s and one segment:
+//   20   33.0/34.2/32.5   33.5/34.5/33.3   33.0/32.8/32.9   33.4/34.0/32.8   33.7/33.7/33.0   44.5/33.9/33.3
+//   22   36.5/37.8/36.8   36.1/37.4/36.2   35.5/36.1/34.5   35.6/37.2/35.5   35.7/36.9/35.3   48.6/37.0/38.2
+//   24   40.7/41.5/39.8   39.1/40.0/39.7   39.3/39.6/39.5   38.7/39.9/38.9   39.1/39.7/38.9   54.4/40.2/41.7
+//   28   44.8/45.3/44.6   42.5/43.7/42.8   43.4/42.6/43.5   41.9/43.4/42.5   42.2/43.7/-      61.2/42.0/43.5
+// (means of 4096 and more: the relay up to 6 % faster at 28; of 2048 to 4096 beyond 24 both ways: lognormal 43.5/42.2/44.1.)
 constexpr uint64_t kIrregularLookedUpMax = 7ull << 22;
 inline TileSums irregular_sums(uint64_t n, uint64_t nseg, bool f16, bool vector_stores) {
-    if (n > (!vector_stores ? 27ull << 20 : f16 ? kIrregularLookedUpMax : 37ull << 19)) return kSumsRelayed;
+    if (n > (!vector_stores ? 27ull << 20 : kIrregularLookedUpMax)) return kSumsRelayed;
+    if (vector_stores && !f16 && n > kNearSevenMax) return nseg < n >> 5 && nseg >= n >> (n > (3ull << 23) ? 11 : 12) ? kSumsNear : kSumsRelayed;
     if (nseg >= n >> 9) return kSumsLookedUp;
     return nseg >= n >> (!vector_stores ? 20 : f16 ? 18 : 16) ? kSumsNear : kSumsRelayed;
 }

@@ -51,6 +51,14 @@ def test_limits(tcr, oracle, nseg, flags, tiles):
     check(tcr, oracle, ends(nseg, N - tiles * TILE - 100), flags)
 
 
+# the same for the larger arrays whose binary32 results take the relay for the shortest and the longest segments
+@pytest.mark.parametrize("n,nseg", [(39 * M // 2 + 8, 12), (39 * M // 2, 12), (21 * M + 5, 5), (21 * M + 5, 12), (24 * M, 12), (24 * M + 8, 11), (28 * M, 11)])
+@pytest.mark.parametrize("more", [-1, 0])
+@pytest.mark.parametrize("flags", [0, 1])
+def test_limits_of_larger_arrays(tcr, oracle, n, nseg, more, flags):
+    check(tcr, oracle, ends((n >> nseg) + more, n - 300 * TILE - 100, n), flags, n)
+
+
 # a segment's start 63 to 258 tiles in front of tiles that look its sums up, and on the edges of tiles; modes and alignments
 @pytest.mark.parametrize("flags,shift", [(0, 0), (1, 3), (2, 5), (3, 0)])
 @pytest.mark.parametrize("per", [300, 20000])
