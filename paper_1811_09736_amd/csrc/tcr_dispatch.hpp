@@ -860,7 +860,11 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
         // the array streams from memory (seg_len 33 at n = 2^24 / 2^26 / 2^28: 23.2 / 74.8 / 285 us with 8, 23.6 / 73.3 /
         // 276 with 16; 2001: 22.7 / 74.4 / 277 and 24.0 / 77.8 / 290; binary16 results, 33 at 2^26 / 2^27 / 2^28: 42.2 / 91.9 /
         // 179 with 8, 43.8 / 100.8 / 196 with 16), or longer than 8 wavefronts can add up at once
-        if (seg_len > 4096 || (!(MODE & 2) && seg_len <= 1024 && n > (1ull << 24))) launch_tile_scan<1, 16, MODE, true>(a, dev, s);
+        // Long open parts are added in binary64 beyond what the chip holds at once where the relay would take them (tiles_relayed) if it were as fast: 8191 elements in
+        // 2^20 * 22 / off a boundary in 2^20 * 64 32.9 / 181.6 -> 32.7 / 179.5 us.  On a boundary 4097 to 6144 elements would lose 1 to 3 %.
+        if (MODE < 2 && n > scan_held_max() && seg_len > (a.vector_stores != 0u ? 6144u : 4096u))
+            tile_scan_kernel<1, 16, true, MODE, true, kSumsWide, 8, MODE < 2 ? kCarryExact : kCarryEarly><<<dim3((unsigned)ceil_div(n, (uint64_t)(kTile * 16))), dim3(16 * kWave), 0, s>>>(a, dev);
+        else if (seg_len > 4096 || (!(MODE & 2) && seg_len <= 1024 && n > (1ull << 24))) launch_tile_scan<1, 16, MODE, true>(a, dev, s);
         else launch_tile_scan<1, 8, MODE, true>(a, dev, s);
         return check_launch("tile_scan_kernel");
     }
@@ -906,7 +910,13 @@ inline tcr_status launch_scan_once(const _Float16* in, const uint64_t* offsets, 
     if (u == 1) launch_tile_scan<1, 8, MODE, false>(a, dev, s);
     else if (u == 2 && w == 8) launch_tile_scan<2, 8, MODE, false>(a, dev, s);
     else if (u == 2) launch_tile_scan<2, 16, MODE, false>(a, dev, s);
-    else if (w == 8 && offsets == nullptr && n > scan_held_max()) tile_scan_kernel<4, 8, true, MODE, false, kSumsWide, 6><<<dim3((unsigned)tiles_of(4, 8)), dim3(8 * kWave), 0, s>>>(a, dev);
+    else if (w == 8 && offsets == nullptr && n > scan_held_max()) {
+        // (in binary64 where results are stored by element, which hides it: 9001 / 30003 / 100003 elements off a boundary in 2^20 * 64 184.7 / 188.0 / 191.0 -> 184.8 / 187.3 / 190.1;
+        // on one in 2^20 * 22 33.9 / 34.3 / - -> 34.5 / 34.7 / -)
+        const dim3 grid((unsigned)tiles_of(4, 8)), block(8 * kWave);
+        if (a.vector_stores == 0u) tile_scan_kernel<4, 8, true, MODE, false, kSumsWide, 6, MODE < 2 ? kCarryExact : kCarryLate><<<grid, block, 0, s>>>(a, dev);
+        else tile_scan_kernel<4, 8, true, MODE, false, kSumsWide, 6><<<grid, block, 0, s>>>(a, dev);
+    }
     else if (w == 8) launch_tile_scan<4, 8, MODE, false>(a, dev, s);
     else launch_tile_scan<4, 16, MODE, false>(a, dev, s);
     st = check_launch("tile_scan_kernel");

@@ -105,6 +105,14 @@ __device__ __forceinline__ bool lookup_open_sum(const TileScan& a, const ScanWor
 enum TileSums { kSumsWide = 0, kSumsLookedUp = 1, kSumsNear = 2, kSumsRelayed = 3 };
 constexpr uint32_t kNearTiles = 64 * kRelayWaves;
 
+// How the sum in front reaches a lane's elements.  It may be millions of times one of them, so kCarryLate adds it once, behind the lane's eight additions, not in front of
+// them.  Where workgroups follow each other (tiles of four wavefronts, and regular ones beyond what the chip holds at once) the two more operations per element are
+// free; where all run at once they cost 5 to 10 % (seven segments in 2^24 elements: 23.5 us, 25.3 with them).  kCarryExact: and what goes into that sum --
+// the wavefronts' values, what is looked up, the parts of the open sum -- is added up in binary64, the wavefronts' by one scan over the lanes in place
+// of a loop over up to sixteen of them.  Error against 64 bits (2-norms, uniform values; early / late / exact): 8191 elements, added up by each tile, 6.0e-8 / 5.2e-8 / 3.4e-8;
+// 100003, looked up, - / 5.4e-8 / 4.4e-8 (the relay's tiles 4.4e-8 and 4.5e-8).  Binary16 results don't show it.
+enum CarryKind { kCarryEarly = 0, kCarryLate = 1, kCarryExact = 2 };
+
 // LOCAL (regular segments of 2 to WAVES * 512 elements): no sum is ever looked up, no workspace.
 // Relayed regular tiles all wait for the relay, in the order of the array; irregular ones only where it is more than the four
 // wavefronts add up themselves (segments of 16 in 2^27 elements 165 us, 174 where all wait; seven segments 151 and 149).  The
@@ -114,7 +122,8 @@ constexpr uint32_t kNearTiles = 64 * kRelayWaves;
 // (lognormal lengths / segments of 16 / seven segments in 2^24 elements 21.7 / 23.9 / 23.6 -> 21.0 / 23.5 / 22.7 us).  Not with fewer
 // sub-tiles, which lose 2 to 5 %, nor with binary16 results (15.7 -> 16.0): 64 registers, 28 to 76 bytes.
 // MOST: wavefronts per SIMD at most.
-template <int U, int WAVES, bool REGULAR, int MODE, bool LOCAL, int SUMS = kSumsWide, int MOST = 8>
+template <int U, int WAVES, bool REGULAR, int MODE, bool LOCAL, int SUMS = kSumsWide, int MOST = 8,
+          int CARRY = SUMS != kSumsWide || (!LOCAL && MOST < 8) ? kCarryLate : kCarryEarly>
 __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U < 4 ? 4 : MOST, MOST))) void tile_scan_kernel(TileScan a, ScanWorkspace ws_arg) {
     static_assert(!LOCAL || REGULAR, "");
     static_assert(SUMS == kSumsWide || (WAVES == kRelayWaves && !LOCAL), "");
@@ -341,17 +350,31 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
         s_back[wave] = back_sum;
     }
     __syncthreads();
+    constexpr bool LATE = CARRY != kCarryEarly, EXACT = CARRY == kCarryExact;
+    static_assert(!EXACT || (SUMS == kSumsWide && REGULAR), "");
+    // the wavefronts' values and, in the row of lanes behind them (LOCAL), the parts of the open sum
+    double waves[1] = {};
+    uint64_t waves_flags = 0;
+    if constexpr (EXACT) {
+        static_assert(WAVES <= 16, "");
+        waves[0] = lane < WAVES ? s_wave_value[lane] : LOCAL && lane >= 16 && lane < 16 + WAVES ? s_back[lane - 16] : 0.0f;
+        waves_flags = wave_seg_scan_inclusive_bits<1>(__ballot(lane < WAVES && s_wave_flag[lane] != 0u) | 1ull << 16, waves);
+    }
     if constexpr (!LOCAL) {
         const ScanWorkspace ws = resolve_workspace(ws_arg);
         if (wave == 0) {
             // what later tiles may need of this one: the sum behind its last head
             float total = 0.0f;
             bool tail = false;
-            for (int v = WAVES - 1; v >= 0; --v) {
-                total += s_wave_value[v];
-                if (s_wave_flag[v]) {
-                    tail = true;
-                    break;
+            if constexpr (EXACT) {
+                total = (float)read_lane(waves[0], WAVES - 1);
+            } else {
+                for (int v = WAVES - 1; v >= 0; --v) {
+                    total += s_wave_value[v];
+                    if (s_wave_flag[v]) {
+                        tail = true;
+                        break;
+                    }
                 }
             }
             if (lane == 0) {
@@ -364,7 +387,11 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
                 constexpr bool AGAIN = RELAY || (U == 4 && !F16);      // (elements asked for again by a wavefront that has waited in vain)
                 bool got;
                 if constexpr (RELAY) got = relay_wait(ws, gridDim.x - 1u, tile, a.patience, pre);
-                else got = lookup_open_sum<AGAIN>(a, ws, tile, s0, kTileLog2, lane, pre);
+                else {
+                    std::conditional_t<EXACT, double, float> looked_up = 0;
+                    got = lookup_open_sum<AGAIN>(a, ws, tile, s0, kTileLog2, lane, looked_up);
+                    pre = (float)looked_up;
+                }
                 if constexpr (AGAIN) {
                     if (__builtin_expect(!got, 0)) {
                         pre = add_up_in_front<RELAY>(ws, gridDim.x - 1u, (uint32_t)(s0 >> kTileLog2), tile,
@@ -389,31 +416,39 @@ __global__ __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(U
     }
     // carry from the wavefronts in front, back to the nearest one that holds a head, else from in front of the tile
     float ext = 0.0f;
-    bool open = true;
-    for (int v = wave - 1; v >= 0; --v) {
-        ext += s_wave_value[v];
-        if (s_wave_flag[v]) {
-            open = false;
-            break;
-        }
-    }
-    if (open && back != 0) {
-        float sum = 0.0f;
-        if constexpr (LOOKERS > 1) {
-            sum = looks ? (float)((s_far[0] + s_far[1]) + (s_far[2] + s_far[3])) : pairwise_sum(s_back);
-        } else {
+    if constexpr (EXACT) {
+        double carried = wave != 0 ? read_lane(waves[0], wave - 1) : 0.0;
+        if ((wave == 0 || ((waves_flags >> (wave - 1)) & 1ull) == 0ull) && back != 0) {
+            if constexpr (LOCAL) {
+                carried += read_lane(waves[0], 31);
+            } else {
 #pragma unroll
-            for (int v = 0; v < WAVES; ++v) sum += s_back[v];
+                for (int v = 0; v < WAVES; ++v) carried += (double)s_back[v];
+            }
         }
-        ext += sum;
+        ext = (float)carried;
+    } else {
+        bool open = true;
+        for (int v = wave - 1; v >= 0; --v) {
+            ext += s_wave_value[v];
+            if (s_wave_flag[v]) {
+                open = false;
+                break;
+            }
+        }
+        if (open && back != 0) {
+            float sum = 0.0f;
+            if constexpr (LOOKERS > 1) {
+                sum = looks ? (float)((s_far[0] + s_far[1]) + (s_far[2] + s_far[3])) : pairwise_sum(s_back);
+            } else {
+#pragma unroll
+                for (int v = 0; v < WAVES; ++v) sum += s_back[v];
+            }
+            ext += sum;
+        }
     }
     const uint32_t valid_lo = first > base ? (uint32_t)(first - base < kChunk ? first - base : kChunk) : 0u;
     const uint32_t valid_hi = last > base ? (uint32_t)(last - base < kChunk ? last - base : kChunk) : 0u;
-    // LATE: the sum in front may be millions of times an element, and is added once, behind the sums of the tile, not in front of
-    // a lane's eight additions.  Where workgroups follow each other (tiles of four wavefronts, and regular ones beyond what the chip holds at once,
-    // MOST < 8) the two more operations per element are free; where all run at once they cost 5 to 10 % (seven segments in 2^24
-    // elements: 23.5 us, 25.3 with them).
-    constexpr bool LATE = SUMS != kSumsWide || (!LOCAL && MOST < 8);
     const bool inside = valid_lo == 0u && valid_hi == kChunk && a.vector_stores != 0u;
     void* const dst = F16 ? static_cast<void*>(static_cast<_Float16*>(a.out) + base) : static_cast<void*>(static_cast<float*>(a.out) + base);
     // A whole share that lies in no segment (the middle third of 2^20 * 24 / 64 / 128 elements in segments of 37, the rest in none: 66 / 150 / 293 us ->

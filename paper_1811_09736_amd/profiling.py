@@ -100,7 +100,7 @@ def _write(name: str, lines) -> None:
 TEMPLATE_NOTE = [
     "Template arguments: reduce_small<FORM,LOG2L,U,W,LOAD>, scan_small<FORM,LOG2L,U,W,MODE,LOAD>, reduce_span<FORM,U,W,COMBINE,FINISH>,",
     "scan_block<FORM,U,W,CARRY,MODE>, scan_chain<FORM,U,W,MODE,IRREG,KIND>, rows_reduce<KIND,U,W>, packed_rows_reduce<KIND,U,W>, scan_half<U,W,CARRY,EXCL>; FORM 0 = MFMA, 1 = DPP;",
-    "CARRY 0 = none, 1 = look-back; irregular_scan<U,W,REGULAR,MODE,SECOND>, tile_scan<U,W,REGULAR,MODE,LOCAL,SUMS,MOST>, irregular_reduce<U,W,REGULAR,KIND,LINKED>, segments_reduce<KIND>, reduce_gather<FORM> (REGULAR 1:",
+    "CARRY 0 = none, 1 = look-back; irregular_scan<U,W,REGULAR,MODE,SECOND>, tile_scan<U,W,REGULAR,MODE,LOCAL,SUMS,MOST,LATE>, irregular_reduce<U,W,REGULAR,KIND,LINKED>, segments_reduce<KIND>, reduce_gather<FORM> (REGULAR 1:",
     "regular segments of an untuned length; the context rows mix three offset arrays).",
 ]
 
@@ -353,7 +353,7 @@ def four(call):
 four(lambda: b.scan(x, out))                                        # the relay: scan_chain<0,4,4,0,0,2>
 four(lambda: b.segmented_scan(x, 4096, out))                        # no carries: scan_block<0,1,8,0,0>
 m = n - n % 100003
-four(lambda: b.segmented_scan(x[:m], 100003, out[:m]))              # the relay in tiles of the array: tile_scan<4,4,1,0,0,3,8>
+four(lambda: b.segmented_scan(x[:m], 100003, out[:m]))              # the relay in tiles of the array: tile_scan<4,4,1,0,0,3,8,1>
 b.set_workspace(torch.zeros(1 << 19, dtype=torch.uint8, device="cuda"))
 four(lambda: b.scan(x, out))                                        # no room for the relay's words: the persistent chain, scan_chain<0,4,16,0,0,0>
 b.set_workspace(None)

@@ -51,6 +51,21 @@ def test_the_sum_in_front_is_added_once(tcr, seg, limit, flags):
     assert roundings(got, want) < limit
 
 
+# The same where the sum in front goes through binary64: long open parts that each tile adds up (2.2 roundings; 4.8 to 7.0 in binary32, in front of a lane's
+# additions), and what is looked up where results are stored by element (2.5 to 3.4; 3.3 to 4.8).
+@pytest.mark.parametrize("n,seg,shift,limit", [(HELD + (1 << 22), 6145, 0, 2.6), (HELD + (1 << 22), 8191, 0, 2.6), (HELD + (1 << 22), 4097, 3, 2.6), (3 << 24, 5001, 1, 2.6),
+                                               (3 << 24, 8191, 5, 2.6), (3 << 24, 9001, 3, 2.9), (3 << 24, 50003, 2, 3.6), (3 << 24, 65536, 3, 4.0), (3 << 24, 100003, 7, 3.6)])
+@pytest.mark.parametrize("flags", [0, 1])
+def test_the_sum_in_front_in_binary64(tcr, n, seg, shift, limit, flags):
+    n -= n % seg
+    x = fractions(n + shift)[shift:]
+    want = torch.cumsum(x.double().view(-1, seg), 1)
+    if flags & tcr.SCAN_EXCLUSIVE:
+        want -= x.double().view(-1, seg)
+    got = tcr.segmented_scan_ex(x, seg, flags).view(-1, seg)
+    assert roundings(got, want) < limit
+
+
 # Irregular segments whose sum in front all four wavefronts of a tile look up, from a table or near by, or get from the relay: 2.6 to 3.1 roundings
 # whichever it is; with looked-up sums added in binary32 3.9 to 6.1.
 @pytest.mark.parametrize("recipe,n", [("lognormal100", 17 << 20), ("lognormal20", 17 << 20), ("half", 17 << 20), ("lognormal100", 21 << 20), ("lognormal100", 24 << 20)])
