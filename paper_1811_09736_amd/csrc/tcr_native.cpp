@@ -1,8 +1,8 @@
 // The operations of binding.py in their ordinary form, as native calls: plain tensors on the current device, the current stream, results
 // new or given.  What costs a small call its time is the host -- 5.3 us through Python, of which the launch is 2.85 -- and most of the
-// rest was Python's: torch.empty 1.35, attribute look-ups and checks 0.6, ctypes 0.4.  us, before / now: scan of 65541 elements
-// 5.31 / 4.47 (4.1 are the kernel), sums of 2^20 elements in segments of 256 5.21 / 3.99, moments of 6.4 million in segments of 784
-// 6.49 / 5.47.
+// rest was Python's: torch.empty 1.35, attribute look-ups and checks 0.6, ctypes 0.4.  us, through Python / native, in most runs (some hosts
+// are faster: the last figure): scan of 65541 elements 5.5 / 4.9, 4.3 (4.1 are the kernel), sums of 2^20 elements in segments of 256 5.3 / 4.4, 3.9, moments
+// of 6.4 million in segments of 784 6.3 / 5.4, 4.9 (the last with smaller shares than before too).
 // Everything else is left to binding.py: a function here returns None, before it has done anything, where an argument is not what
 // is expected (subclasses and wrapped tensors, modes, other devices, wrong types and sizes), and binding.py goes on to its own
 // checks and errors.  Nothing is computed here; libtcr.so's functions come as addresses from binding.py, which has loaded it.
